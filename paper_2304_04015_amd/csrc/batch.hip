@@ -230,7 +230,7 @@ extern "C" int simrank_batch_plan_create_ex(simrank_graph *const *graphs, int32_
     if ((rc = device_alloc((void **)&p->desc_dev, sizeof(QueryDesc) * nq, &p->bytes))) return bail(rc);
     if ((rc = device_alloc((void **)&p->units, 4 * units_words(nq), &p->bytes)))
         return bail(rc);
-    if ((rc = device_alloc((void **)&p->counters, 8 * 8, &p->bytes))) return bail(rc);
+    if ((rc = device_alloc((void **)&p->counters, 8 * CTR_WORDS, &p->bytes))) return bail(rc);
     if (ngr > 0) {
         if ((rc = device_alloc((void **)&p->gdesc_dev, sizeof(GroupDesc) * ngr, &p->bytes)))
             return bail(rc);

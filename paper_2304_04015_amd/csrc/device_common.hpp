@@ -18,6 +18,35 @@ __device__ __forceinline__ uint32_t entry_slot(const IndexView &ix, PhiloxKey ke
     return (uint32_t)(b + (int64_t)pick64(x.x, (uint64_t)P));
 }
 
+// Set of work counters that this block adds to.
+__device__ __forceinline__ unsigned long long *ctr_set(unsigned long long *counters) {
+    return counters + 8 * (1 + (blockIdx.x % CTR_SETS));
+}
+
+// Adds the lanes' work (moves, draws, meets, tail steps, pairs) to the
+// counters at `to`: the waves' sums meet in LDS, so a block makes one atomic
+// per counter.  Block-wide (blocks of up to 1024 threads).
+__device__ __forceinline__ void add_work(unsigned long long *to, uint32_t moves, uint32_t draws,
+                                         uint32_t meets, uint32_t tail, uint32_t pairs) {
+    __shared__ unsigned long long part[16][5];
+    unsigned long long w[5] = {moves, draws, meets, tail, pairs};
+#pragma unroll
+    for (int c = 0; c < 5; ++c)
+        for (int dd = 32; dd > 0; dd >>= 1) w[c] += __shfl_xor(w[c], dd, 64);
+    if ((threadIdx.x & 63) == 0)
+#pragma unroll
+        for (int c = 0; c < 5; ++c) part[threadIdx.x >> 6][c] = w[c];
+    __syncthreads();
+    static_assert(C_MOVES == 0 && C_DRAWS == 1 && C_MEETS == 2 && C_TAIL == 3 && C_PAIRS == 4,
+                  "one thread per counter");
+    if (threadIdx.x < 5) {
+        unsigned long long sum = 0;
+        for (uint32_t i = 0; i < (blockDim.x >> 6); ++i) sum += part[i][threadIdx.x];
+        if (sum) atomicAdd(&to[threadIdx.x], sum);
+    }
+    __syncthreads();
+}
+
 template <typename T>
 __device__ __forceinline__ T block_excl_sum(T x, T *total) {
     __shared__ T part[16];

@@ -575,21 +575,7 @@ __global__ __launch_bounds__(GROUP_BLOCK) void k_meet_group(const GroupDesc *__r
         }
     }
 
-    unsigned long long v0 = st_moves, v1 = st_draws, v2 = st_meets, v3 = st_tail, v4 = st_pairs;
-    for (int dd = 32; dd > 0; dd >>= 1) {
-        v0 += __shfl_xor(v0, dd, 64);
-        v1 += __shfl_xor(v1, dd, 64);
-        v2 += __shfl_xor(v2, dd, 64);
-        v3 += __shfl_xor(v3, dd, 64);
-        v4 += __shfl_xor(v4, dd, 64);
-    }
-    if (lane == 0) {
-        atomicAdd(&counters[C_MOVES], v0);
-        atomicAdd(&counters[C_DRAWS], v1);
-        atomicAdd(&counters[C_MEETS], v2);
-        atomicAdd(&counters[C_TAIL], v3);
-        atomicAdd(&counters[C_PAIRS], v4);
-    }
+    add_work(ctr_set(counters), st_moves, st_draws, st_meets, st_tail, st_pairs);
 }
 
 #ifndef SRK_GROUP_SLOTS_STITCHED

@@ -51,7 +51,7 @@ constexpr size_t NOALLOC_BYTES =
     align256(4 * 8) +                                   // meta
     align256(4 * (N_KINDS * 2 + N_KINDS)) +             // units (units_words(1))
     align256(NOALLOC_MAX_R) +                           // slen
-    align256(8 * 8) +                                   // counters
+    align256(8 * CTR_WORDS) +                           // counters
     align256(sizeof(QueryDesc));                        // desc
 
 Carve carve(char *base) {
@@ -70,7 +70,7 @@ Carve carve(char *base) {
     c.meta = (uint32_t *)take(4 * 8);
     c.units = (uint32_t *)take(4 * units_words(1));
     c.slen = (uint8_t *)take(NOALLOC_MAX_R);
-    c.counters = (unsigned long long *)take(8 * 8);
+    c.counters = (unsigned long long *)take(8 * CTR_WORDS);
     c.desc = (QueryDesc *)take(sizeof(QueryDesc));
     return c;
 }

@@ -25,14 +25,14 @@ namespace {
 
 __global__ void k_set_desc(QueryDesc *dst, QueryDesc d) { *dst = d; }
 
-// grid (x over nodes, y = query)
-__global__ void k_init(const QueryDesc *__restrict__ qd, unsigned long long *__restrict__ counters) {
+// grid (x over nodes, y = query); clears `words` words of counters
+__global__ void k_init(const QueryDesc *__restrict__ qd, unsigned long long *__restrict__ counters,
+                       int32_t words) {
     const QueryDesc &d = qd[blockIdx.y];
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (blockIdx.x == 0 && threadIdx.x < 8) {
-        d.meta[threadIdx.x] = 0u;
-        if (blockIdx.y == 0) counters[threadIdx.x] = 0ull;
-    }
+    if (blockIdx.x == 0 && threadIdx.x < 8) d.meta[threadIdx.x] = 0u;
+    if (blockIdx.x == 0 && blockIdx.y == 0)
+        for (int32_t w = threadIdx.x; w < words; w += blockDim.x) counters[w] = 0ull;
     if (strat_kind(d.kind)) {
         for (int64_t v = i; v < d.n; v += (int64_t)gridDim.x * blockDim.x) d.wsum[v] = 0ull;
     } else {
@@ -55,9 +55,15 @@ __device__ __forceinline__ void estimate_one(const QueryDesc &d, int64_t v) {
     if (d.out) d.out[v] = (v == d.s) ? 1.0 : (double)d.cnt[v] / (double)d.R;
 }
 
-// grid (x over nodes, y = query)
-__global__ void k_estimate(const QueryDesc *__restrict__ qd) {
+// grid (x over nodes, y = query); the last kernel of a launch sequence, it also
+// folds the sets of work counters into the totals.
+__global__ void k_estimate(const QueryDesc *__restrict__ qd, unsigned long long *__restrict__ counters) {
     const QueryDesc &d = qd[blockIdx.y];
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 8) {
+        unsigned long long sum = 0;
+        for (int i = 1; i <= CTR_SETS; ++i) sum += counters[8 * i + threadIdx.x];
+        counters[threadIdx.x] = sum;
+    }
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < d.n;
          v += (int64_t)gridDim.x * blockDim.x)
         estimate_one(d, v);
@@ -66,9 +72,11 @@ __global__ void k_estimate(const QueryDesc *__restrict__ qd) {
 // ------------------------------------------------------------ source walks
 // Walk (s, j) for j < R: positions 1..len as o() values.  Stratified: walk j
 // of s is the fixed-length walk generated in slot pi_s(j); its class goes to
-// scls[j].  grid (x over j, y = query)
+// scls[j].  grid (x over j, y = query); sets: the counters are a query set's
+// (CTR_SETS sets), else a ring entry's 8.
 __global__ __launch_bounds__(256) void k_source_walks(const QueryDesc *__restrict__ qd,
-                                                      unsigned long long *__restrict__ counters) {
+                                                      unsigned long long *__restrict__ counters,
+                                                      bool sets) {
     const QueryDesc &d = qd[blockIdx.y];
     const int32_t j = blockIdx.x * blockDim.x + threadIdx.x;
     uint32_t steps = 0;
@@ -119,7 +127,8 @@ __global__ __launch_bounds__(256) void k_source_walks(const QueryDesc *__restric
     }
     unsigned long long m64 = steps;
     for (int dd = 32; dd > 0; dd >>= 1) m64 += __shfl_xor(m64, dd, 64);
-    if ((threadIdx.x & 63) == 0 && m64) atomicAdd(&counters[C_SRC_MOVES], m64);
+    if ((threadIdx.x & 63) == 0 && m64)
+        atomicAdd(&(sets ? ctr_set(counters) : counters)[C_SRC_MOVES], m64);
 }
 
 // ------------------------------------------------------------ compaction
@@ -288,25 +297,10 @@ __device__ void ring_claim(const StreamRing &ring, int lane, uint32_t *o_slot, u
 // then clears); the block whose report completes the entry writes the
 // request's estimate and then its flag in host memory.  Block-wide.
 __device__ void ring_report(const StreamRing &ring, const QueryDesc &d, uint32_t slot,
-                            uint32_t tag, uint32_t units, int lane, uint32_t &st_moves,
+                            uint32_t tag, uint32_t units, uint32_t &st_moves,
                             uint32_t &st_draws, uint32_t &st_meets, uint32_t &st_tail,
                             uint32_t &st_pairs, uint32_t *s_last) {
-    unsigned long long w0 = st_moves, w1 = st_draws, w2 = st_meets, w3 = st_tail, w4 = st_pairs;
-    for (int dd = 32; dd > 0; dd >>= 1) {
-        w0 += __shfl_xor(w0, dd, 64);
-        w1 += __shfl_xor(w1, dd, 64);
-        w2 += __shfl_xor(w2, dd, 64);
-        w3 += __shfl_xor(w3, dd, 64);
-        w4 += __shfl_xor(w4, dd, 64);
-    }
-    unsigned long long *ec = ring.counters + (size_t)slot * 8;
-    if (lane == 0) {
-        if (w0) atomicAdd(&ec[C_MOVES], w0);
-        if (w1) atomicAdd(&ec[C_DRAWS], w1);
-        if (w2) atomicAdd(&ec[C_MEETS], w2);
-        if (w3) atomicAdd(&ec[C_TAIL], w3);
-        if (w4) atomicAdd(&ec[C_PAIRS], w4);
-    }
+    add_work(ring.counters + (size_t)slot * 8, st_moves, st_draws, st_meets, st_tail, st_pairs);
     st_moves = st_draws = st_meets = st_tail = st_pairs = 0;
     __threadfence();
     __syncthreads();
@@ -381,7 +375,7 @@ __global__ __launch_bounds__(meet_block_of(KIND)) void k_meet(const QueryDesc *_
             // the block reports the units it finished of a request, and their
             // work, once: when it moves on to another request or runs out
             if (acc_units && (nslot >= (uint32_t)RING_MAX || nseq != acc_tag)) {
-                ring_report(ring, qd[acc_slot], acc_slot, acc_tag, acc_units, lane,
+                ring_report(ring, qd[acc_slot], acc_slot, acc_tag, acc_units,
                             st_moves, st_draws, st_meets, st_tail, st_pairs, &s_last);
                 acc_units = 0;
             }
@@ -728,21 +722,7 @@ __global__ __launch_bounds__(meet_block_of(KIND)) void k_meet(const QueryDesc *_
     }
     if constexpr (STREAM) return;
 
-    unsigned long long v0 = st_moves, v1 = st_draws, v2 = st_meets, v3 = st_tail, v4 = st_pairs;
-    for (int dd = 32; dd > 0; dd >>= 1) {
-        v0 += __shfl_xor(v0, dd, 64);
-        v1 += __shfl_xor(v1, dd, 64);
-        v2 += __shfl_xor(v2, dd, 64);
-        v3 += __shfl_xor(v3, dd, 64);
-        v4 += __shfl_xor(v4, dd, 64);
-    }
-    if (lane == 0) {
-        atomicAdd(&counters[C_MOVES], v0);
-        atomicAdd(&counters[C_DRAWS], v1);
-        atomicAdd(&counters[C_MEETS], v2);
-        atomicAdd(&counters[C_TAIL], v3);
-        atomicAdd(&counters[C_PAIRS], v4);
-    }
+    add_work(ctr_set(counters), st_moves, st_draws, st_meets, st_tail, st_pairs);
 }
 
 // ------------------------------------------------------ walk materialisation
@@ -973,8 +953,8 @@ int launch_query_set(const QuerySet &qs, hipStream_t st, hipEvent_t ev_meet0, hi
     if (qs.nq <= 0) return SIMRANK_OK;
     const unsigned nq = (unsigned)qs.nq;
     const unsigned gx_n = std::min<unsigned>(grid_for(std::max(qs.max_n, 1), 256), 1024u);
-    k_init<<<dim3(gx_n, nq), 256, 0, st>>>(qs.desc, qs.counters);
-    k_source_walks<<<dim3(grid_for(qs.max_R, 256), nq), 256, 0, st>>>(qs.desc, qs.counters);
+    k_init<<<dim3(gx_n, nq), 256, 0, st>>>(qs.desc, qs.counters, CTR_WORDS);
+    k_source_walks<<<dim3(grid_for(qs.max_R, 256), nq), 256, 0, st>>>(qs.desc, qs.counters, true);
     k_compact<<<nq, 1024, 0, st>>>(qs.desc);
     k_unit_offsets<<<1, 1024, 0, st>>>(qs.desc, qs.nq, qs.units);
     if (ev_meet0) SRK_HIP(hipEventRecord(ev_meet0, st));
@@ -986,7 +966,7 @@ int launch_query_set(const QuerySet &qs, hipStream_t st, hipEvent_t ev_meet0, hi
         if (rc) return rc;
     }
     if (ev_meet1) SRK_HIP(hipEventRecord(ev_meet1, st));
-    k_estimate<<<dim3(gx_n, nq), 256, 0, st>>>(qs.desc);
+    k_estimate<<<dim3(gx_n, nq), 256, 0, st>>>(qs.desc, qs.counters);
     SRK_HIP(hipGetLastError());
     return SIMRANK_OK;
 }
@@ -1000,8 +980,8 @@ int enqueue_ring_request(const QueryDesc &d, const StreamRing &ring, int32_t slo
     unsigned long long *ctr = ring.counters + (size_t)slot * 8;
     const unsigned gx_n = std::min<unsigned>(grid_for(std::max(d.n, 1), 256), 1024u);
     k_set_desc<<<1, 1, 0, st>>>(qd, d);
-    k_init<<<dim3(gx_n, 1), 256, 0, st>>>(qd, ctr);
-    k_source_walks<<<dim3(grid_for(d.R, 256), 1), 256, 0, st>>>(qd, ctr);
+    k_init<<<dim3(gx_n, 1), 256, 0, st>>>(qd, ctr, 8);
+    k_source_walks<<<dim3(grid_for(d.R, 256), 1), 256, 0, st>>>(qd, ctr, false);
     k_compact<<<1, 256, 0, st>>>(qd);
     k_publish<<<1, 256, 0, st>>>(ring, slot, seq);
     SRK_HIP(hipGetLastError());
@@ -1174,7 +1154,7 @@ int workspace_init(const Graph *g, int32_t max_R, int32_t max_L, Workspace *ws) 
     if ((rc = device_alloc((void **)&ws->swc, 4 * RL, nullptr))) return rc;
     if ((rc = device_alloc((void **)&ws->tiles, 4 * ((size_t)ws->max_tiles + 1), nullptr))) return rc;
     if ((rc = device_alloc((void **)&ws->meta, 4 * 8, nullptr))) return rc;
-    if ((rc = device_alloc((void **)&ws->counters, 8 * 8, nullptr))) return rc;
+    if ((rc = device_alloc((void **)&ws->counters, 8 * CTR_WORDS, nullptr))) return rc;
     if ((rc = device_alloc((void **)&ws->desc, sizeof(QueryDesc), nullptr))) return rc;
     if ((rc = device_alloc((void **)&ws->units, 4 * units_words(1), nullptr))) return rc;
     if ((rc = device_alloc((void **)&ws->scls, (size_t)max_R, nullptr))) return rc;

@@ -743,7 +743,7 @@ extern "C" int simrank_server_create(simrank_graph *g, const simrank_server_para
         if (!rc) rc = device_alloc((void **)&gr.gdesc_dev, sizeof(GroupDesc), nullptr);
         if (!rc) rc = device_alloc((void **)&gr.units, 4 * units_words(gmax), nullptr);
         if (!rc) rc = device_alloc((void **)&gr.gunits, 4 * group_units_words(1), nullptr);
-        if (!rc) rc = device_alloc((void **)&gr.counters, 8 * 8, nullptr);
+        if (!rc) rc = device_alloc((void **)&gr.counters, 8 * CTR_WORDS, nullptr);
         hip(hipHostMalloc((void **)&gr.desc_host, sizeof(QueryDesc) * gmax, hipHostMallocDefault));
         hip(hipHostMalloc((void **)&gr.gdesc_host, sizeof(GroupDesc), hipHostMallocDefault));
         hip(hipHostMalloc((void **)&gr.tabs_host, sizeof(StratTab) * gmax, hipHostMallocDefault));
