@@ -307,11 +307,12 @@ __global__ __launch_bounds__(GROUP_BLOCK) void k_meet_group(const GroupDesc *__r
         const uint32_t chunk = local - tile * (uint32_t)n_chunks;
         const PhiloxKey key{uni(d.k0), uni(d.k1)};
         const uint32_t T = uni(d.T);
+        const GlobalPtr<uint64_t> E = gp_uni((const uint64_t *)d.E);
         const uint32_t gmask = G >= 32 ? 0xffffffffu : (1u << G) - 1u;
         const uint32_t NN = uni((uint32_t)d.Rmax), sa = uni((uint32_t)d.sa), sb = uni((uint32_t)d.sb);
         const int32_t phi = (int32_t)uni((uint32_t)d.L);
         if ((uint32_t)gi != cur_g || tile != cur_tile) {
-            const uint32_t k0 = d.tiles[tile], k1 = d.tiles[tile + 1];
+            const uint32_t k0 = uni(d.tiles[tile]), k1 = uni(d.tiles[tile + 1]);
             const uint32_t nb = d.joff[k0], ne = d.joff[k1];
             K = k1 - k0;
             for (uint32_t i = threadIdx.x; i < K; i += blockDim.x) {
@@ -332,7 +333,7 @@ __global__ __launch_bounds__(GROUP_BLOCK) void k_meet_group(const GroupDesc *__r
             cur_tile = tile;
         }
         const int32_t vbase = (int32_t)chunk * vb;
-        const uint32_t nv = (uint32_t)min(vb, d.n_active - vbase);
+        const uint32_t nv = uni((uint32_t)min(vb, d.n_active - vbase));
         if (STRAT)
             for (uint32_t i = threadIdx.x; i < GM * VBW; i += blockDim.x) s_w[i] = 0ull;
         else
@@ -350,7 +351,9 @@ __global__ __launch_bounds__(GROUP_BLOCK) void k_meet_group(const GroupDesc *__r
         __syncthreads();
 
         // item i = vl * K + k for node vl < nv and entry k < K
-        const uint32_t total = nv * K;
+        // (K and nv are the same in all lanes; said so, the refill's bookkeeping
+        // stays in scalar registers)
+        const uint32_t total = nv * uni(K);
         uint32_t ci = 0, ce = 0, cvl = 0, ck = 0;
         bool drained = false;
         GSlot<GW> sl[NS];
@@ -465,7 +468,7 @@ __global__ __launch_bounds__(GROUP_BLOCK) void k_meet_group(const GroupDesc *__r
             int64_t tb[NS], te[NS];
 #pragma unroll
             for (int qq = 0; qq < NS; ++qq) {
-                if (go[qq]) e[qq] = load_edge(d.E + at[qq]);
+                if (go[qq]) e[qq] = load_edge(E, at[qq]);
                 if (STITCHED && sl[qq].busy && sl[qq].ph) {
                     const GSlot<GW> &w = sl[qq];
                     switch (w.ph) {

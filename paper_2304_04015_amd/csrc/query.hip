@@ -411,11 +411,12 @@ __global__ __launch_bounds__(meet_block_of(KIND)) void k_meet(const QueryDesc *_
         const uint32_t chunk = local - tile * (uint32_t)n_chunks;
         const PhiloxKey key{uni(d.k0), uni(d.k1)};
         const uint32_t T = uni(d.T);
+        const GlobalPtr<uint64_t> E = gp_uni((const uint64_t *)d.E);
         const int32_t src = (int32_t)uni((uint32_t)d.s);
         const uint32_t NN = uni((uint32_t)d.R), sa = uni((uint32_t)d.sa), sb = uni((uint32_t)d.sb);
         const int32_t phi = (int32_t)uni((uint32_t)d.L);
         if (tag != cur_q || tile != cur_tile) {
-            const uint32_t k0 = d.tiles[tile], k1 = d.tiles[tile + 1];
+            const uint32_t k0 = uni(d.tiles[tile]), k1 = uni(d.tiles[tile + 1]);
             const uint32_t nb = d.joff[k0], ne = d.joff[k1];
             K = k1 - k0;
             for (uint32_t i = threadIdx.x; i < K; i += blockDim.x) {
@@ -433,7 +434,7 @@ __global__ __launch_bounds__(meet_block_of(KIND)) void k_meet(const QueryDesc *_
             cur_tile = tile;
         }
         const int32_t vbase = (int32_t)chunk * vb;
-        const uint32_t nv = (uint32_t)min(vb, d.n_active - vbase);
+        const uint32_t nv = uni((uint32_t)min(vb, d.n_active - vbase));
         for (uint32_t i = threadIdx.x; i < MEET_VB; i += blockDim.x) {
             if (STRAT) s_w[i] = 0ull; else s_cnt[i] = 0u;
             if (i < nv) {
@@ -447,7 +448,9 @@ __global__ __launch_bounds__(meet_block_of(KIND)) void k_meet(const QueryDesc *_
         __syncthreads();
 
         // Pairs of the unit: item i = vl * K + k for node vl < nv and walk k < K.
-        const uint32_t total = nv * K;
+        // (K and nv are the same in all lanes; said so, the refill's bookkeeping
+        // stays in scalar registers)
+        const uint32_t total = nv * uni(K);
         // wave-uniform chunk of items [ci, ce) and the (node, walk) of item ci
         uint32_t ci = 0, ce = 0, cvl = 0, ck = 0;
         bool drained = false;
@@ -659,7 +662,7 @@ __global__ __launch_bounds__(meet_block_of(KIND)) void k_meet(const QueryDesc *_
             uint2 e[NS];
 #pragma unroll
             for (int qq = 0; qq < NS; ++qq)
-                if (go[qq]) e[qq] = load_edge(d.E + at[qq]);
+                if (go[qq]) e[qq] = load_edge(E, at[qq]);
             bool tails[NS];
 #pragma unroll
             for (int qq = 0; qq < NS; ++qq) tails[qq] = false;
