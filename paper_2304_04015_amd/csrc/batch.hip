@@ -190,10 +190,9 @@ extern "C" int simrank_batch_plan_create_ex(simrank_graph *const *graphs, int32_
         for (int32_t i = 0; i < nq; ++i) {
             if (group_of[i] >= 0) continue;
             const Graph *g = graphs[qs[i].graph];
-            const int64_t vb = default_unit_nodes(g);
             const int kind = modes[i] == SIMRANK_MODE_STITCHED ? K_STITCHED
                              : modes[i] == SIMRANK_MODE_STRATIFIED ? K_STRAT : K_PLAIN;
-            kind_units[kind] += (int64_t)max_tiles_for(ps[i].R, ps[i].L) * ((g->n_active + vb - 1) / vb);
+            kind_units[kind] += units_bound_of(g, ps[i].R, ps[i].L);
         }
         for (int k = 0; k < N_KINDS; ++k)
             if (kind_units[k] >= (int64_t)0xffffffffu - (1 << 20))
@@ -252,7 +251,7 @@ extern "C" int simrank_batch_plan_create_ex(simrank_graph *const *graphs, int32_
         const simrank_graph *g = graphs[qs[i].graph];
         const simrank_params &pp = ps[i];
         QueryDesc &d = p->desc[i];
-        describe_query(g, &qs[i], pp, modes[i], default_unit_nodes(g), &d);
+        describe_query(g, &qs[i], pp, modes[i], &d);
         carve_request(pp, modes[i], g->n, take(request_bytes(pp, modes[i], g->n)), &d);
         if (modes[i] == SIMRANK_MODE_STRATIFIED) {
             StratParams sp;
@@ -272,8 +271,7 @@ extern "C" int simrank_batch_plan_create_ex(simrank_graph *const *graphs, int32_
             d.kind = d.kind == K_STITCHED ? K_GROUPED_STITCHED   // walked with its group
                      : d.kind == K_STRAT  ? K_GROUPED_STRAT : K_GROUPED;
         } else {
-            const int64_t ub = (int64_t)max_tiles_for(pp.R, pp.L) * d.n_chunks;
-            set.units_bound[d.kind] += ub;
+            set.units_bound[d.kind] += units_bound_of(g, pp.R, pp.L);
         }
     }
     GroupSet gset;

@@ -171,19 +171,18 @@ struct QueryDesc {
     const int32_t *active;
     IndexView ix;
     uint32_t *sw;          // [R][L] source walk positions 1..L (o values)
-    uint8_t *slen;         // [R]
+    uint8_t *slen;         // [R rounded up to 256]; after the compaction the tiles' first units
     uint32_t *jj;          // [R] walk index of compact entry k
     uint32_t *joff;        // [R + 1] start of entry k in swc
     uint32_t *swc;         // [R * L] packed positions
     uint32_t *tiles;       // [max tiles + 1]
-    uint32_t *meta;        // [8]: R1, packed positions, tiles
+    uint32_t *meta;        // [8]: R1, packed positions, tiles, entries of the largest tile
     uint32_t *cnt;         // [n] meet counts (caller's; plain and stitched)
     double *out;           // [n] estimate or NULL
     uint32_t k0, k1;       // Philox key of the query's walks
     uint32_t T;            // continue threshold
     int32_t n, n_active, s, R, L;
-    int32_t vb;            // nodes per work unit (<= MEET_VB)
-    int32_t n_chunks;      // ceil(n_active / vb)
+    int32_t vb;            // nodes per work unit at most (<= MEET_VB); 0: sized on the device
     int32_t kind;          // Kind
     int32_t tile_j;        // source walks per LDS tile, MIN_TILE_J .. tile_j_of(kind)
     // stratified only (R = N walks per node, L = phi)
@@ -405,11 +404,16 @@ int query_params(const simrank_query *q, int32_t n, simrank_params *out, int *mo
 // Stratified estimator: z, N, phi, shuffle width and (if tab) the class table.
 int strat_params(const simrank_query *q, int32_t n, StratParams *sp, StratTab *tab);
 int32_t max_tiles_for(int32_t R, int32_t L);
+// Nodes per unit that the unit counts of a query are bounded with; a graph that
+// was not tuned has its units sized on the device (lay_units, query.hip).
 int32_t default_unit_nodes(const Graph *g);
+// Work units of a query with nominal nodes per unit, which the launch limits
+// are stated in; lay_units makes at most one per tile and 2^14 a launch more.
+int64_t units_bound_of(const Graph *g, int32_t R, int32_t L);
 IndexView index_view(const Graph *g);
 // Fills everything but the buffers (sw .. out) of a descriptor.
 void describe_query(const Graph *g, const simrank_query *q, const simrank_params &p, int mode,
-                    int32_t vb, QueryDesc *d);
+                    QueryDesc *d);
 // Enqueues init, source walks, compaction, unit offsets, meet and estimate for
 // every query of the set; records ev_meet0 / ev_meet1 (may be NULL) around the
 // meet kernels.

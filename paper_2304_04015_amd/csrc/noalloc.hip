@@ -137,7 +137,7 @@ extern "C" int simrank_single_source_noalloc(const simrank_graph *g, const simra
     const Carve c = carve(base);
 
     QueryDesc d;
-    describe_query(g, q, p, mode, default_unit_nodes(g), &d);
+    describe_query(g, q, p, mode, &d);
     d.sw = c.sw;
     d.slen = c.slen;
     d.jj = c.jj;
@@ -148,7 +148,7 @@ extern "C" int simrank_single_source_noalloc(const simrank_graph *g, const simra
     d.cnt = counts_dev;
     d.out = out_dev;
     // the meet kernel counts work units (tile x node chunk) in 32 bits
-    const int64_t units_bound = (int64_t)max_tiles_for(d.R, d.L) * d.n_chunks;
+    const int64_t units_bound = units_bound_of(g, d.R, d.L);
     if (units_bound >= (int64_t)0xffffffffu - (1 << 20))
         return fail(SIMRANK_EINVAL, "R * L * n too large for one launch");
     QuerySet qs;

@@ -176,26 +176,166 @@ __global__ __launch_bounds__(1024) void k_compact(const QueryDesc *__restrict__ 
             d.meta[1] = total;
             d.meta[2] = n_tiles;
         }
+        uint32_t km = 0;
+        for (uint32_t t = threadIdx.x; t < n_tiles; t += 64)
+            km = max(km, (t + 1 < n_tiles ? d.tiles[t + 1] : R1) - d.tiles[t]);
+        for (int dd = 32; dd > 0; dd >>= 1) km = max(km, __shfl_xor(km, dd, 64));
+        if (threadIdx.x == 0) d.meta[3] = km;
     }
 }
 
-// Work-unit offsets of the queries (one block): one list of nq + 1 offsets per
-// kind (a query of another kind has no units in a list), then one cursor per
-// kind.
+// ------------------------------------------------------------ work units
+//
+// A unit is a tile of a query's source walks and a run of its nodes with
+// in-edges; a persistent block takes one at a time.  A unit costs a block 10
+// to 25 us beside its pairs (claim, staging, the wait for its longest pair),
+// and the grid waits for the block that ends last.  Unless the graph was
+// tuned, the units of a launch therefore all hold about the same number of
+// pairs, such that every block of the grid takes a whole number of rounds of
+// them: one round per 2^27 pairs (about 0.5 ms of work), 16 at most, more only
+// where MEET_VB nodes a unit ask for it.  Meet kernel, with units of a fixed
+// number of nodes by graph size (256 from 2^19 nodes with in-edges, 128, 64,
+// 32 below) and with this rule: n = 500, R = 2,000: 96 and 32 us; n = 5,003,
+// R = 1,521: 98 and 61; R = 9,502: 404 and 264; n = 40,000, R = 1,521: 386 and
+// 303; R = 9,502: 1,738 and 1,680; n = 150,001, R = 9,502: 6,108 and 6,061;
+// n = 2^18: 11.56 and 11.65 ms; n = 2^20: 50.3 ms both.
+constexpr int UNIT_ROUNDS_LOG2_PAIRS = 27, UNIT_MAX_ROUNDS = 16;
+
+// First unit of each tile and, behind them, the number of units: kept where the
+// lengths of the source walks were, which only the compaction before reads.
+// The max_tiles_for + 1 words fit there: 4 (3 + R / 2048 + R L / (20480 - L))
+// bytes are fewer than R rounded up to 256, for every R and L up to MAX_CAP.
+__device__ __forceinline__ uint32_t *tunits_of(const QueryDesc &d) {
+    return reinterpret_cast<uint32_t *>(d.slen);
+}
+
+// Rounds of units that a launch of `pairs` pairs on `grid` blocks is cut into,
+// its largest tile holding km walks.
+__device__ __forceinline__ uint64_t unit_rounds(uint64_t pairs, uint32_t km, uint32_t grid) {
+    const uint64_t by_work = (pairs + ((1ull << UNIT_ROUNDS_LOG2_PAIRS) - 1)) >> UNIT_ROUNDS_LOG2_PAIRS;
+    const uint64_t rounds = by_work < 1 ? 1 : by_work > UNIT_MAX_ROUNDS ? UNIT_MAX_ROUNDS : by_work;
+    const uint64_t full = (uint64_t)MEET_VB * max(km, 1u) * grid;   // a round of full units
+    const uint64_t least = (pairs + full - 1) / full;
+    return rounds < least ? least : rounds;
+}
+
+__device__ __forceinline__ uint64_t pairs_each(uint64_t pairs, uint64_t units) {
+    const uint64_t per = units ? (pairs + units - 1) / units : pairs;
+    return per < 1 ? 1 : per;
+}
+
+// Pairs per unit of the queries of a kind in qd[0 .. nq).  A tile of few walks
+// reaches MEET_VB nodes a unit below the common number of pairs, so it has more
+// units than its share; the other tiles then take that many fewer.  Called by
+// all lanes of one wave; results uniform.
+__device__ uint64_t unit_pairs(const QueryDesc *qd, int32_t nq, int32_t kind, uint64_t pairs,
+                               uint32_t km, uint32_t grid, int lane) {
+    uint64_t units = unit_rounds(pairs, km, grid) * grid;
+    uint64_t per = pairs_each(pairs, units);
+    for (int it = 0; it < 3; ++it) {
+        unsigned long long small_pairs = 0, small_units = 0;
+        for (int32_t q = 0; q < nq; ++q) {
+            if (qd[q].kind != kind) continue;
+            const uint32_t n = (uint32_t)qd[q].n_active, nt = qd[q].meta[2];
+            const uint64_t least = (n + MEET_VB - 1) / MEET_VB;
+            for (uint32_t t = (uint32_t)lane; t < nt; t += 64) {
+                const uint64_t p = (uint64_t)n * (qd[q].tiles[t + 1] - qd[q].tiles[t]);
+                if (p < least * per) {
+                    small_pairs += p;
+                    small_units += least;
+                }
+            }
+        }
+        for (int dd = 32; dd > 0; dd >>= 1) {
+            small_pairs += __shfl_xor(small_pairs, dd, 64);
+            small_units += __shfl_xor(small_units, dd, 64);
+        }
+        if (small_units == 0ull || small_pairs >= pairs) break;
+        while (units < small_units + grid / 2) units += grid;   // room for the others
+        per = pairs_each(pairs - small_pairs, units - small_units);
+    }
+    return per;
+}
+
+// Lays the units of query d, `per` pairs each where the graph is not tuned:
+// writes the first unit of each tile and returns their number.  Called by all
+// lanes of one wave.
+__device__ uint32_t lay_units(const QueryDesc &d, uint64_t per, int lane) {
+    const uint32_t nt = d.meta[2], n = (uint32_t)d.n_active;
+    const uint32_t vb = d.vb > 0 ? (uint32_t)d.vb : (uint32_t)MEET_VB;
+    uint32_t first = 0;
+    for (uint32_t t0 = 0; t0 < nt; t0 += 64) {
+        const uint32_t t = t0 + (uint32_t)lane;
+        uint32_t c = 0;
+        if (t < nt) {
+            c = (n + vb - 1) / vb;
+            if (d.vb <= 0 && n) {
+                const uint64_t want = (uint64_t)n * (d.tiles[t + 1] - d.tiles[t]) / per;
+                c = max(c, (uint32_t)min(want, (uint64_t)n));
+            }
+        }
+        uint32_t inc = c;
+        for (int dd = 1; dd < 64; dd <<= 1) {
+            const uint32_t y = __shfl_up(inc, dd, 64);
+            if (lane >= dd) inc += y;
+        }
+        if (t < nt) tunits_of(d)[t] = first + inc - c;
+        first += __shfl(inc, 63, 64);
+    }
+    if (lane == 0) tunits_of(d)[nt] = first;
+    return first;
+}
+
+// Units of the queries (one block): each query's tiles, then one list of
+// nq + 1 offsets per kind (a query of another kind has no units in a list) and
+// one cursor per kind.  grid: blocks of each kind's meet launch.
 __global__ __launch_bounds__(1024) void k_unit_offsets(const QueryDesc *__restrict__ qd, int32_t nq,
-                                                       uint32_t *__restrict__ units) {
+                                                       uint32_t *units, uint3 grid) {
+    __shared__ unsigned long long s_pairs[N_KINDS], s_per[N_KINDS];
+    __shared__ uint32_t s_km[N_KINDS];
+    if (threadIdx.x < N_KINDS) {
+        s_pairs[threadIdx.x] = 0ull;
+        s_km[threadIdx.x] = 0u;
+    }
+    __syncthreads();
+    for (int32_t q = threadIdx.x; q < nq; q += blockDim.x) {
+        const int32_t kind = qd[q].kind;
+        if (kind >= N_KINDS) continue;
+        atomicAdd(&s_pairs[kind], (unsigned long long)qd[q].meta[0] * (unsigned long long)qd[q].n_active);
+        atomicMax(&s_km[kind], qd[q].meta[3]);
+    }
+    __syncthreads();
+    if (threadIdx.x < 64 * N_KINDS) {
+        // (many queries in one launch have units of all sizes: their common
+        // number of pairs is not refined)
+        const int kind = (int)(threadIdx.x >> 6);
+        const uint64_t p = unit_pairs(qd, nq <= 16 ? nq : 0, kind, s_pairs[kind], s_km[kind],
+                                      kind == 0 ? grid.x : kind == 1 ? grid.y : grid.z,
+                                      (int)(threadIdx.x & 63));
+        if ((threadIdx.x & 63) == 0) s_per[kind] = p;
+    }
+    __syncthreads();
+    for (int32_t q = threadIdx.x >> 6; q < nq; q += (int32_t)(blockDim.x >> 6)) {
+        const int32_t kind = qd[q].kind;
+        uint32_t total = 0;
+        if (kind < N_KINDS) total = lay_units(qd[q], s_per[kind], (int)(threadIdx.x & 63));
+        if ((threadIdx.x & 63) < N_KINDS)
+            units[(threadIdx.x & 63) * (nq + 1) + q] = (int32_t)(threadIdx.x & 63) == kind ? total : 0u;
+    }
+    __threadfence_block();
+    __syncthreads();
     const int32_t per = (nq + blockDim.x - 1) / blockDim.x;
     const int32_t q0 = min(nq, (int32_t)threadIdx.x * per), q1 = min(nq, q0 + per);
     for (int list = 0; list < N_KINDS; ++list) {
+        uint32_t *u = units + list * (nq + 1);
         uint32_t sum = 0;
-        for (int32_t q = q0; q < q1; ++q)
-            if (qd[q].kind == list) sum += qd[q].meta[2] * (uint32_t)qd[q].n_chunks;
+        for (int32_t q = q0; q < q1; ++q) sum += u[q];
         uint32_t total;
         uint32_t run = block_excl_sum(sum, &total);
-        uint32_t *u = units + list * (nq + 1);
         for (int32_t q = q0; q < q1; ++q) {
+            const uint32_t x = u[q];
             u[q] = run;
-            if (qd[q].kind == list) run += qd[q].meta[2] * (uint32_t)qd[q].n_chunks;
+            run += x;
         }
         if (threadIdx.x == 0) {
             u[nq] = total;
@@ -207,7 +347,7 @@ __global__ __launch_bounds__(1024) void k_unit_offsets(const QueryDesc *__restri
 // ------------------------------------------------------------ meet kernel
 //
 // Persistent blocks take work units from a device cursor.  A unit is (query,
-// tile of its source walks, chunk of vb of its nodes with in-edges); the units
+// tile of its source walks, run of its nodes with in-edges); the units
 // of all queries of a launch form one list, so queries on graphs of any size
 // share the launch and its tail.  A block stages its tile (walk ids, packed
 // positions) in LDS once and keeps it while consecutive units share it, and
@@ -272,7 +412,9 @@ __device__ void ring_claim(const StreamRing &ring, int lane, uint32_t *o_slot, u
         const int best = (int)(uint32_t)key;
         const unsigned long long cb = __shfl(c, best, 64);
         const uint32_t left = (uint32_t)cb;
-        const uint32_t take = min(RING_RUN, left);
+        // runs shorten towards a request's end, so that its last units spread
+        // over the blocks
+        const uint32_t take = min(RING_RUN, max(1u, left / (2u * gridDim.x)));
         bool won = false;
         if (lane == 0) {
             unsigned long long expect = cb;
@@ -405,10 +547,15 @@ __global__ __launch_bounds__(meet_block_of(KIND)) void k_meet(const QueryDesc *_
         const uint32_t local = STREAM ? unit : unit - ustart[q];
         const uint32_t tag = STREAM ? tag_s : (uint32_t)q;
         const QueryDesc &d = qd[q];
-        const int32_t n_chunks = (int32_t)uni((uint32_t)d.n_chunks);
-        const int32_t vb = (int32_t)uni((uint32_t)d.vb);
-        const uint32_t tile = local / (uint32_t)n_chunks;
-        const uint32_t chunk = local - tile * (uint32_t)n_chunks;
+        // tile of the unit: the last one that starts at or before it (a tile
+        // of a query with units has at least one)
+        uint32_t tile = 0, tile_hi = uni(d.meta[2]);
+        while (tile_hi - tile > 1) {
+            const uint32_t mid = (tile + tile_hi) >> 1;
+            if (uni(tunits_of(d)[mid]) <= local) tile = mid; else tile_hi = mid;
+        }
+        const uint32_t unit0 = uni(tunits_of(d)[tile]);
+        const uint32_t chunks = uni(tunits_of(d)[tile + 1]) - unit0, chunk = local - unit0;
         const PhiloxKey key{uni(d.k0), uni(d.k1)};
         const uint32_t T = uni(d.T);
         const GlobalPtr<uint64_t> E = gp_uni((const uint64_t *)d.E);
@@ -433,8 +580,10 @@ __global__ __launch_bounds__(meet_block_of(KIND)) void k_meet(const QueryDesc *_
             cur_q = tag;
             cur_tile = tile;
         }
-        const int32_t vbase = (int32_t)chunk * vb;
-        const uint32_t nv = uni((uint32_t)min(vb, d.n_active - vbase));
+        // the tile's units split the nodes evenly
+        const uint32_t na = uni((uint32_t)d.n_active), nq0 = na / chunks, nrem = na - nq0 * chunks;
+        const int32_t vbase = (int32_t)(chunk * nq0 + min(chunk, nrem));
+        const uint32_t nv = nq0 + (chunk < nrem ? 1u : 0u);
         for (uint32_t i = threadIdx.x; i < MEET_VB; i += blockDim.x) {
             if (STRAT) s_w[i] = 0ull; else s_cnt[i] = 0u;
             if (i < nv) {
@@ -852,7 +1001,7 @@ int meet_grid_blocks() {
 
 template <int KIND, int NS>
 void launch_meet(const QuerySet &qs, hipStream_t st) {
-    const int blocks = (int)std::min<int64_t>(qs.units_bound[KIND], meet_grid_blocks<KIND, NS, false>());
+    const int blocks = meet_grid_blocks<KIND, NS, false>();
     const uint32_t *ustart = qs.units + (size_t)KIND * (qs.nq + 1);
     uint32_t *cursor = qs.units + (size_t)N_KINDS * (qs.nq + 1) + KIND;
     k_meet<KIND, NS, false><<<blocks, meet_block_of(KIND), 0, st>>>(qs.desc, qs.nq, ustart, cursor,
@@ -866,12 +1015,21 @@ void launch_meet_ring(const StreamRing &ring, hipStream_t st) {
 }
 
 // Publication of a ring entry, the last kernel of its request's preparation:
-// the entry's unit count (tiles x node chunks, from the compaction), then its
-// (seq, 0) claim word.  A request with nothing to walk is finished here:
+// its units (for meet launches of `grid` blocks) and their count, then its
+// claim word.  A request with nothing to walk is finished here:
 // estimate, then its flag.  One block.
-__global__ __launch_bounds__(256) void k_publish(StreamRing ring, int32_t slot, uint32_t seq) {
+__global__ __launch_bounds__(256) void k_publish(StreamRing ring, int32_t slot, uint32_t seq,
+                                                 uint32_t grid) {
     const QueryDesc &d = ring.desc[slot];
-    const uint32_t nu = d.meta[2] * (uint32_t)d.n_chunks;
+    __shared__ uint32_t s_nu;
+    if (threadIdx.x < 64) {
+        const uint64_t pairs = (uint64_t)d.meta[0] * (uint64_t)(uint32_t)d.n_active;
+        const uint32_t nu = lay_units(
+            d, unit_pairs(&d, 1, d.kind, pairs, d.meta[3], grid, (int)threadIdx.x), (int)threadIdx.x);
+        if (threadIdx.x == 0) s_nu = nu;
+    }
+    __syncthreads();
+    const uint32_t nu = s_nu;
     if (nu > 0u) {
         if (threadIdx.x == 0) {
             RingCtl &c = ring.ctl[slot];
@@ -918,8 +1076,8 @@ int32_t max_tiles_for(int32_t R, int32_t L) {
     return (int32_t)(2 + R / TJ + ((int64_t)R * L) / NW);
 }
 
-// Nodes per work unit: small graphs use small chunks so that their units
-// still spread over all CUs; simrank_tune replaces this by a measured choice.
+// Nodes per work unit that unit counts are bounded with (the tuner's choice, if
+// any; else a nominal one by graph size).
 int32_t default_unit_nodes(const Graph *g) {
     if (g->tuned_vb > 0) return g->tuned_vb;
     if (g->n_active >= (1 << 19)) return 256;
@@ -928,8 +1086,13 @@ int32_t default_unit_nodes(const Graph *g) {
     return 32;
 }
 
+int64_t units_bound_of(const Graph *g, int32_t R, int32_t L) {
+    const int64_t vb = default_unit_nodes(g);
+    return (int64_t)max_tiles_for(R, L) * ((g->n_active + vb - 1) / vb);
+}
+
 void describe_query(const Graph *g, const simrank_query *q, const simrank_params &p, int mode,
-                    int32_t vb, QueryDesc *d) {
+                    QueryDesc *d) {
     *d = QueryDesc{};
     d->nodes = g->nodes;
     d->E = g->E;
@@ -944,8 +1107,7 @@ void describe_query(const Graph *g, const simrank_query *q, const simrank_params
     d->s = q->s;
     d->R = p.R;
     d->L = p.L;
-    d->vb = vb;
-    d->n_chunks = (g->n_active + vb - 1) / vb;
+    d->vb = g->tuned_vb;
     d->kind = mode == SIMRANK_MODE_STITCHED ? K_STITCHED
               : mode == SIMRANK_MODE_STRATIFIED ? K_STRAT : K_PLAIN;
     const int32_t tj = g->tuned_tile_j[d->kind];
@@ -959,7 +1121,10 @@ int launch_query_set(const QuerySet &qs, hipStream_t st, hipEvent_t ev_meet0, hi
     k_init<<<dim3(gx_n, nq), 256, 0, st>>>(qs.desc, qs.counters, CTR_WORDS);
     k_source_walks<<<dim3(grid_for(qs.max_R, 256), nq), 256, 0, st>>>(qs.desc, qs.counters, true);
     k_compact<<<nq, 1024, 0, st>>>(qs.desc);
-    k_unit_offsets<<<1, 1024, 0, st>>>(qs.desc, qs.nq, qs.units);
+    const uint3 grid = make_uint3((uint32_t)meet_grid_blocks<K_PLAIN, SRK_MEET_SLOTS, false>(),
+                                  (uint32_t)meet_grid_blocks<K_STITCHED, SRK_MEET_SLOTS_STITCHED, false>(),
+                                  (uint32_t)meet_grid_blocks<K_STRAT, SRK_MEET_SLOTS_STRAT, false>());
+    k_unit_offsets<<<1, 1024, 0, st>>>(qs.desc, qs.nq, qs.units, grid);
     if (ev_meet0) SRK_HIP(hipEventRecord(ev_meet0, st));
     if (qs.units_bound[K_PLAIN] > 0) launch_meet<K_PLAIN, SRK_MEET_SLOTS>(qs, st);
     if (qs.units_bound[K_STITCHED] > 0) launch_meet<K_STITCHED, SRK_MEET_SLOTS_STITCHED>(qs, st);
@@ -974,6 +1139,13 @@ int launch_query_set(const QuerySet &qs, hipStream_t st, hipEvent_t ev_meet0, hi
     return SIMRANK_OK;
 }
 
+// Blocks of a kind's persistent serving kernel.
+static uint32_t ring_grid(int kind) {
+    return (uint32_t)(kind == K_PLAIN      ? meet_grid_blocks<K_PLAIN, SRK_MEET_SLOTS, true>()
+                      : kind == K_STITCHED ? meet_grid_blocks<K_STITCHED, SRK_MEET_SLOTS_STITCHED, true>()
+                                           : meet_grid_blocks<K_STRAT, SRK_MEET_SLOTS_STRAT, true>());
+}
+
 // Preparation of a served request in ring entry `slot`.  Every kernel is
 // small (one wave per SIMD at most) so that it fits beside a running
 // persistent meet kernel on the same CUs.
@@ -986,7 +1158,7 @@ int enqueue_ring_request(const QueryDesc &d, const StreamRing &ring, int32_t slo
     k_init<<<dim3(gx_n, 1), 256, 0, st>>>(qd, ctr, 8);
     k_source_walks<<<dim3(grid_for(d.R, 256), 1), 256, 0, st>>>(qd, ctr, false);
     k_compact<<<1, 256, 0, st>>>(qd);
-    k_publish<<<1, 256, 0, st>>>(ring, slot, seq);
+    k_publish<<<1, 256, 0, st>>>(ring, slot, seq, ring_grid(d.kind));
     SRK_HIP(hipGetLastError());
     return SIMRANK_OK;
 }
@@ -1151,7 +1323,7 @@ int workspace_init(const Graph *g, int32_t max_R, int32_t max_L, Workspace *ws) 
     const size_t RL = (size_t)max_R * (size_t)max_L;
     int rc;
     if ((rc = device_alloc((void **)&ws->sw, 4 * RL, nullptr))) return rc;
-    if ((rc = device_alloc((void **)&ws->slen, (size_t)max_R, nullptr))) return rc;
+    if ((rc = device_alloc((void **)&ws->slen, align256((size_t)max_R), nullptr))) return rc;
     if ((rc = device_alloc((void **)&ws->jj, 4 * (size_t)max_R, nullptr))) return rc;
     if ((rc = device_alloc((void **)&ws->joff, 4 * ((size_t)max_R + 1), nullptr))) return rc;
     if ((rc = device_alloc((void **)&ws->swc, 4 * RL, nullptr))) return rc;
@@ -1197,7 +1369,7 @@ void workspace_release(Workspace *ws) {
 // One query on a workspace: its descriptor, then the whole launch sequence.
 static int launch_single(const Graph *g, Workspace *ws, const QueryDesc &d, hipStream_t st) {
     // the meet kernel counts work units (tile x node chunk) in 32 bits
-    const int64_t units_bound = (int64_t)max_tiles_for(d.R, d.L) * d.n_chunks;
+    const int64_t units_bound = units_bound_of(g, d.R, d.L);
     if (units_bound >= (int64_t)0xffffffffu - (1 << 20))
         return fail(SIMRANK_EINVAL, "R * L * n too large for one launch");
     QuerySet qs;
@@ -1248,7 +1420,7 @@ int enqueue_query(const Graph *g, const simrank_query *q, const simrank_params &
     if (stitched && g->index->T != p.T)
         return fail(SIMRANK_EINVAL, "stitched query's c differs from the index's c");
     QueryDesc d;
-    describe_query(g, q, p, mode, default_unit_nodes(g), &d);
+    describe_query(g, q, p, mode, &d);
     attach_buffers(ws, &d);
     d.cnt = counts_dev;
     d.out = out_dev;
@@ -1269,7 +1441,7 @@ int enqueue_stratified(const Graph *g, const simrank_query *q, Workspace *ws, do
         return fail(SIMRANK_EINVAL, "query needs N or phi beyond the workspace's size");
     simrank_params p{sp.N, sp.phi, 0u, 0};
     QueryDesc d;
-    describe_query(g, q, p, SIMRANK_MODE_STRATIFIED, default_unit_nodes(g), &d);
+    describe_query(g, q, p, SIMRANK_MODE_STRATIFIED, &d);
     attach_buffers(ws, &d);
     d.wsum = wsum_dev;
     d.out = out_dev;

@@ -285,7 +285,7 @@ static bool reserve(simrank_server *S, Request *r, bool lone) {
     r->mem_bytes = bytes;
     r->slot = slot;
     if (lone) S->slot_req[slot] = r;
-    describe_query(S->g, &r->q, r->p, r->mode, default_unit_nodes(S->g), &r->d);
+    describe_query(S->g, &r->q, r->p, r->mode, &r->d);
     carve_request(r->p, r->mode, S->g->n, S->pool + off, &r->d);
     ++S->inflight;
     S->inflight_peak = std::max(S->inflight_peak, S->inflight);
