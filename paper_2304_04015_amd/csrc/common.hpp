@@ -414,10 +414,13 @@ IndexView index_view(const Graph *g);
 // Fills everything but the buffers (sw .. out) of a descriptor.
 void describe_query(const Graph *g, const simrank_query *q, const simrank_params &p, int mode,
                     QueryDesc *d);
-// Enqueues init, source walks, compaction, unit offsets, meet and estimate for
+// Enqueues init, source walks, tiles and units, meet and estimate for
 // every query of the set; records ev_meet0 / ev_meet1 (may be NULL) around the
 // meet kernels.
-int launch_query_set(const QuerySet &qs, hipStream_t st, hipEvent_t ev_meet0, hipEvent_t ev_meet1);
+// one (may be NULL): the descriptor of a set of one query, not yet in device
+// memory.
+int launch_query_set(const QuerySet &qs, hipStream_t st, hipEvent_t ev_meet0, hipEvent_t ev_meet1,
+                     const QueryDesc *one = nullptr);
 int enqueue_query(const Graph *g, const simrank_query *q, const simrank_params &p, int mode,
                   Workspace *ws, double *out_dev, uint32_t *counts_dev, hipStream_t st);
 int enqueue_stratified(const Graph *g, const simrank_query *q, Workspace *ws, double *out_dev,

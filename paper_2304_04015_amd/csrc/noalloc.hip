@@ -75,8 +75,6 @@ Carve carve(char *base) {
     return c;
 }
 
-__global__ void k_put_desc(QueryDesc *dst, QueryDesc d) { *dst = d; }
-
 constexpr int MAX_DEVICES = 64;
 std::mutex scratch_mu;
 char *scratch_dev[MAX_DEVICES] = {};
@@ -160,7 +158,5 @@ extern "C" int simrank_single_source_noalloc(const simrank_graph *g, const simra
     qs.units = c.units;
     qs.counters = c.counters;
     hipStream_t st = (hipStream_t)stream;
-    k_put_desc<<<1, 1, 0, st>>>(c.desc, d);
-    SRK_HIP(hipGetLastError());
-    return launch_query_set(qs, st, nullptr, nullptr);
+    return launch_query_set(qs, st, nullptr, nullptr, &d);
 }

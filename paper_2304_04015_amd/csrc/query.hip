@@ -1,4 +1,4 @@
-// Single-source query: source walks, their compaction into LDS tiles, the
+// Single-source query: source walks, packed and cut into LDS tiles, the
 // fused walk + meet + count kernel, and the estimate.
 //
 // Method (Section 2.2; Lemma 2; Section 3.2 pairing): walk j of the source s
@@ -23,21 +23,34 @@ namespace {
 
 // ------------------------------------------------------------ small kernels
 
-__global__ void k_set_desc(QueryDesc *dst, QueryDesc d) { *dst = d; }
-
-// grid (x over nodes, y = query); clears `words` words of counters
-__global__ void k_init(const QueryDesc *__restrict__ qd, unsigned long long *__restrict__ counters,
-                       int32_t words) {
-    const QueryDesc &d = qd[blockIdx.y];
+// Clears a query's counts or sums and its meta words; x over nodes.
+__device__ __forceinline__ void clear_query(const QueryDesc &d) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (blockIdx.x == 0 && threadIdx.x < 8) d.meta[threadIdx.x] = 0u;
-    if (blockIdx.x == 0 && blockIdx.y == 0)
-        for (int32_t w = threadIdx.x; w < words; w += blockDim.x) counters[w] = 0ull;
     if (strat_kind(d.kind)) {
         for (int64_t v = i; v < d.n; v += (int64_t)gridDim.x * blockDim.x) d.wsum[v] = 0ull;
     } else {
         for (int64_t v = i; v < d.n; v += (int64_t)gridDim.x * blockDim.x) d.cnt[v] = 0u;
     }
+}
+
+// grid (x over nodes, y = query); clears `words` words of counters
+__global__ void k_init(const QueryDesc *__restrict__ qd, unsigned long long *__restrict__ counters,
+                       int32_t words) {
+    if (blockIdx.x == 0 && blockIdx.y == 0)
+        for (int32_t w = threadIdx.x; w < words; w += blockDim.x) counters[w] = 0ull;
+    clear_query(qd[blockIdx.y]);
+}
+
+// The same for one query whose descriptor comes with the launch and is put in
+// device memory for the kernels behind it; grid (x over nodes).
+__global__ void k_init_one(QueryDesc *__restrict__ dst, QueryDesc d,
+                           unsigned long long *__restrict__ counters, int32_t words) {
+    if (blockIdx.x == 0) {
+        for (int32_t w = threadIdx.x; w < words; w += blockDim.x) counters[w] = 0ull;
+        if (threadIdx.x == 0) *dst = d;
+    }
+    clear_query(d);
 }
 
 // s_hat(s, v) = cnt[v] / R; the pair (s, s) meets at step 0 for every j.
@@ -74,37 +87,65 @@ __global__ void k_estimate(const QueryDesc *__restrict__ qd, unsigned long long 
 // of s is the fixed-length walk generated in slot pi_s(j); its class goes to
 // scls[j].  grid (x over j, y = query); sets: the counters are a query set's
 // (CTR_SETS sets), else a ring entry's 8.
+//
+// A group member's walks go to its padded table (sw, slen), from which its
+// group packs them.  A lone query's are packed here: the block keeps its walks'
+// first WALK_LDS positions in LDS, drops the walks of length 0 (they can only
+// meet at step 0, i.e. only the source itself), and takes room for the others'
+// entries and positions with one atomic on meta[0..1]; so entries are in no
+// order of j, and entry k + 1 starts where entry k ends.  Packing from the
+// padded table by one block, a thread copying its walks word by word, took 13
+// us at R = 1,521 and 60 at R = 9,502.  All kernels of a query but the meet
+// kernel, before and now: 44 and 31 us at R = 1,521, 95 and 40 at R = 9,502,
+// 305 and 45 at R = 38,005.
+constexpr int WALK_LDS = 32;
 __global__ __launch_bounds__(256) void k_source_walks(const QueryDesc *__restrict__ qd,
                                                       unsigned long long *__restrict__ counters,
                                                       bool sets) {
+    __shared__ uint32_t s_pos[WALK_LDS][256];
+    __shared__ uint32_t s_at[2];
     const QueryDesc &d = qd[blockIdx.y];
     const int32_t j = blockIdx.x * blockDim.x + threadIdx.x;
-    uint32_t steps = 0;
+    if ((int32_t)(blockIdx.x * blockDim.x) >= d.R) return;
+    const bool grouped = d.kind >= K_GROUPED;
+    uint32_t *row = d.sw + (size_t)j * d.L;
+    auto put = [&](int32_t t, uint32_t o) {   // position t + 1
+        if (!grouped && t < WALK_LDS) s_pos[t][threadIdx.x] = o;
+        else row[t] = o;
+    };
+    int32_t len = 0;
     if (j < d.R) {
-        const PhiloxKey key{d.k0, d.k1};
-        uint32_t *row = d.sw + (size_t)j * d.L;
+        const PhiloxKey key{uni(d.k0), uni(d.k1)};
+        const GlobalPtr<uint64_t> E = gp_uni((const uint64_t *)d.E);
         uint2 cur = d.nodes[d.s];
-        int32_t len = 0;
+        // the draw of the next step is made while the step's gather is on its way
         if (strat_kind(d.kind)) {
             const uint4 fk = philox4x32_10((uint32_t)d.s, 0u, 0u, DOM_SHUFFLE, key);
             const uint32_t r = shuffle_slot((uint32_t)j, (uint32_t)d.R, (uint32_t)d.sa, (uint32_t)d.sb, fk);
             const uint32_t cls = slot_class(r, d.tab->ccum, d.L);
+            WalkDraws w = walk_draws_begin((uint32_t)d.s, r, key, DOM_STRAT);
+            uint2 x = walk_draw_next(w, key);
             for (int32_t t = 1; t <= (int32_t)cls; ++t) {
                 if (cur.y == 0) break;
-                const uint4 x = philox4x32_10((uint32_t)d.s, r, (uint32_t)t, DOM_STRAT, key);
-                cur = d.E[cur.x + pick32(x.y, cur.y)];
-                row[t - 1] = cur.x;
+                const uint2 to = load_edge(E, cur.x + pick32(x.y, cur.y));
+                x = walk_draw_next(w, key);
+                cur = to;
+                put(t - 1, cur.x);
                 len = t;
             }
             d.scls[j] = (uint8_t)cls;
         } else {
             const bool stitched = d.kind == K_STITCHED || d.kind == K_GROUPED_STITCHED;
             const int32_t head = stitched ? min(d.ix.seg_len, d.L) : d.L;
+            const uint32_t T = d.T;
+            WalkDraws w = walk_draws_begin((uint32_t)d.s, (uint32_t)j, key);
+            uint2 x = walk_draw_next(w, key);
             for (int32_t t = 1; t <= head; ++t) {
-                const uint4 x = philox4x32_10((uint32_t)d.s, (uint32_t)j, (uint32_t)t, DOM_WALK, key);
-                if (x.x >= d.T || cur.y == 0) break;
-                cur = d.E[cur.x + pick32(x.y, cur.y)];
-                row[t - 1] = cur.x;
+                if (x.x >= T || cur.y == 0) break;
+                const uint2 to = load_edge(E, cur.x + pick32(x.y, cur.y));
+                x = walk_draw_next(w, key);
+                cur = to;
+                put(t - 1, cur.x);
                 len = t;
             }
             if (stitched && len == d.ix.seg_len && len < d.L) {
@@ -115,73 +156,66 @@ __global__ __launch_bounds__(256) void k_source_walks(const QueryDesc *__restric
                     if (sg == NIL) break;
                     const int32_t sl = d.ix.seg_lens[sg];
                     for (int32_t u = 0; u < sl && len < d.L; ++u) {
-                        row[len] = d.ix.seg[(size_t)sg * d.ix.seg_len + u];
+                        put(len, d.ix.seg[(size_t)sg * d.ix.seg_len + u]);
                         ++len;
                     }
                     if (sl < d.ix.seg_len) break;
                 }
             }
         }
-        d.slen[j] = (uint8_t)len;
-        steps = (uint32_t)len;
+        if (grouped) d.slen[j] = (uint8_t)len;
     }
-    unsigned long long m64 = steps;
-    for (int dd = 32; dd > 0; dd >>= 1) m64 += __shfl_xor(m64, dd, 64);
-    if ((threadIdx.x & 63) == 0 && m64)
-        atomicAdd(&(sets ? ctr_set(counters) : counters)[C_SRC_MOVES], m64);
+    uint32_t entries, words;
+    const uint32_t ek = block_excl_sum<uint32_t>(len > 0 ? 1u : 0u, &entries);
+    const uint32_t eo = block_excl_sum<uint32_t>((uint32_t)len, &words);
+    if (threadIdx.x == 0) {
+        if (words) atomicAdd(&(sets ? ctr_set(counters) : counters)[C_SRC_MOVES], (unsigned long long)words);
+        if (!grouped && entries) {
+            const unsigned long long at =
+                atomicAdd((unsigned long long *)d.meta, ((unsigned long long)words << 32) | entries);
+            s_at[0] = (uint32_t)at;
+            s_at[1] = (uint32_t)(at >> 32);
+        }
+    }
+    if (grouped) return;
+    __syncthreads();
+    if (len == 0) return;
+    const uint32_t k = s_at[0] + ek, off = s_at[1] + eo;
+    d.jj[k] = (uint32_t)j;
+    d.joff[k] = off;
+    uint32_t *dst = d.swc + off;
+    for (int32_t t = 0; t < min(len, WALK_LDS); ++t) dst[t] = s_pos[t][threadIdx.x];
+    for (int32_t t = WALK_LDS; t < len; ++t) dst[t] = row[t];
 }
 
-// ------------------------------------------------------------ compaction
-// One block per query.  Keeps the walks with at least one step (a walk of
-// length 0 can only meet at step 0, i.e. only the source itself), packs their
-// positions back to back (swc), and cuts the packed list into tiles that fit
-// the meet kernel's LDS: with the kind's shape (TJ walks, TN positions), each
-// tile is the longest run of walks from the previous one's end that holds at
-// most TJ walks and TN positions (cut_tiles).
-__global__ __launch_bounds__(1024) void k_compact(const QueryDesc *__restrict__ qd) {
-    const QueryDesc &d = qd[blockIdx.x];
-    if (d.kind >= K_GROUPED) return;   // compacted with its group
-    const int32_t R = d.R, L = d.L;
-    const uint32_t TJ = (uint32_t)d.tile_j;
-    const uint32_t TN = (uint32_t)tile_nodes_of(d.kind);
-    const int32_t per = (R + blockDim.x - 1) / blockDim.x;
-    const int32_t j0 = min(R, (int32_t)threadIdx.x * per), j1 = min(R, j0 + per);
-    uint32_t cnt = 0, nodes = 0;
-    for (int32_t j = j0; j < j1; ++j) {
-        const uint32_t l = d.slen[j];
-        cnt += l > 0;
-        nodes += l;
-    }
-    uint32_t R1, total;
-    const uint32_t kb = block_excl_sum(cnt, &R1);
-    const uint32_t nb = block_excl_sum(nodes, &total);
-    uint32_t k = kb, off = nb;
-    for (int32_t j = j0; j < j1; ++j) {
-        const uint32_t l = d.slen[j];
-        if (!l) continue;
-        d.jj[k] = (uint32_t)j;
-        d.joff[k] = off;
-        const uint32_t *src = d.sw + (size_t)j * L;
-        for (uint32_t t = 0; t < l; ++t) d.swc[off + t] = src[t];
-        ++k;
-        off += l;
-    }
-    if (threadIdx.x == 0) d.joff[R1] = total;
-    __syncthreads();
-    if (threadIdx.x < 64) {
-        const uint32_t n_tiles = cut_tiles(d.joff, R1, TJ, TN, d.tiles, (int)threadIdx.x);
-        if (threadIdx.x == 0) {
-            d.tiles[n_tiles] = R1;
-            d.meta[0] = R1;
-            d.meta[1] = total;
-            d.meta[2] = n_tiles;
-        }
-        uint32_t km = 0;
-        for (uint32_t t = threadIdx.x; t < n_tiles; t += 64)
+// ------------------------------------------------------------ tiles
+// Cuts the packed entries of a query into tiles that fit the meet kernel's LDS:
+// with the kind's shape (TJ walks, TN positions), each tile is the longest run
+// of walks from the previous one's end that holds at most TJ walks and TN
+// positions (cut_tiles).  Called by all lanes of one wave.
+__device__ void make_tiles(const QueryDesc &d, int lane) {
+    const uint32_t R1 = d.meta[0], total = d.meta[1];
+    const uint32_t TJ = (uint32_t)d.tile_j, TN = (uint32_t)tile_nodes_of(d.kind);
+    if (lane == 0) d.joff[R1] = total;
+    uint32_t n_tiles, km = R1;
+    if (R1 <= TJ && total <= TN) {
+        n_tiles = R1 > 0u ? 1u : 0u;
+        if (lane == 0 && R1 > 0u) d.tiles[0] = 0u;
+    } else {
+        __threadfence_block();   // joff[R1] is read below
+        n_tiles = cut_tiles(d.joff, R1, TJ, TN, d.tiles, lane);
+        __threadfence_block();
+        km = 0;
+        for (uint32_t t = (uint32_t)lane; t < n_tiles; t += 64)
             km = max(km, (t + 1 < n_tiles ? d.tiles[t + 1] : R1) - d.tiles[t]);
         for (int dd = 32; dd > 0; dd >>= 1) km = max(km, __shfl_xor(km, dd, 64));
-        if (threadIdx.x == 0) d.meta[3] = km;
     }
+    if (lane == 0) {
+        d.tiles[n_tiles] = R1;
+        d.meta[2] = n_tiles;
+        d.meta[3] = km;
+    }
+    __threadfence_block();
 }
 
 // ------------------------------------------------------------ work units
@@ -286,9 +320,17 @@ __device__ uint32_t lay_units(const QueryDesc &d, uint64_t per, int lane) {
     return first;
 }
 
-// Units of the queries (one block): each query's tiles, then one list of
-// nq + 1 offsets per kind (a query of another kind has no units in a list) and
-// one cursor per kind.  grid: blocks of each kind's meet launch.
+// Tiles of one query per block, for sets of more than TILES_IN_UNITS queries.
+constexpr int32_t TILES_IN_UNITS = 16;
+__global__ __launch_bounds__(64) void k_tiles(const QueryDesc *__restrict__ qd) {
+    const QueryDesc &d = qd[blockIdx.x];
+    if (d.kind < N_KINDS) make_tiles(d, (int)threadIdx.x);
+}
+
+// Tiles (where there are few queries) and units of the queries (one block),
+// then one list of nq + 1 offsets per kind (a query of another kind has
+// no units in a list) and one cursor per kind.  grid: blocks of each kind's
+// meet launch.
 __global__ __launch_bounds__(1024) void k_unit_offsets(const QueryDesc *__restrict__ qd, int32_t nq,
                                                        uint32_t *units, uint3 grid) {
     __shared__ unsigned long long s_pairs[N_KINDS], s_per[N_KINDS];
@@ -297,6 +339,8 @@ __global__ __launch_bounds__(1024) void k_unit_offsets(const QueryDesc *__restri
         s_pairs[threadIdx.x] = 0ull;
         s_km[threadIdx.x] = 0u;
     }
+    for (int32_t q = threadIdx.x >> 6; nq <= TILES_IN_UNITS && q < nq; q += (int32_t)(blockDim.x >> 6))
+        if (qd[q].kind < N_KINDS) make_tiles(qd[q], (int)(threadIdx.x & 63));
     __syncthreads();
     for (int32_t q = threadIdx.x; q < nq; q += blockDim.x) {
         const int32_t kind = qd[q].kind;
@@ -1023,6 +1067,7 @@ __global__ __launch_bounds__(256) void k_publish(StreamRing ring, int32_t slot, 
     const QueryDesc &d = ring.desc[slot];
     __shared__ uint32_t s_nu;
     if (threadIdx.x < 64) {
+        make_tiles(d, (int)threadIdx.x);
         const uint64_t pairs = (uint64_t)d.meta[0] * (uint64_t)(uint32_t)d.n_active;
         const uint32_t nu = lay_units(
             d, unit_pairs(&d, 1, d.kind, pairs, d.meta[3], grid, (int)threadIdx.x), (int)threadIdx.x);
@@ -1114,13 +1159,17 @@ void describe_query(const Graph *g, const simrank_query *q, const simrank_params
     d->tile_j = tj > 0 ? std::min<int32_t>(tj, tile_j_of(d->kind)) : tile_j_of(d->kind);
 }
 
-int launch_query_set(const QuerySet &qs, hipStream_t st, hipEvent_t ev_meet0, hipEvent_t ev_meet1) {
+int launch_query_set(const QuerySet &qs, hipStream_t st, hipEvent_t ev_meet0, hipEvent_t ev_meet1,
+                     const QueryDesc *one) {
     if (qs.nq <= 0) return SIMRANK_OK;
     const unsigned nq = (unsigned)qs.nq;
     const unsigned gx_n = std::min<unsigned>(grid_for(std::max(qs.max_n, 1), 256), 1024u);
-    k_init<<<dim3(gx_n, nq), 256, 0, st>>>(qs.desc, qs.counters, CTR_WORDS);
+    if (one)
+        k_init_one<<<gx_n, 256, 0, st>>>(const_cast<QueryDesc *>(qs.desc), *one, qs.counters, CTR_WORDS);
+    else
+        k_init<<<dim3(gx_n, nq), 256, 0, st>>>(qs.desc, qs.counters, CTR_WORDS);
     k_source_walks<<<dim3(grid_for(qs.max_R, 256), nq), 256, 0, st>>>(qs.desc, qs.counters, true);
-    k_compact<<<nq, 1024, 0, st>>>(qs.desc);
+    if (qs.nq > TILES_IN_UNITS) k_tiles<<<nq, 64, 0, st>>>(qs.desc);
     const uint3 grid = make_uint3((uint32_t)meet_grid_blocks<K_PLAIN, SRK_MEET_SLOTS, false>(),
                                   (uint32_t)meet_grid_blocks<K_STITCHED, SRK_MEET_SLOTS_STITCHED, false>(),
                                   (uint32_t)meet_grid_blocks<K_STRAT, SRK_MEET_SLOTS_STRAT, false>());
@@ -1154,10 +1203,8 @@ int enqueue_ring_request(const QueryDesc &d, const StreamRing &ring, int32_t slo
     QueryDesc *qd = ring.desc + slot;
     unsigned long long *ctr = ring.counters + (size_t)slot * 8;
     const unsigned gx_n = std::min<unsigned>(grid_for(std::max(d.n, 1), 256), 1024u);
-    k_set_desc<<<1, 1, 0, st>>>(qd, d);
-    k_init<<<dim3(gx_n, 1), 256, 0, st>>>(qd, ctr, 8);
+    k_init_one<<<gx_n, 256, 0, st>>>(qd, d, ctr, 8);
     k_source_walks<<<dim3(grid_for(d.R, 256), 1), 256, 0, st>>>(qd, ctr, false);
-    k_compact<<<1, 256, 0, st>>>(qd);
     k_publish<<<1, 256, 0, st>>>(ring, slot, seq, ring_grid(d.kind));
     SRK_HIP(hipGetLastError());
     return SIMRANK_OK;
@@ -1381,8 +1428,7 @@ static int launch_single(const Graph *g, Workspace *ws, const QueryDesc &d, hipS
     qs.units = ws->units;
     qs.counters = ws->counters;
     SRK_HIP(hipEventRecord(ws->ev0, st));
-    k_set_desc<<<1, 1, 0, st>>>(ws->desc, d);
-    int rc = launch_query_set(qs, st, ws->evm0, ws->evm1);
+    int rc = launch_query_set(qs, st, ws->evm0, ws->evm1, &d);
     if (rc) return rc;
     SRK_HIP(hipEventRecord(ws->ev1, st));
     ws->last_stream = st;
