@@ -291,6 +291,7 @@ extern "C" int simrank_batch_plan_create_ex(simrank_graph *const *graphs, int32_
         if (e != hipSuccess) return bail(fail(SIMRANK_EDEVICE, hipGetErrorString(e)));
         gset.desc = p->gdesc_dev;
         gset.ng = ngr;
+        for (const GroupDesc &gd : p->gdesc) gset.max_R = std::max(gset.max_R, gd.Rmax);
         gset.units = p->gunits;
         set.groups = &gset;
     }

@@ -253,7 +253,8 @@ struct GroupDesc {
     // Compacted walks: entry e is a walk index jj[e] for which at least one
     // member's walk has a step; from pos[joff[e]], one block per step t of its
     // longest member walk: a word with bit q set for each member q whose walk
-    // j has a position at step t, then those positions in member order.
+    // j has a position at step t, then those positions in member order, NIL up
+    // to a multiple of four words.
     // Member q's length is byte q of the entry's gw words glen[e gw ...].
     uint32_t *jj;                        // [Rmax]
     uint32_t *joff;                      // [Rmax + 1]
@@ -272,6 +273,7 @@ __host__ __device__ inline int group_list(int32_t G, int32_t wk) { return 2 * wk
 struct GroupSet {
     const GroupDesc *desc = nullptr;     // device [ng]
     int32_t ng = 0;
+    int32_t max_R = 0;                   // largest Rmax
     int64_t units_bound[GROUP_LISTS] = {};       // work units per kernel instance (group_list)
     uint32_t *units = nullptr;           // device [group_units_words(ng)]
 };
@@ -279,9 +281,9 @@ struct GroupSet {
 // one cursor per list.
 inline size_t group_units_words(int32_t ng) { return GROUP_LISTS * ((size_t)ng + 1) + GROUP_LISTS; }
 
-// Words of a group's compacted walks, at most: every member position and one
-// member word per step of each entry.
-inline int64_t group_pos_words(int64_t Rmax, int64_t sum_RL, int32_t L) { return sum_RL + Rmax * L; }
+// Words of a group's compacted walks, at most: every member position, and one
+// member word and up to three words of padding per step of each entry.
+inline int64_t group_pos_words(int64_t Rmax, int64_t sum_RL, int32_t L) { return sum_RL + 4 * Rmax * L; }
 // Tiles of a group's compacted walks, at most.
 int32_t group_max_tiles(int64_t Rmax, int64_t sum_RL, int32_t L, int32_t G, int32_t wk);
 // Nodes per work unit of a group of G members with walks wk on a graph with

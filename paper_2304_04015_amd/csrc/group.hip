@@ -65,11 +65,16 @@ __host__ __device__ constexpr int group_tile_nodes(int GW, int WK) {   // < 2^16
 }
 // Nodes per work unit whose sums a stratified instance keeps in LDS.
 __host__ __device__ constexpr int group_strat_vb(int GW) { return GW > 2 ? GROUP_STRAT32_VB : MEET_VB; }
-// a tile holds at least one entry of the longest form ((G + 1) L words)
-static_assert(group_tile_nodes(2, 0) < 65536 && group_tile_nodes(2, 0) > 9 * MAX_CAP, "tile shape");
-static_assert(group_tile_nodes(8, 0) < 65536 && group_tile_nodes(8, 0) > 33 * MAX_CAP, "tile shape");
-static_assert(group_tile_nodes(2, 2) < 65536 && group_tile_nodes(2, 2) > 9 * MAX_CAP, "tile shape");
-static_assert(group_tile_nodes(8, 2) < 65536 && group_tile_nodes(8, 2) > 33 * MAX_CAP, "tile shape");
+// Words of an entry's block for a step with c member positions: the members'
+// word and the positions, in whole 16-byte pieces.
+__host__ __device__ constexpr uint32_t block_words(uint32_t c) { return (c + 4u) & ~3u; }
+// a tile holds at least one entry of the longest form (L blocks of G positions)
+static_assert(group_tile_nodes(2, 0) < 65536 && group_tile_nodes(2, 0) > 12 * MAX_CAP, "tile shape");
+static_assert(group_tile_nodes(8, 0) < 65536 && group_tile_nodes(8, 0) > 36 * MAX_CAP, "tile shape");
+static_assert(group_tile_nodes(2, 2) < 65536 && group_tile_nodes(2, 2) > 12 * MAX_CAP, "tile shape");
+static_assert(group_tile_nodes(8, 2) < 65536 && group_tile_nodes(8, 2) > 36 * MAX_CAP, "tile shape");
+static_assert(group_tile_nodes(2, 0) % 4 == 0 && group_tile_nodes(8, 0) % 4 == 0 &&
+              group_tile_nodes(2, 2) % 4 == 0 && group_tile_nodes(8, 2) % 4 == 0, "16-byte pieces");
 static_assert(GROUP_MAX == 32, "length words");
 
 // The kernel instance (its GW) for groups of G members.
@@ -79,89 +84,124 @@ __host__ __device__ inline int group_gw(int32_t G) { return G <= 8 ? 2 : 8; }
 __device__ __forceinline__ uint32_t byte_of(uint32_t w, int q) { return (w >> (8 * (q & 3))) & 0xffu; }
 
 // ------------------------------------------------------------ compaction
-// One block per group.  Keeps the walk indices j for which at least one
-// member's walk j has a step and packs the members' positions of walk j step
-// by step: for each step t up to the longest member walk, the word of members
-// with a position at t, then their positions at t in member order.  Cuts the
-// entries into tiles of at most TJ entries and TN words, each the longest run
-// from the previous one's end (cut_tiles; an entry holds at most (G + 1) L
-// words).  (TJ, TN) is the shape of the kernel instance that runs the group.
-__global__ __launch_bounds__(1024) void k_group_compact(const GroupDesc *__restrict__ gd) {
-    const GroupDesc &d = gd[blockIdx.x];
-    const int32_t Rmax = d.Rmax, L = d.L, G = d.G, gw = d.gw;
-    const uint32_t TJ = (uint32_t)group_tile_j(group_gw(G), d.wk);
-    const uint32_t TN = (uint32_t)group_tile_nodes(group_gw(G), d.wk);
-    const int32_t per = (Rmax + (int32_t)blockDim.x - 1) / (int32_t)blockDim.x;
-    const int32_t j0 = min(Rmax, (int32_t)threadIdx.x * per), j1 = min(Rmax, j0 + per);
-    uint32_t cnt = 0, nodes = 0;
-    for (int32_t j = j0; j < j1; ++j) {
-        uint32_t tot = 0, mx = 0;
-        for (int32_t q = 0; q < G; ++q) {
-            const uint32_t l = j < d.R[q] ? (uint32_t)d.slen[q][j] : 0u;
-            tot += l;
-            mx = max(mx, l);
+// Keeps the walk indices j for which at least one member's walk j has a step
+// and packs the members' positions of walk j step by step: for each step t up
+// to the longest member walk, the word of members with a position at t, then
+// their positions at t in member order, NIL up to a multiple of four words (the
+// meet kernel reads 16-byte pieces).  grid (x over blocks of PACK_J walk
+// indices, y = group); a half wave packs an entry, one member per lane, and a
+// block takes the room of its entries with one atomic on meta[0..1], so entries
+// are in no order of j.  One block per group, a thread per walk index copying
+// word by word, took 3.2 ms of the 66 ms of 32 queries on a graph of n = 2^18
+// (R = 9,502); this takes 0.05, and cutting the tiles 0.03.
+constexpr int PACK_J = 32;
+__global__ __launch_bounds__(256) void k_group_pack(const GroupDesc *__restrict__ gd) {
+    __shared__ uint32_t s_words[PACK_J], s_first[PACK_J + 1], s_base[2];
+    const GroupDesc &d = gd[blockIdx.y];
+    const int32_t j00 = (int32_t)blockIdx.x * PACK_J;
+    if (j00 >= d.Rmax) return;
+    const int32_t L = d.L, G = d.G, gw = d.gw;
+    const int lane = threadIdx.x & 63, q = lane & 31, half = threadIdx.x >> 5;   // 8 half waves
+    const bool member = q < G;
+    const uint32_t hshift = (uint32_t)(lane & 32);
+    const uint8_t *slen = member ? d.slen[q] : nullptr;
+    const uint32_t *sw = member ? d.sw[q] : nullptr;
+    const int32_t Rq = member ? d.R[q] : 0;
+    uint32_t len[PACK_J / 8];
+#pragma unroll
+    for (int i = 0; i < PACK_J / 8; ++i) {
+        const int32_t jl = i * 8 + half, j = j00 + jl;
+        len[i] = j < Rq ? (uint32_t)slen[j] : 0u;
+        uint32_t mx = len[i];
+        for (int dd = 16; dd > 0; dd >>= 1) mx = max(mx, __shfl_xor(mx, dd, 32));
+        uint32_t words = 0;
+        for (uint32_t t = 0; __ballot(t < mx) != 0ull; ++t) {
+            const uint32_t am = (uint32_t)(__ballot(t < len[i]) >> hshift);
+            if (t < mx) words += block_words((uint32_t)__popc(am));
         }
-        cnt += tot > 0;
-        nodes += tot + mx;
+        if (q == 0) s_words[jl] = words;
     }
-    uint32_t E1, total;
-    const uint32_t kb = block_excl_sum(cnt, &E1);
-    const uint32_t nb = block_excl_sum(nodes, &total);
-    uint32_t k = kb, off = nb;
-    for (int32_t j = j0; j < j1; ++j) {
-        uint32_t tot = 0, mx = 0;
-        for (int32_t q = 0; q < G; ++q) {
-            const uint32_t l = j < d.R[q] ? (uint32_t)d.slen[q][j] : 0u;
-            tot += l;
-            mx = max(mx, l);
-        }
-        if (!tot) continue;
-        d.jj[k] = (uint32_t)j;
-        d.joff[k] = off;
-        for (int32_t wd = 0; wd < gw; ++wd) {
-            uint32_t w = 0;
-            for (int32_t b = 0; b < 4; ++b) {
-                const int32_t q = 4 * wd + b;
-                const uint32_t l = (q < G && j < d.R[q]) ? (uint32_t)d.slen[q][j] : 0u;
-                w |= l << (8 * b);
-            }
-            d.glen[(size_t)k * gw + wd] = w;
-        }
-        // the lengths again from the words just written (registers), not
-        // from the members' length arrays at every step
-        uint32_t lw[GROUP_MAX / 4];
-#pragma unroll
-        for (int wd = 0; wd < GROUP_MAX / 4; ++wd)
-            lw[wd] = wd < gw ? d.glen[(size_t)k * gw + wd] : 0u;
-        for (uint32_t t = 0; t < mx; ++t) {
-            const uint32_t at = off++;
-            uint32_t am = 0;
-#pragma unroll
-            for (int wd = 0; wd < GROUP_MAX / 4; ++wd) {
-#pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    const int q = 4 * wd + b;
-                    if (t < byte_of(lw[wd], b)) {
-                        am |= 1u << q;
-                        d.pos[off++] = d.sw[q][(size_t)j * L + t];
-                    }
-                }
-            }
-            d.pos[at] = am;
-        }
-        ++k;
-    }
-    if (threadIdx.x == 0) d.joff[E1] = total;
     __syncthreads();
     if (threadIdx.x < 64) {
-        const uint32_t n_tiles = cut_tiles(d.joff, E1, TJ, TN, d.tiles, (int)threadIdx.x);
-        if (threadIdx.x == 0) {
-            d.tiles[n_tiles] = E1;
-            d.meta[0] = E1;
-            d.meta[1] = total;
-            d.meta[2] = n_tiles;
+        const uint32_t w = threadIdx.x < PACK_J ? s_words[threadIdx.x] : 0u;
+        const uint64_t has = __ballot(w > 0u);
+        uint32_t inc = w;
+        for (int dd = 1; dd < PACK_J; dd <<= 1) {
+            const uint32_t y = __shfl_up(inc, dd, 64);
+            if (lane >= dd) inc += y;
+        }
+        if (threadIdx.x < PACK_J) s_first[threadIdx.x] = inc - w;
+        if (threadIdx.x == PACK_J - 1) {
+            unsigned long long at = 0;
+            if (has) at = atomicAdd((unsigned long long *)d.meta,
+                                    ((unsigned long long)inc << 32) | (uint32_t)__popcll(has));
+            s_base[0] = (uint32_t)at;
+            s_base[1] = (uint32_t)(at >> 32);
+        }
+        if (threadIdx.x < PACK_J) s_words[threadIdx.x] = w ? lane_rank(has) : NIL;   // rank of the entry
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < PACK_J / 8; ++i) {
+        const int32_t jl = i * 8 + half, j = j00 + jl;
+        const uint32_t rank = s_words[jl];
+        const bool on = rank != NIL;
+        const uint32_t k = s_base[0] + rank;
+        uint32_t off = s_base[1] + s_first[jl];
+        if (on && q == 0) {
+            d.jj[k] = (uint32_t)j;
+            d.joff[k] = off;
+        }
+        const uint32_t l1 = __shfl_down(len[i], 1, 32), l2 = __shfl_down(len[i], 2, 32),
+                       l3 = __shfl_down(len[i], 3, 32);
+        if (on && (q & 3) == 0 && (q >> 2) < gw)
+            d.glen[(size_t)k * gw + (q >> 2)] = len[i] | (l1 << 8) | (l2 << 16) | (l3 << 24);
+        uint32_t mx = on ? len[i] : 0u;
+        for (int dd = 16; dd > 0; dd >>= 1) mx = max(mx, __shfl_xor(mx, dd, 32));
+        const uint32_t *row = sw + (size_t)j * L;
+        uint32_t next = len[i] > 0u ? row[0] : NIL;
+        for (uint32_t t = 0; __ballot(t < mx) != 0ull; ++t) {
+            const uint32_t here = next;
+            next = t + 1 < len[i] ? row[t + 1] : NIL;   // the next step's load is on its way
+            const uint32_t am = (uint32_t)(__ballot(t < len[i]) >> hshift);
+            const uint32_t c = (uint32_t)__popc(am), bw = block_words(c);
+            if (t < mx) {
+                if (q == 0) d.pos[off] = am;
+                if (t < len[i]) d.pos[off + 1u + (uint32_t)__popc(am & ((1u << q) - 1u))] = here;
+                if ((uint32_t)q < bw - 1u - c) d.pos[off + 1u + c + (uint32_t)q] = NIL;
+                off += bw;
+            }
         }
     }
+}
+
+// Tiles of one group per block: cuts the entries into tiles of at most TJ
+// entries and TN words, each the longest run from the previous one's end
+// (cut_tiles).  (TJ, TN) is the shape of the kernel instance that runs the
+// group.
+__global__ __launch_bounds__(64) void k_group_tiles(const GroupDesc *__restrict__ gd) {
+    const GroupDesc &d = gd[blockIdx.x];
+    const uint32_t TJ = (uint32_t)group_tile_j(group_gw(d.G), d.wk);
+    const uint32_t TN = (uint32_t)group_tile_nodes(group_gw(d.G), d.wk);
+    const uint32_t E1 = d.meta[0], total = d.meta[1];
+    if (threadIdx.x == 0) d.joff[E1] = total;
+    __threadfence_block();
+    const uint32_t n_tiles = cut_tiles(d.joff, E1, TJ, TN, d.tiles, (int)threadIdx.x);
+    __threadfence_block();
+    uint32_t km = 0;
+    for (uint32_t t = threadIdx.x; t < n_tiles; t += 64)
+        km = max(km, (t + 1 < n_tiles ? d.tiles[t + 1] : E1) - d.tiles[t]);
+    for (int dd = 32; dd > 0; dd >>= 1) km = max(km, __shfl_xor(km, dd, 64));
+    if (threadIdx.x == 0) {
+        d.tiles[n_tiles] = E1;
+        d.meta[2] = n_tiles;
+        d.meta[3] = km;
+    }
+}
+
+// The groups' counters of packed entries start at zero.
+__global__ void k_group_clear(const GroupDesc *__restrict__ gd) {
+    if (threadIdx.x < 8) gd[blockIdx.x].meta[threadIdx.x] = 0u;
 }
 
 // Work-unit offsets of the groups (one block), one list per kernel instance
@@ -224,35 +264,45 @@ struct GSlot {
     uint32_t cv, jw;   // stratified: class (and last step) of walk (v, j), and j
 };
 
-// Compares the pair's position at step t with the members' positions at step
-// t.  The entry's block for step t is the word of members with a position at
-// t, then those positions in member order; the slot's offset b moves on to the
-// next step's block (every step is compared once, in order).  A hit sends the
-// lane to an exact pass that names the members; meets are rare, so the common
-// step reads and compares only the positions of the members still walking.
-// Returns the members still tested that meet at this step.
+// Compares the pair's position at step t with the members' positions at step t,
+// for the lanes in `act`.  The entry's block for step t is the word of members
+// with a position at t, then those positions in member order, padded with NIL;
+// the slot's offset b moves on to the next step's block (every step is compared
+// once, in order).  Meets are rare: the common step reads the block in 16-byte
+// pieces and only asks whether any position is the pair's.  For each lane with
+// a hit the whole wave then names the members, one per lane.  Returns the
+// members still tested that meet at this step.  Called by all lanes of a wave.
+// Reading word by word, with each read's index held inside the block, and
+// naming the members one by one on the lane that hit, the kernel took 61.7 ms
+// for 32 queries at n = 2^18 and was bound by its instructions; now 50.9, at
+// 53 G L2 misses/s (random 8-byte gathers over its 33 MB: 58).
 template <int GW>
-__device__ __forceinline__ uint32_t group_compare(GSlot<GW> &w, const uint32_t *s_nodes) {
-    const uint32_t B = w.b;
-    const uint32_t am = s_nodes[B];
-    const uint32_t c = (uint32_t)__popc(am);
-    w.b = B + 1u + c;
+__device__ __forceinline__ uint32_t group_compare(GSlot<GW> &w, bool act, const uint32_t *s_nodes,
+                                                  int lane) {
     bool hit = false;
-    // four positions per round; a read past the block takes word B instead,
-    // and a false hit from it is cleared by the exact pass
-    for (uint32_t i = 0; i < c; i += 4u) {
-        uint32_t pv[4];
-#pragma unroll
-        for (uint32_t u = 0; u < 4u; ++u) pv[u] = s_nodes[i + u < c ? B + 1u + i + u : B];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) hit |= pv[u] == w.o;
+    uint32_t am = 0;
+    const uint32_t B = w.b;
+    if (act) {
+        const uint4 *blk = reinterpret_cast<const uint4 *>(s_nodes + B);
+        const uint4 h = blk[0];
+        am = h.x;
+        const uint32_t pieces = block_words((uint32_t)__popc(am)) >> 2;
+        hit = h.y == w.o || h.z == w.o || h.w == w.o;
+        for (uint32_t i = 1; i < pieces; ++i) {
+            const uint4 p = blk[i];
+            hit |= p.x == w.o || p.y == w.o || p.z == w.o || p.w == w.o;
+        }
+        w.b = B + 4u * pieces;
     }
-    if (!hit) return 0u;
-    uint32_t met = 0, m = am;
-    for (uint32_t i = 0; i < c; ++i) {
-        const uint32_t q = (uint32_t)__builtin_ctz(m);
-        m &= m - 1u;
-        if (s_nodes[B + 1u + i] == w.o) met |= 1u << q;
+    uint32_t met = 0;
+    for (uint64_t hm = __ballot(hit); hm != 0ull; hm &= hm - 1ull) {
+        const int from = __builtin_ctzll(hm);
+        const uint32_t fam = __builtin_amdgcn_readlane(am, from), fB = __builtin_amdgcn_readlane(B, from),
+                       fo = __builtin_amdgcn_readlane(w.o, from);
+        const bool mine = lane < 32 && ((fam >> lane) & 1u);
+        const uint32_t at = fB + 1u + (uint32_t)__popc(fam & ((1u << (lane & 31)) - 1u));
+        const uint32_t who = (uint32_t)__ballot(mine && s_nodes[mine ? at : fB] == fo);
+        if (lane == from) met = who;
     }
     return met & w.live;
 }
@@ -264,7 +314,7 @@ __global__ __launch_bounds__(GROUP_BLOCK) void k_meet_group(const GroupDesc *__r
                                                             unsigned long long *__restrict__ counters) {
     constexpr bool STITCHED = WK == 1, STRAT = WK == 2;
     constexpr int TJ = group_tile_j(GW, WK), TN = group_tile_nodes(GW, WK), GM = 4 * GW;
-    __shared__ uint32_t s_nodes[TN];
+    __shared__ __attribute__((aligned(16))) uint32_t s_nodes[TN];
     __shared__ uint32_t s_j[TJ];
     __shared__ uint16_t s_off[TJ];
     __shared__ uint32_t s_cnt[STRAT ? 1 : GM / 2 * MEET_VB];   // members 2i, 2i+1 in the low, high half
@@ -498,8 +548,8 @@ __global__ __launch_bounds__(GROUP_BLOCK) void k_meet_group(const GroupDesc *__r
                     w.o = tv[qq];
                     ++w.tu;
                 }
-                if (go[qq] || tail_step) {
-                    const uint32_t met = group_compare(w, s_nodes);
+                {
+                    const uint32_t met = group_compare(w, go[qq] || tail_step, s_nodes, lane);
                     if (met) {
                         const uint32_t vl = w.pos >> 24;
                         st_meets += (uint32_t)__popc(met);
@@ -613,7 +663,7 @@ void launch_group_list(const GroupSet &gs, int list, unsigned long long *counter
 
 int32_t group_max_tiles(int64_t Rmax, int64_t sum_RL, int32_t L, int32_t G, int32_t wk) {
     const int GW = group_gw(G);
-    const int64_t NW = group_tile_nodes(GW, wk) - (int64_t)(G + 1) * L;
+    const int64_t NW = group_tile_nodes(GW, wk) - (int64_t)block_words((uint32_t)G) * L;
     return (int32_t)(2 + Rmax / group_tile_j(GW, wk) + group_pos_words(Rmax, sum_RL, L) / NW);
 }
 
@@ -686,7 +736,9 @@ static_assert(GROUP_LISTS == 6, "one launch below per group kernel instance");
 
 int launch_groups(const GroupSet &gs, unsigned long long *counters, hipStream_t st) {
     if (gs.ng <= 0) return SIMRANK_OK;
-    k_group_compact<<<gs.ng, 1024, 0, st>>>(gs.desc);
+    k_group_clear<<<gs.ng, 64, 0, st>>>(gs.desc);
+    k_group_pack<<<dim3((unsigned)((gs.max_R + PACK_J - 1) / PACK_J), (unsigned)gs.ng), 256, 0, st>>>(gs.desc);
+    k_group_tiles<<<gs.ng, 64, 0, st>>>(gs.desc);
     k_group_units<<<1, 1024, 0, st>>>(gs.desc, gs.ng, gs.units);
     launch_group_list<SRK_GROUP_SLOTS, 2, 0>(gs, 0, counters, st);
     launch_group_list<SRK_GROUP_SLOTS, 8, 0>(gs, 1, counters, st);

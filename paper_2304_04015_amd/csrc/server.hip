@@ -346,6 +346,7 @@ static int launch_group(simrank_server *S, const std::vector<Request *> &rs, hip
     GroupSet gs;
     gs.desc = gr.gdesc_dev;
     gs.ng = 1;
+    gs.max_R = gd->Rmax;
     gs.units_bound[group_list(G, gd->wk)] = units;
     gs.units = gr.gunits;
     QuerySet qs;
