@@ -184,6 +184,7 @@ struct QueryDesc {
     int32_t n, n_active, s, R, L;
     int32_t vb;            // nodes per work unit at most (<= MEET_VB); 0: sized on the device
     int32_t kind;          // Kind
+    int32_t items;         // items a wave takes at once, at most (item_chunk)
     int32_t tile_j;        // source walks per LDS tile, MIN_TILE_J .. tile_j_of(kind)
     // stratified only (R = N walks per node, L = phi)
     const StratTab *tab;

@@ -155,7 +155,12 @@ struct Slot {
                      // stitched: the tile entry of walk (s, j)
 };
 
+// Items (pairs of a unit) a wave takes from the block's cursor at once: 64, up
+// to `most` where the unit has enough of them for its 16 waves.
 constexpr uint32_t ITEM_CHUNK = 64;
+__device__ __forceinline__ uint32_t item_chunk(uint32_t total, uint32_t most) {
+    return min(max((total >> 8) & ~63u, ITEM_CHUNK), most);
+}
 // Pairs waiting for their stitched tails, per wave: a ring, a power of two
 // above 63 + 64 (a wave drains 64 as soon as 64 wait, after each slot's push).
 constexpr uint32_t TAIL_Q = 128;

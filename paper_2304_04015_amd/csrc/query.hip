@@ -520,12 +520,16 @@ __global__ __launch_bounds__(meet_block_of(KIND)) void k_meet(const QueryDesc *_
     constexpr bool STRAT = KIND == K_STRAT;
     constexpr int TJ = tile_j_of(KIND), TN = tile_nodes_of(KIND);
     __shared__ uint32_t s_nodes[TN];
-    __shared__ uint32_t s_j[TJ];
-    __shared__ uint16_t s_off[TJ + 1];
+    // the tile's entries: walk index j (below 2^24) | number of positions << 24,
+    // and their LDS offset
+    static_assert(MAX_R <= 1 << 24 && MAX_CAP < 256, "packed entries");
+    __shared__ uint32_t s_jl[TJ];
+    __shared__ uint16_t s_off[TJ];
     __shared__ uint32_t s_cnt[STRAT ? 1 : MEET_VB];
     __shared__ uint32_t s_vid[MEET_VB];
     __shared__ uint2 s_vrow[MEET_VB];
-    __shared__ uint32_t s_unit, s_item, s_slot, s_seq, s_last, s_run;
+    __shared__ uint32_t s_va[MEET_VB], s_vb[MEET_VB], s_vcc[MEET_VB];   // the draws' constants
+    __shared__ uint32_t s_unit, s_item, s_slot, s_seq, s_last, s_run, s_srcvl;
     // stratified: classes of the tile's source walks, class starts, the
     // shuffle keys of the unit's nodes, weighted sums
     __shared__ uint8_t s_cls[STRAT ? TJ : 1];
@@ -611,12 +615,11 @@ __global__ __launch_bounds__(meet_block_of(KIND)) void k_meet(const QueryDesc *_
             const uint32_t nb = d.joff[k0], ne = d.joff[k1];
             K = k1 - k0;
             for (uint32_t i = threadIdx.x; i < K; i += blockDim.x) {
-                const uint32_t jw = d.jj[k0 + i];
-                s_j[i] = jw;
-                s_off[i] = (uint16_t)(d.joff[k0 + i] - nb);
+                const uint32_t jw = d.jj[k0 + i], at = d.joff[k0 + i];
+                s_jl[i] = jw | ((d.joff[k0 + i + 1] - at) << 24);
+                s_off[i] = (uint16_t)(at - nb);
                 if (STRAT) s_cls[i] = d.scls[jw];
             }
-            if (threadIdx.x == 0) s_off[K] = (uint16_t)(ne - nb);
             for (uint32_t i = threadIdx.x; i < ne - nb; i += blockDim.x) s_nodes[i] = d.swc[nb + i];
             if (STRAT)
                 for (uint32_t i = threadIdx.x; i < (uint32_t)phi + 2; i += blockDim.x)
@@ -628,24 +631,45 @@ __global__ __launch_bounds__(meet_block_of(KIND)) void k_meet(const QueryDesc *_
         const uint32_t na = uni((uint32_t)d.n_active), nq0 = na / chunks, nrem = na - nq0 * chunks;
         const int32_t vbase = (int32_t)(chunk * nq0 + min(chunk, nrem));
         const uint32_t nv = nq0 + (chunk < nrem ? 1u : 0u);
+        if (threadIdx.x == 0) {
+            s_item = 0u;
+            s_srcvl = NIL;
+        }
+        __syncthreads();
         for (uint32_t i = threadIdx.x; i < MEET_VB; i += blockDim.x) {
             if (STRAT) s_w[i] = 0ull; else s_cnt[i] = 0u;
             if (i < nv) {
                 const uint32_t id = (uint32_t)d.active[vbase + (int32_t)i];
                 s_vid[i] = id;
                 s_vrow[i] = d.nodes[id];
+                const WalkDraws w = walk_draws_begin(id, 0u, key, STRAT ? DOM_STRAT : DOM_WALK);
+                s_va[i] = w.a;
+                s_vb[i] = w.b;
+                s_vcc[i] = w.cc;
+                if ((int32_t)id == src) s_srcvl = i;
                 if (STRAT) s_fk[i] = philox4x32_10(id, 0u, 0u, DOM_SHUFFLE, key);
             }
         }
-        if (threadIdx.x == 0) s_item = 0u;
         __syncthreads();
 
         // Pairs of the unit: item i = vl * K + k for node vl < nv and walk k < K.
         // (K and nv are the same in all lanes; said so, the refill's bookkeeping
         // stays in scalar registers)
-        const uint32_t total = nv * uni(K);
+        const uint32_t Ku = uni(K), total = nv * Ku;
         // wave-uniform chunk of items [ci, ce) and the (node, walk) of item ci
         uint32_t ci = 0, ce = 0, cvl = 0, ck = 0;
+        uint32_t vo = 0, vd = 0, va = 0, vb = 0, vcc = 0;   // node cvl's row and draw constants
+        const uint32_t srcvl = uni(s_srcvl), chunk_items = item_chunk(total, uni((uint32_t)d.items));
+        uint32_t at_vl = NIL;   // the node those are of
+        auto enter_node = [&]() {
+            at_vl = cvl;
+            const uint2 row = s_vrow[cvl];
+            vo = uni(row.x);
+            vd = uni(row.y);
+            va = uni(s_va[cvl]);
+            vb = uni(s_vb[cvl]);
+            vcc = uni(s_vcc[cvl]);
+        };
         bool drained = false;
         uint32_t qh = 0, qn = 0;   // stratified: the wave's queue of prepared pairs [qh, qn)
 
@@ -659,13 +683,12 @@ __global__ __launch_bounds__(meet_block_of(KIND)) void k_meet(const QueryDesc *_
             if (lane < (int)c) {
                 const uint2 r = s_tq[wave * TAIL_Q + ((tq_head + (uint32_t)lane) & (TAIL_Q - 1))];
                 const uint32_t vl = r.x >> 16, k = r.x & 0xffffu;
-                const uint32_t base = s_off[k];
-                const uint32_t len = (uint32_t)s_off[k + 1] - base;
+                const uint32_t base = s_off[k], jl = s_jl[k], len = jl >> 24;
                 const uint32_t seg_len = (uint32_t)d.ix.seg_len, width = (uint32_t)d.ix.width;
                 const uint32_t y = d.ix.node_of[r.y];
                 const int64_t pb = d.ix.pool_off[y];
                 const int64_t pe = d.ix.pool_off[y + 1];
-                const uint4 x = philox4x32_10(s_vid[vl], s_j[k], 0u, DOM_ENTRY, key);
+                const uint4 x = philox4x32_10(s_vid[vl], jl & 0xffffffu, 0u, DOM_ENTRY, key);
                 const uint32_t sigma = (uint32_t)(pb + (int64_t)pick64(x.x, (uint64_t)(pe - pb)));
                 const uint32_t *crow = d.ix.chain + (size_t)sigma * width;
                 uint32_t t = seg_len;
@@ -726,7 +749,7 @@ __global__ __launch_bounds__(meet_block_of(KIND)) void k_meet(const QueryDesc *_
                                 ok = (int32_t)s_vid[vl] != src;
                             }
                             if (ok) {
-                                r = shuffle_slot(s_j[k], NN, sa, sb, s_fk[vl]);
+                                r = shuffle_slot(s_jl[k] & 0xffffffu, NN, sa, sb, s_fk[vl]);
                                 cv = slot_class(r, s_ccum, phi);
                                 ok = cv > 0u;
                             }
@@ -745,10 +768,10 @@ __global__ __launch_bounds__(meet_block_of(KIND)) void k_meet(const QueryDesc *_
                             const uint2 e = s_q[wave * 64 + qh + rank];
                             const uint32_t vl = e.x >> 24, k = (e.x >> 8) & 0xffffu, cv = e.x & 0xffu;
                             const uint32_t base = s_off[k];
-                            const uint32_t len = min((uint32_t)s_off[k + 1] - base, cv);
+                            const uint32_t len = min(s_jl[k] >> 24, cv);
                             const uint2 row = s_vrow[vl];
                             sl[qq].aux = ((uint32_t)s_cls[k] << 8) | cv;
-                            sl[qq].rng = walk_draws_begin(s_vid[vl], e.y, key, DOM_STRAT);
+                            sl[qq].rng = WalkDraws{e.y, s_va[vl], s_vb[vl], s_vcc[vl], 0ull};
                             sl[qq].pos = base | (len << 16) | (vl << 24);
                             sl[qq].t = 0;
                             sl[qq].o = row.x;
@@ -768,51 +791,47 @@ __global__ __launch_bounds__(meet_block_of(KIND)) void k_meet(const QueryDesc *_
                         if (ci == ce) {
                             if (drained) break;
                             uint32_t x = 0;
-                            if (lane == 0) x = atomicAdd(&s_item, ITEM_CHUNK);
-                            x = __builtin_amdgcn_readfirstlane(x);
+                            if (lane == 0) x = atomicAdd(&s_item, chunk_items);
+                            x = uni(x);
                             if (x >= total) {
                                 drained = true;
                                 break;
                             }
                             ci = x;
-                            ce = min(x + ITEM_CHUNK, total);
-                            cvl = x / K;
-                            ck = x - cvl * K;
+                            ce = min(x + chunk_items, total);
+                            cvl = x / Ku;
+                            ck = x - cvl * Ku;
+                            if (cvl != at_vl) enter_node();
                         }
-                        const uint32_t want = (uint32_t)__popcll(need);
-                        const uint32_t avail = ce - ci;
-                        const uint32_t take = avail < want ? avail : want;
-                        const uint32_t rank = lane_rank(need);
-                        const bool mine = ((need >> lane) & 1ull) && rank < take;
-                        bool filled = false;
-                        if (mine) {
-                            uint32_t k = ck + rank, vl = cvl;
-                            while (k >= K) {
-                                k -= K;
-                                ++vl;
-                            }
-                            const uint32_t id = s_vid[vl];
-                            if ((int32_t)id != src) {   // the source's own pairs are not walked
-                                const uint32_t base = s_off[k];
-                                const uint32_t len = (uint32_t)s_off[k + 1] - base;
-                                const uint2 row = s_vrow[vl];
-                                sl[qq].rng = walk_draws_begin(id, s_j[k], key);
-                                sl[qq].pos = base | (len << 16) | (vl << 24);
-                                sl[qq].t = 0;
-                                sl[qq].o = row.x;
-                                sl[qq].d = row.y;
-                                sl[qq].busy = true;
-                                if (STITCHED) sl[qq].aux = k;
-                                filled = true;
+                        // the chunk's items of one node: its row and the draws'
+                        // constants are uniform (per lane, with the constants
+                        // formed anew for each pair and 64 items a chunk:
+                        // n = 40,000, R = 9,502: 1,688 us against 1,501)
+                        uint32_t take = min(ce - ci, Ku - ck);
+                        if (cvl != srcvl) {   // (the source's own pairs are not walked)
+                            take = min(take, (uint32_t)__popcll(need));
+                            const uint32_t rank = lane_rank(need);
+                            const bool mine = !sl[qq].busy && rank < take;
+                            if (mine) {
+                                const uint32_t jl = s_jl[ck + rank];
+                                Slot &w = sl[qq];
+                                w.rng = WalkDraws{jl & 0xffffffu, va, vb, vcc, 0ull};
+                                w.pos = (uint32_t)s_off[ck + rank] | ((jl >> 24) << 16) | (cvl << 24);
+                                w.t = 0;
+                                w.o = vo;
+                                w.d = vd;
+                                w.busy = true;
+                                if (STITCHED) w.aux = ck + rank;
                                 ++st_pairs;
                             }
+                            need &= ~__ballot(mine);
                         }
-                        need &= ~__ballot(filled);
                         ci += take;
                         ck += take;
-                        while (ck >= K && K > 0) {
-                            ck -= K;
+                        if (ck == Ku) {
+                            ck = 0;
                             ++cvl;
+                            if (ci < ce) enter_node();
                         }
                     }
                 }
@@ -1136,6 +1155,18 @@ int64_t units_bound_of(const Graph *g, int32_t R, int32_t L) {
     return (int64_t)max_tiles_for(R, L) * ((g->n_active + vb - 1) / vb);
 }
 
+// Items that a wave takes at once, at most.  The fewer, the closer together the
+// block's pairs are and the more rows they share in the L1; the more, the fewer
+// refills are cut short by a chunk's end.  Meet kernel with 64 / 128 / 256 / 512
+// items: n = 20,000 (2.5 MB of E), R = 38,005: 2,978 / 2,701 / 2,575 / 2,549 us;
+// n = 40,000 (5 MB), R = 9,502: 1,636 / 1,512 / 1,456 / 1,445; n = 150,001
+// (19 MB): 6,144 / 6,013 / 6,063 / 6,238; n = 2^18 (33 MB): 11.60 / 11.70 /
+// 11.92 / 12.40 ms; n = 2^20 (133 MB): 51.96 / 52.26 / 53.13 / 55.06.
+static int32_t items_for(const Graph *g) {
+    const int64_t e = 8 * g->m_slots;
+    return e <= (int64_t)8 << 20 ? 256 : e <= (int64_t)24 << 20 ? 128 : 64;
+}
+
 void describe_query(const Graph *g, const simrank_query *q, const simrank_params &p, int mode,
                     QueryDesc *d) {
     *d = QueryDesc{};
@@ -1153,6 +1184,7 @@ void describe_query(const Graph *g, const simrank_query *q, const simrank_params
     d->R = p.R;
     d->L = p.L;
     d->vb = g->tuned_vb;
+    d->items = items_for(g);
     d->kind = mode == SIMRANK_MODE_STITCHED ? K_STITCHED
               : mode == SIMRANK_MODE_STRATIFIED ? K_STRAT : K_PLAIN;
     const int32_t tj = g->tuned_tile_j[d->kind];
