@@ -591,9 +591,10 @@ def bench_tuples(args):
                       tuples_per_s=st.moves / (st.ms / 1e3), equal_to_fused=same,
                       sort_ms=st.meet_ms, sort_bytes=st.draws)
     r8 = res[8]
-    # the radix sort dominates the call: its algorithmic bytes (8 per key a
-    # histogram pass reads, 24 per tuple a scatter pass reads and writes) over
-    # its passes' device time (HIP events on the call's stream)
+    # the sort runs in LDS inside the tuple kernel: the bytes its passes move
+    # there (4 per key a pass counts, 12 per tuple it reads and writes) over the
+    # kernel's device time (HIP events on the call's stream), against the LDS
+    # bandwidth of 256 CUs (128 bytes a clock at 2.4 GHz)
     sort_gbs = r8["sort_bytes"] / (r8["sort_ms"] / 1e3) / 1e9
     result = {
         "metric": METRIC,
@@ -616,12 +617,12 @@ def bench_tuples(args):
         "k8": res[8],
         "k32": res[32],
         "roofline": {
-            "bound": "hbm",
-            "kernel": "radix sort passes (k_rs_hist + k_rs_scatter), 8 sources",
+            "bound": "lds",
+            "kernel": "k_tuples (walks, LDS sort, PREDECESSOR, link), 8 sources",
             "achieved": sort_gbs,
-            "peak": HBM_PEAK_GBS,
+            "peak": 256 * 128 * 2.4,
             "unit": "GB/s",
-            "frac": sort_gbs / HBM_PEAK_GBS,
+            "frac": sort_gbs / (256 * 128 * 2.4),
             "traffic": None,
         },
     }

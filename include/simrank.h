@@ -275,12 +275,15 @@ int simrank_stratified_walks(const simrank_graph *g, const simrank_query *q, con
  * sums: host uint64[k][n].  Plain queries: meet counts, sums[q][s_q] = R (equal
  * to simrank_single_source_ex's counts).  Stratified queries: weighted sums in
  * units of 2^-40, sums[q][s_q] = 0 (equal to simrank_single_source_stratified's
- * wsum).  Nodes are processed in chunks whose tuples fit a 2^28-entry buffer.
+ * wsum).  The tuples of walks j of a run of nodes are sorted in LDS, those of one
+ * or several steps at a time; steps (j, i) that no source's walk has are not
+ * sorted.  No device memory beyond the results is taken.
  * st_opt: moves = steps of the nodes' walks (= tuples), meets = meeting pairs,
- * ms = device time; for this call meet_ms is the device time of the radix
- * sort's passes (summed over the chunks) and draws the bytes they move (8 per
- * key a histogram pass reads, 24 per tuple a scatter pass reads and writes).  EINVAL for stitched queries, k outside [1, 32], queries
- * that differ in anything but s, or a source out of range.
+ * ms = device time; for this call meet_ms is the device time of the kernel
+ * that walks, sorts and links, and draws the bytes the sort's passes move (4
+ * per key a pass counts, 12 per tuple it reads and writes).  EINVAL for
+ * stitched queries, k outside [1, 32], queries that differ in anything but s,
+ * a source out of range, or sources' tuples and one node's beyond 2^32 - 2.
  */
 int simrank_tuple_meets(const simrank_graph *g, const simrank_query *qs, int32_t k,
                         uint64_t *sums, simrank_stats *st_opt);

@@ -92,23 +92,30 @@ __device__ __forceinline__ WalkDraws walk_draws_begin(uint32_t v, uint32_t j, Ph
     return w;
 }
 
-// Draw for the next step t (the first call gives t = 1): returns (x0, x1).
-__device__ __forceinline__ uint2 walk_draw_next(WalkDraws &w, PhiloxKey key) {
-    w.mt += (uint64_t)philox_m1();
+// Draw (x0, x1) of step t of a walk: its index j, its constants (WalkDraws a,
+// b, cc) and mt = M1 * t.
+__device__ __forceinline__ uint2 walk_draw_at(uint32_t j, uint32_t wa, uint32_t wb, uint32_t wcc,
+                                              uint64_t mt, PhiloxKey key) {
     // round 1: word 0 = hi(M1 t) ^ j ^ k0, word 1 = lo(M1 t); words 2, 3 fixed
-    const uint32_t r1w0 = xor_key((uint32_t)(w.mt >> 32), w.j, round_key0(key, 0));
-    const uint32_t r1w1 = (uint32_t)w.mt;
+    const uint32_t r1w0 = xor_key((uint32_t)(mt >> 32), j, round_key0(key, 0));
+    const uint32_t r1w1 = (uint32_t)mt;
     // round 2
     const uint64_t p0 = (uint64_t)philox_m0() * (uint64_t)r1w0;
-    uint32_t c0 = w.a ^ r1w1;
-    uint32_t c1 = w.b;
-    uint32_t c2 = (uint32_t)(p0 >> 32) ^ w.cc;
+    uint32_t c0 = wa ^ r1w1;
+    uint32_t c1 = wb;
+    uint32_t c2 = (uint32_t)(p0 >> 32) ^ wcc;
     uint32_t c3 = (uint32_t)p0;
 #pragma unroll
     for (int r = 2; r < 9; ++r) philox_round(c0, c1, c2, c3, round_key0(key, r), round_key1(key, r));
     // round 10: words 0 and 1 only
     const uint64_t p1 = (uint64_t)philox_m1() * (uint64_t)c2;
     return make_uint2(xor_key((uint32_t)(p1 >> 32), c1, round_key0(key, 9)), (uint32_t)p1);
+}
+
+// Draw for the next step t (the first call gives t = 1): returns (x0, x1).
+__device__ __forceinline__ uint2 walk_draw_next(WalkDraws &w, PhiloxKey key) {
+    w.mt += (uint64_t)philox_m1();
+    return walk_draw_at(w.j, w.a, w.b, w.cc, w.mt, key);
 }
 
 // floor(x * k / 2^32): a uniform index in [0, k) from one 32-bit word.

@@ -7,18 +7,24 @@
 // equal (j, i, node) is a meet of walk j of that source and walk j of the
 // tuple's start node, counted once per pair.
 //
-// On one GPU the tuples of all walks do not fit at once (3.3e10 at the medium
-// size), so the nodes are cut into chunks whose tuples fit a buffer, and each
-// chunk's tuples are sorted together with the sources' own.  A chunk:
-//   1. lengths of its walks (and the sources'), an exclusive scan of them;
-//   2. the walks again, writing 64-bit keys j | i | o | flag and a 32-bit
-//      payload (walk id, or source number), flag 0 for a source tuple;
-//   3. an LSD radix sort of the keys, 8 bits per pass, stable;
-//   4. PREDECESSOR as an inclusive running maximum of (position + 1) over the
-//      source tuples; each other tuple walks back over the source tuples of its
-//      key and sets one bit per meeting source in its walk's mask;
-//   5. per node, the masks are reduced to counts (plain walks) or Lemma 5's
-//      weighted sums (stratified walks).
+// The first two parts of the key need no sort: a block takes the walks j of a
+// run of TU_ROWS start nodes and of the sources, steps them together, and so
+// makes the tuples of one (j, i) at a time, of several once fewer walks are
+// left (up to TU_STEPS steps that fit the buffer).  It sorts those in LDS by
+// (i, node), sources first (an LSD radix sort, stable), finds each tuple's predecessor
+// among the sources' tuples as a running maximum, and links; the pairs that
+// have met are kept in one bit per source and start node.  Tuples never leave
+// the CU.  Where no source's walk j has a step i, no tuple of (j, i) can be
+// linked: the walks are then only followed to their ends and counted.
+//
+// What bounds it: at n = 2^14 the LDS passes and their barriers, at n = 2^20 the
+// L2 misses of the steps.  The form before it wrote the tuples of a chunk of
+// nodes to memory (12 bytes each), sorted them on the whole key in five or six
+// passes over memory of 32 bytes a tuple, and took a scan and a link pass more.
+// Before and now, 8 sources: n = 2^14, R = 1,521 (5.6e7 tuples) 9.6 and 2.5 ms;
+// n = 50,000 23.8 and 7.3 ms; n = 2^20, R = 9,502 (1.73e10 tuples) 2.54 and
+// 0.73 s, of which sorting each step by itself took another 0.16 s.
+//
 // Walks are the same as the fused kernel's (same keys, same steps), but are
 // followed to their full length rather than to the first meet, so the counts
 // must agree with the fused path: an independent cross-check of it, and the
@@ -35,245 +41,350 @@ namespace srk {
 namespace {
 
 constexpr int MAX_TUPLE_SOURCES = 32;
-constexpr int RS_BLOCK = 256;                     // threads of the sort kernels
-#ifndef SRK_RS_ROUNDS
-#define SRK_RS_ROUNDS 8
-#endif
-constexpr int RS_ROUNDS = SRK_RS_ROUNDS;          // 64-key rounds per wave and tile
-constexpr int RS_TILE = RS_BLOCK * RS_ROUNDS;     // 2048 keys per tile
-constexpr int32_t MAX_GRID_Y = 65535;
+constexpr int TU_BLOCK = 512;                     // two blocks a CU
+constexpr int TU_WAVES = TU_BLOCK / 64;
+constexpr int TU_RPT = 7;                         // start nodes per thread
+constexpr int TU_ROWS = TU_RPT * TU_BLOCK;        // start nodes per unit
+constexpr int TU_CAP = TU_ROWS + MAX_TUPLE_SOURCES;   // tuples sorted at once
+constexpr int TU_STEP_BITS = 3;                   // of up to 8 steps
+constexpr int TU_DIGITS = 512;                    // digits of a sort pass, at most (9 bits)
+constexpr int TU_ROUNDS = (TU_CAP + TU_BLOCK - 1) / TU_BLOCK;
+constexpr uint32_t TU_SRC = 0x8000u;              // payload flag of a source's tuple
+static_assert(TU_DIGITS == TU_BLOCK, "one digit per thread");
+static_assert(TU_ROWS < (int)TU_SRC, "payloads in 16 bits");
 
 struct TupleArgs {
     const uint2 *nodes;
     const uint2 *E;
-    const int32_t *active;       // chunk node vl is active[a0 + vl]
-    int32_t a0, V;               // first active index of the chunk, its nodes
+    const int32_t *active;       // start nodes
+    int32_t na;                  // their number
     int32_t N, L;                // walks per node; cap (stratified: phi)
     PhiloxKey key;
     uint32_t T;                  // plain: continue threshold
-    int32_t strat;
     const StratTab *tab;         // stratified: class table
     uint32_t sa, sb;             // stratified: shuffle grid
     const int32_t *src;          // [k] source nodes
     int32_t k;
-    uint32_t ib, nb;             // key fields: bits of the step, of the o-value
+    int32_t nb, step_bits;       // bits of an o-value; of a step's number within a sort
+    int32_t n;
+    int64_t units;               // runs of start nodes x N
+    unsigned long long *out;     // [k][n]
+    unsigned long long *counters;
 };
 
-// Walk (v, j) of the query's kind, followed to its end; f(i, o) for every
-// position i >= 1 (o-value of the node).  *cls_out: the stratified class.
-template <typename F>
-__device__ __forceinline__ uint32_t tuple_walk(const TupleArgs &a, uint32_t v, uint32_t j,
-                                               uint32_t *cls_out, F f) {
-    uint2 cur = a.nodes[v];
-    uint32_t len = 0;
-    if (a.strat) {
-        const uint4 fk = philox4x32_10(v, 0u, 0u, DOM_SHUFFLE, a.key);
-        const uint32_t r = shuffle_slot(j, (uint32_t)a.N, a.sa, a.sb, fk);
-        const uint32_t cls = slot_class(r, a.tab->ccum, a.L);
-        *cls_out = cls;
-        WalkDraws w = walk_draws_begin(v, r, a.key, DOM_STRAT);
-        for (uint32_t t = 1; t <= cls; ++t) {
-            if (cur.y == 0) break;
-            const uint2 x = walk_draw_next(w, a.key);
-            cur = a.E[cur.x + pick32(x.y, cur.y)];
-            f(t, cur.x);
-            len = t;
-        }
-    } else {
-        *cls_out = 0;
-        WalkDraws w = walk_draws_begin(v, j, a.key);
-        for (uint32_t t = 1; t <= (uint32_t)a.L; ++t) {
-            const uint2 x = walk_draw_next(w, a.key);
-            if (x.x >= a.T || cur.y == 0) break;
-            cur = a.E[cur.x + pick32(x.y, cur.y)];
-            f(t, cur.x);
-            len = t;
-        }
-    }
-    return len;
-}
-
-__device__ __forceinline__ uint32_t row_node(const TupleArgs &a, int32_t row) {
-    return row < a.V ? (uint32_t)a.active[a.a0 + row] : (uint32_t)a.src[row - a.V];
-}
-
-// Walk lengths.  Rows 0..V-1 are the chunk's nodes, rows V..rows-1 the
-// sources; grid (x over j, y over rows, strided).  lens[row N + j] (may be
-// NULL); row_sum[row] += the row's tuples (may be NULL); cls_src[q N + j] the
-// class of the sources' walks (stratified).
-__global__ __launch_bounds__(256) void k_tw_len(TupleArgs a, int32_t rows, uint32_t *lens,
-                                                unsigned long long *row_sum, uint8_t *cls_src) {
-    __shared__ unsigned long long part[4];
-    const int32_t j = blockIdx.x * 256 + threadIdx.x;
-    for (int32_t row = blockIdx.y; row < rows; row += gridDim.y) {
-        uint32_t len = 0;
-        if (j < a.N) {
-            uint32_t cls;
-            len = tuple_walk(a, row_node(a, row), (uint32_t)j, &cls, [](uint32_t, uint32_t) {});
-            if (lens) lens[(size_t)row * a.N + j] = len;
-            if (cls_src && row >= a.V) cls_src[(size_t)(row - a.V) * a.N + j] = (uint8_t)cls;
-        }
-        if (row_sum) {
-            unsigned long long s = len;
-            for (int d = 32; d > 0; d >>= 1) s += __shfl_xor(s, d, 64);
-            if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
-            __syncthreads();
-            if (threadIdx.x == 0) {
-                const unsigned long long t = part[0] + part[1] + part[2] + part[3];
-                if (t) atomicAdd(&row_sum[row], t);
-            }
-            __syncthreads();
-        }
-    }
-}
-
-// The tuples of every walk at its scanned offset.
-__global__ __launch_bounds__(256) void k_tw_emit(TupleArgs a, int32_t rows,
-                                                 const int64_t *__restrict__ offs,
-                                                 uint64_t *__restrict__ keys,
-                                                 uint32_t *__restrict__ vals) {
-    const int32_t j = blockIdx.x * 256 + threadIdx.x;
-    if (j >= a.N) return;
-    for (int32_t row = blockIdx.y; row < rows; row += gridDim.y) {
-        const bool is_src = row >= a.V;
-        const uint64_t flag = is_src ? 0ull : 1ull;
-        const uint32_t val = is_src ? (uint32_t)(row - a.V) : (uint32_t)(row * a.N + j);
-        const uint64_t hj = (uint64_t)j << (a.ib + a.nb + 1);
-        int64_t p = offs[(size_t)row * a.N + j];
-        uint32_t cls;
-        tuple_walk(a, row_node(a, row), (uint32_t)j, &cls, [&](uint32_t i, uint32_t o) {
-            keys[p] = hj | ((uint64_t)i << (a.nb + 1)) | ((uint64_t)o << 1) | flag;
-            vals[p] = val;
-            ++p;
-        });
-    }
-}
-
-// ---------------------------------------------------------------- radix sort
-// LSD, 8-bit digits, stable.  Tile = 2048 keys: 4 waves x 8 rounds x 64
-// (against 4096 keys: 2.54 vs 2.99 s per 8-source call on the medium graph,
-// with four blocks per CU instead of two).
-
-__device__ __forceinline__ uint64_t match_digit(uint32_t d, bool valid) {
+// Lanes of the wave with the same digit (db bits) as this one.
+__device__ __forceinline__ uint64_t match_digit(uint32_t d, int db, bool valid) {
     uint64_t m = __ballot(valid);
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
+    for (int b = 0; b < db; ++b) {
         const uint64_t bb = __ballot((d >> b) & 1u);
         m &= ((d >> b) & 1u) ? bb : ~bb;
     }
     return m;
 }
 
-__global__ __launch_bounds__(RS_BLOCK) void k_rs_hist(const uint64_t *__restrict__ keys,
-                                                      int64_t count, int shift,
-                                                      uint32_t *__restrict__ hist, int64_t tiles) {
-    __shared__ uint32_t h[256];
-    const int64_t tile = blockIdx.x;
-    h[threadIdx.x] = 0u;
-    __syncthreads();
-    const int64_t base = tile * RS_TILE;
-    for (int it = 0; it < RS_ROUNDS; ++it) {
-        const int64_t idx = base + (int64_t)it * RS_BLOCK + threadIdx.x;
-        if (idx < count) atomicAdd(&h[(uint32_t)(keys[idx] >> shift) & 255u], 1u);
+// One walker: the walk j of a start node or source.
+struct Walker {
+    uint32_t id, o, d;   // start node; current node
+    uint32_t r;          // the draws' walk index (stratified: the slot pi(j))
+    uint32_t end;        // steps it may take: L, or its class
+    bool alive;
+};
+
+template <bool STRAT>
+__device__ __forceinline__ Walker walker_begin(const TupleArgs &a, uint32_t id, uint32_t j,
+                                               const uint32_t *ccum) {
+    const uint2 row = a.nodes[id];
+    Walker w{id, row.x, row.y, j, (uint32_t)a.L, true};
+    if (STRAT) {
+        const uint4 fk = philox4x32_10(id, 0u, 0u, DOM_SHUFFLE, a.key);
+        w.r = shuffle_slot(j, (uint32_t)a.N, a.sa, a.sb, fk);
+        w.end = slot_class(w.r, ccum, a.L);
+        w.alive = w.end > 0u;
     }
-    __syncthreads();
-    hist[(int64_t)threadIdx.x * tiles + tile] = h[threadIdx.x];
+    return w;
 }
 
-// offs[d * tiles + t]: exclusive scan of hist, i.e. where tile t's keys with
-// digit d start.  Within a tile the keys are first put in digit order in LDS
-// (earlier waves first, then rounds, then lanes: the input order, so the sort
-// stays stable); then consecutive threads write consecutive keys, so each
-// digit's run of a tile goes out as contiguous stores.
-__global__ __launch_bounds__(RS_BLOCK) void k_rs_scatter(const uint64_t *__restrict__ kin,
-                                                         const uint32_t *__restrict__ vin,
-                                                         uint64_t *__restrict__ kout,
-                                                         uint32_t *__restrict__ vout,
-                                                         int64_t count, int shift,
-                                                         const int64_t *__restrict__ offs,
-                                                         int64_t tiles) {
-    __shared__ uint64_t sk[RS_TILE];
-    __shared__ uint32_t sv[RS_TILE];
-    __shared__ uint32_t wtot[4][256];   // per wave and digit: count, then local start
-    __shared__ uint32_t wrun[4][256];
-    __shared__ uint32_t dstart[256];    // tile-local start of each digit
+// Whether the walker takes step i (its draw in *x1 then picks the neighbour).
+template <bool STRAT>
+__device__ __forceinline__ bool walker_goes(const TupleArgs &a, const Walker &w, uint32_t i,
+                                            uint32_t *x1) {
+    if (!w.alive || i > w.end || w.d == 0u) return false;
+    const WalkDraws c = walk_draws_begin(w.id, w.r, a.key, STRAT ? DOM_STRAT : DOM_WALK);
+    const uint2 x = walk_draw_at(c.j, c.a, c.b, c.cc, (uint64_t)philox_m1() * i, a.key);
+    *x1 = x.y;
+    return STRAT || x.x < a.T;
+}
+
+template <bool STRAT>
+__global__ __launch_bounds__(TU_BLOCK) void k_tuples(TupleArgs a) {
+    __shared__ uint32_t s_key[2][TU_CAP];            // tuples: step within the sort, o-value
+    __shared__ uint16_t s_val[2][TU_CAP];            // and start node (run-local) or source
+    __shared__ uint32_t s_met[TU_ROWS];              // sources that walk (v, j) has met
+    __shared__ uint32_t s_cnt[TU_WAVES][TU_DIGITS];  // per wave and digit: count, then start
+    __shared__ uint32_t s_ccum[STRAT ? MAX_CAP + 2 : 1];
+    __shared__ uint32_t s_srccls[MAX_TUPLE_SOURCES];
+    // tuples in the buffer, sources' tuples of the step: of even and odd steps,
+    // so that a wave a step ahead leaves the others' alone
+    __shared__ uint32_t s_n[2], s_nsrc[2], s_last[TU_WAVES];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t tile = blockIdx.x;
-    const int64_t tbase = tile * RS_TILE;
-    const int64_t base = tbase + (int64_t)wave * (RS_ROUNDS * 64);
-    const int32_t n_tile = (int32_t)min((int64_t)RS_TILE, count - tbase);
-    for (int i = threadIdx.x; i < 4 * 256; i += RS_BLOCK) {
-        (&wtot[0][0])[i] = 0u;
-        (&wrun[0][0])[i] = 0u;
+    const GlobalPtr<uint64_t> E = (GlobalPtr<uint64_t>)a.E;
+    unsigned long long moves = 0, sorted = 0;
+    uint32_t meets = 0;
+    if (STRAT) {
+        for (int i = threadIdx.x; i < a.L + 2; i += TU_BLOCK) s_ccum[i] = a.tab->ccum[i];
+        __syncthreads();
     }
-    __syncthreads();
-    uint64_t key[RS_ROUNDS];   // the wave's keys of the tile, kept for the second pass
+
+    for (int64_t unit = blockIdx.x; unit < a.units; unit += gridDim.x) {
+        const int64_t run = unit / a.N;
+        const uint32_t j = (uint32_t)(unit - run * a.N);
+        const int32_t row0 = (int32_t)(run * TU_ROWS);
+        Walker w[TU_RPT], sw{};
 #pragma unroll
-    for (int r = 0; r < RS_ROUNDS; ++r) {
-        const int64_t idx = base + r * 64 + lane;
-        const bool valid = idx < count;
-        key[r] = valid ? kin[idx] : 0ull;
-        const uint32_t d = (uint32_t)(key[r] >> shift) & 255u;
-        const uint64_t m = match_digit(d, valid);
-        if (valid && lane == __ffsll((long long)m) - 1) atomicAdd(&wtot[wave][d], (uint32_t)__popcll(m));
-    }
-    __syncthreads();
-    {
-        // digit dg: its count over the tile, then an exclusive scan over digits
-        const int dg = threadIdx.x;   // RS_BLOCK == 256: one digit per thread
-        uint32_t c = 0;
-        for (int w = 0; w < 4; ++w) c += wtot[w][dg];
-        uint32_t total;
-        const uint32_t start = block_excl_sum(c, &total);
-        dstart[dg] = start;
-        uint32_t acc = start;
-        for (int w = 0; w < 4; ++w) {
-            const uint32_t x = wtot[w][dg];
-            wtot[w][dg] = acc;
-            acc += x;
+        for (int q = 0; q < TU_RPT; ++q) {
+            const int32_t row = q * TU_BLOCK + (int32_t)threadIdx.x;
+            s_met[row] = 0u;
+            w[q].alive = false;
+            if (row0 + row < a.na) w[q] = walker_begin<STRAT>(a, (uint32_t)a.active[row0 + row], j, s_ccum);
         }
-    }
-    __syncthreads();
-    const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+        if ((int)threadIdx.x < a.k) {
+            sw = walker_begin<STRAT>(a, (uint32_t)a.src[threadIdx.x], j, s_ccum);
+            if (STRAT) s_srccls[threadIdx.x] = sw.end;
+        }
+
+        uint32_t steps = 0, held = 0;   // steps and tuples in the buffer (uniform)
+        for (uint32_t i = 1; i <= (uint32_t)a.L; ++i) {
+            // ---- the step: all draws, then all gathers
+            bool go[TU_RPT];
+            uint2 e[TU_RPT];
 #pragma unroll
-    for (int r = 0; r < RS_ROUNDS; ++r) {
-        const int64_t idx = base + r * 64 + lane;
-        const bool valid = idx < count;
-        const uint32_t d = (uint32_t)(key[r] >> shift) & 255u;
-        const uint64_t m = match_digit(d, valid);
-        const int leader = valid ? __ffsll((long long)m) - 1 : lane;
-        uint32_t old = 0;
-        if (valid && lane == leader) old = atomicAdd(&wrun[wave][d], (uint32_t)__popcll(m));
-        old = __shfl(old, leader, 64);
-        if (valid) {
-            const uint32_t lp = wtot[wave][d] + old + (uint32_t)__popcll(m & lt);
-            sk[lp] = key[r];
-            sv[lp] = vin[idx];
+            for (int q = 0; q < TU_RPT; ++q) {
+                uint32_t x1 = 0;
+                go[q] = walker_goes<STRAT>(a, w[q], i, &x1);
+                w[q].alive = go[q];
+                if (go[q]) e[q] = load_edge(E, w[q].o + pick32(x1, w[q].d));
+            }
+            bool any = false;
+#pragma unroll
+            for (int q = 0; q < TU_RPT; ++q)
+                if (go[q]) {
+                    w[q].o = e[q].x;
+                    w[q].d = e[q].y;
+                    ++moves;
+                    any = true;
+                }
+            // ---- the sources' tuples first
+            if (wave == 0) {
+                uint32_t x1 = 0;
+                const bool sgo = walker_goes<STRAT>(a, sw, i, &x1);
+                sw.alive = sgo;
+                if (sgo) {
+                    const uint2 se = load_edge(E, sw.o + pick32(x1, sw.d));
+                    sw.o = se.x;
+                    sw.d = se.y;
+                }
+                const uint64_t m = __ballot(sgo);
+                if (sgo) {
+                    const uint32_t p = held + lane_rank(m);
+                    s_key[0][p] = sw.o | (steps << a.nb);
+                    s_val[0][p] = (uint16_t)(TU_SRC | threadIdx.x);
+                }
+                if (lane == 0) {
+                    s_n[i & 1u] = held + (uint32_t)__popcll(m);
+                    s_nsrc[i & 1u] = (uint32_t)__popcll(m);
+                }
+            }
+            __syncthreads();
+            const uint32_t nsrc = uni(s_nsrc[i & 1u]), before = held + nsrc;
+            // ---- then the start nodes' tuples, in any order
+            if (nsrc != 0u) {
+#pragma unroll
+                for (int q = 0; q < TU_RPT; ++q) {
+                    const uint64_t m = __ballot(go[q]);
+                    uint32_t base = 0;
+                    if (m && lane == 0) base = atomicAdd(&s_n[i & 1u], (uint32_t)__popcll(m));
+                    base = uni(base);
+                    if (go[q]) {
+                        const uint32_t p = base + lane_rank(m);
+                        s_key[0][p] = w[q].o | (steps << a.nb);
+                        s_val[0][p] = (uint16_t)(q * TU_BLOCK + (int)threadIdx.x);
+                    }
+                }
+                ++steps;
+            } else {
+                // no tuple of this or a later step can be linked: follow the
+                // walks to their ends
+                for (uint32_t t = i + 1; __ballot(any) != 0ull && t <= (uint32_t)a.L; ++t) {
+                    any = false;
+#pragma unroll
+                    for (int q = 0; q < TU_RPT; ++q) {
+                        uint32_t x1 = 0;
+                        go[q] = walker_goes<STRAT>(a, w[q], t, &x1);
+                        w[q].alive = go[q];
+                        if (go[q]) e[q] = load_edge(E, w[q].o + pick32(x1, w[q].d));
+                    }
+#pragma unroll
+                    for (int q = 0; q < TU_RPT; ++q)
+                        if (go[q]) {
+                            w[q].o = e[q].x;
+                            w[q].d = e[q].y;
+                            ++moves;
+                            any = true;
+                        }
+                }
+            }
+            __syncthreads();
+            const uint32_t count = uni(s_n[i & 1u]);
+            held = count;
+            // the walks end when no source or no start node has a step i; the
+            // buffer is sorted then, or when the next step (which has no more
+            // tuples than this one) may not fit
+            const bool ended = nsrc == 0u || count == before || i == (uint32_t)a.L;
+            if (!ended && steps < (1u << a.step_bits) && count + (count - before) + nsrc <= (uint32_t)TU_CAP)
+                continue;
+            if (count == 0u) break;   // (then ended)
+
+            // ---- stable LSD sort by (step, o-value): wave w takes the w-th run of
+            // the tuples, so earlier waves, rounds and lanes come first
+            const int bits = a.nb + (steps > 1u ? 32 - __builtin_clz(steps - 1u) : 0);
+            const int passes = (bits + 8) / 9, digit_bits = (bits + passes - 1) / passes;
+            if (threadIdx.x == 0) sorted += (unsigned long long)count * passes;
+            const uint32_t rounds = (count + TU_BLOCK - 1) / TU_BLOCK;
+            int buf = 0;
+            for (int ps = 0; ps < passes; ++ps) {
+                const int shift = ps * digit_bits;
+                const uint32_t dmask = (1u << digit_bits) - 1u;
+                for (int b = threadIdx.x; b < TU_WAVES * TU_DIGITS; b += TU_BLOCK) (&s_cnt[0][0])[b] = 0u;
+                __syncthreads();
+                uint32_t key[TU_ROUNDS], rank[TU_ROUNDS];
+#pragma unroll
+                for (int r = 0; r < TU_ROUNDS; ++r) {
+                    if ((uint32_t)r >= rounds) break;
+                    const uint32_t p = (uint32_t)wave * rounds * 64u + (uint32_t)r * 64u + (uint32_t)lane;
+                    const bool valid = p < count;
+                    key[r] = valid ? s_key[buf][p] : 0u;
+                    const uint32_t dg = (key[r] >> shift) & dmask;
+                    const uint64_t m = match_digit(dg, digit_bits, valid);
+                    const int leader = valid ? __builtin_ctzll(m) : lane;
+                    uint32_t old = 0;
+                    if (valid && lane == leader) old = atomicAdd(&s_cnt[wave][dg], (uint32_t)__popcll(m));
+                    old = __shfl(old, leader, 64);
+                    rank[r] = old + lane_rank(m);
+                }
+                __syncthreads();
+                {
+                    uint32_t c[TU_WAVES], sum = 0, total;
+#pragma unroll
+                    for (int v = 0; v < TU_WAVES; ++v) {
+                        c[v] = s_cnt[v][threadIdx.x];
+                        sum += c[v];
+                    }
+                    uint32_t at = block_excl_sum(sum, &total);
+#pragma unroll
+                    for (int v = 0; v < TU_WAVES; ++v) {
+                        s_cnt[v][threadIdx.x] = at;
+                        at += c[v];
+                    }
+                }
+                __syncthreads();
+#pragma unroll
+                for (int r = 0; r < TU_ROUNDS; ++r) {
+                    if ((uint32_t)r >= rounds) break;
+                    const uint32_t p = (uint32_t)wave * rounds * 64u + (uint32_t)r * 64u + (uint32_t)lane;
+                    if (p >= count) continue;
+                    const uint32_t to = s_cnt[wave][(key[r] >> shift) & dmask] + rank[r];
+                    s_key[buf ^ 1][to] = key[r];
+                    s_val[buf ^ 1][to] = s_val[buf][p];
+                }
+                __syncthreads();
+                buf ^= 1;
+            }
+
+            // ---- PREDECESSOR: (position + 1) of the last source tuple at or
+            // before each position, a running maximum
+            const uint32_t p0 = min(count, threadIdx.x * rounds), p1 = min(count, p0 + rounds);
+            uint32_t mine = 0;
+            for (uint32_t p = p0; p < p1; ++p)
+                if (s_val[buf][p] & TU_SRC) mine = p + 1u;
+            uint32_t inc = mine;
+            for (int dd = 1; dd < 64; dd <<= 1) {
+                const uint32_t y = __shfl_up(inc, dd, 64);
+                if (lane >= dd) inc = max(inc, y);
+            }
+            if (lane == 63) s_last[wave] = inc;
+            uint32_t last = __shfl_up(inc, 1, 64);
+            if (lane == 0) last = 0;
+            __syncthreads();
+            for (int v = 0; v < wave; ++v) last = max(last, s_last[v]);
+            // ---- link: the closest source tuple, and those before it with the
+            // same key (the sources' tuples of a key are contiguous, and first)
+            for (uint32_t p = p0; p < p1; ++p) {
+                const uint32_t val = s_val[buf][p];
+                if (val & TU_SRC) {
+                    last = p + 1u;
+                    continue;
+                }
+                const uint32_t kp = s_key[buf][p];
+                uint32_t bits = 0;
+                for (uint32_t q = last; q > 0u && s_key[buf][q - 1u] == kp; --q)
+                    bits |= 1u << (s_val[buf][q - 1u] & 31u);
+                if (!bits) continue;
+                uint32_t fresh = bits & ~atomicOr(&s_met[val], bits);   // a pair counts once
+                if (!fresh) continue;
+                const uint32_t v = (uint32_t)a.active[row0 + (int32_t)val];
+                uint32_t cv = 0;
+                if (STRAT) {
+                    const uint4 fk = philox4x32_10(v, 0u, 0u, DOM_SHUFFLE, a.key);
+                    cv = slot_class(shuffle_slot(j, (uint32_t)a.N, a.sa, a.sb, fk), s_ccum, a.L);
+                }
+                for (; fresh; fresh &= fresh - 1u) {
+                    const int q = __builtin_ctz(fresh);
+                    if ((uint32_t)a.src[q] == v) continue;
+                    atomicAdd(&a.out[(size_t)q * a.n + v],
+                              STRAT ? strat_weight(a.tab->a, s_srccls[q], cv) : 1ull);
+                    ++meets;
+                }
+            }
+            if (ended) break;
+            steps = held = 0;
+            __syncthreads();
         }
+        __syncthreads();
     }
-    __syncthreads();
-    for (int32_t i = threadIdx.x; i < n_tile; i += RS_BLOCK) {
-        const uint64_t k = sk[i];
-        const uint32_t d = (uint32_t)(k >> shift) & 255u;
-        const int64_t pos = offs[(int64_t)d * tiles + tile] + (i - (int32_t)dstart[d]);
-        kout[pos] = k;
-        vout[pos] = sv[i];
+    for (int dd = 32; dd > 0; dd >>= 1) {
+        moves += __shfl_xor(moves, dd, 64);
+        meets += __shfl_xor(meets, dd, 64);
+    }
+    if (lane == 0) {
+        unsigned long long *to = ctr_set(a.counters);
+        if (moves) atomicAdd(&to[C_MOVES], moves);
+        if (meets) atomicAdd(&to[C_MEETS], (unsigned long long)meets);
+        if (sorted) atomicAdd(&to[C_SPARE], sorted);
     }
 }
 
-// ------------------------------------------------------------- PREDECESSOR
-
-__global__ void k_tw_last_init(const uint64_t *__restrict__ keys, int64_t count,
-                               uint32_t *__restrict__ last) {
-    for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < count;
-         p += (int64_t)gridDim.x * blockDim.x)
-        last[p] = (keys[p] & 1ull) ? 0u : (uint32_t)(p + 1);
-}
-
-__global__ void k_fill_u32(uint32_t *p, int64_t n, uint32_t v) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = v;
+// Steps of each start node's walks (grid: x over j, y over nodes, strided), for
+// the limit on one node's tuples.
+__global__ __launch_bounds__(256) void k_row_tuples(TupleArgs a, bool strat, unsigned long long *row_sum) {
+    const int32_t j = blockIdx.x * 256 + threadIdx.x;
+    for (int32_t row = blockIdx.y; row < a.na; row += gridDim.y) {
+        unsigned long long len = 0;
+        if (j < a.N) {
+            const uint32_t id = (uint32_t)a.active[row];
+            Walker w = strat ? walker_begin<true>(a, id, (uint32_t)j, a.tab->ccum)
+                             : walker_begin<false>(a, id, (uint32_t)j, nullptr);
+            for (uint32_t i = 1; i <= (uint32_t)a.L; ++i) {
+                uint32_t x1 = 0;
+                if (!(strat ? walker_goes<true>(a, w, i, &x1) : walker_goes<false>(a, w, i, &x1))) break;
+                const uint2 e = a.E[w.o + pick32(x1, w.d)];
+                w.o = e.x;
+                w.d = e.y;
+                ++len;
+            }
+        }
+        for (int d = 32; d > 0; d >>= 1) len += __shfl_xor(len, d, 64);
+        if ((threadIdx.x & 63) == 0 && len) atomicAdd(&row_sum[row], len);
+    }
 }
 
 __global__ void k_fill_u64(unsigned long long *p, int64_t n) {
@@ -282,64 +393,16 @@ __global__ void k_fill_u64(unsigned long long *p, int64_t n) {
         p[i] = 0ull;
 }
 
-// A tuple of a node's walk is linked to the closest source tuple before it; if
-// that has the same (j, i, o), so do the source tuples just before it (the
-// sources' tuples of one key are contiguous and come first): each is a meet.
-__global__ void k_tw_link(const uint64_t *__restrict__ keys, const uint32_t *__restrict__ vals,
-                          const uint32_t *__restrict__ last, int64_t count,
-                          uint32_t *__restrict__ mask) {
-    for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < count;
-         p += (int64_t)gridDim.x * blockDim.x) {
-        const uint64_t kp = keys[p];
-        if (!(kp & 1ull)) continue;
-        uint32_t bits = 0;
-        for (int64_t q = (int64_t)last[p] - 1; q >= 0 && (keys[q] >> 1) == (kp >> 1); --q)
-            bits |= 1u << vals[q];
-        if (bits) atomicOr(&mask[vals[p]], bits);
-    }
-}
-
-// Per node of the chunk (one block each): counts or weighted sums per source.
-__global__ __launch_bounds__(256) void k_tw_reduce(TupleArgs a, const uint32_t *__restrict__ mask,
-                                                   const uint8_t *__restrict__ cls_src,
-                                                   unsigned long long *__restrict__ out,
-                                                   int32_t n,
-                                                   unsigned long long *__restrict__ counters) {
-    __shared__ unsigned long long acc[MAX_TUPLE_SOURCES];
-    const int32_t vl = blockIdx.x;
-    const uint32_t v = (uint32_t)a.active[a.a0 + vl];
-    if (threadIdx.x < MAX_TUPLE_SOURCES) acc[threadIdx.x] = 0ull;
-    __syncthreads();
-    uint32_t meets = 0;
-    uint4 fk = make_uint4(0, 0, 0, 0);
-    if (a.strat) fk = philox4x32_10(v, 0u, 0u, DOM_SHUFFLE, a.key);
-    for (int32_t j = threadIdx.x; j < a.N; j += blockDim.x) {
-        uint32_t m = mask[(size_t)vl * a.N + j];
-        if (!m) continue;
-        uint32_t cv = 0;
-        if (a.strat) cv = slot_class(shuffle_slot((uint32_t)j, (uint32_t)a.N, a.sa, a.sb, fk),
-                                     a.tab->ccum, a.L);
-        while (m) {
-            const int q = __ffs(m) - 1;
-            m &= m - 1;
-            if ((uint32_t)a.src[q] == v) continue;
-            const unsigned long long w =
-                a.strat ? strat_weight(a.tab->a, cls_src[(size_t)q * a.N + j], cv) : 1ull;
-            atomicAdd(&acc[q], w);
-            ++meets;
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x < a.k) out[(size_t)threadIdx.x * n + v] = acc[threadIdx.x];
-    unsigned long long s = meets;
-    for (int d = 32; d > 0; d >>= 1) s += __shfl_xor(s, d, 64);
-    if ((threadIdx.x & 63) == 0 && s) atomicAdd(&counters[C_MEETS], s);
-}
-
-// A source's own entry: R (plain: every pair meets at step 0) or 0 (stratified).
-__global__ void k_tw_sources(TupleArgs a, unsigned long long *out, int32_t n) {
+// A source's own entry: R (plain: every pair meets at step 0) or 0 (stratified);
+// and the folded work counters.
+__global__ void k_tuples_end(TupleArgs a, bool strat) {
     const int q = threadIdx.x;
-    if (q < a.k) out[(size_t)q * n + a.src[q]] = a.strat ? 0ull : (unsigned long long)a.N;
+    if (q < a.k) a.out[(size_t)q * a.n + a.src[q]] = strat ? 0ull : (unsigned long long)a.N;
+    if (q < 8) {
+        unsigned long long sum = 0;
+        for (int i = 1; i <= CTR_SETS; ++i) sum += a.counters[8 * i + q];
+        a.counters[q] = sum;
+    }
 }
 
 int bits_for(uint64_t max_value) {
@@ -352,6 +415,19 @@ struct DevBuf {
     void *p = nullptr;
     ~DevBuf() { device_free(p); }
 };
+
+// Blocks of the tuple kernel that are resident at once.
+template <bool STRAT>
+int tuple_grid() {
+    static const int blocks = [] {
+        int dev = 0, cus = 0, per = 0;
+        (void)hipGetDevice(&dev);
+        (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+        (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_tuples<STRAT>, TU_BLOCK, 0);
+        return (cus > 0 ? cus : 256) * (per > 0 ? per : 1);
+    }();
+    return blocks;
+}
 
 }  // namespace
 }  // namespace srk
@@ -391,7 +467,7 @@ extern "C" int simrank_tuple_meets(const simrank_graph *g, const simrank_query *
     const int32_t N = p0.R, L = p0.L;
     SRK_HIP(hipSetDevice(g->device));
     hipStream_t st = g->stream;
-    // e0 / e1 around the call, s0 / s1 around each chunk's radix sort
+    // e0 / e1 around the call, s0 / s1 around the tuple kernel
     struct EvGuard {
         hipEvent_t e[4] = {nullptr, nullptr, nullptr, nullptr};
         ~EvGuard() {
@@ -401,173 +477,67 @@ extern "C" int simrank_tuple_meets(const simrank_graph *g, const simrank_query *
     } evg;
     for (hipEvent_t &x : evg.e) SRK_HIP(hipEventCreate(&x));
     hipEvent_t e0 = evg.e[0], e1 = evg.e[1], s0 = evg.e[2], s1 = evg.e[3];
-    double sort_ms = 0.0;
-    uint64_t sort_bytes = 0;
     SRK_HIP(hipEventRecord(e0, st));
 
     const size_t n = (size_t)g->n;
-    DevBuf d_src, d_tab, d_out, d_rowsum, d_cnt;
+    DevBuf d_src, d_tab, d_out, d_cnt;
     if ((rc = device_alloc(&d_src.p, 4 * (size_t)k, nullptr))) return rc;
     if ((rc = device_alloc(&d_tab.p, sizeof(StratTab), nullptr))) return rc;
     if ((rc = device_alloc(&d_out.p, 8 * n * (size_t)k, nullptr))) return rc;
-    if ((rc = device_alloc(&d_cnt.p, 8 * 8, nullptr))) return rc;
+    if ((rc = device_alloc(&d_cnt.p, 8 * CTR_WORDS, nullptr))) return rc;
     SRK_HIP(hipMemcpyAsync(d_src.p, srcs.data(), 4 * (size_t)k, hipMemcpyHostToDevice, st));
     SRK_HIP(hipMemcpyAsync(d_tab.p, &tab, sizeof(StratTab), hipMemcpyHostToDevice, st));
     auto *out = (unsigned long long *)d_out.p;
     auto *counters = (unsigned long long *)d_cnt.p;
-    k_fill_u64<<<grid_for((int64_t)(n * k), 256), 256, 0, st>>>(out, (int64_t)(n * k));
-    k_fill_u64<<<1, 64, 0, st>>>(counters, 8);
+    k_fill_u64<<<std::min(grid_for((int64_t)(n * k), 256), 4096u), 256, 0, st>>>(out, (int64_t)(n * k));
+    k_fill_u64<<<1, 256, 0, st>>>(counters, CTR_WORDS);
 
     TupleArgs a{};
     a.nodes = g->nodes;
     a.E = g->E;
     a.active = g->active;
+    a.na = g->n_active;
     a.N = N;
     a.L = L;
     a.key = make_key(qs[0].seed);
     a.T = p0.T;
-    a.strat = strat ? 1 : 0;
     a.tab = (const StratTab *)d_tab.p;
     a.sa = (uint32_t)sp.sa;
     a.sb = (uint32_t)sp.sb;
     a.src = (const int32_t *)d_src.p;
     a.k = k;
-    a.ib = (uint32_t)bits_for((uint64_t)L);
-    a.nb = (uint32_t)bits_for((uint64_t)std::max<int64_t>(g->m_slots - 1, 1));
-    const int jb = bits_for((uint64_t)std::max(N - 1, 1));
-    const int key_bits = jb + (int)a.ib + (int)a.nb + 1;
-    if (key_bits > 64) return fail(SIMRANK_EINVAL, "tuple keys exceed 64 bits");
+    a.n = g->n;
+    a.out = out;
+    a.counters = counters;
+    a.nb = bits_for((uint64_t)std::max<int64_t>(g->m_slots - 1, 1));   // at most 31
+    a.step_bits = std::min(TU_STEP_BITS, 32 - a.nb);
+    a.units = (int64_t)((a.na + TU_ROWS - 1) / TU_ROWS) * N;
 
-    // tuples per node (all active nodes), to cut the chunks
-    const int32_t na = g->n_active;
-    std::vector<unsigned long long> row_sum(std::max(na, 1), 0ull);
-    if (na > 0) {
-        if ((rc = device_alloc(&d_rowsum.p, 8 * (size_t)na, nullptr))) return rc;
-        k_fill_u64<<<grid_for(na, 256), 256, 0, st>>>((unsigned long long *)d_rowsum.p, na);
-        TupleArgs all = a;
-        all.a0 = 0;
-        all.V = na;
-        k_tw_len<<<dim3(grid_for(N, 256), std::min(na, MAX_GRID_Y)), 256, 0, st>>>(
-            all, na, nullptr, (unsigned long long *)d_rowsum.p, nullptr);
-        SRK_HIP(hipGetLastError());
-        SRK_HIP(hipMemcpyAsync(row_sum.data(), d_rowsum.p, 8 * (size_t)na, hipMemcpyDeviceToHost, st));
-        SRK_HIP(hipStreamSynchronize(st));
-    }
-    // chunk limits: tuples per chunk (keys and payloads twice, running maxima)
-    // and walks per chunk (lengths, offsets, masks)
+    // The tuples of one start node and of all sources are counted in 32 bits.
     const int64_t src_tuples_max = (int64_t)k * N * L;
-    const int64_t cap_tuples = (int64_t)1 << 28, cap_walks = (int64_t)1 << 27;
-    std::vector<std::pair<int32_t, int32_t>> chunks;   // (first active index, nodes)
-    {
-        int32_t c0 = 0;
-        int64_t tup = 0;
-        for (int32_t i = 0; i < na; ++i) {
-            const int64_t t = (int64_t)row_sum[i];
-            const bool full = i > c0 && (tup + t + src_tuples_max > cap_tuples ||
-                                         (int64_t)(i - c0 + 1) * N > cap_walks ||
-                                         i - c0 + 1 + k > MAX_GRID_Y);
-            if (full) {
-                chunks.push_back({c0, i - c0});
-                c0 = i;
-                tup = 0;
-            }
-            tup += t;
-        }
-        if (na > 0) chunks.push_back({c0, na - c0});
+    if (a.na > 0 && src_tuples_max + (int64_t)N * L >= (int64_t)0xffffffffu) {
+        DevBuf rs;
+        if ((rc = device_alloc(&rs.p, 8 * (size_t)a.na, nullptr))) return rc;
+        k_fill_u64<<<std::min(grid_for(a.na, 256), 4096u), 256, 0, st>>>((unsigned long long *)rs.p, a.na);
+        k_row_tuples<<<dim3(grid_for(N, 256), std::min(a.na, 65535)), 256, 0, st>>>(
+            a, strat, (unsigned long long *)rs.p);
+        SRK_HIP(hipGetLastError());
+        std::vector<unsigned long long> row_sum(a.na);
+        SRK_HIP(hipMemcpyAsync(row_sum.data(), rs.p, 8 * (size_t)a.na, hipMemcpyDeviceToHost, st));
+        SRK_HIP(hipStreamSynchronize(st));
+        const int64_t most = (int64_t)*std::max_element(row_sum.begin(), row_sum.end());
+        if (src_tuples_max + most >= (int64_t)0xffffffffu)
+            return fail(SIMRANK_EINVAL, "one node's walks exceed the tuple buffer");
     }
-    int64_t max_tuples = 0, max_walks = 0;
-    for (auto &c : chunks) {
-        int64_t t = src_tuples_max;
-        for (int32_t i = c.first; i < c.first + c.second; ++i) t += (int64_t)row_sum[i];
-        max_tuples = std::max(max_tuples, t);
-        max_walks = std::max(max_walks, (int64_t)(c.second + k) * N);
+    SRK_HIP(hipEventRecord(s0, st));
+    if (a.units > 0) {
+        if (strat)
+            k_tuples<true><<<(unsigned)std::min<int64_t>(a.units, tuple_grid<true>()), TU_BLOCK, 0, st>>>(a);
+        else
+            k_tuples<false><<<(unsigned)std::min<int64_t>(a.units, tuple_grid<false>()), TU_BLOCK, 0, st>>>(a);
     }
-    if (max_tuples >= (int64_t)0xffffffffu)
-        return fail(SIMRANK_EINVAL, "one node's walks exceed the tuple buffer");
-    uint64_t total_moves = 0;
-    if (!chunks.empty()) {
-        const int64_t tiles_max = (max_tuples + RS_TILE - 1) / RS_TILE;
-        DevBuf k0, k1, v0, v1, last, lens, offs, mask, hist, hoffs, tot, cls;
-        if ((rc = device_alloc(&k0.p, 8 * (size_t)max_tuples, nullptr)) ||
-            (rc = device_alloc(&k1.p, 8 * (size_t)max_tuples, nullptr)) ||
-            (rc = device_alloc(&v0.p, 4 * (size_t)max_tuples, nullptr)) ||
-            (rc = device_alloc(&v1.p, 4 * (size_t)max_tuples, nullptr)) ||
-            (rc = device_alloc(&last.p, 4 * (size_t)max_tuples, nullptr)) ||
-            (rc = device_alloc(&lens.p, 4 * (size_t)max_walks, nullptr)) ||
-            (rc = device_alloc(&offs.p, 8 * (size_t)max_walks, nullptr)) ||
-            (rc = device_alloc(&mask.p, 4 * (size_t)max_walks, nullptr)) ||
-            (rc = device_alloc(&hist.p, 4 * 256 * (size_t)std::max<int64_t>(tiles_max, 1), nullptr)) ||
-            (rc = device_alloc(&hoffs.p, 8 * 256 * (size_t)std::max<int64_t>(tiles_max, 1), nullptr)) ||
-            (rc = device_alloc(&tot.p, 8, nullptr)) ||
-            (rc = device_alloc(&cls.p, (size_t)k * N, nullptr)))
-            return rc;
-        for (auto &c : chunks) {
-            TupleArgs ca = a;
-            ca.a0 = c.first;
-            ca.V = c.second;
-            const int32_t rows = c.second + k;
-            const dim3 grid(grid_for(N, 256), std::min(rows, MAX_GRID_Y));
-            k_tw_len<<<grid, 256, 0, st>>>(ca, rows, (uint32_t *)lens.p, nullptr, (uint8_t *)cls.p);
-            if ((rc = scan_exclusive_u32_to_i64((const uint32_t *)lens.p, (int64_t)rows * N,
-                                                (int64_t *)offs.p, (int64_t *)tot.p, st)))
-                return rc;
-            int64_t count = 0;
-            SRK_HIP(hipMemcpyAsync(&count, tot.p, 8, hipMemcpyDeviceToHost, st));
-            SRK_HIP(hipStreamSynchronize(st));
-            if (count > max_tuples) return fail(SIMRANK_EDEVICE, "tuple count beyond its bound");
-            if (count == 0) continue;
-            k_tw_emit<<<grid, 256, 0, st>>>(ca, rows, (const int64_t *)offs.p, (uint64_t *)k0.p,
-                                           (uint32_t *)v0.p);
-            SRK_HIP(hipGetLastError());
-            // stable LSD radix sort on the key bits in use
-            uint64_t *kin = (uint64_t *)k0.p, *kout = (uint64_t *)k1.p;
-            uint32_t *vin = (uint32_t *)v0.p, *vout = (uint32_t *)v1.p;
-            const int64_t tiles = (count + RS_TILE - 1) / RS_TILE;
-            SRK_HIP(hipEventRecord(s0, st));
-            int passes = 0;
-            for (int shift = 0; shift < key_bits; shift += 8, ++passes) {
-                k_rs_hist<<<(unsigned)tiles, RS_BLOCK, 0, st>>>(kin, count, shift, (uint32_t *)hist.p,
-                                                               tiles);
-                if ((rc = scan_exclusive_u32_to_i64((const uint32_t *)hist.p, 256 * tiles,
-                                                    (int64_t *)hoffs.p, (int64_t *)tot.p, st)))
-                    return rc;
-                k_rs_scatter<<<(unsigned)tiles, RS_BLOCK, 0, st>>>(kin, vin, kout, vout, count, shift,
-                                                                  (const int64_t *)hoffs.p, tiles);
-                std::swap(kin, kout);
-                std::swap(vin, vout);
-            }
-            SRK_HIP(hipEventRecord(s1, st));
-            SRK_HIP(hipGetLastError());
-            // a histogram pass reads each 8-byte key; a scatter pass reads and
-            // writes each key and its 4-byte payload
-            sort_bytes += (uint64_t)passes * (uint64_t)count * (8u + 24u);
-            // PREDECESSOR: running maximum of (position + 1) over the sources' tuples
-            k_tw_last_init<<<grid_for(count, 256), 256, 0, st>>>(kin, count, (uint32_t *)last.p);
-            if ((rc = scan_inclusive_max_u32((uint32_t *)last.p, count, st))) return rc;
-            k_fill_u32<<<grid_for((int64_t)c.second * N, 256), 256, 0, st>>>(
-                (uint32_t *)mask.p, (int64_t)c.second * N, 0u);
-            k_tw_link<<<std::min<unsigned>(grid_for(count, 256), 65536u), 256, 0, st>>>(
-                kin, vin, (const uint32_t *)last.p, count, (uint32_t *)mask.p);
-            k_tw_reduce<<<(unsigned)c.second, 256, 0, st>>>(ca, (const uint32_t *)mask.p,
-                                                           (const uint8_t *)cls.p, out, g->n,
-                                                           counters);
-            SRK_HIP(hipGetLastError());
-            int64_t src_count = 0;
-            {
-                // the sources' tuples: the scanned offset of row V is where they start
-                int64_t first_src = 0;
-                SRK_HIP(hipMemcpyAsync(&first_src, (int64_t *)offs.p + (size_t)c.second * N, 8,
-                                       hipMemcpyDeviceToHost, st));
-                SRK_HIP(hipStreamSynchronize(st));
-                src_count = count - first_src;
-                float sms = 0.f;
-                SRK_HIP(hipEventElapsedTime(&sms, s0, s1));
-                sort_ms += sms;
-            }
-            total_moves += (uint64_t)(count - src_count);
-        }
-    }
-    k_tw_sources<<<1, 64, 0, st>>>(a, out, g->n);
+    SRK_HIP(hipEventRecord(s1, st));
+    k_tuples_end<<<1, 64, 0, st>>>(a, strat);
     SRK_HIP(hipGetLastError());
     SRK_HIP(hipEventRecord(e1, st));
     SRK_HIP(hipMemcpyAsync(sums, out, 8 * n * (size_t)k, hipMemcpyDeviceToHost, st));
@@ -575,13 +545,16 @@ extern "C" int simrank_tuple_meets(const simrank_graph *g, const simrank_query *
     SRK_HIP(hipMemcpyAsync(c, counters, sizeof(c), hipMemcpyDeviceToHost, st));
     SRK_HIP(hipStreamSynchronize(st));
     if (st_opt) {
-        float ms = 0.f;
+        float ms = 0.f, sms = 0.f;
         SRK_HIP(hipEventElapsedTime(&ms, e0, e1));
+        SRK_HIP(hipEventElapsedTime(&sms, s0, s1));
         *st_opt = simrank_stats{};
         st_opt->pairs = (uint64_t)(g->n - 1) * (uint64_t)N * (uint64_t)k;
-        st_opt->moves = total_moves;
-        st_opt->draws = sort_bytes;        // bytes the sort passes move (see simrank.h)
-        st_opt->meet_ms = sort_ms;
+        st_opt->moves = c[C_MOVES];
+        // bytes the sort passes move (see simrank.h): 4 per key a pass counts,
+        // 12 per tuple it reads and writes
+        st_opt->draws = c[C_SPARE] * 16u;
+        st_opt->meet_ms = sms;
         st_opt->meets = c[C_MEETS];
         st_opt->ms = ms;
         st_opt->R = N;
