@@ -17,12 +17,9 @@
 #include "common.hpp"
 #include "philox.hpp"
 
-// Segments in flight per lane and consecutive slots per wave of k_segments.
+// Segments in flight per lane of k_segments.
 #ifndef SRK_SEG_SLOTS
 #define SRK_SEG_SLOTS 2
-#endif
-#ifndef SRK_SEG_CHUNK
-#define SRK_SEG_CHUNK 2048
 #endif
 // 1: rows of up to 16 positions are assembled in registers and written once.
 #ifndef SRK_SEG_BUFFER
@@ -58,6 +55,19 @@ __global__ void k_owner_scatter(const int64_t *__restrict__ pool_off, const int6
     if (P[y] > 0) owner[pool_off[y]] = (uint32_t)y;
 }
 
+// The waves' counts of moves go to this many words, a cache line apart.
+constexpr int SEG_SETS = 256;
+
+// Consecutive slots that a wave builds: as many as its lanes hold at once, or
+// half as many again for segments of 16 steps and more, whose longest walks the
+// wave waits for.  k_segments with 2,048 (and one counter of moves for all
+// waves, whose atomics cost about 16 ns each) / 512 / 256 / 192 / 128 slots:
+// 2^3 steps, n = 5,000: 243 / 64 / 37 / 30 / 20 us; n = 300,007: 457 / 328 /
+// 313 / 299 / 280; n = 2^22: 5.83 / 4.91 / 4.49 / 4.31 / 4.56 ms; 2^4 steps,
+// n = 5,000: 235 / 75 / 49 / 42 / 35 us; n = 300,007: 431 / 395 / 371 / 363 /
+// 376; n = 2^22: 6.84 / 6.21 / 6.05 / 6.17 / 6.71 ms.
+int64_t seg_chunk(int32_t seg_len) { return (seg_len >= 16 ? 96 : 64) * SRK_SEG_SLOTS; }
+
 struct SegArgs {
     const uint2 *nodes;
     const uint2 *E;
@@ -68,7 +78,7 @@ struct SegArgs {
     uint8_t *seg_lens;
     uint32_t *succ;
     uint32_t *chain;
-    unsigned long long *moves;
+    unsigned long long *moves;   // [8 SEG_SETS], one in eight used
     PhiloxKey key;
     uint32_t T;
     int32_t seg_len, width;
@@ -261,7 +271,7 @@ __global__ __launch_bounds__(256) void k_segments(SegArgs a) {
     }
     unsigned long long m = moves;
     for (int d = 32; d > 0; d >>= 1) m += __shfl_xor(m, d, 64);
-    if (lane == 0 && m) atomicAdd(a.moves, m);
+    if (lane == 0 && m) atomicAdd(&a.moves[8 * (wave % SEG_SETS)], m);
 }
 
 // Round r of pointer doubling: chain[s][h + i] = chain[J[s]][i] for i < h = 2^r,
@@ -407,11 +417,11 @@ extern "C" int simrank_build_index(simrank_graph *g, const simrank_index_params 
     IX_TRY(device_alloc((void **)&P, 8 * (size_t)n, nullptr));
     IX_TRY(device_alloc((void **)&tot, 8 * 2, nullptr));
     IX_TRY(device_alloc((void **)&flag, 4, nullptr));
-    IX_TRY(device_alloc((void **)&moves, 8, nullptr));
+    IX_TRY(device_alloc((void **)&moves, 64 * SEG_SETS, nullptr));
     IX_TRY(device_alloc((void **)&ix->pool_off, 8 * ((size_t)n + 1), &ix->bytes));
     IX_HIP(hipEventRecord(e0, st));
     k_fill_u32i<<<1, 64, 0, st>>>(flag, 1, 0u);
-    k_fill_u32i<<<1, 64, 0, st>>>((uint32_t *)moves, 2, 0u);
+    k_fill_u32i<<<4, 256, 0, st>>>((uint32_t *)moves, 16 * SEG_SETS, 0u);
     k_pool_sizes<<<grid_for(n, 256), 256, 0, st>>>(g->dbar, n, p->kappa, P, flag);
     IX_TRY(scan_exclusive_i64(P, n, ix->pool_off, tot, st));
     IX_HIP(hipMemcpyAsync(ix->pool_off + n, tot, 8, hipMemcpyDeviceToDevice, st));
@@ -439,8 +449,8 @@ extern "C" int simrank_build_index(simrank_graph *g, const simrank_index_params 
         IX_TRY(scan_inclusive_max_u32(owner, total, st));
         SegArgs sa{g->nodes, g->E, g->node_of, ix->pool_off, owner, ix->seg, ix->seg_lens,
                    ix->succ, ix->chain, moves, make_key(p->seed), ix->T, ix->seg_len, ix->width,
-                   total, SRK_SEG_CHUNK};
-        const int64_t waves = (total + SRK_SEG_CHUNK - 1) / SRK_SEG_CHUNK;
+                   total, seg_chunk(ix->seg_len)};
+        const int64_t waves = (total + sa.chunk - 1) / sa.chunk;
         IX_HIP(hipEventRecord(es0, st));
         // rows of up to 16 positions are assembled in registers and written
         // once; longer ones are written position by position
@@ -464,9 +474,10 @@ extern "C" int simrank_build_index(simrank_graph *g, const simrank_index_params 
         IX_HIP(hipGetLastError());
     }
     IX_HIP(hipEventRecord(e1, st));
-    unsigned long long mv = 0;
-    IX_HIP(hipMemcpyAsync(&mv, moves, 8, hipMemcpyDeviceToHost, st));
+    unsigned long long mvs[8 * SEG_SETS], mv = 0;
+    IX_HIP(hipMemcpyAsync(mvs, moves, sizeof(mvs), hipMemcpyDeviceToHost, st));
     IX_HIP(hipStreamSynchronize(st));
+    for (int i = 0; i < SEG_SETS; ++i) mv += mvs[8 * i];
     float ms = 0.f, sms = 0.f, dms = 0.f;
     IX_HIP(hipEventElapsedTime(&ms, e0, e1));
     if (total > 0) {
