@@ -306,7 +306,7 @@ extern "C" int simrank_batch_plan_create_ex(simrank_graph *const *graphs, int32_
     if (e != hipSuccess) return bail(fail(SIMRANK_EDEVICE, hipGetErrorString(e)));
     e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
-        rc = launch_query_set(set, cs, nullptr, nullptr);
+        rc = launch_query_set(set, cs);
         hipGraph_t gr = nullptr;
         hipError_t e2 = hipStreamEndCapture(cs, &gr);
         p->graph = gr;
@@ -497,14 +497,13 @@ extern "C" int simrank_batch(simrank_graph *const *graphs, int32_t ngraphs,
 // the caches) with the graph's current tuning.
 static int time_meet(simrank_graph *g, const simrank_query *q, const simrank_params &p, int mode,
                      Workspace *ws, uint32_t *cnt, float *ms_out) {
-    float ms = 0.f;
+    double ms = 0.0;
     for (int rep = 0; rep < 2; ++rep) {
         int rc = enqueue_query(g, q, p, mode, ws, nullptr, cnt, g->stream);
+        if (!rc) rc = query_times(ws, nullptr, &ms, nullptr);
         if (rc) return rc;
-        SRK_HIP(hipEventSynchronize(ws->ev1));
-        SRK_HIP(hipEventElapsedTime(&ms, ws->evm0, ws->evm1));
     }
-    *ms_out = ms;
+    *ms_out = (float)ms;
     return SIMRANK_OK;
 }
 

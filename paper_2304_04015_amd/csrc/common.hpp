@@ -362,11 +362,8 @@ struct Workspace {
     uint32_t *units = nullptr;     // device [units_words(1)]
     uint8_t *scls = nullptr;       // [max_R] stratified: class of walk (s, j)
     StratTab *tab = nullptr;       // device table of the last stratified query
-    StratTab *tab_host = nullptr;  // its pinned host staging copy
-    hipEvent_t ev_tab = nullptr;   // after the copy of tab_host
     int32_t max_tiles = 0;
-    hipEvent_t ev0 = nullptr, ev1 = nullptr;     // around the whole query
-    hipEvent_t evm0 = nullptr, evm1 = nullptr;   // around the meet kernel
+    hipEvent_t ev1 = nullptr;      // behind the query
     hipStream_t last_stream = nullptr;
     simrank_params last_params{};
     int32_t last_n = 0;
@@ -386,7 +383,15 @@ enum Counter : int {
 // 5 counters) took 330 us.  Measured per query (R = 1,521): 382 us before and 162 after at
 // n = 5,003, 980 and 686 at n = 40,000.
 constexpr int CTR_SETS = 64;
-constexpr int CTR_WORDS = 8 * (1 + CTR_SETS);
+constexpr int CTR_SUMS = 8 * (1 + CTR_SETS);
+// Behind them, device times of a query (ticks of the constant 100 MHz clock):
+// start of its first kernel, end of the kernel before the meet kernel, start of
+// the one behind it, end of the last.  HIP events there were packets of their
+// own between the kernels and held each of them up by 3 to 6 us.  A query at
+// n = 5,003 took 95 us with them and 84 without.
+enum Stamp : int { STAMP_BEGIN = CTR_SUMS, STAMP_MEET = CTR_SUMS + 1, STAMP_MET = CTR_SUMS + 2,
+                   STAMP_END = CTR_SUMS + 3 };
+constexpr int CTR_WORDS = CTR_SUMS + 8;
 
 // ----------------------------------------------------------------- helpers
 int device_alloc(void **p, size_t bytes, int64_t *acct);
@@ -418,12 +423,12 @@ IndexView index_view(const Graph *g);
 void describe_query(const Graph *g, const simrank_query *q, const simrank_params &p, int mode,
                     QueryDesc *d);
 // Enqueues init, source walks, tiles and units, meet and estimate for
-// every query of the set; records ev_meet0 / ev_meet1 (may be NULL) around the
-// meet kernels.
-// one (may be NULL): the descriptor of a set of one query, not yet in device
-// memory.
-int launch_query_set(const QuerySet &qs, hipStream_t st, hipEvent_t ev_meet0, hipEvent_t ev_meet1,
-                     const QueryDesc *one = nullptr);
+// every query of the set.  one (may be NULL): the descriptor of a set of one
+// query, not yet in device memory.
+int launch_query_set(const QuerySet &qs, hipStream_t st, const QueryDesc *one = nullptr);
+// Waits for the workspace's last query; its device time and its meet kernel's,
+// in ms, and its counters (each pointer may be NULL).
+int query_times(const Workspace *ws, double *ms, double *meet_ms, unsigned long long *counters);
 int enqueue_query(const Graph *g, const simrank_query *q, const simrank_params &p, int mode,
                   Workspace *ws, double *out_dev, uint32_t *counts_dev, hipStream_t st);
 int enqueue_stratified(const Graph *g, const simrank_query *q, Workspace *ws, double *out_dev,

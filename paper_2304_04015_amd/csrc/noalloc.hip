@@ -158,5 +158,5 @@ extern "C" int simrank_single_source_noalloc(const simrank_graph *g, const simra
     qs.units = c.units;
     qs.counters = c.counters;
     hipStream_t st = (hipStream_t)stream;
-    return launch_query_set(qs, st, nullptr, nullptr, &d);
+    return launch_query_set(qs, st, &d);
 }

@@ -42,13 +42,22 @@ __global__ void k_init(const QueryDesc *__restrict__ qd, unsigned long long *__r
     clear_query(qd[blockIdx.y]);
 }
 
+// A stratified query's class table, which comes with the launch.
+__global__ void k_put_tab(StratTab *dst, StratTab t) {
+    for (int i = threadIdx.x; i < MAX_CAP + 2; i += blockDim.x) dst->ccum[i] = t.ccum[i];
+    for (int i = threadIdx.x; i < MAX_CAP + 1; i += blockDim.x) dst->a[i] = t.a[i];
+}
+
 // The same for one query whose descriptor comes with the launch and is put in
 // device memory for the kernels behind it; grid (x over nodes).
 __global__ void k_init_one(QueryDesc *__restrict__ dst, QueryDesc d,
                            unsigned long long *__restrict__ counters, int32_t words) {
     if (blockIdx.x == 0) {
         for (int32_t w = threadIdx.x; w < words; w += blockDim.x) counters[w] = 0ull;
-        if (threadIdx.x == 0) *dst = d;
+        if (threadIdx.x == 0) {
+            *dst = d;
+            if (words == CTR_SUMS) counters[STAMP_BEGIN] = wall_clock64();
+        }
     }
     clear_query(d);
 }
@@ -71,15 +80,19 @@ __device__ __forceinline__ void estimate_one(const QueryDesc &d, int64_t v) {
 // grid (x over nodes, y = query); the last kernel of a launch sequence, it also
 // folds the sets of work counters into the totals.
 __global__ void k_estimate(const QueryDesc *__restrict__ qd, unsigned long long *__restrict__ counters) {
+    const unsigned long long begun = wall_clock64();
     const QueryDesc &d = qd[blockIdx.y];
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 8) {
         unsigned long long sum = 0;
         for (int i = 1; i <= CTR_SETS; ++i) sum += counters[8 * i + threadIdx.x];
         counters[threadIdx.x] = sum;
+        if (threadIdx.x == 0) counters[STAMP_MET] = begun;
     }
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < d.n;
          v += (int64_t)gridDim.x * blockDim.x)
         estimate_one(d, v);
+    if (blockIdx.x == gridDim.x - 1 && blockIdx.y == gridDim.y - 1 && threadIdx.x == 0)
+        counters[STAMP_END] = wall_clock64();
 }
 
 // ------------------------------------------------------------ source walks
@@ -332,7 +345,8 @@ __global__ __launch_bounds__(64) void k_tiles(const QueryDesc *__restrict__ qd) 
 // no units in a list) and one cursor per kind.  grid: blocks of each kind's
 // meet launch.
 __global__ __launch_bounds__(1024) void k_unit_offsets(const QueryDesc *__restrict__ qd, int32_t nq,
-                                                       uint32_t *units, uint3 grid) {
+                                                       uint32_t *units, uint3 grid,
+                                                       unsigned long long *counters) {
     __shared__ unsigned long long s_pairs[N_KINDS], s_per[N_KINDS];
     __shared__ uint32_t s_km[N_KINDS];
     if (threadIdx.x < N_KINDS) {
@@ -386,6 +400,7 @@ __global__ __launch_bounds__(1024) void k_unit_offsets(const QueryDesc *__restri
             units[N_KINDS * (nq + 1) + list] = 0u;
         }
     }
+    if (threadIdx.x == 0) counters[STAMP_MEET] = wall_clock64();
 }
 
 // ------------------------------------------------------------ meet kernel
@@ -1191,22 +1206,20 @@ void describe_query(const Graph *g, const simrank_query *q, const simrank_params
     d->tile_j = tj > 0 ? std::min<int32_t>(tj, tile_j_of(d->kind)) : tile_j_of(d->kind);
 }
 
-int launch_query_set(const QuerySet &qs, hipStream_t st, hipEvent_t ev_meet0, hipEvent_t ev_meet1,
-                     const QueryDesc *one) {
+int launch_query_set(const QuerySet &qs, hipStream_t st, const QueryDesc *one) {
     if (qs.nq <= 0) return SIMRANK_OK;
     const unsigned nq = (unsigned)qs.nq;
     const unsigned gx_n = std::min<unsigned>(grid_for(std::max(qs.max_n, 1), 256), 1024u);
     if (one)
-        k_init_one<<<gx_n, 256, 0, st>>>(const_cast<QueryDesc *>(qs.desc), *one, qs.counters, CTR_WORDS);
+        k_init_one<<<gx_n, 256, 0, st>>>(const_cast<QueryDesc *>(qs.desc), *one, qs.counters, CTR_SUMS);
     else
-        k_init<<<dim3(gx_n, nq), 256, 0, st>>>(qs.desc, qs.counters, CTR_WORDS);
+        k_init<<<dim3(gx_n, nq), 256, 0, st>>>(qs.desc, qs.counters, CTR_SUMS);
     k_source_walks<<<dim3(grid_for(qs.max_R, 256), nq), 256, 0, st>>>(qs.desc, qs.counters, true);
     if (qs.nq > TILES_IN_UNITS) k_tiles<<<nq, 64, 0, st>>>(qs.desc);
     const uint3 grid = make_uint3((uint32_t)meet_grid_blocks<K_PLAIN, SRK_MEET_SLOTS, false>(),
                                   (uint32_t)meet_grid_blocks<K_STITCHED, SRK_MEET_SLOTS_STITCHED, false>(),
                                   (uint32_t)meet_grid_blocks<K_STRAT, SRK_MEET_SLOTS_STRAT, false>());
-    k_unit_offsets<<<1, 1024, 0, st>>>(qs.desc, qs.nq, qs.units, grid);
-    if (ev_meet0) SRK_HIP(hipEventRecord(ev_meet0, st));
+    k_unit_offsets<<<1, 1024, 0, st>>>(qs.desc, qs.nq, qs.units, grid, qs.counters);
     if (qs.units_bound[K_PLAIN] > 0) launch_meet<K_PLAIN, SRK_MEET_SLOTS>(qs, st);
     if (qs.units_bound[K_STITCHED] > 0) launch_meet<K_STITCHED, SRK_MEET_SLOTS_STITCHED>(qs, st);
     if (qs.units_bound[K_STRAT] > 0) launch_meet<K_STRAT, SRK_MEET_SLOTS_STRAT>(qs, st);
@@ -1214,7 +1227,6 @@ int launch_query_set(const QuerySet &qs, hipStream_t st, hipEvent_t ev_meet0, hi
         const int rc = launch_groups(*qs.groups, qs.counters, st);
         if (rc) return rc;
     }
-    if (ev_meet1) SRK_HIP(hipEventRecord(ev_meet1, st));
     k_estimate<<<dim3(gx_n, nq), 256, 0, st>>>(qs.desc, qs.counters);
     SRK_HIP(hipGetLastError());
     return SIMRANK_OK;
@@ -1413,12 +1425,7 @@ int workspace_init(const Graph *g, int32_t max_R, int32_t max_L, Workspace *ws) 
     if ((rc = device_alloc((void **)&ws->units, 4 * units_words(1), nullptr))) return rc;
     if ((rc = device_alloc((void **)&ws->scls, (size_t)max_R, nullptr))) return rc;
     if ((rc = device_alloc((void **)&ws->tab, sizeof(StratTab), nullptr))) return rc;
-    SRK_HIP(hipHostMalloc((void **)&ws->tab_host, sizeof(StratTab), hipHostMallocDefault));
-    SRK_HIP(hipEventCreate(&ws->ev_tab));
-    SRK_HIP(hipEventCreate(&ws->ev0));
-    SRK_HIP(hipEventCreate(&ws->ev1));
-    SRK_HIP(hipEventCreate(&ws->evm0));
-    SRK_HIP(hipEventCreate(&ws->evm1));
+    SRK_HIP(hipEventCreateWithFlags(&ws->ev1, hipEventDisableTiming));
     return SIMRANK_OK;
 }
 
@@ -1436,12 +1443,7 @@ void workspace_release(Workspace *ws) {
     device_free(ws->units);
     device_free(ws->scls);
     device_free(ws->tab);
-    if (ws->tab_host) (void)hipHostFree(ws->tab_host);
-    if (ws->ev_tab) (void)hipEventDestroy(ws->ev_tab);
-    if (ws->ev0) (void)hipEventDestroy(ws->ev0);
     if (ws->ev1) (void)hipEventDestroy(ws->ev1);
-    if (ws->evm0) (void)hipEventDestroy(ws->evm0);
-    if (ws->evm1) (void)hipEventDestroy(ws->evm1);
     *ws = Workspace{};
 }
 
@@ -1459,8 +1461,7 @@ static int launch_single(const Graph *g, Workspace *ws, const QueryDesc &d, hipS
     qs.units_bound[d.kind] = units_bound;
     qs.units = ws->units;
     qs.counters = ws->counters;
-    SRK_HIP(hipEventRecord(ws->ev0, st));
-    int rc = launch_query_set(qs, st, ws->evm0, ws->evm1, &d);
+    int rc = launch_query_set(qs, st, &d);
     if (rc) return rc;
     SRK_HIP(hipEventRecord(ws->ev1, st));
     ws->last_stream = st;
@@ -1510,10 +1511,9 @@ int enqueue_stratified(const Graph *g, const simrank_query *q, Workspace *ws, do
     if (q->s < 0 || q->s >= g->n) return fail(SIMRANK_EINVAL, "source out of range");
     if (q->mode != SIMRANK_MODE_STRATIFIED) return fail(SIMRANK_EINVAL, "not a stratified query");
     if (!wsum_dev) return fail(SIMRANK_EINVAL, "weighted-sum buffer is NULL");
-    // the staging copy of the class table may still be read by the previous call
-    if (ws->pending) SRK_HIP(hipEventSynchronize(ws->ev_tab));
     StratParams sp;
-    int rc = strat_params(q, g->n, &sp, ws->tab_host);
+    StratTab tab{};
+    int rc = strat_params(q, g->n, &sp, &tab);
     if (rc) return rc;
     if (sp.N > ws->max_R || sp.phi > ws->max_L)
         return fail(SIMRANK_EINVAL, "query needs N or phi beyond the workspace's size");
@@ -1527,18 +1527,32 @@ int enqueue_stratified(const Graph *g, const simrank_query *q, Workspace *ws, do
     d.z = sp.z;
     d.sa = sp.sa;
     d.sb = sp.sb;
-    SRK_HIP(hipMemcpyAsync(ws->tab, ws->tab_host, sizeof(StratTab), hipMemcpyHostToDevice, st));
-    SRK_HIP(hipEventRecord(ws->ev_tab, st));
+    static_assert(sizeof(StratTab) <= 3584, "the class table travels as a kernel argument");
+    k_put_tab<<<1, 256, 0, st>>>(ws->tab, tab);
     return launch_single(g, ws, d, st);
 }
 
-static int read_stats(Workspace *ws, simrank_stats *st) {
+int query_times(const Workspace *ws, double *ms, double *meet_ms, unsigned long long *counters) {
     SRK_HIP(hipEventSynchronize(ws->ev1));
+    unsigned long long c[8], t[4];
+    SRK_HIP(hipMemcpy(t, ws->counters + STAMP_BEGIN, sizeof(t), hipMemcpyDeviceToHost));
+    if (counters) {
+        SRK_HIP(hipMemcpy(c, ws->counters, sizeof(c), hipMemcpyDeviceToHost));
+        std::copy(c, c + 8, counters);
+    }
+    int khz = 0;   // of the device's constant clock
+    SRK_HIP(hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, ws->g->device));
+    const double tick = 1.0 / (double)std::max(khz, 1);
+    if (ms) *ms = (double)(t[STAMP_END - STAMP_BEGIN] - t[0]) * tick;
+    if (meet_ms) *meet_ms = (double)(t[STAMP_MET - STAMP_BEGIN] - t[STAMP_MEET - STAMP_BEGIN]) * tick;
+    return SIMRANK_OK;
+}
+
+static int read_stats(Workspace *ws, simrank_stats *st) {
     unsigned long long c[8];
-    SRK_HIP(hipMemcpy(c, ws->counters, sizeof(c), hipMemcpyDeviceToHost));
-    float ms = 0.f, mms = 0.f;
-    SRK_HIP(hipEventElapsedTime(&ms, ws->ev0, ws->ev1));
-    SRK_HIP(hipEventElapsedTime(&mms, ws->evm0, ws->evm1));
+    double ms = 0.0, mms = 0.0;
+    const int rc = query_times(ws, &ms, &mms, c);
+    if (rc) return rc;
     if (st) {
         *st = simrank_stats{};
         st->pairs = (uint64_t)(ws->last_n - 1) * (uint64_t)ws->last_params.R;

@@ -360,7 +360,7 @@ static int launch_group(simrank_server *S, const std::vector<Request *> &rs, hip
     SRK_HIP(hipMemcpyAsync(gr.desc_dev, gr.desc_host, sizeof(QueryDesc) * G, hipMemcpyHostToDevice, st));
     SRK_HIP(hipMemcpyAsync(gr.gdesc_dev, gr.gdesc_host, sizeof(GroupDesc), hipMemcpyHostToDevice, st));
     SRK_HIP(hipEventRecord(gr.ev0, st));
-    int rc = launch_query_set(qs, st, nullptr, nullptr);
+    int rc = launch_query_set(qs, st);
     if (rc) return rc;
     SRK_HIP(hipEventRecord(gr.ev1, st));
     gr.members = rs;
