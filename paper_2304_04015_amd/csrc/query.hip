@@ -112,12 +112,10 @@ __global__ void k_estimate(const QueryDesc *__restrict__ qd, unsigned long long 
 // kernel, before and now: 44 and 31 us at R = 1,521, 95 and 40 at R = 9,502,
 // 305 and 45 at R = 38,005.
 constexpr int WALK_LDS = 32;
-__global__ __launch_bounds__(256) void k_source_walks(const QueryDesc *__restrict__ qd,
-                                                      unsigned long long *__restrict__ counters,
-                                                      bool sets) {
+__device__ __forceinline__ void source_walks(const QueryDesc &d, unsigned long long *counters,
+                                             bool sets) {
     __shared__ uint32_t s_pos[WALK_LDS][256];
     __shared__ uint32_t s_at[2];
-    const QueryDesc &d = qd[blockIdx.y];
     const int32_t j = blockIdx.x * blockDim.x + threadIdx.x;
     if ((int32_t)(blockIdx.x * blockDim.x) >= d.R) return;
     const bool grouped = d.kind >= K_GROUPED;
@@ -199,6 +197,18 @@ __global__ __launch_bounds__(256) void k_source_walks(const QueryDesc *__restric
     uint32_t *dst = d.swc + off;
     for (int32_t t = 0; t < min(len, WALK_LDS); ++t) dst[t] = s_pos[t][threadIdx.x];
     for (int32_t t = WALK_LDS; t < len; ++t) dst[t] = row[t];
+}
+
+__global__ __launch_bounds__(256) void k_source_walks(const QueryDesc *__restrict__ qd,
+                                                      unsigned long long *__restrict__ counters,
+                                                      bool sets) {
+    source_walks(qd[blockIdx.y], counters, sets);
+}
+
+// The same for one query, its descriptor a kernel argument.
+__global__ __launch_bounds__(256) void k_source_walks_one(QueryDesc d,
+                                                          unsigned long long *__restrict__ counters) {
+    source_walks(d, counters, true);
 }
 
 // ------------------------------------------------------------ tiles
@@ -397,10 +407,55 @@ __global__ __launch_bounds__(1024) void k_unit_offsets(const QueryDesc *__restri
         }
         if (threadIdx.x == 0) {
             u[nq] = total;
-            units[N_KINDS * (nq + 1) + list] = 0u;
+            // (a meet launch's blocks take one unit each, then those from here)
+            units[N_KINDS * (nq + 1) + list] = list == 0 ? grid.x : list == 1 ? grid.y : grid.z;
         }
     }
     if (threadIdx.x == 0) counters[STAMP_MEET] = wall_clock64();
+}
+
+// The same for a set of one query, its descriptor a kernel argument, by one
+// wave.  Most queries of up to some 7,000 walks have one tile: their units
+// follow from the two words that the source walks left.  (8 us before and 4
+// now at R = 1,521: a chain of dependent reads.)
+__global__ __launch_bounds__(64) void k_units_one(QueryDesc d, uint32_t *__restrict__ units,
+                                                  uint3 grid, unsigned long long *counters) {
+    const int lane = (int)threadIdx.x;
+    const uint32_t blocks = d.kind == 0 ? grid.x : d.kind == 1 ? grid.y : grid.z;
+    const uint32_t R1 = uni(d.meta[0]), total = uni(d.meta[1]), n = (uint32_t)d.n_active;
+    uint32_t n_units = 0;
+    if (R1 <= (uint32_t)d.tile_j && total <= (uint32_t)tile_nodes_of(d.kind)) {
+        const uint32_t nt = R1 > 0u ? 1u : 0u;
+        if (nt && n) {
+            const uint32_t most = d.vb > 0 ? (uint32_t)d.vb : (uint32_t)MEET_VB;
+            n_units = (n + most - 1) / most;
+            if (d.vb <= 0) {
+                // (rounds enough for full units: no tile is smaller than the others)
+                const uint64_t pairs = (uint64_t)n * R1;
+                const uint64_t per = pairs_each(pairs, unit_rounds(pairs, R1, blocks) * blocks);
+                n_units = max(n_units, (uint32_t)min(pairs / per, (uint64_t)n));
+            }
+        }
+        if (lane == 0) {
+            d.joff[R1] = total;
+            d.tiles[0] = 0u;
+            d.tiles[nt] = R1;
+            d.meta[2] = nt;
+            d.meta[3] = R1;
+            tunits_of(d)[0] = 0u;
+            tunits_of(d)[nt] = n_units;
+        }
+    } else {
+        make_tiles(d, lane);
+        const uint64_t pairs = (uint64_t)R1 * n;
+        n_units = lay_units(d, unit_pairs(&d, 1, d.kind, pairs, d.meta[3], blocks, lane), lane);
+    }
+    if (lane < N_KINDS) {
+        units[lane * 2] = 0u;
+        units[lane * 2 + 1] = lane == d.kind ? n_units : 0u;
+        units[N_KINDS * 2 + lane] = lane == 0 ? grid.x : lane == 1 ? grid.y : grid.z;
+    }
+    if (lane == 0) counters[STAMP_MEET] = wall_clock64();
 }
 
 // ------------------------------------------------------------ meet kernel
@@ -561,6 +616,7 @@ __global__ __launch_bounds__(meet_block_of(KIND)) void k_meet(const QueryDesc *_
     // serving: the request whose finished units this block has not reported yet
     uint32_t acc_slot = 0, acc_tag = 0, acc_units = 0;
     uint32_t run_next = 0, run_left = 0;   // serving: claimed units not yet taken
+    uint32_t next_unit = blockIdx.x;       // thread 0: taken while the unit before ran
     uint32_t cur_q = 0xffffffffu, cur_tile = 0xffffffffu;
     uint32_t K = 0;
     uint32_t st_moves = 0, st_draws = 0, st_meets = 0, st_tail = 0, st_pairs = 0;
@@ -590,10 +646,11 @@ __global__ __launch_bounds__(meet_block_of(KIND)) void k_meet(const QueryDesc *_
             // buffers as its publication left them
             if (tag_s != cur_q) __threadfence();
         } else {
-            if (threadIdx.x == 0) s_unit = atomicAdd(cursor, 1u);
+            if (threadIdx.x == 0) s_unit = next_unit;
             __syncthreads();
             unit = s_unit;
             if (unit >= n_units) break;
+            if (threadIdx.x == 0) next_unit = atomicAdd(cursor, 1u);
         }
         int32_t lo = 0;
         if constexpr (STREAM) {
@@ -1214,12 +1271,18 @@ int launch_query_set(const QuerySet &qs, hipStream_t st, const QueryDesc *one) {
         k_init_one<<<gx_n, 256, 0, st>>>(const_cast<QueryDesc *>(qs.desc), *one, qs.counters, CTR_SUMS);
     else
         k_init<<<dim3(gx_n, nq), 256, 0, st>>>(qs.desc, qs.counters, CTR_SUMS);
-    k_source_walks<<<dim3(grid_for(qs.max_R, 256), nq), 256, 0, st>>>(qs.desc, qs.counters, true);
+    if (one)
+        k_source_walks_one<<<grid_for(qs.max_R, 256), 256, 0, st>>>(*one, qs.counters);
+    else
+        k_source_walks<<<dim3(grid_for(qs.max_R, 256), nq), 256, 0, st>>>(qs.desc, qs.counters, true);
     if (qs.nq > TILES_IN_UNITS) k_tiles<<<nq, 64, 0, st>>>(qs.desc);
     const uint3 grid = make_uint3((uint32_t)meet_grid_blocks<K_PLAIN, SRK_MEET_SLOTS, false>(),
                                   (uint32_t)meet_grid_blocks<K_STITCHED, SRK_MEET_SLOTS_STITCHED, false>(),
                                   (uint32_t)meet_grid_blocks<K_STRAT, SRK_MEET_SLOTS_STRAT, false>());
-    k_unit_offsets<<<1, 1024, 0, st>>>(qs.desc, qs.nq, qs.units, grid, qs.counters);
+    if (one)
+        k_units_one<<<1, 64, 0, st>>>(*one, qs.units, grid, qs.counters);
+    else
+        k_unit_offsets<<<1, 1024, 0, st>>>(qs.desc, qs.nq, qs.units, grid, qs.counters);
     if (qs.units_bound[K_PLAIN] > 0) launch_meet<K_PLAIN, SRK_MEET_SLOTS>(qs, st);
     if (qs.units_bound[K_STITCHED] > 0) launch_meet<K_STITCHED, SRK_MEET_SLOTS_STITCHED>(qs, st);
     if (qs.units_bound[K_STRAT] > 0) launch_meet<K_STRAT, SRK_MEET_SLOTS_STRAT>(qs, st);
