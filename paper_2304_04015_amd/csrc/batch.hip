@@ -500,7 +500,7 @@ static int time_meet(simrank_graph *g, const simrank_query *q, const simrank_par
     double ms = 0.0;
     for (int rep = 0; rep < 2; ++rep) {
         int rc = enqueue_query(g, q, p, mode, ws, nullptr, cnt, g->stream);
-        if (!rc) rc = query_times(ws, nullptr, &ms, nullptr);
+        if (!rc) rc = query_times(ws, nullptr, &ms);
         if (rc) return rc;
     }
     *ms_out = (float)ms;

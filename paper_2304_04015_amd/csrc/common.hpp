@@ -358,6 +358,7 @@ struct Workspace {
     uint32_t *tiles = nullptr;     // [max tiles + 1] first compact entry of each tile
     uint32_t *meta = nullptr;      // [8]: R1, total nodes, n_tiles, ...
     unsigned long long *counters = nullptr;  // [CTR_WORDS] stats
+    bool own_counters = false;
     QueryDesc *desc = nullptr;     // device [1]
     uint32_t *units = nullptr;     // device [units_words(1)]
     uint8_t *scls = nullptr;       // [max_R] stratified: class of walk (s, j)
@@ -427,13 +428,15 @@ void describe_query(const Graph *g, const simrank_query *q, const simrank_params
 // query, not yet in device memory.
 int launch_query_set(const QuerySet &qs, hipStream_t st, const QueryDesc *one = nullptr);
 // Waits for the workspace's last query; its device time and its meet kernel's,
-// in ms, and its counters (each pointer may be NULL).
-int query_times(const Workspace *ws, double *ms, double *meet_ms, unsigned long long *counters);
+// in ms (each pointer may be NULL).
+int query_times(const Workspace *ws, double *ms, double *meet_ms);
 int enqueue_query(const Graph *g, const simrank_query *q, const simrank_params &p, int mode,
                   Workspace *ws, double *out_dev, uint32_t *counts_dev, hipStream_t st);
 int enqueue_stratified(const Graph *g, const simrank_query *q, Workspace *ws, double *out_dev,
                        double *out_n_dev, unsigned long long *wsum_dev, hipStream_t st);
-int workspace_init(const Graph *g, int32_t max_R, int32_t max_L, Workspace *ws);
+// counters: device [CTR_WORDS] of the caller's, or NULL for the workspace's own.
+int workspace_init(const Graph *g, int32_t max_R, int32_t max_L, Workspace *ws,
+                   unsigned long long *counters = nullptr);
 void workspace_release(Workspace *ws);
 
 // Index (index.hip).

@@ -13,6 +13,8 @@
 #include <math.h>
 
 #include <algorithm>
+#include <cstring>
+#include <vector>
 
 #include "common.hpp"
 #include "device_common.hpp"
@@ -1467,7 +1469,8 @@ int strat_params(const simrank_query *q, int32_t n, StratParams *sp, StratTab *t
     return SIMRANK_OK;
 }
 
-int workspace_init(const Graph *g, int32_t max_R, int32_t max_L, Workspace *ws) {
+int workspace_init(const Graph *g, int32_t max_R, int32_t max_L, Workspace *ws,
+                   unsigned long long *counters) {
     if (max_R < 1 || max_R > MAX_R) return fail(SIMRANK_EINVAL, "max_R must lie in [1, 2^24]");
     if (max_L < 1 || max_L > MAX_CAP) return fail(SIMRANK_EINVAL, "max_L must lie in [1, 255]");
     ws->g = g;
@@ -1483,7 +1486,9 @@ int workspace_init(const Graph *g, int32_t max_R, int32_t max_L, Workspace *ws) 
     if ((rc = device_alloc((void **)&ws->swc, 4 * RL, nullptr))) return rc;
     if ((rc = device_alloc((void **)&ws->tiles, 4 * ((size_t)ws->max_tiles + 1), nullptr))) return rc;
     if ((rc = device_alloc((void **)&ws->meta, 4 * 8, nullptr))) return rc;
-    if ((rc = device_alloc((void **)&ws->counters, 8 * CTR_WORDS, nullptr))) return rc;
+    ws->counters = counters;
+    ws->own_counters = !counters;
+    if (!counters && (rc = device_alloc((void **)&ws->counters, 8 * CTR_WORDS, nullptr))) return rc;
     if ((rc = device_alloc((void **)&ws->desc, sizeof(QueryDesc), nullptr))) return rc;
     if ((rc = device_alloc((void **)&ws->units, 4 * units_words(1), nullptr))) return rc;
     if ((rc = device_alloc((void **)&ws->scls, (size_t)max_R, nullptr))) return rc;
@@ -1501,7 +1506,7 @@ void workspace_release(Workspace *ws) {
     device_free(ws->swc);
     device_free(ws->tiles);
     device_free(ws->meta);
-    device_free(ws->counters);
+    if (ws->own_counters) device_free(ws->counters);
     device_free(ws->desc);
     device_free(ws->units);
     device_free(ws->scls);
@@ -1595,45 +1600,92 @@ int enqueue_stratified(const Graph *g, const simrank_query *q, Workspace *ws, do
     return launch_single(g, ws, d, st);
 }
 
-int query_times(const Workspace *ws, double *ms, double *meet_ms, unsigned long long *counters) {
-    SRK_HIP(hipEventSynchronize(ws->ev1));
-    unsigned long long c[8], t[4];
-    SRK_HIP(hipMemcpy(t, ws->counters + STAMP_BEGIN, sizeof(t), hipMemcpyDeviceToHost));
-    if (counters) {
-        SRK_HIP(hipMemcpy(c, ws->counters, sizeof(c), hipMemcpyDeviceToHost));
-        std::copy(c, c + 8, counters);
-    }
+// Device times of a query, in ms, from its counters and stamps.
+static int times_of(const Workspace *ws, const unsigned long long *c, double *ms, double *meet_ms) {
     int khz = 0;   // of the device's constant clock
     SRK_HIP(hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, ws->g->device));
     const double tick = 1.0 / (double)std::max(khz, 1);
-    if (ms) *ms = (double)(t[STAMP_END - STAMP_BEGIN] - t[0]) * tick;
-    if (meet_ms) *meet_ms = (double)(t[STAMP_MET - STAMP_BEGIN] - t[STAMP_MEET - STAMP_BEGIN]) * tick;
+    if (ms) *ms = (double)(c[STAMP_END] - c[STAMP_BEGIN]) * tick;
+    if (meet_ms) *meet_ms = (double)(c[STAMP_MET] - c[STAMP_MEET]) * tick;
+    return SIMRANK_OK;
+}
+
+int query_times(const Workspace *ws, double *ms, double *meet_ms) {
+    SRK_HIP(hipEventSynchronize(ws->ev1));
+    unsigned long long c[CTR_WORDS];
+    SRK_HIP(hipMemcpy(c, ws->counters, sizeof(c), hipMemcpyDeviceToHost));
+    return times_of(ws, c, ms, meet_ms);
+}
+
+// The last query's statistics from its counters and stamps.
+static int fill_stats(Workspace *ws, const unsigned long long *c, simrank_stats *st) {
+    ws->pending = false;
+    if (!st) return SIMRANK_OK;
+    double ms = 0.0, mms = 0.0;
+    const int rc = times_of(ws, c, &ms, &mms);
+    if (rc) return rc;
+    *st = simrank_stats{};
+    st->pairs = (uint64_t)(ws->last_n - 1) * (uint64_t)ws->last_params.R;
+    st->pairs_walked = c[C_PAIRS];
+    st->moves = c[C_MOVES];
+    st->draws = c[C_DRAWS];
+    st->meets = c[C_MEETS];
+    st->tail_steps = c[C_TAIL];
+    st->source_moves = c[C_SRC_MOVES];
+    st->ms = ms;
+    st->meet_ms = mms;
+    st->R = ws->last_params.R;
+    st->L = ws->last_params.L;
+    st->T = ws->last_params.T;
     return SIMRANK_OK;
 }
 
 static int read_stats(Workspace *ws, simrank_stats *st) {
-    unsigned long long c[8];
-    double ms = 0.0, mms = 0.0;
-    const int rc = query_times(ws, &ms, &mms, c);
-    if (rc) return rc;
-    if (st) {
-        *st = simrank_stats{};
-        st->pairs = (uint64_t)(ws->last_n - 1) * (uint64_t)ws->last_params.R;
-        st->pairs_walked = c[C_PAIRS];
-        st->moves = c[C_MOVES];
-        st->draws = c[C_DRAWS];
-        st->meets = c[C_MEETS];
-        st->tail_steps = c[C_TAIL];
-        st->source_moves = c[C_SRC_MOVES];
-        st->ms = ms;
-        st->meet_ms = mms;
-        st->R = ws->last_params.R;
-        st->L = ws->last_params.L;
-        st->T = ws->last_params.T;
-    }
-    ws->pending = false;
-    return SIMRANK_OK;
+    SRK_HIP(hipEventSynchronize(ws->ev1));
+    unsigned long long c[CTR_WORDS];   // (one copy: each costs 10 us and more)
+    SRK_HIP(hipMemcpy(c, ws->counters, sizeof(c), hipMemcpyDeviceToHost));
+    return fill_stats(ws, c, st);
 }
+
+// A synchronous call's results: its counters and up to three arrays of n, which
+// lie behind one another in device memory.  A copy to the host costs 11 to 13
+// us however small, so small results come in one and are dealt out here: the
+// call at n = 500 took 118 us with a copy for each and takes @S12@.
+struct Results {
+    char *dev = nullptr;
+    size_t at[4] = {0, 0, 0, 0}, bytes[4] = {0, 0, 0, 0}, total = 0;
+    void *host[4] = {nullptr, nullptr, nullptr, nullptr};
+    unsigned long long ctr[CTR_WORDS];
+
+    ~Results() { device_free(dev); }
+    void add(int i, void *to, size_t b) {
+        host[i] = to;
+        bytes[i] = b;
+        at[i] = total;
+        total += (b + 255) & ~(size_t)255;
+    }
+    int alloc() { return device_alloc((void **)&dev, total, nullptr); }
+    template <typename T>
+    T *at_dev(int i) { return bytes[i] ? reinterpret_cast<T *>(dev + at[i]) : nullptr; }
+    // Copies behind the work on st and waits.
+    int fetch(hipStream_t st) {
+        constexpr size_t SMALL = 1 << 19;
+        if (total <= SMALL) {
+            std::vector<char> tmp(total);
+            SRK_HIP(hipMemcpyAsync(tmp.data(), dev, total, hipMemcpyDeviceToHost, st));
+            SRK_HIP(hipStreamSynchronize(st));
+            for (int i = 0; i < 4; ++i)
+                if (host[i]) std::memcpy(host[i], tmp.data() + at[i], bytes[i]);
+            return SIMRANK_OK;
+        }
+        // (the synchronous copy pins large arrays in place; the asynchronous
+        // one took 100 us more for 320 and 160 KB)
+        SRK_HIP(hipStreamSynchronize(st));
+        for (int i = 0; i < 4; ++i)
+            if (host[i]) SRK_HIP(hipMemcpy(host[i], dev + at[i], bytes[i], hipMemcpyDeviceToHost));
+        return SIMRANK_OK;
+    }
+};
 
 }  // namespace srk
 
@@ -1715,23 +1767,16 @@ extern "C" int simrank_single_source_ex(const simrank_graph *g, const simrank_qu
         return fail(SIMRANK_EINVAL, "stitched query's c differs from the index's c");
     SRK_HIP(hipSetDevice(g->device));
     Workspace ws;
-    double *out_dev = nullptr;
-    uint32_t *cnt_dev = nullptr;
-    rc = workspace_init(g, p.R, p.L, &ws);
-    if (!rc) rc = device_alloc((void **)&cnt_dev, 4 * (size_t)g->n, nullptr);
-    if (!rc && out_host) rc = device_alloc((void **)&out_dev, 8 * (size_t)g->n, nullptr);
-    if (!rc) rc = enqueue_query(g, q, p, mode, &ws, out_dev, cnt_dev, g->stream);
-    if (!rc) rc = read_stats(&ws, st_opt);
-    if (!rc && out_host) {
-        hipError_t e = hipMemcpy(out_host, out_dev, 8 * (size_t)g->n, hipMemcpyDeviceToHost);
-        if (e != hipSuccess) rc = fail(SIMRANK_EDEVICE, hipGetErrorString(e));
-    }
-    if (!rc && counts_host) {
-        hipError_t e = hipMemcpy(counts_host, cnt_dev, 4 * (size_t)g->n, hipMemcpyDeviceToHost);
-        if (e != hipSuccess) rc = fail(SIMRANK_EDEVICE, hipGetErrorString(e));
-    }
-    device_free(out_dev);
-    device_free(cnt_dev);
+    Results res;
+    const size_t n = (size_t)g->n;
+    res.add(0, res.ctr, sizeof(res.ctr));
+    res.add(1, out_host, out_host ? 8 * n : 0);
+    res.add(2, counts_host, 4 * n);   // needed on the device in any case
+    rc = res.alloc();
+    if (!rc) rc = workspace_init(g, p.R, p.L, &ws, res.at_dev<unsigned long long>(0));
+    if (!rc) rc = enqueue_query(g, q, p, mode, &ws, res.at_dev<double>(1), res.at_dev<uint32_t>(2), g->stream);
+    if (!rc) rc = res.fetch(g->stream);
+    if (!rc) rc = fill_stats(&ws, res.ctr, st_opt);
     workspace_release(&ws);
     return rc;
 }
@@ -1851,23 +1896,19 @@ extern "C" int simrank_single_source_stratified(const simrank_graph *g, const si
     if (q->s < 0 || q->s >= g->n) return fail(SIMRANK_EINVAL, "source out of range");
     SRK_HIP(hipSetDevice(g->device));
     Workspace ws;
-    double *out_dev = nullptr, *out_n_dev = nullptr;
-    unsigned long long *w_dev = nullptr;
+    Results res;
     const size_t n = (size_t)g->n;
-    rc = workspace_init(g, p.R, p.L, &ws);
-    if (!rc) rc = device_alloc((void **)&w_dev, 8 * n, nullptr);
-    if (!rc && out) rc = device_alloc((void **)&out_dev, 8 * n, nullptr);
-    if (!rc && out_n) rc = device_alloc((void **)&out_n_dev, 8 * n, nullptr);
-    if (!rc) rc = enqueue_stratified(g, q, &ws, out_dev, out_n_dev, w_dev, g->stream);
-    if (!rc) rc = read_stats(&ws, st_opt);
-    hipError_t e = hipSuccess;
-    if (!rc && out) e = hipMemcpy(out, out_dev, 8 * n, hipMemcpyDeviceToHost);
-    if (!rc && e == hipSuccess && out_n) e = hipMemcpy(out_n, out_n_dev, 8 * n, hipMemcpyDeviceToHost);
-    if (!rc && e == hipSuccess && wsum) e = hipMemcpy(wsum, w_dev, 8 * n, hipMemcpyDeviceToHost);
-    if (!rc && e != hipSuccess) rc = fail(SIMRANK_EDEVICE, hipGetErrorString(e));
-    device_free(out_dev);
-    device_free(out_n_dev);
-    device_free(w_dev);
+    res.add(0, res.ctr, sizeof(res.ctr));
+    res.add(1, out, out ? 8 * n : 0);
+    res.add(2, out_n, out_n ? 8 * n : 0);
+    res.add(3, wsum, 8 * n);   // needed on the device in any case
+    rc = res.alloc();
+    if (!rc) rc = workspace_init(g, p.R, p.L, &ws, res.at_dev<unsigned long long>(0));
+    if (!rc)
+        rc = enqueue_stratified(g, q, &ws, res.at_dev<double>(1), res.at_dev<double>(2),
+                                res.at_dev<unsigned long long>(3), g->stream);
+    if (!rc) rc = res.fetch(g->stream);
+    if (!rc) rc = fill_stats(&ws, res.ctr, st_opt);
     workspace_release(&ws);
     return rc;
 }
