@@ -113,17 +113,23 @@ __global__ void k_estimate(const QueryDesc *__restrict__ qd, unsigned long long 
 // us at R = 1,521 and 60 at R = 9,502.  All kernels of a query but the meet
 // kernel, before and now: 44 and 31 us at R = 1,521, 95 and 40 at R = 9,502,
 // 305 and 45 at R = 38,005.
+//
+// A served request's walks run beside a persistent meet kernel, which leaves
+// its compute unit a few KB of LDS: KEEP false keeps the positions in the
+// padded table instead, from which each thread copies its own.
 constexpr int WALK_LDS = 32;
+template <bool KEEP>
 __device__ __forceinline__ void source_walks(const QueryDesc &d, unsigned long long *counters,
                                              bool sets) {
-    __shared__ uint32_t s_pos[WALK_LDS][256];
+    constexpr int HELD = KEEP ? WALK_LDS : 0;
+    __shared__ uint32_t s_pos[KEEP ? WALK_LDS : 1][KEEP ? 256 : 1];
     __shared__ uint32_t s_at[2];
     const int32_t j = blockIdx.x * blockDim.x + threadIdx.x;
     if ((int32_t)(blockIdx.x * blockDim.x) >= d.R) return;
     const bool grouped = d.kind >= K_GROUPED;
     uint32_t *row = d.sw + (size_t)j * d.L;
     auto put = [&](int32_t t, uint32_t o) {   // position t + 1
-        if (!grouped && t < WALK_LDS) s_pos[t][threadIdx.x] = o;
+        if (!grouped && t < HELD) s_pos[t][threadIdx.x] = o;
         else row[t] = o;
     };
     int32_t len = 0;
@@ -197,20 +203,21 @@ __device__ __forceinline__ void source_walks(const QueryDesc &d, unsigned long l
     d.jj[k] = (uint32_t)j;
     d.joff[k] = off;
     uint32_t *dst = d.swc + off;
-    for (int32_t t = 0; t < min(len, WALK_LDS); ++t) dst[t] = s_pos[t][threadIdx.x];
-    for (int32_t t = WALK_LDS; t < len; ++t) dst[t] = row[t];
+    for (int32_t t = 0; t < min(len, HELD); ++t) dst[t] = s_pos[t][threadIdx.x];
+    for (int32_t t = HELD; t < len; ++t) dst[t] = row[t];
 }
 
+template <bool KEEP>
 __global__ __launch_bounds__(256) void k_source_walks(const QueryDesc *__restrict__ qd,
                                                       unsigned long long *__restrict__ counters,
                                                       bool sets) {
-    source_walks(qd[blockIdx.y], counters, sets);
+    source_walks<KEEP>(qd[blockIdx.y], counters, sets);
 }
 
 // The same for one query, its descriptor a kernel argument.
 __global__ __launch_bounds__(256) void k_source_walks_one(QueryDesc d,
                                                           unsigned long long *__restrict__ counters) {
-    source_walks(d, counters, true);
+    source_walks<true>(d, counters, true);
 }
 
 // ------------------------------------------------------------ tiles
@@ -582,12 +589,15 @@ __device__ void ring_report(const StreamRing &ring, const QueryDesc &d, uint32_t
     __syncthreads();
 }
 
+// At most 112 registers, which the attribute counts in pairs: 4 waves leave a
+// SIMD 64 of its 512, and a wave of a served request's preparation fits beside.
 template <int KIND, int NS, bool STREAM>
-__global__ __launch_bounds__(meet_block_of(KIND)) void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
-                                                     const uint32_t *__restrict__ ustart,
-                                                     uint32_t *__restrict__ cursor,
-                                                     unsigned long long *__restrict__ counters,
-                                                     StreamRing ring) {
+__global__ __launch_bounds__(meet_block_of(KIND)) __attribute__((amdgpu_num_vgpr(56)))
+void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
+            const uint32_t *__restrict__ ustart,
+            uint32_t *__restrict__ cursor,
+            unsigned long long *__restrict__ counters,
+            StreamRing ring) {
     constexpr bool STITCHED = KIND == K_STITCHED;
     constexpr bool STRAT = KIND == K_STRAT;
     constexpr int TJ = tile_j_of(KIND), TN = tile_nodes_of(KIND);
@@ -1276,7 +1286,7 @@ int launch_query_set(const QuerySet &qs, hipStream_t st, const QueryDesc *one) {
     if (one)
         k_source_walks_one<<<grid_for(qs.max_R, 256), 256, 0, st>>>(*one, qs.counters);
     else
-        k_source_walks<<<dim3(grid_for(qs.max_R, 256), nq), 256, 0, st>>>(qs.desc, qs.counters, true);
+        k_source_walks<true><<<dim3(grid_for(qs.max_R, 256), nq), 256, 0, st>>>(qs.desc, qs.counters, true);
     if (qs.nq > TILES_IN_UNITS) k_tiles<<<nq, 64, 0, st>>>(qs.desc);
     const uint3 grid = make_uint3((uint32_t)meet_grid_blocks<K_PLAIN, SRK_MEET_SLOTS, false>(),
                                   (uint32_t)meet_grid_blocks<K_STITCHED, SRK_MEET_SLOTS_STITCHED, false>(),
@@ -1313,7 +1323,7 @@ int enqueue_ring_request(const QueryDesc &d, const StreamRing &ring, int32_t slo
     unsigned long long *ctr = ring.counters + (size_t)slot * 8;
     const unsigned gx_n = std::min<unsigned>(grid_for(std::max(d.n, 1), 256), 1024u);
     k_init_one<<<gx_n, 256, 0, st>>>(qd, d, ctr, 8);
-    k_source_walks<<<dim3(grid_for(d.R, 256), 1), 256, 0, st>>>(qd, ctr, false);
+    k_source_walks<false><<<dim3(grid_for(d.R, 256), 1), 256, 0, st>>>(qd, ctr, false);
     k_publish<<<1, 256, 0, st>>>(ring, slot, seq, ring_grid(d.kind));
     SRK_HIP(hipGetLastError());
     return SIMRANK_OK;
