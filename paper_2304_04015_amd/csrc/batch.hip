@@ -185,8 +185,8 @@ extern "C" int simrank_batch_plan_create_ex(simrank_graph *const *graphs, int32_
     // Each kind's meet launch numbers the work units of all its queries in 32
     // bits (unit offsets and the persistent cursor, which the grid's blocks
     // advance past the end once each): refuse a plan whose units could wrap.
+    int64_t kind_units[N_KINDS] = {0, 0, 0};
     {
-        int64_t kind_units[N_KINDS] = {0, 0, 0};
         for (int32_t i = 0; i < nq; ++i) {
             if (group_of[i] >= 0) continue;
             const Graph *g = graphs[qs[i].graph];
@@ -272,6 +272,9 @@ extern "C" int simrank_batch_plan_create_ex(simrank_graph *const *graphs, int32_
                      : d.kind == K_STRAT  ? K_GROUPED_STRAT : K_GROUPED;
         } else {
             set.units_bound[d.kind] += units_bound_of(g, pp.R, pp.L);
+            // (small tiles could make the units twice as many)
+            if (kind_units[d.kind] >= (int64_t)1 << 30) d.tile_nodes = tile_nodes_of(d.kind);
+            set.rows[d.kind] |= rows_wish(*g, d);
         }
     }
     GroupSet gset;

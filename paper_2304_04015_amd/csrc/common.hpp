@@ -88,6 +88,15 @@ __host__ __device__ constexpr int meet_block_of(int kind) {
            : kind == K_STITCHED ? SRK_STITCH_MEET_BLOCK : SRK_STRAT_MEET_BLOCK;
 }
 
+// Rows of a packed graph's hubs that a kind's meet kernel has LDS for, beside
+// its tile and a served request's preparation: plain and stitched queries only.
+// A graph with more hubs has its tiles cut to HUB_TILE_NODES positions, to make
+// room for HUB_ROWS.
+__host__ __device__ constexpr int hub_rows_of(int kind) {
+    return kind == K_PLAIN ? 1280 : kind == K_STITCHED ? 768 : 0;
+}
+constexpr int HUB_TILE_NODES = 12288, HUB_ROWS = 6912;
+
 // ------------------------------------------------------------ device graph
 // Gather layout of the reversed graph.  Every node v owns the edge slots
 // [o(v), o(v) + max(deg(v), 1)) of E; E[o(v) + k] describes the k-th
@@ -95,6 +104,9 @@ __host__ __device__ constexpr int meet_block_of(int kind) {
 // already yields the row of the node it lands on.  o() is strictly increasing,
 // so it identifies nodes; nodes without in-neighbours own one unused slot.
 struct Index;
+
+// Hubs a graph may have and still be packed (E4).
+constexpr uint32_t HUB_CAP = HUB_ROWS;
 
 struct Graph {
     int device = 0;
@@ -105,6 +117,10 @@ struct Graph {
     int32_t max_deg = 0;
     uint2 *nodes = nullptr;       // [n]     (o(v), deg(v))
     uint2 *E = nullptr;           // [m_slots]
+    uint32_t *E4 = nullptr;       // [m_slots] E packed for the meet kernels (graph.hip), or NULL
+    uint2 *hubs = nullptr;        // [HUB_CAP] rows of the nodes whose degree E4 cannot hold
+    int32_t obits = 0;            // bits of o() in an E4 entry; 0: there is no E4
+    int32_t n_hubs = 0;
     uint32_t *node_of = nullptr;  // [m_slots] node id owning slot o (valid at o(v))
     int32_t *active = nullptr;    // [n_active] nodes with deg >= 1, ascending
     uint32_t *dbar = nullptr;     // [n] rows of the CSR that list v (v's in-degree in the
@@ -168,6 +184,9 @@ struct StratParams {
 struct QueryDesc {
     const uint2 *nodes;
     const uint2 *E;
+    const uint32_t *E4;    // the packed rows of the graph, if obits > 0
+    const uint2 *hubs;
+    int32_t obits, n_hubs;
     const int32_t *active;
     IndexView ix;
     uint32_t *sw;          // [R][L] source walk positions 1..L (o values)
@@ -186,6 +205,7 @@ struct QueryDesc {
     int32_t kind;          // Kind
     int32_t items;         // items a wave takes at once, at most (item_chunk)
     int32_t tile_j;        // source walks per LDS tile, MIN_TILE_J .. tile_j_of(kind)
+    int32_t tile_nodes;    // and their positions: tile_nodes_of(kind), or HUB_TILE_NODES
     // stratified only (R = N walks per node, L = phi)
     const StratTab *tab;
     uint8_t *scls;         // [R] length class of walk (s, j)
@@ -195,12 +215,47 @@ struct QueryDesc {
     int32_t sa, sb;        // shuffle grid
 };
 
+// Rows that a meet kernel gathers (graph.hip): the 8 bytes of E, or those packed
+// in 4; HUBS: packed, with the small tiles of a graph with many hubs; MIXED: as
+// each query's graph has it.
+enum Rows : int { ROWS_E, ROWS_PACKED, ROWS_HUBS, ROWS_MIXED };
+// What a query can use.  E is better where all of it is within an XCD's L2
+// (packed rows only add their decoding; n = 20,000, R = 38,005: 2,677 us with E,
+// 2,717 packed), packed rows are beyond it (n = 2^18, R = 9,502: 11,681 and
+// 9,455).  Stratified queries are bound by their instructions: E (n = 2^18: 21.6
+// ms with E, 21.9 packed), as are the groups (32 members: 50.8 and 52.3 ms).
+constexpr int WANTS_E = 1, WANTS_PACKED = 2, WANTS_HUBS = 4, HAS_NONE = 8;
+inline int rows_wish(const Graph &g, const QueryDesc &d) {
+    if (g.obits == 0 || d.kind == K_STRAT) return HAS_NONE;
+    if (g.n_hubs > hub_rows_of(d.kind)) return d.tile_nodes == HUB_TILE_NODES ? WANTS_HUBS : HAS_NONE;
+    return 8 * g.m_slots <= (int64_t)4 << 20 ? WANTS_E : WANTS_PACKED;
+}
+// Rows of a launch for queries of these wishes.  A kernel that asks its graph
+// at each gather takes 2 to 4% longer, so it is left for queries of which only
+// some can have packed rows.
+inline Rows rows_of(int wishes) {
+    return wishes == WANTS_HUBS                    ? ROWS_HUBS
+           : !(wishes & WANTS_PACKED)              ? ROWS_E
+           : !(wishes & (WANTS_HUBS | HAS_NONE))   ? ROWS_PACKED
+                                                   : ROWS_MIXED;
+}
+// Positions of a tile of source walks.  The small tiles of a graph with many
+// hubs are up to twice as many: they are taken where even units of one node
+// could be numbered.
+inline int32_t tile_nodes_for(const Graph &g, int kind, int32_t R, int32_t L) {
+    const int64_t tiles = 2 + R / MIN_TILE_J + (int64_t)R * L / (HUB_TILE_NODES - L);
+    return kind != K_STRAT && g.obits > 0 && g.n_hubs > hub_rows_of(kind) &&
+                   tiles * g.n_active < (int64_t)1 << 31
+               ? HUB_TILE_NODES : tile_nodes_of(kind);
+}
+
 // A set of queries whose descriptors are already in device memory.
 struct QuerySet {
     const QueryDesc *desc;        // device [nq]
     int32_t nq = 0;
     int32_t max_R = 0, max_n = 0;
     int64_t units_bound[N_KINDS] = {0, 0, 0};   // work units of each kind's queries, at most
+    int rows[N_KINDS] = {0, 0, 0};              // rows_wish of each kind's queries
     uint32_t *units = nullptr;    // device [units_words(nq)]: unit offsets per kind, then cursors
     unsigned long long *counters = nullptr;  // device [CTR_WORDS]
     const struct GroupSet *groups = nullptr;  // grouped plain queries, if any
@@ -234,6 +289,9 @@ __host__ __device__ inline bool strat_kind(int32_t kind) { return kind == K_STRA
 struct GroupDesc {
     const uint2 *nodes;
     const uint2 *E;
+    const uint32_t *E4;
+    const uint2 *hubs;
+    int32_t obits, n_hubs;
     const int32_t *active;
     int32_t n_active, vb, n_chunks;
     int32_t G, L, Rmax;
@@ -341,7 +399,7 @@ struct StreamRing {
 // when none is left.  Bytes of device memory a request needs for its buffers.
 int enqueue_ring_request(const QueryDesc &d, const StreamRing &ring, int32_t slot, uint32_t seq,
                          hipStream_t st);
-int launch_ring_meet(int kind, const StreamRing &ring, hipStream_t st);
+int launch_ring_meet(Rows rows, int kind, const StreamRing &ring, hipStream_t st);
 size_t request_bytes(const simrank_params &p, int mode, int32_t n);
 // Carves a request's buffers (request_bytes of them) from base into d.
 void carve_request(const simrank_params &p, int mode, int32_t n, char *base, QueryDesc *d);

@@ -135,6 +135,23 @@ __device__ __forceinline__ uint2 load_edge(GlobalPtr<uint64_t> E, uint32_t at) {
     return make_uint2((uint32_t)v, (uint32_t)(v >> 32));
 }
 
+// The meet kernels' gathers: packed rows (4 bytes a slot) where the graph has
+// them and its hubs' rows fit the kernel's LDS, else load_edge.
+struct Gather {
+    GlobalPtr<uint64_t> E;
+    GlobalPtr<uint32_t> E4;
+    uint32_t obits;   // 0: no packed rows
+};
+template <int HL, typename Desc>   // HL: hubs' rows the kernel's LDS holds
+__device__ __forceinline__ Gather gather_of(const Desc &d) {
+    return {gp_uni((const uint64_t *)d.E), gp_uni(d.E4),
+            uni((uint32_t)d.n_hubs) <= (uint32_t)HL ? uni((uint32_t)d.obits) : 0u};
+}
+__device__ __forceinline__ uint2 unpack_row(uint32_t r, uint32_t obits, const uint2 *s_hub) {
+    const uint32_t d = r >> obits, x = r & ((1u << obits) - 1u);
+    return d != 0xffffffffu >> obits ? make_uint2(x, d) : s_hub[x];
+}
+
 __device__ __forceinline__ uint32_t lane_rank(uint64_t mask) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
                                      __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));

@@ -10,12 +10,32 @@
 // the next node's identity o and its degree, so a move never needs a second,
 // dependent gather of a row array.  Edge order inside a row is preserved, so
 // the k-th in-neighbour is the same as in the caller's CSR.
+//
+// A graph also has its rows packed in 4 bytes, for the meet kernels: where E is
+// larger than an XCD's 4 MB of L2 those are bound by the cache lines their
+// gathers fetch from behind it, and of half the footprint the L2 holds twice the
+// share.  E4[i] = degree << obits | o with just the bits that o needs; the
+// largest degree code stands for a hub, a node whose degree does not fit, with
+// its place in `hubs` in place of o.  A graph with more than HUB_CAP hubs has no
+// packed rows.  Meet kernel with E and packed: n = 40,000 (5 MB of E), R = 9,502:
+// 1,499 and 1,335 us; n = 150,001 (18 MB): 5,949 and 5,093; n = 2^18 (32 MB):
+// 11.68 and 9.46 ms; n = 2^19 (66 MB): 24.8 and 21.2; n = 2^20 (133 MB, 6,256
+// hubs): 51.9 and 47.8.
 #include <vector>
 
 #include "common.hpp"
 
 namespace srk {
 namespace {
+
+// Packing of the rows in 4 bytes; E4 NULL: not wanted.
+struct PackArgs {
+    uint32_t *E4;
+    uint32_t obits;
+    uint2 *hubs;                  // [HUB_CAP]
+    uint32_t *hub_at;             // [n] place of a node that is a hub
+    unsigned long long *last_hub;   // place of the last hub, -1 before
+};
 
 __global__ void k_slot_counts(const int32_t *__restrict__ off, int32_t n,
                               uint32_t *__restrict__ slots, uint32_t *__restrict__ has_in) {
@@ -29,7 +49,7 @@ __global__ void k_slot_counts(const int32_t *__restrict__ off, int32_t n,
 __global__ void k_nodes(const int32_t *__restrict__ off, const int64_t *__restrict__ o, int32_t n,
                         const int64_t *__restrict__ act_pos, uint2 *__restrict__ nodes,
                         uint2 *__restrict__ E, uint32_t *__restrict__ node_of,
-                        int32_t *__restrict__ active) {
+                        int32_t *__restrict__ active, PackArgs pk) {
     const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (v >= n) return;
     const int32_t d = off[v + 1] - off[v];
@@ -37,6 +57,13 @@ __global__ void k_nodes(const int32_t *__restrict__ off, const int64_t *__restri
     node_of[o[v]] = (uint32_t)v;
     if (d > 0) active[act_pos[v]] = (int32_t)v;
     else E[o[v]] = make_uint2(NIL, NIL);
+    if (!pk.E4) return;
+    if (d == 0) pk.E4[o[v]] = 0u;
+    if ((uint32_t)d >= 0xffffffffu >> pk.obits) {
+        const unsigned long long k = atomicAdd(pk.last_hub, 1ull) + 1ull;
+        if (k < HUB_CAP) pk.hubs[k] = make_uint2((uint32_t)o[v], (uint32_t)d);
+        pk.hub_at[v] = (uint32_t)k;
+    }
 }
 
 __global__ void k_fill_u32(uint32_t *__restrict__ p, int64_t n, uint32_t val) {
@@ -66,7 +93,8 @@ __global__ __launch_bounds__(EDGE_BLOCK) void k_edges(const int32_t *__restrict_
                                                       int64_t m, const uint2 *__restrict__ nodes,
                                                       uint2 *__restrict__ E,
                                                       uint32_t *__restrict__ dbar,
-                                                      unsigned long long *__restrict__ bad) {
+                                                      unsigned long long *__restrict__ bad,
+                                                      PackArgs pk) {
     __shared__ int32_t s_row[EDGE_TILE];
     __shared__ int32_t s_part[EDGE_BLOCK / 64];
     __shared__ uint32_t s_key[EDGE_HASH], s_cnt[EDGE_HASH];
@@ -120,7 +148,13 @@ __global__ __launch_bounds__(EDGE_BLOCK) void k_edges(const int32_t *__restrict_
             atomicMin(bad, (unsigned long long)e);
             continue;
         }
-        E[(int64_t)nodes[v].x + (e - off[v])] = nodes[u];
+        const int64_t at = (int64_t)nodes[v].x + (e - off[v]);
+        const uint2 to = nodes[u];
+        E[at] = to;
+        if (pk.E4) {
+            const uint32_t most = 0xffffffffu >> pk.obits;
+            pk.E4[at] = to.y < most ? (to.y << pk.obits) | to.x : (most << pk.obits) | pk.hub_at[u];
+        }
         const uint32_t h = (u * 0x9E3779B1u) >> 21;
         static_assert(EDGE_HASH == 1u << 11, "hash bits");
         const uint32_t old = atomicCAS(&s_key[h], NIL, u);
@@ -152,6 +186,16 @@ void device_free(void *p) {
     if (p) (void)hipFree(p);
 }
 
+static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
+
+// Bits of o() in a packed row, or 0 if so few would be left for the degree that
+// most nodes were hubs.
+static int32_t pack_bits(int64_t m_slots) {
+    int32_t b = 1;
+    while ((m_slots - 1) >> b) ++b;
+    return b <= 26 ? b : 0;
+}
+
 static void graph_release(simrank_graph *g) {
     if (!g) return;
     if (g->index) {
@@ -160,8 +204,7 @@ static void graph_release(simrank_graph *g) {
         g->index = nullptr;
     }
     device_free(g->nodes);
-    device_free(g->E);
-    device_free(g->node_of);
+    device_free(g->E);   // (and node_of, E4 and hubs behind it)
     device_free(g->active);
     device_free(g->dbar);
     if (g->stream) (void)hipStreamDestroy(g->stream);
@@ -233,9 +276,26 @@ extern "C" int simrank_load_graph(int32_t n, int64_t m, const int32_t *in_off,
         SRK_TRYHIP(hipStreamCreateWithFlags(&g->stream, hipStreamNonBlocking));
         hipStream_t st = g->stream;
         SRK_TRY(device_alloc((void **)&g->nodes, sizeof(uint2) * (size_t)n, &g->bytes));
-        SRK_TRY(device_alloc((void **)&g->E, sizeof(uint2) * (size_t)g->m_slots, &g->bytes));
-        SRK_TRY(device_alloc((void **)&g->node_of, sizeof(uint32_t) * (size_t)g->m_slots,
-                             &g->bytes));
+        // E, node_of and the packed rows in one piece (a free of its own for each
+        // took 0.3 ms at n = 300,007); a graph that leaves no room for the packed
+        // rows does without them
+        const int32_t obits = pack_bits(g->m_slots);
+        const bool may_hub = obits && (uint32_t)max_deg >= 0xffffffffu >> obits;
+        const size_t sE = align256(sizeof(uint2) * (size_t)g->m_slots);
+        const size_t s4 = align256(sizeof(uint32_t) * (size_t)g->m_slots);
+        const size_t packed = obits ? s4 + (may_hub ? sizeof(uint2) * HUB_CAP : 0) : 0;
+        rc = device_alloc((void **)&g->E, sE + s4 + packed, &g->bytes);
+        const bool pack = packed && rc == SIMRANK_OK;
+        if (packed && !pack) {
+            clear_error();
+            rc = device_alloc((void **)&g->E, sE + s4, &g->bytes);
+        }
+        SRK_TRY(rc);
+        g->node_of = (uint32_t *)((char *)g->E + sE);
+        if (pack) {
+            g->E4 = (uint32_t *)((char *)g->node_of + s4);
+            g->hubs = (uint2 *)((char *)g->E4 + s4);
+        }
         SRK_TRY(device_alloc((void **)&g->active, sizeof(int32_t) * (size_t)(n_active ? n_active : 1),
                              &g->bytes));
         SRK_TRY(device_alloc((void **)&g->dbar, sizeof(uint32_t) * (size_t)n, &g->bytes));
@@ -245,24 +305,26 @@ extern "C" int simrank_load_graph(int32_t n, int64_t m, const int32_t *in_off,
         SRK_TRY(device_alloc((void **)&d_has, sizeof(uint32_t) * (size_t)n, nullptr));
         SRK_TRY(device_alloc((void **)&d_o, sizeof(int64_t) * (size_t)n, nullptr));
         SRK_TRY(device_alloc((void **)&d_apos, sizeof(int64_t) * (size_t)n, nullptr));
-        SRK_TRY(device_alloc((void **)&d_tot, sizeof(int64_t) * 3, nullptr));   // totals, first bad edge
+        // totals, first bad edge, hubs
+        SRK_TRY(device_alloc((void **)&d_tot, sizeof(int64_t) * 4, nullptr));
+        const PackArgs pk{g->E4, (uint32_t)obits, g->hubs, d_slots, (unsigned long long *)(d_tot + 3)};
         SRK_TRYHIP(hipMemcpyAsync(d_off, in_off, sizeof(int32_t) * (size_t)(n + 1),
                                   hipMemcpyHostToDevice, st));
         k_slot_counts<<<grid_for(n, 256), 256, 0, st>>>(d_off, n, d_slots, d_has);
         SRK_TRY(scan_exclusive_u32_to_i64(d_slots, n, d_o, d_tot, st));
         SRK_TRY(scan_exclusive_u32_to_i64(d_has, n, d_apos, d_tot + 1, st));
         k_fill_u32<<<1024, 256, 0, st>>>(g->node_of, g->m_slots, NIL);
-        k_fill_u32<<<1, 64, 0, st>>>((uint32_t *)(d_tot + 2), 2, NIL);
+        k_fill_u32<<<1, 64, 0, st>>>((uint32_t *)(d_tot + 2), 4, NIL);
         k_fill_u32<<<1024, 256, 0, st>>>(g->dbar, n, 0u);
         k_nodes<<<grid_for(n, 256), 256, 0, st>>>(d_off, d_o, n, d_apos, g->nodes, g->E, g->node_of,
-                                                   g->active);
+                                                   g->active, pk);
         if (m) {
             SRK_TRYHIP(hipMemcpyAsync(d_src, in_src, sizeof(int32_t) * (size_t)m, hipMemcpyHostToDevice, st));
             k_edges<<<grid_for(m, EDGE_TILE), EDGE_BLOCK, 0, st>>>(
-                d_off, d_src, n, m, g->nodes, g->E, g->dbar, (unsigned long long *)(d_tot + 2));
+                d_off, d_src, n, m, g->nodes, g->E, g->dbar, (unsigned long long *)(d_tot + 2), pk);
         }
         SRK_TRYHIP(hipGetLastError());
-        int64_t tot[3];
+        int64_t tot[4];
         SRK_TRYHIP(hipMemcpyAsync(tot, d_tot, sizeof(tot), hipMemcpyDeviceToHost, st));
         SRK_TRYHIP(hipStreamSynchronize(st));
         if (tot[2] != -1) {
@@ -272,6 +334,12 @@ extern "C" int simrank_load_graph(int32_t n, int64_t m, const int32_t *in_off,
         if (tot[0] != g->m_slots || tot[1] != n_active) {
             rc = fail(SIMRANK_EDEVICE, "ingest totals disagree with the host count");
             goto bad;
+        }
+        const int64_t hubs = tot[3] + 1;
+        // (no more than HUB_CAP have a row; with more, E4 stays unused)
+        if (pack && hubs <= (int64_t)HUB_CAP) {
+            g->obits = obits;
+            g->n_hubs = (int32_t)hubs;
         }
     }
     device_free(d_off); device_free(d_src); device_free(d_slots); device_free(d_has);

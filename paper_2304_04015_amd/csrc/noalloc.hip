@@ -155,6 +155,7 @@ extern "C" int simrank_single_source_noalloc(const simrank_graph *g, const simra
     qs.max_R = d.R;
     qs.max_n = g->n;
     qs.units_bound[d.kind] = units_bound;
+    qs.rows[d.kind] = rows_wish(*g, d);
     qs.units = c.units;
     qs.counters = c.counters;
     hipStream_t st = (hipStream_t)stream;

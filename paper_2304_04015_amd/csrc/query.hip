@@ -221,29 +221,38 @@ __global__ __launch_bounds__(256) void k_source_walks_one(QueryDesc d,
 }
 
 // ------------------------------------------------------------ tiles
+// First entries of a query's tiles.  HUB_TILE_NODES' tiles can be more than the
+// buffer was sized for (max_tiles_for) where the positions may fill several:
+// they lie where the source walks' padded table was, which the packing before
+// was the last to read.
+__device__ __forceinline__ uint32_t *tiles_of(const QueryDesc &d) {
+    return d.tile_nodes == HUB_TILE_NODES && (uint64_t)d.R * (uint64_t)d.L > (uint64_t)HUB_TILE_NODES
+               ? d.sw : d.tiles;
+}
+
 // Cuts the packed entries of a query into tiles that fit the meet kernel's LDS:
 // with the kind's shape (TJ walks, TN positions), each tile is the longest run
 // of walks from the previous one's end that holds at most TJ walks and TN
 // positions (cut_tiles).  Called by all lanes of one wave.
 __device__ void make_tiles(const QueryDesc &d, int lane) {
     const uint32_t R1 = d.meta[0], total = d.meta[1];
-    const uint32_t TJ = (uint32_t)d.tile_j, TN = (uint32_t)tile_nodes_of(d.kind);
+    const uint32_t TJ = (uint32_t)d.tile_j, TN = (uint32_t)d.tile_nodes;
     if (lane == 0) d.joff[R1] = total;
     uint32_t n_tiles, km = R1;
     if (R1 <= TJ && total <= TN) {
         n_tiles = R1 > 0u ? 1u : 0u;
-        if (lane == 0 && R1 > 0u) d.tiles[0] = 0u;
+        if (lane == 0 && R1 > 0u) tiles_of(d)[0] = 0u;
     } else {
         __threadfence_block();   // joff[R1] is read below
-        n_tiles = cut_tiles(d.joff, R1, TJ, TN, d.tiles, lane);
+        n_tiles = cut_tiles(d.joff, R1, TJ, TN, tiles_of(d), lane);
         __threadfence_block();
         km = 0;
         for (uint32_t t = (uint32_t)lane; t < n_tiles; t += 64)
-            km = max(km, (t + 1 < n_tiles ? d.tiles[t + 1] : R1) - d.tiles[t]);
+            km = max(km, (t + 1 < n_tiles ? tiles_of(d)[t + 1] : R1) - tiles_of(d)[t]);
         for (int dd = 32; dd > 0; dd >>= 1) km = max(km, __shfl_xor(km, dd, 64));
     }
     if (lane == 0) {
-        d.tiles[n_tiles] = R1;
+        tiles_of(d)[n_tiles] = R1;
         d.meta[2] = n_tiles;
         d.meta[3] = km;
     }
@@ -269,7 +278,7 @@ constexpr int UNIT_ROUNDS_LOG2_PAIRS = 27, UNIT_MAX_ROUNDS = 16;
 
 // First unit of each tile and, behind them, the number of units: kept where the
 // lengths of the source walks were, which only the compaction before reads.
-// The max_tiles_for + 1 words fit there: 4 (3 + R / 2048 + R L / (20480 - L))
+// They and one word more fit there: 4 (3 + R / 2048 + R L / (12288 - L))
 // bytes are fewer than R rounded up to 256, for every R and L up to MAX_CAP.
 __device__ __forceinline__ uint32_t *tunits_of(const QueryDesc &d) {
     return reinterpret_cast<uint32_t *>(d.slen);
@@ -305,7 +314,7 @@ __device__ uint64_t unit_pairs(const QueryDesc *qd, int32_t nq, int32_t kind, ui
             const uint32_t n = (uint32_t)qd[q].n_active, nt = qd[q].meta[2];
             const uint64_t least = (n + MEET_VB - 1) / MEET_VB;
             for (uint32_t t = (uint32_t)lane; t < nt; t += 64) {
-                const uint64_t p = (uint64_t)n * (qd[q].tiles[t + 1] - qd[q].tiles[t]);
+                const uint64_t p = (uint64_t)n * (tiles_of(qd[q])[t + 1] - tiles_of(qd[q])[t]);
                 if (p < least * per) {
                     small_pairs += p;
                     small_units += least;
@@ -336,7 +345,7 @@ __device__ uint32_t lay_units(const QueryDesc &d, uint64_t per, int lane) {
         if (t < nt) {
             c = (n + vb - 1) / vb;
             if (d.vb <= 0 && n) {
-                const uint64_t want = (uint64_t)n * (d.tiles[t + 1] - d.tiles[t]) / per;
+                const uint64_t want = (uint64_t)n * (tiles_of(d)[t + 1] - tiles_of(d)[t]) / per;
                 c = max(c, (uint32_t)min(want, (uint64_t)n));
             }
         }
@@ -433,7 +442,7 @@ __global__ __launch_bounds__(64) void k_units_one(QueryDesc d, uint32_t *__restr
     const uint32_t blocks = d.kind == 0 ? grid.x : d.kind == 1 ? grid.y : grid.z;
     const uint32_t R1 = uni(d.meta[0]), total = uni(d.meta[1]), n = (uint32_t)d.n_active;
     uint32_t n_units = 0;
-    if (R1 <= (uint32_t)d.tile_j && total <= (uint32_t)tile_nodes_of(d.kind)) {
+    if (R1 <= (uint32_t)d.tile_j && total <= (uint32_t)d.tile_nodes) {
         const uint32_t nt = R1 > 0u ? 1u : 0u;
         if (nt && n) {
             const uint32_t most = d.vb > 0 ? (uint32_t)d.vb : (uint32_t)MEET_VB;
@@ -447,8 +456,8 @@ __global__ __launch_bounds__(64) void k_units_one(QueryDesc d, uint32_t *__restr
         }
         if (lane == 0) {
             d.joff[R1] = total;
-            d.tiles[0] = 0u;
-            d.tiles[nt] = R1;
+            tiles_of(d)[0] = 0u;
+            tiles_of(d)[nt] = R1;
             d.meta[2] = nt;
             d.meta[3] = R1;
             tunits_of(d)[0] = 0u;
@@ -591,7 +600,7 @@ __device__ void ring_report(const StreamRing &ring, const QueryDesc &d, uint32_t
 
 // At most 112 registers, which the attribute counts in pairs: 4 waves leave a
 // SIMD 64 of its 512, and a wave of a served request's preparation fits beside.
-template <int KIND, int NS, bool STREAM>
+template <int KIND, int NS, bool STREAM, int ROWS>
 __global__ __launch_bounds__(meet_block_of(KIND)) __attribute__((amdgpu_num_vgpr(56)))
 void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
             const uint32_t *__restrict__ ustart,
@@ -600,7 +609,9 @@ void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
             StreamRing ring) {
     constexpr bool STITCHED = KIND == K_STITCHED;
     constexpr bool STRAT = KIND == K_STRAT;
-    constexpr int TJ = tile_j_of(KIND), TN = tile_nodes_of(KIND);
+    constexpr int TJ = tile_j_of(KIND), TN = ROWS == ROWS_HUBS ? HUB_TILE_NODES : tile_nodes_of(KIND);
+    constexpr int HL = ROWS == ROWS_HUBS ? HUB_ROWS : hub_rows_of(KIND);
+    __shared__ uint2 s_hub[ROWS == ROWS_E ? 1 : HL];   // rows of a packed graph's hubs
     __shared__ uint32_t s_nodes[TN];
     // the tile's entries: walk index j (below 2^24) | number of positions << 24,
     // and their LDS offset
@@ -610,13 +621,13 @@ void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
     __shared__ uint32_t s_cnt[STRAT ? 1 : MEET_VB];
     __shared__ uint32_t s_vid[MEET_VB];
     __shared__ uint2 s_vrow[MEET_VB];
-    __shared__ uint32_t s_va[MEET_VB], s_vb[MEET_VB], s_vcc[MEET_VB];   // the draws' constants
     __shared__ uint32_t s_unit, s_item, s_slot, s_seq, s_last, s_run, s_srcvl;
     // stratified: classes of the tile's source walks, class starts, the
-    // shuffle keys of the unit's nodes, weighted sums
+    // shuffle keys and draw constants of the unit's nodes, weighted sums
     __shared__ uint8_t s_cls[STRAT ? TJ : 1];
     __shared__ uint32_t s_ccum[STRAT ? MAX_CAP + 2 : 1];
     __shared__ uint4 s_fk[STRAT ? MEET_VB : 1];
+    __shared__ uint32_t s_va[STRAT ? MEET_VB : 1], s_vb[STRAT ? MEET_VB : 1], s_vcc[STRAT ? MEET_VB : 1];
     __shared__ unsigned long long s_w[STRAT ? MEET_VB : 1];
     __shared__ uint2 s_q[STRAT ? meet_block_of(KIND) : 1];   // 64 prepared pairs per wave
     // stitched: per-wave ring of pairs waiting for their tails, (vl << 16 | k, o)
@@ -690,12 +701,13 @@ void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
         const uint32_t chunks = uni(tunits_of(d)[tile + 1]) - unit0, chunk = local - unit0;
         const PhiloxKey key{uni(d.k0), uni(d.k1)};
         const uint32_t T = uni(d.T);
-        const GlobalPtr<uint64_t> E = gp_uni((const uint64_t *)d.E);
+        const Gather rows = gather_of<HL>(d);
+        const bool packed = ROWS == ROWS_PACKED || ROWS == ROWS_HUBS || (ROWS == ROWS_MIXED && rows.obits > 0u);
         const int32_t src = (int32_t)uni((uint32_t)d.s);
         const uint32_t NN = uni((uint32_t)d.R), sa = uni((uint32_t)d.sa), sb = uni((uint32_t)d.sb);
         const int32_t phi = (int32_t)uni((uint32_t)d.L);
         if (tag != cur_q || tile != cur_tile) {
-            const uint32_t k0 = uni(d.tiles[tile]), k1 = uni(d.tiles[tile + 1]);
+            const uint32_t k0 = uni(tiles_of(d)[tile]), k1 = uni(tiles_of(d)[tile + 1]);
             const uint32_t nb = d.joff[k0], ne = d.joff[k1];
             K = k1 - k0;
             for (uint32_t i = threadIdx.x; i < K; i += blockDim.x) {
@@ -708,6 +720,8 @@ void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
             if (STRAT)
                 for (uint32_t i = threadIdx.x; i < (uint32_t)phi + 2; i += blockDim.x)
                     s_ccum[i] = d.tab->ccum[i];
+            if (packed)
+                for (uint32_t i = threadIdx.x; i < (uint32_t)d.n_hubs; i += blockDim.x) s_hub[i] = d.hubs[i];
             cur_q = tag;
             cur_tile = tile;
         }
@@ -726,12 +740,14 @@ void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
                 const uint32_t id = (uint32_t)d.active[vbase + (int32_t)i];
                 s_vid[i] = id;
                 s_vrow[i] = d.nodes[id];
-                const WalkDraws w = walk_draws_begin(id, 0u, key, STRAT ? DOM_STRAT : DOM_WALK);
-                s_va[i] = w.a;
-                s_vb[i] = w.b;
-                s_vcc[i] = w.cc;
                 if ((int32_t)id == src) s_srcvl = i;
-                if (STRAT) s_fk[i] = philox4x32_10(id, 0u, 0u, DOM_SHUFFLE, key);
+                if (STRAT) {
+                    const WalkDraws w = walk_draws_begin(id, 0u, key, DOM_STRAT);
+                    s_va[i] = w.a;
+                    s_vb[i] = w.b;
+                    s_vcc[i] = w.cc;
+                    s_fk[i] = philox4x32_10(id, 0u, 0u, DOM_SHUFFLE, key);
+                }
             }
         }
         __syncthreads();
@@ -750,9 +766,10 @@ void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
             const uint2 row = s_vrow[cvl];
             vo = uni(row.x);
             vd = uni(row.y);
-            va = uni(s_va[cvl]);
-            vb = uni(s_vb[cvl]);
-            vcc = uni(s_vcc[cvl]);
+            const WalkDraws w = walk_draws_begin(uni(s_vid[cvl]), 0u, key);
+            va = w.a;
+            vb = w.b;
+            vcc = w.cc;
         };
         bool drained = false;
         uint32_t qh = 0, qn = 0;   // stratified: the wave's queue of prepared pairs [qh, qn)
@@ -956,9 +973,15 @@ void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
             }
             // all gathers of the lane's slots, then the compares
             uint2 e[NS];
+            if (packed) {
 #pragma unroll
-            for (int qq = 0; qq < NS; ++qq)
-                if (go[qq]) e[qq] = load_edge(E, at[qq]);
+                for (int qq = 0; qq < NS; ++qq)
+                    if (go[qq]) e[qq].x = rows.E4[at[qq]];
+            } else {
+#pragma unroll
+                for (int qq = 0; qq < NS; ++qq)
+                    if (go[qq]) e[qq] = load_edge(rows.E, at[qq]);
+            }
             bool tails[NS];
 #pragma unroll
             for (int qq = 0; qq < NS; ++qq) tails[qq] = false;
@@ -967,8 +990,9 @@ void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
                 if (!go[qq]) continue;
                 ++st_moves;
                 Slot &w = sl[qq];
-                w.o = e[qq].x;
-                w.d = e[qq].y;
+                const uint2 to = packed ? unpack_row(e[qq].x, rows.obits, s_hub) : e[qq];
+                w.o = to.x;
+                w.d = to.y;
                 const uint32_t base = w.pos & 0xffffu, len = (w.pos >> 16) & 0xffu;
                 if (w.o == s_nodes[base + w.t - 1]) {
                     if (STRAT)
@@ -1137,8 +1161,8 @@ int meet_grid_blocks() {
         int dev = 0, cus = 0, per = 0;
         (void)hipGetDevice(&dev);
         (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-        (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_meet<KIND, NS, STREAM>,
-                                                           meet_block_of(KIND), 0);
+        (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(
+            &per, k_meet<KIND, NS, STREAM, ROWS_E>, meet_block_of(KIND), 0);
         if (cus <= 0) cus = 256;
         if (per <= 0) per = 1;
         return cus * per;
@@ -1151,13 +1175,24 @@ void launch_meet(const QuerySet &qs, hipStream_t st) {
     const int blocks = meet_grid_blocks<KIND, NS, false>();
     const uint32_t *ustart = qs.units + (size_t)KIND * (qs.nq + 1);
     uint32_t *cursor = qs.units + (size_t)N_KINDS * (qs.nq + 1) + KIND;
-    k_meet<KIND, NS, false><<<blocks, meet_block_of(KIND), 0, st>>>(qs.desc, qs.nq, ustart, cursor,
-                                                                    qs.counters, StreamRing{});
+    const Rows rows = rows_of(qs.rows[KIND]);
+    auto kernel = k_meet<KIND, NS, false, ROWS_E>;
+    if constexpr (KIND != K_STRAT) {
+        if (rows == ROWS_PACKED) kernel = k_meet<KIND, NS, false, ROWS_PACKED>;
+        if (rows == ROWS_HUBS) kernel = k_meet<KIND, NS, false, ROWS_HUBS>;
+        if (rows == ROWS_MIXED) kernel = k_meet<KIND, NS, false, ROWS_MIXED>;
+    }
+    kernel<<<blocks, meet_block_of(KIND), 0, st>>>(qs.desc, qs.nq, ustart, cursor, qs.counters, StreamRing{});
 }
 
 template <int KIND, int NS>
-void launch_meet_ring(const StreamRing &ring, hipStream_t st) {
-    k_meet<KIND, NS, true><<<meet_grid_blocks<KIND, NS, true>(), meet_block_of(KIND), 0, st>>>(
+void launch_meet_ring(Rows rows, const StreamRing &ring, hipStream_t st) {
+    auto kernel = k_meet<KIND, NS, true, ROWS_E>;
+    if constexpr (KIND != K_STRAT) {   // (a server's requests are on one graph)
+        if (rows == ROWS_PACKED) kernel = k_meet<KIND, NS, true, ROWS_PACKED>;
+        if (rows == ROWS_HUBS) kernel = k_meet<KIND, NS, true, ROWS_HUBS>;
+    }
+    kernel<<<meet_grid_blocks<KIND, NS, true>(), meet_block_of(KIND), 0, st>>>(
         ring.desc, ring.entries, nullptr, nullptr, ring.counters, ring);
 }
 
@@ -1256,6 +1291,10 @@ void describe_query(const Graph *g, const simrank_query *q, const simrank_params
     *d = QueryDesc{};
     d->nodes = g->nodes;
     d->E = g->E;
+    d->E4 = g->E4;
+    d->hubs = g->hubs;
+    d->obits = g->obits;
+    d->n_hubs = g->n_hubs;
     d->active = g->active;
     d->ix = index_view(g);
     const PhiloxKey key = make_key(q->seed);
@@ -1272,6 +1311,7 @@ void describe_query(const Graph *g, const simrank_query *q, const simrank_params
     d->kind = mode == SIMRANK_MODE_STITCHED ? K_STITCHED
               : mode == SIMRANK_MODE_STRATIFIED ? K_STRAT : K_PLAIN;
     const int32_t tj = g->tuned_tile_j[d->kind];
+    d->tile_nodes = tile_nodes_for(*g, d->kind, p.R, p.L);
     d->tile_j = tj > 0 ? std::min<int32_t>(tj, tile_j_of(d->kind)) : tile_j_of(d->kind);
 }
 
@@ -1329,10 +1369,10 @@ int enqueue_ring_request(const QueryDesc &d, const StreamRing &ring, int32_t slo
     return SIMRANK_OK;
 }
 
-int launch_ring_meet(int kind, const StreamRing &ring, hipStream_t st) {
-    if (kind == K_PLAIN) launch_meet_ring<K_PLAIN, SRK_MEET_SLOTS>(ring, st);
-    else if (kind == K_STITCHED) launch_meet_ring<K_STITCHED, SRK_MEET_SLOTS_STITCHED>(ring, st);
-    else launch_meet_ring<K_STRAT, SRK_MEET_SLOTS_STRAT>(ring, st);
+int launch_ring_meet(Rows rows, int kind, const StreamRing &ring, hipStream_t st) {
+    if (kind == K_PLAIN) launch_meet_ring<K_PLAIN, SRK_MEET_SLOTS>(rows, ring, st);
+    else if (kind == K_STITCHED) launch_meet_ring<K_STITCHED, SRK_MEET_SLOTS_STITCHED>(rows, ring, st);
+    else launch_meet_ring<K_STRAT, SRK_MEET_SLOTS_STRAT>(rows, ring, st);
     SRK_HIP(hipGetLastError());
     return SIMRANK_OK;
 }
@@ -1537,6 +1577,7 @@ static int launch_single(const Graph *g, Workspace *ws, const QueryDesc &d, hipS
     qs.max_R = d.R;
     qs.max_n = g->n;
     qs.units_bound[d.kind] = units_bound;
+    qs.rows[d.kind] = rows_wish(*g, d);
     qs.units = ws->units;
     qs.counters = ws->counters;
     int rc = launch_query_set(qs, st, &d);

@@ -570,7 +570,10 @@ static void server_loop(simrank_server *S) {
             if (e != hipSuccess) rc_launch = fail(SIMRANK_EDEVICE, hipGetErrorString(e));
             for (int k = 0; k < N_KINDS && !rc_launch; ++k)
                 if (kinds[k]) {
-                    rc_launch = launch_ring_meet(k, S->ring, ws);
+                    QueryDesc most{};   // (no request's tiles are full where its largest's are not)
+                    most.kind = k;
+                    most.tile_nodes = tile_nodes_for(*S->g, k, S->prm.max_R, S->prm.max_L);
+                    rc_launch = launch_ring_meet(rows_of(rows_wish(*S->g, most)), k, S->ring, ws);
                     ++S->n_launches;
                 }
         }

@@ -1,0 +1,106 @@
+"""Rows packed in 4 bytes (o and degree, a hub's place in a table where the degree
+does not fit): queries that gather them must count as those that gather 8 bytes.
+
+Counts are integers and must equal the CPU oracle's bit for bit.
+"""
+import numpy as np
+import pytest
+
+import oracle as O
+from paper_2304_04015_amd import inputs
+from paper_2304_04015_amd import simrank as S
+
+pytestmark = pytest.mark.gpu
+
+ISEED = 9
+
+
+def _graph(slots, hubs, hub_deg, seed):
+    """`slots` edge slots: nodes 2 .. hubs + 1 have hub_deg in-edges (node 2 one
+    more, node 3 one less), every fifth of the others none, the rest what is
+    left; half of all edges come from hubs and walks meet them all the time."""
+    rng = np.random.Generator(np.random.PCG64(seed))
+    n = max(1000, slots // 8)
+    deg = np.zeros(n, np.int64)
+    deg[2:hubs + 2] = hub_deg
+    if hubs > 1:
+        deg[2] += 1
+        deg[3] -= 1
+    rest = np.arange(hubs + 2, n)
+    few = rest[rest % 5 != 0]
+    left = slots - int(deg.sum()) - (n - hubs - len(few))   # slots of nodes without in-edges
+    deg[few] = left // len(few)
+    deg[few[: left - int(deg[few].sum())]] += 1
+    assert int(np.maximum(deg, 1).sum()) == slots
+    m = int(deg.sum())
+    src = np.where(rng.random(m) < 0.5, rng.integers(2, max(hubs, 1) + 2, m), rng.integers(0, n, m))
+    off = np.concatenate([[0], np.cumsum(deg)])
+    return inputs.CSR(n, off.astype(np.int32), src.astype(np.int32))
+
+
+def _vs(g):
+    return np.unique(np.r_[0:8, np.linspace(8, g.n - 1, 120).astype(int)]).astype(np.int32)
+
+
+@pytest.fixture(scope="module")
+def others():
+    """A small graph and one of many hubs, with a query on each and its counts."""
+    gs = [inputs.erdos_renyi_in(300, 4.0, seed=1), _graph(2097153, 1400, 1024, 5)]
+    Gs = [S.load_csr(g) for g in gs]
+    qs = [S.make_query(5, seed=8, R=400, walk_cap=40, graph=1), S.make_query(4, seed=8, R=9000, graph=2)]
+    vs = [_vs(g) for g in gs]
+    yield Gs, qs, vs, [O.meet_counts_plain(gs[0], 5, 8, 0.6, 40, 400, vs[0]),
+                       O.meet_counts_plain(gs[1], 4, 8, 0.6, 64, 9000, vs[1])]
+    for G in Gs:
+        G.free()
+
+
+# degrees around the one that just does not fit (2^(32 - b) - 1 for slots of b
+# bits); E at the size up to which it is gathered itself, and one slot more; as
+# many hubs as the stitched, the plain and the small-tile kernels have rows for,
+# and one more (there R is such that small tiles are several)
+@pytest.mark.parametrize("slots, hubs, hub_deg", [
+    (4000, 0, 0), (524288, 3, 8191), (524289, 3, 4095), (700001, 255, 2000), (1048577, 5, 2047),
+    (2097153, 3, 1023), (2097153, 768, 1024), (2097153, 769, 1024), (2097153, 1280, 1024),
+    (2097153, 1281, 1024), (4194305, 6912, 512), (4194305, 6913, 512)])
+def test_packed_rows_equal_oracle(slots, hubs, hub_deg, others):
+    print(f"packed: {slots} slots, {hubs} nodes of in-degree {hub_deg}", flush=True)
+    g = _graph(slots, hubs, hub_deg, slots + hubs)
+    vs, G = _vs(g), S.load_csr(g)
+    R = 9000 if hubs > 700 else 400
+    S.simrank_build_index(G, seg_log2=1, kappa=0.05, c=0.6, seed=ISEED)
+    qs = [S.make_query(2, seed=3, R=R), S.make_query(g.n - 1, seed=4, R=R, walk_cap=40),
+          S.make_query(3, seed=3, R=R, mode=S.MODE_STITCHED)]
+    want = [O.meet_counts_plain(g, 2, 3, 0.6, 64, R, vs), O.meet_counts_plain(g, g.n - 1, 4, 0.6, 40, R, vs),
+            O.meet_counts_stitched(g, 3, 3, ISEED, 0.6, 64, 2, O.pool_sizes(g, 0.05), R, vs)]
+    for q, w in zip(qs, want):                    # lone
+        assert np.array_equal(S.simrank_single_source_ex(G, q)[1][vs], w)
+    # in one launch with a small graph's query, with a many-hub graph's, with both
+    Gs, oq, ovs, owant = others
+    for k in ([0], [1], [0, 1]):
+        cnts = S.simrank_batch([G] + Gs, qs + [oq[i] for i in k])[1]
+        for c, w in zip(cnts, want):
+            assert np.array_equal(c[vs], w), k
+        for i, c in zip(k, cnts[3:]):
+            assert np.array_equal(c[ovs[i]], owant[i]), k
+    srv = S.Server(G, max_slots=3, max_R=R, max_L=64)
+    ts = [srv.submit(q) for q in qs]
+    for t, w in zip(ts, want):
+        assert np.array_equal(srv.wait(t)[1][vs], w)
+    srv.destroy()
+    G.free()
+
+
+def test_all_hubs_and_no_edges():
+    """Every node a hub, and a graph of no edges."""
+    n = 3000
+    rng = np.random.Generator(np.random.PCG64(1))
+    off = np.arange(n + 1, dtype=np.int64) * 1400      # 4.2e6 slots: 23 bits, 3000 hubs
+    g = inputs.CSR(n, off.astype(np.int32), rng.integers(0, n, n * 1400).astype(np.int32))
+    vs, G = _vs(g), S.load_csr(g)
+    cnt = S.simrank_single_source_ex(G, S.make_query(7, seed=3, R=300, walk_cap=40))[1]
+    assert np.array_equal(cnt[vs], O.meet_counts_plain(g, 7, 3, 0.6, 40, 300, vs))
+    G.free()
+    e = S.simrank_load_graph(5, np.zeros(6, np.int32), np.zeros(0, np.int32))
+    assert S.simrank_single_source_ex(e, S.make_query(1, R=10))[1].tolist() == [0, 10, 0, 0, 0]
+    e.free()
