@@ -239,6 +239,13 @@ __device__ __forceinline__ uint32_t slot_class(uint32_t r, const uint32_t *ccum,
     return (uint32_t)lo;
 }
 
+// Runs of 2^class_run_log2(N) slots, CLASS_RUNS at most: the class of a run's
+// first slot and a step or two up the class starts give a slot's class.
+constexpr uint32_t CLASS_RUNS = 4096;
+__device__ __forceinline__ uint32_t class_run_log2(uint32_t N) {
+    return N <= CLASS_RUNS ? 0u : 20u - (uint32_t)__builtin_clz(N - 1u);
+}
+
 // Meet weight of classes (l1, l2) in units of 2^-40 (Lemma 5's ratio
 // Z_l1 Z_l2 / (Zhat_l1 Zhat_l2), truncated).
 __device__ __forceinline__ unsigned long long strat_weight(const double *a, uint32_t l1, uint32_t l2) {

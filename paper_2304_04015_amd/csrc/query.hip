@@ -622,12 +622,13 @@ void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
     __shared__ uint32_t s_vid[MEET_VB];
     __shared__ uint2 s_vrow[MEET_VB];
     __shared__ uint32_t s_unit, s_item, s_slot, s_seq, s_last, s_run, s_srcvl;
-    // stratified: classes of the tile's source walks, class starts, the
-    // shuffle keys and draw constants of the unit's nodes, weighted sums
+    // stratified: classes of the tile's source walks, class starts and the class
+    // of each run of slots' first, the shuffle keys of the unit's nodes, weighted
+    // sums
     __shared__ uint8_t s_cls[STRAT ? TJ : 1];
     __shared__ uint32_t s_ccum[STRAT ? MAX_CAP + 2 : 1];
     __shared__ uint4 s_fk[STRAT ? MEET_VB : 1];
-    __shared__ uint32_t s_va[STRAT ? MEET_VB : 1], s_vb[STRAT ? MEET_VB : 1], s_vcc[STRAT ? MEET_VB : 1];
+    __shared__ uint8_t s_run_cls[STRAT ? CLASS_RUNS : 1];
     __shared__ unsigned long long s_w[STRAT ? MEET_VB : 1];
     __shared__ uint2 s_q[STRAT ? meet_block_of(KIND) : 1];   // 64 prepared pairs per wave
     // stitched: per-wave ring of pairs waiting for their tails, (vl << 16 | k, o)
@@ -706,6 +707,7 @@ void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
         const int32_t src = (int32_t)uni((uint32_t)d.s);
         const uint32_t NN = uni((uint32_t)d.R), sa = uni((uint32_t)d.sa), sb = uni((uint32_t)d.sb);
         const int32_t phi = (int32_t)uni((uint32_t)d.L);
+        const uint32_t run_log2 = STRAT ? class_run_log2(NN) : 0u;
         if (tag != cur_q || tile != cur_tile) {
             const uint32_t k0 = uni(tiles_of(d)[tile]), k1 = uni(tiles_of(d)[tile + 1]);
             const uint32_t nb = d.joff[k0], ne = d.joff[k1];
@@ -717,9 +719,12 @@ void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
                 if (STRAT) s_cls[i] = d.scls[jw];
             }
             for (uint32_t i = threadIdx.x; i < ne - nb; i += blockDim.x) s_nodes[i] = d.swc[nb + i];
-            if (STRAT)
+            if (STRAT) {
                 for (uint32_t i = threadIdx.x; i < (uint32_t)phi + 2; i += blockDim.x)
                     s_ccum[i] = d.tab->ccum[i];
+                for (uint32_t i = threadIdx.x; i <= (NN - 1u) >> run_log2; i += blockDim.x)
+                    s_run_cls[i] = (uint8_t)slot_class(i << run_log2, d.tab->ccum, phi);
+            }
             if (packed)
                 for (uint32_t i = threadIdx.x; i < (uint32_t)d.n_hubs; i += blockDim.x) s_hub[i] = d.hubs[i];
             cur_q = tag;
@@ -741,13 +746,7 @@ void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
                 s_vid[i] = id;
                 s_vrow[i] = d.nodes[id];
                 if ((int32_t)id == src) s_srcvl = i;
-                if (STRAT) {
-                    const WalkDraws w = walk_draws_begin(id, 0u, key, DOM_STRAT);
-                    s_va[i] = w.a;
-                    s_vb[i] = w.b;
-                    s_vcc[i] = w.cc;
-                    s_fk[i] = philox4x32_10(id, 0u, 0u, DOM_SHUFFLE, key);
-                }
+                if (STRAT) s_fk[i] = philox4x32_10(id, 0u, 0u, DOM_SHUFFLE, key);
             }
         }
         __syncthreads();
@@ -755,21 +754,29 @@ void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
         // Pairs of the unit: item i = vl * K + k for node vl < nv and walk k < K.
         // (K and nv are the same in all lanes; said so, the refill's bookkeeping
         // stays in scalar registers)
-        const uint32_t Ku = uni(K), total = nv * Ku;
+        // (stratified: an item is 64 walks of a node)
+        const uint32_t Ku = uni(K), node_chunks = (Ku + 63u) >> 6;
+        const uint32_t total = nv * (STRAT ? node_chunks : Ku);
         // wave-uniform chunk of items [ci, ce) and the (node, walk) of item ci
         uint32_t ci = 0, ce = 0, cvl = 0, ck = 0;
         uint32_t vo = 0, vd = 0, va = 0, vb = 0, vcc = 0;   // node cvl's row and draw constants
-        const uint32_t srcvl = uni(s_srcvl), chunk_items = item_chunk(total, uni((uint32_t)d.items));
+        const uint32_t srcvl = uni(s_srcvl), chunk_items =
+            STRAT ? item_chunk(64u * total, uni((uint32_t)d.items)) >> 6 : item_chunk(total, uni((uint32_t)d.items));
+        uint4 vfk = make_uint4(0u, 0u, 0u, 0u);             // stratified: and its shuffle key
         uint32_t at_vl = NIL;   // the node those are of
         auto enter_node = [&]() {
             at_vl = cvl;
             const uint2 row = s_vrow[cvl];
             vo = uni(row.x);
             vd = uni(row.y);
-            const WalkDraws w = walk_draws_begin(uni(s_vid[cvl]), 0u, key);
+            const WalkDraws w = walk_draws_begin(uni(s_vid[cvl]), 0u, key, STRAT ? DOM_STRAT : DOM_WALK);
             va = w.a;
             vb = w.b;
             vcc = w.cc;
+            if (STRAT) {
+                const uint4 k = s_fk[cvl];
+                vfk = make_uint4(uni(k.x), uni(k.y), uni(k.z), uni(k.w));
+            }
         };
         bool drained = false;
         uint32_t qh = 0, qn = 0;   // stratified: the wave's queue of prepared pairs [qh, qn)
@@ -824,60 +831,69 @@ void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
             // has nothing to walk (the source's own pair, or a stratified walk
             // of length 0) takes the next item
             if constexpr (STRAT) {
-                // A pair's shuffle and class search cost about a hundred
-                // instructions: they are done for 64 items at once by all
-                // lanes of the wave, and the pairs with steps to walk wait in
-                // the wave's queue in LDS until slots free up.
+                // A pair's shuffle and class cost some eighty instructions: they
+                // are done for 64 walks of one node at once by all lanes of the
+                // wave, and the pairs with steps to walk wait in the wave's
+                // queue in LDS until slots free up.  All that need not be done
+                // by the third of the lanes that fill a slot is done there.
 #pragma unroll
                 for (int qq = 0; qq < NS; ++qq) {
                     uint64_t need = __ballot(!sl[qq].busy);
                     while (need != 0ull) {
                         if (qh == qn) {
-                            if (drained) break;
-                            uint32_t x = 0;
-                            if (lane == 0) x = atomicAdd(&s_item, ITEM_CHUNK);
-                            x = __builtin_amdgcn_readfirstlane(x);
-                            if (x >= total) {
-                                drained = true;
-                                break;
+                            if (ci == ce) {
+                                if (drained) break;
+                                uint32_t x = 0;
+                                if (lane == 0) x = atomicAdd(&s_item, chunk_items);
+                                x = uni(x);
+                                if (x >= total) {
+                                    drained = true;
+                                    break;
+                                }
+                                ci = x;
+                                ce = min(x + chunk_items, total);
+                                cvl = x / node_chunks;
+                                ck = x - cvl * node_chunks;
+                            } else if (ck == node_chunks) {
+                                ck = 0;
+                                ++cvl;
                             }
-                            const uint32_t item = x + (uint32_t)lane;
-                            bool ok = item < total;
-                            uint32_t vl = 0, k = 0, r = 0, cv = 0;
+                            if (cvl != at_vl) enter_node();
+                            const uint32_t k = 64u * ck + (uint32_t)lane;
+                            ++ci;
+                            ++ck;
+                            bool ok = k < Ku && cvl != srcvl;   // (the source's own pairs are not walked)
+                            uint32_t r = 0, cv = 0, jl = 0;
                             if (ok) {
-                                vl = item / K;
-                                k = item - vl * K;
-                                ok = (int32_t)s_vid[vl] != src;
-                            }
-                            if (ok) {
-                                r = shuffle_slot(s_jl[k] & 0xffffffu, NN, sa, sb, s_fk[vl]);
-                                cv = slot_class(r, s_ccum, phi);
+                                jl = s_jl[k];
+                                r = shuffle_slot(jl & 0xffffffu, NN, sa, sb, vfk);
+                                cv = s_run_cls[r >> run_log2];
+                                while (s_ccum[cv + 1u] <= r) ++cv;   // (ends: ccum[phi + 1] = N > r)
                                 ok = cv > 0u;
                             }
                             const uint64_t m = __ballot(ok);
-                            if (ok) s_q[wave * 64 + lane_rank(m)] = make_uint2((vl << 24) | (k << 8) | cv, r);
+                            if (ok)
+                                s_q[wave * 64 + lane_rank(m)] =
+                                    make_uint2((uint32_t)s_off[k] | (min(jl >> 24, cv) << 16) |
+                                                   ((uint32_t)s_cls[k] << 24),
+                                               (r << 8) | cv);
                             qn = (uint32_t)__popcll(m);
                             qh = 0;
                             continue;
                         }
-                        const uint32_t want = (uint32_t)__popcll(need);
-                        const uint32_t avail = qn - qh;
-                        const uint32_t take = avail < want ? avail : want;
+                        const uint32_t take = min(qn - qh, (uint32_t)__popcll(need));
                         const uint32_t rank = lane_rank(need);
-                        const bool mine = ((need >> lane) & 1ull) && rank < take;
+                        const bool mine = !sl[qq].busy && rank < take;
                         if (mine) {
                             const uint2 e = s_q[wave * 64 + qh + rank];
-                            const uint32_t vl = e.x >> 24, k = (e.x >> 8) & 0xffffu, cv = e.x & 0xffu;
-                            const uint32_t base = s_off[k];
-                            const uint32_t len = min(s_jl[k] >> 24, cv);
-                            const uint2 row = s_vrow[vl];
-                            sl[qq].aux = ((uint32_t)s_cls[k] << 8) | cv;
-                            sl[qq].rng = WalkDraws{e.y, s_va[vl], s_vb[vl], s_vcc[vl], 0ull};
-                            sl[qq].pos = base | (len << 16) | (vl << 24);
-                            sl[qq].t = 0;
-                            sl[qq].o = row.x;
-                            sl[qq].d = row.y;
-                            sl[qq].busy = true;
+                            Slot &w = sl[qq];
+                            w.rng = WalkDraws{e.y >> 8, va, vb, vcc, 0ull};
+                            w.pos = e.x;
+                            w.aux = (cvl << 8) | (e.y & 0xffu);
+                            w.t = 0;
+                            w.o = vo;
+                            w.d = vd;
+                            w.busy = true;
                             ++st_pairs;
                         }
                         need &= ~__ballot(mine);
@@ -996,7 +1012,7 @@ void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
                 const uint32_t base = w.pos & 0xffffu, len = (w.pos >> 16) & 0xffu;
                 if (w.o == s_nodes[base + w.t - 1]) {
                     if (STRAT)
-                        atomicAdd(&s_w[w.pos >> 24], strat_weight(d.tab->a, w.aux >> 8, w.aux & 0xffu));
+                        atomicAdd(&s_w[w.aux >> 8], strat_weight(d.tab->a, w.pos >> 24, w.aux & 0xffu));
                     else
                         atomicAdd(&s_cnt[w.pos >> 24], 1u);
                     ++st_meets;
