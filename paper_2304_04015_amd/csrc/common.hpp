@@ -89,11 +89,11 @@ __host__ __device__ constexpr int meet_block_of(int kind) {
 }
 
 // Rows of a packed graph's hubs that a kind's meet kernel has LDS for, beside
-// its tile and a served request's preparation: plain and stitched queries only.
-// A graph with more hubs has its tiles cut to HUB_TILE_NODES positions, to make
+// its tile and a served request's preparation.  A graph with more hubs has the
+// tiles of plain and stitched queries cut to HUB_TILE_NODES positions, to make
 // room for HUB_ROWS.
 __host__ __device__ constexpr int hub_rows_of(int kind) {
-    return kind == K_PLAIN ? 1280 : kind == K_STITCHED ? 768 : 0;
+    return kind == K_PLAIN ? 1280 : kind == K_STITCHED ? 768 : 1536;
 }
 constexpr int HUB_TILE_NODES = 12288, HUB_ROWS = 6912;
 
@@ -222,11 +222,11 @@ enum Rows : int { ROWS_E, ROWS_PACKED, ROWS_HUBS, ROWS_MIXED };
 // What a query can use.  E is better where all of it is within an XCD's L2
 // (packed rows only add their decoding; n = 20,000, R = 38,005: 2,677 us with E,
 // 2,717 packed), packed rows are beyond it (n = 2^18, R = 9,502: 11,681 and
-// 9,455).  Stratified queries are bound by their instructions: E (n = 2^18: 21.6
-// ms with E, 21.9 packed), as are the groups (32 members: 50.8 and 52.3 ms).
+// 9,455; stratified, N = 16,508: 20.2 and 18.1 ms).  Groups are bound by their
+// instructions and read E (32 members: 50.8 ms, 52.3 packed).
 constexpr int WANTS_E = 1, WANTS_PACKED = 2, WANTS_HUBS = 4, HAS_NONE = 8;
 inline int rows_wish(const Graph &g, const QueryDesc &d) {
-    if (g.obits == 0 || d.kind == K_STRAT) return HAS_NONE;
+    if (g.obits == 0) return HAS_NONE;
     if (g.n_hubs > hub_rows_of(d.kind)) return d.tile_nodes == HUB_TILE_NODES ? WANTS_HUBS : HAS_NONE;
     return 8 * g.m_slots <= (int64_t)4 << 20 ? WANTS_E : WANTS_PACKED;
 }

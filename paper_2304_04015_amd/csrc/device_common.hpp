@@ -26,8 +26,9 @@ __device__ __forceinline__ unsigned long long *ctr_set(unsigned long long *count
 // Adds the lanes' work (moves, draws, meets, tail steps, pairs) to the
 // counters at `to`: the waves' sums meet in LDS, so a block makes one atomic
 // per counter.  Block-wide (blocks of up to 1024 threads).
-__device__ __forceinline__ void add_work(unsigned long long *to, uint32_t moves, uint32_t draws,
-                                         uint32_t meets, uint32_t tail, uint32_t pairs) {
+__device__ __forceinline__ void add_work(unsigned long long *to, unsigned long long moves,
+                                         unsigned long long draws, unsigned long long meets,
+                                         unsigned long long tail, unsigned long long pairs) {
     __shared__ unsigned long long part[16][5];
     unsigned long long w[5] = {moves, draws, meets, tail, pairs};
 #pragma unroll
@@ -157,20 +158,30 @@ __device__ __forceinline__ uint32_t lane_rank(uint64_t mask) {
                                      __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-// One pair in flight on a lane.  The six unused words keep the layout the
-// plain kind's hot loop was measured with: the compiler's register assignment
-// follows the struct, and without them the plain kernel takes 3% longer at
-// n = 2^24 (74 instead of 68 VGPRs, extra register moves).
+// One pair in flight on a lane.
 struct Slot {
-    uint32_t pos;    // packed: LDS offset of walk (s, j) (16 bits) | its length << 16 | node index << 24
-    uint32_t t;      // steps taken
+    uint32_t at;     // LDS index of the position of walk (s, j) that the next step is tested
+                     // against (16 bits); stratified: | class of walk (s, j) << 16
+    uint32_t end;    // LDS index of its last one (16 bits) | node index << 16; stitched:
+                     // | HEAD_ONLY if the walk goes on beyond it
     uint32_t o, d;   // current node: slot offset in E and in-degree
     WalkDraws rng;
-    bool busy;
-    uint32_t unused[6];
-    uint32_t aux;    // stratified: class of walk (s, j) << 8 | class of walk (v, j);
-                     // stitched: the tile entry of walk (s, j)
+    uint32_t aux;    // stratified: class of walk (v, j); stitched: the tile entry of walk (s, j)
 };
+constexpr uint32_t HEAD_ONLY = 1u << 31;
+
+// The lanes of a mask that is the same in all lanes.
+__device__ __forceinline__ bool in_mask(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+
+// Work of a wave: the same in all lanes, but for the tail steps.
+struct Work {
+    unsigned long long moves = 0, draws = 0, meets = 0, pairs = 0;
+    uint32_t tail = 0;
+};
+__device__ __forceinline__ void add_work(unsigned long long *to, const Work &w) {
+    const bool one = (threadIdx.x & 63) == 0;
+    add_work(to, one ? w.moves : 0ull, one ? w.draws : 0ull, one ? w.meets : 0ull, w.tail, one ? w.pairs : 0ull);
+}
 
 // Items (pairs of a unit) a wave takes from the block's cursor at once: 64, up
 // to `most` where the unit has enough of them for its 16 waves.

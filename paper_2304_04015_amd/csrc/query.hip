@@ -571,11 +571,9 @@ __device__ void ring_claim(const StreamRing &ring, int lane, uint32_t *o_slot, u
 // then clears); the block whose report completes the entry writes the
 // request's estimate and then its flag in host memory.  Block-wide.
 __device__ void ring_report(const StreamRing &ring, const QueryDesc &d, uint32_t slot,
-                            uint32_t tag, uint32_t units, uint32_t &st_moves,
-                            uint32_t &st_draws, uint32_t &st_meets, uint32_t &st_tail,
-                            uint32_t &st_pairs, uint32_t *s_last) {
-    add_work(ring.counters + (size_t)slot * 8, st_moves, st_draws, st_meets, st_tail, st_pairs);
-    st_moves = st_draws = st_meets = st_tail = st_pairs = 0;
+                            uint32_t tag, uint32_t units, Work &work, uint32_t *s_last) {
+    add_work(ring.counters + (size_t)slot * 8, work);
+    work = Work{};
     __threadfence();
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -630,7 +628,10 @@ void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
     __shared__ uint4 s_fk[STRAT ? MEET_VB : 1];
     __shared__ uint8_t s_run_cls[STRAT ? CLASS_RUNS : 1];
     __shared__ unsigned long long s_w[STRAT ? MEET_VB : 1];
-    __shared__ uint2 s_q[STRAT ? meet_block_of(KIND) : 1];   // 64 prepared pairs per wave
+    // 64 prepared pairs per wave: (LDS offset | class of walk (s, j) << 16,
+    // slot << 8 | class), LDS index of the last position
+    __shared__ uint2 s_q[STRAT ? meet_block_of(KIND) : 1];
+    __shared__ uint16_t s_qend[STRAT ? meet_block_of(KIND) : 1];
     // stitched: per-wave ring of pairs waiting for their tails, (vl << 16 | k, o)
     __shared__ uint2 s_tq[STITCHED ? (meet_block_of(KIND) / 64) * TAIL_Q : 1];
 
@@ -643,7 +644,7 @@ void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
     uint32_t next_unit = blockIdx.x;       // thread 0: taken while the unit before ran
     uint32_t cur_q = 0xffffffffu, cur_tile = 0xffffffffu;
     uint32_t K = 0;
-    uint32_t st_moves = 0, st_draws = 0, st_meets = 0, st_tail = 0, st_pairs = 0;
+    Work work;
 
     for (;;) {
         uint32_t unit = 0, tag_s = 0;
@@ -660,8 +661,7 @@ void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
             // the block reports the units it finished of a request, and their
             // work, once: when it moves on to another request or runs out
             if (acc_units && (nslot >= (uint32_t)RING_MAX || nseq != acc_tag)) {
-                ring_report(ring, qd[acc_slot], acc_slot, acc_tag, acc_units,
-                            st_moves, st_draws, st_meets, st_tail, st_pairs, &s_last);
+                ring_report(ring, qd[acc_slot], acc_slot, acc_tag, acc_units, work, &s_last);
                 acc_units = 0;
             }
             if (nslot >= (uint32_t)RING_MAX) break;
@@ -770,9 +770,9 @@ void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
             vo = uni(row.x);
             vd = uni(row.y);
             const WalkDraws w = walk_draws_begin(uni(s_vid[cvl]), 0u, key, STRAT ? DOM_STRAT : DOM_WALK);
-            va = w.a;
-            vb = w.b;
-            vcc = w.cc;
+            va = uni(w.a);
+            vb = uni(w.b);
+            vcc = uni(w.cc);
             if (STRAT) {
                 const uint4 k = s_fk[cvl];
                 vfk = make_uint4(uni(k.x), uni(k.y), uni(k.z), uni(k.w));
@@ -781,13 +781,21 @@ void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
         bool drained = false;
         uint32_t qh = 0, qn = 0;   // stratified: the wave's queue of prepared pairs [qh, qn)
 
+        // The wave's slots, and which lanes' have a pair.  (Lane masks, and fills
+        // that select: with a flag per lane and assignments under it the
+        // compiler copied every slot's and the node's registers at each fill)
         Slot sl[NS];
+        uint64_t busy[NS];
 #pragma unroll
-        for (int qq = 0; qq < NS; ++qq) sl[qq].busy = false;
+        for (int qq = 0; qq < NS; ++qq) {
+            sl[qq] = Slot{};
+            busy[qq] = 0ull;
+        }
 
         // Stitched: follow the tails of the first `c` queued pairs (one per
         // lane) through the index; meets go to the unit's LDS counters.
         auto drain_tails = [&](uint32_t c) {
+            bool met = false;
             if (lane < (int)c) {
                 const uint2 r = s_tq[wave * TAIL_Q + ((tq_head + (uint32_t)lane) & (TAIL_Q - 1))];
                 const uint32_t vl = r.x >> 16, k = r.x & 0xffffu;
@@ -808,11 +816,10 @@ void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
                     const uint32_t *srow = d.ix.seg + (size_t)sg * seg_len;
                     for (uint32_t u = 0; u < sln; ++u) {
                         ++t;
-                        ++st_tail;
+                        ++work.tail;
                         if (srow[u] == s_nodes[base + t - 1]) {
                             atomicAdd(&s_cnt[vl], 1u);
-                            ++st_meets;
-                            done = true;
+                            done = met = true;
                             break;
                         }
                         if (t == len) {
@@ -824,6 +831,23 @@ void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
                 }
             }
             tq_head += c;
+            work.meets += (uint32_t)__popcll(__ballot(met));
+        };
+
+        // The masked lanes' slot starts a pair of node cvl.
+        auto start = [&](Slot &w, uint64_t mine, uint32_t at, uint32_t end, uint32_t j, uint32_t aux) {
+            const bool me = in_mask(mine);
+            w.at = me ? at : w.at;
+            w.end = me ? end : w.end;
+            w.o = me ? vo : w.o;
+            w.d = me ? vd : w.d;
+            w.rng.j = me ? j : w.rng.j;
+            w.rng.a = me ? va : w.rng.a;
+            w.rng.b = me ? vb : w.rng.b;
+            w.rng.cc = me ? vcc : w.rng.cc;
+            w.rng.mt = me ? 0ull : w.rng.mt;
+            if (STRAT || STITCHED) w.aux = me ? aux : w.aux;
+            work.pairs += (uint32_t)__popcll(mine);
         };
 
         for (;;) {
@@ -838,7 +862,7 @@ void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
                 // by the third of the lanes that fill a slot is done there.
 #pragma unroll
                 for (int qq = 0; qq < NS; ++qq) {
-                    uint64_t need = __ballot(!sl[qq].busy);
+                    uint64_t need = ~busy[qq];
                     while (need != 0ull) {
                         if (qh == qn) {
                             if (ci == ce) {
@@ -852,7 +876,7 @@ void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
                                 }
                                 ci = x;
                                 ce = min(x + chunk_items, total);
-                                cvl = x / node_chunks;
+                                cvl = uni(x / node_chunks);
                                 ck = x - cvl * node_chunks;
                             } else if (ck == node_chunks) {
                                 ck = 0;
@@ -872,38 +896,30 @@ void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
                                 ok = cv > 0u;
                             }
                             const uint64_t m = __ballot(ok);
-                            if (ok)
-                                s_q[wave * 64 + lane_rank(m)] =
-                                    make_uint2((uint32_t)s_off[k] | (min(jl >> 24, cv) << 16) |
-                                                   ((uint32_t)s_cls[k] << 24),
-                                               (r << 8) | cv);
+                            if (ok) {
+                                const uint32_t at = wave * 64 + lane_rank(m), off = s_off[k];
+                                s_q[at] = make_uint2(off | ((uint32_t)s_cls[k] << 16), (r << 8) | cv);
+                                s_qend[at] = (uint16_t)(off + min(jl >> 24, cv) - 1u);
+                            }
                             qn = (uint32_t)__popcll(m);
                             qh = 0;
                             continue;
                         }
                         const uint32_t take = min(qn - qh, (uint32_t)__popcll(need));
                         const uint32_t rank = lane_rank(need);
-                        const bool mine = !sl[qq].busy && rank < take;
-                        if (mine) {
-                            const uint2 e = s_q[wave * 64 + qh + rank];
-                            Slot &w = sl[qq];
-                            w.rng = WalkDraws{e.y >> 8, va, vb, vcc, 0ull};
-                            w.pos = e.x;
-                            w.aux = (cvl << 8) | (e.y & 0xffu);
-                            w.t = 0;
-                            w.o = vo;
-                            w.d = vd;
-                            w.busy = true;
-                            ++st_pairs;
-                        }
-                        need &= ~__ballot(mine);
+                        const uint64_t mine = need & __ballot(rank < take);
+                        const uint32_t from = wave * 64 + ((qh + rank) & 63u);
+                        const uint2 e = s_q[from];
+                        start(sl[qq], mine, e.x, s_qend[from] | (cvl << 16), e.y >> 8, e.y & 0xffu);
+                        busy[qq] |= mine;
+                        need &= ~mine;
                         qh += take;
                     }
                 }
             } else {
 #pragma unroll
                 for (int qq = 0; qq < NS; ++qq) {
-                    uint64_t need = __ballot(!sl[qq].busy);
+                    uint64_t need = ~busy[qq];
                     while (need != 0ull) {
                         if (ci == ce) {
                             if (drained) break;
@@ -916,7 +932,7 @@ void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
                             }
                             ci = x;
                             ce = min(x + chunk_items, total);
-                            cvl = x / Ku;
+                            cvl = uni(x / Ku);
                             ck = x - cvl * Ku;
                             if (cvl != at_vl) enter_node();
                         }
@@ -928,20 +944,17 @@ void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
                         if (cvl != srcvl) {   // (the source's own pairs are not walked)
                             take = min(take, (uint32_t)__popcll(need));
                             const uint32_t rank = lane_rank(need);
-                            const bool mine = !sl[qq].busy && rank < take;
-                            if (mine) {
-                                const uint32_t jl = s_jl[ck + rank];
-                                Slot &w = sl[qq];
-                                w.rng = WalkDraws{jl & 0xffffffu, va, vb, vcc, 0ull};
-                                w.pos = (uint32_t)s_off[ck + rank] | ((jl >> 24) << 16) | (cvl << 24);
-                                w.t = 0;
-                                w.o = vo;
-                                w.d = vd;
-                                w.busy = true;
-                                if (STITCHED) w.aux = ck + rank;
-                                ++st_pairs;
+                            const uint64_t mine = need & __ballot(rank < take);
+                            const uint32_t k = min(ck + rank, Ku - 1u);
+                            const uint32_t jl = s_jl[k], off = s_off[k];
+                            uint32_t end = off + (jl >> 24) + ((cvl << 16) - 1u);
+                            if (STITCHED) {
+                                const uint32_t seg_len = (uint32_t)d.ix.seg_len;
+                                if (jl >> 24 > seg_len) end = (off + seg_len + ((cvl << 16) - 1u)) | HEAD_ONLY;
                             }
-                            need &= ~__ballot(mine);
+                            start(sl[qq], mine, off, end, jl & 0xffffffu, k);
+                            busy[qq] |= mine;
+                            need &= ~mine;
                         }
                         ci += take;
                         ck += take;
@@ -953,12 +966,12 @@ void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
                     }
                 }
             }
-            bool any = false;
+            uint64_t any = 0ull;
 #pragma unroll
-            for (int qq = 0; qq < NS; ++qq) any |= sl[qq].busy;
+            for (int qq = 0; qq < NS; ++qq) any |= busy[qq];
             // A refill round can hand out only pairs with nothing to walk: a
             // wave leaves only once the block's cursor is drained.
-            if (__ballot(any) == 0ull) {
+            if (any == 0ull) {
                 if (drained && qh == qn) {
                     if constexpr (STITCHED) {
                         while (tq_tail != tq_head) drain_tails(min(64u, tq_tail - tq_head));
@@ -969,77 +982,64 @@ void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
             }
 
             // ---- head steps: draws, then all gathers, then the compares
-            bool go[NS];
-            uint32_t at[NS];
+            uint64_t go[NS];
+            uint32_t from[NS];
 #pragma unroll
             for (int qq = 0; qq < NS; ++qq) {
-                go[qq] = false;
-                at[qq] = 0;
-                if (sl[qq].busy) {
-                    ++sl[qq].t;
-                    const uint2 x = walk_draw_next(sl[qq].rng, key);
-                    ++st_draws;
-                    if (!STRAT && x.x >= T) {
-                        sl[qq].busy = false;
-                    } else {
-                        go[qq] = true;
-                        at[qq] = sl[qq].o + pick32(x.y, sl[qq].d);
-                    }
-                }
+                const uint2 x = walk_draw_next(sl[qq].rng, key);
+                work.draws += (uint32_t)__popcll(busy[qq]);
+                go[qq] = STRAT ? busy[qq] : busy[qq] & __ballot(x.x < T);
+                from[qq] = sl[qq].o + pick32(x.y, sl[qq].d);
             }
-            // all gathers of the lane's slots, then the compares
             uint2 e[NS];
             if (packed) {
 #pragma unroll
                 for (int qq = 0; qq < NS; ++qq)
-                    if (go[qq]) e[qq].x = rows.E4[at[qq]];
+                    if (in_mask(go[qq])) e[qq].x = rows.E4[from[qq]];
             } else {
 #pragma unroll
                 for (int qq = 0; qq < NS; ++qq)
-                    if (go[qq]) e[qq] = load_edge(rows.E, at[qq]);
+                    if (in_mask(go[qq])) e[qq] = load_edge(rows.E, from[qq]);
             }
-            bool tails[NS];
-#pragma unroll
-            for (int qq = 0; qq < NS; ++qq) tails[qq] = false;
+            uint64_t tails[NS];
 #pragma unroll
             for (int qq = 0; qq < NS; ++qq) {
-                if (!go[qq]) continue;
-                ++st_moves;
+                work.moves += (uint32_t)__popcll(go[qq]);
                 Slot &w = sl[qq];
-                const uint2 to = packed ? unpack_row(e[qq].x, rows.obits, s_hub) : e[qq];
-                w.o = to.x;
-                w.d = to.y;
-                const uint32_t base = w.pos & 0xffffu, len = (w.pos >> 16) & 0xffu;
-                if (w.o == s_nodes[base + w.t - 1]) {
-                    if (STRAT)
-                        atomicAdd(&s_w[w.aux >> 8], strat_weight(d.tab->a, w.pos >> 24, w.aux & 0xffu));
-                    else
-                        atomicAdd(&s_cnt[w.pos >> 24], 1u);
-                    ++st_meets;
-                    w.busy = false;
-                } else if (w.t == len || w.d == 0u) {
-                    w.busy = false;
-                } else if (STITCHED && w.t == (uint32_t)d.ix.seg_len) {
-                    w.busy = false;   // the head made all its moves: its tail is queued
-                    tails[qq] = true;
+                bool met = false, more = false, tail = false;
+                if (in_mask(go[qq])) {
+                    const uint2 to = packed ? unpack_row(e[qq].x, rows.obits, s_hub) : e[qq];
+                    w.o = to.x;
+                    w.d = to.y;
+                    met = w.o == s_nodes[w.at & 0xffffu];
+                    const bool last = (uint16_t)w.at == (uint16_t)w.end;
+                    more = !met && !last && w.d != 0u;
+                    // stitched: a head that made all its moves queues its tail
+                    if (STITCHED) tail = !met && last && w.d != 0u && w.end >= HEAD_ONLY;
+                    ++w.at;
+                }
+                busy[qq] = __ballot(more);
+                tails[qq] = STITCHED ? __ballot(tail) : 0ull;
+                if (const uint64_t m = __ballot(met)) {
+                    work.meets += (uint32_t)__popcll(m);
+                    const uint32_t vl = (w.end >> 16) & 0xffu;
+                    if (met) {
+                        if (STRAT) atomicAdd(&s_w[vl], strat_weight(d.tab->a, w.at >> 16, w.aux));
+                        else atomicAdd(&s_cnt[vl], 1u);
+                    }
                 }
             }
             if constexpr (STITCHED) {
-                // queue the pairs whose heads ended open (tails[qq]), then
-                // follow queued tails while a wave's worth is waiting
-                bool any_tail = false;
+                // queue the pairs whose heads ended open, then follow queued
+                // tails while a wave's worth is waiting
 #pragma unroll
-                for (int qq = 0; qq < NS; ++qq) any_tail |= tails[qq];
-                if (__ballot(any_tail) != 0ull) {
-#pragma unroll
-                    for (int qq = 0; qq < NS; ++qq) {
-                        const uint64_t m = __ballot(tails[qq]);
-                        if (tails[qq])
-                            s_tq[wave * TAIL_Q + ((tq_tail + lane_rank(m)) & (TAIL_Q - 1))] =
-                                make_uint2(((sl[qq].pos >> 24) << 16) | sl[qq].aux, sl[qq].o);
-                        tq_tail += (uint32_t)__popcll(m);
-                        if (tq_tail - tq_head >= 64u) drain_tails(64u);
-                    }
+                for (int qq = 0; qq < NS; ++qq) {
+                    if (tails[qq] == 0ull) continue;
+                    if (in_mask(tails[qq]))
+                        s_tq[wave * TAIL_Q + ((tq_tail + lane_rank(tails[qq])) & (TAIL_Q - 1))] =
+                            make_uint2((sl[qq].end & 0xff0000u) | sl[qq].aux, sl[qq].o);
+                    tq_tail += (uint32_t)__popcll(tails[qq]);
+                    if (tq_tail - tq_head >= 64u) drain_tails(64u);
                 }
             }
         }
@@ -1061,7 +1061,7 @@ void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
     }
     if constexpr (STREAM) return;
 
-    add_work(ctr_set(counters), st_moves, st_draws, st_meets, st_tail, st_pairs);
+    add_work(ctr_set(counters), work);
 }
 
 // ------------------------------------------------------ walk materialisation
@@ -1192,22 +1192,20 @@ void launch_meet(const QuerySet &qs, hipStream_t st) {
     const uint32_t *ustart = qs.units + (size_t)KIND * (qs.nq + 1);
     uint32_t *cursor = qs.units + (size_t)N_KINDS * (qs.nq + 1) + KIND;
     const Rows rows = rows_of(qs.rows[KIND]);
-    auto kernel = k_meet<KIND, NS, false, ROWS_E>;
-    if constexpr (KIND != K_STRAT) {
-        if (rows == ROWS_PACKED) kernel = k_meet<KIND, NS, false, ROWS_PACKED>;
+    auto kernel = rows == ROWS_E        ? k_meet<KIND, NS, false, ROWS_E>
+                  : rows == ROWS_PACKED ? k_meet<KIND, NS, false, ROWS_PACKED>
+                                        : k_meet<KIND, NS, false, ROWS_MIXED>;
+    if constexpr (KIND != K_STRAT)
         if (rows == ROWS_HUBS) kernel = k_meet<KIND, NS, false, ROWS_HUBS>;
-        if (rows == ROWS_MIXED) kernel = k_meet<KIND, NS, false, ROWS_MIXED>;
-    }
     kernel<<<blocks, meet_block_of(KIND), 0, st>>>(qs.desc, qs.nq, ustart, cursor, qs.counters, StreamRing{});
 }
 
 template <int KIND, int NS>
 void launch_meet_ring(Rows rows, const StreamRing &ring, hipStream_t st) {
-    auto kernel = k_meet<KIND, NS, true, ROWS_E>;
-    if constexpr (KIND != K_STRAT) {   // (a server's requests are on one graph)
-        if (rows == ROWS_PACKED) kernel = k_meet<KIND, NS, true, ROWS_PACKED>;
+    // (a server's requests are on one graph)
+    auto kernel = rows == ROWS_E ? k_meet<KIND, NS, true, ROWS_E> : k_meet<KIND, NS, true, ROWS_PACKED>;
+    if constexpr (KIND != K_STRAT)
         if (rows == ROWS_HUBS) kernel = k_meet<KIND, NS, true, ROWS_HUBS>;
-    }
     kernel<<<meet_grid_blocks<KIND, NS, true>(), meet_block_of(KIND), 0, st>>>(
         ring.desc, ring.entries, nullptr, nullptr, ring.counters, ring);
 }

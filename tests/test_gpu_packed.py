@@ -91,6 +91,33 @@ def test_packed_rows_equal_oracle(slots, hubs, hub_deg, others):
     G.free()
 
 
+# E and packed rows, with as many hubs as the stratified kernel has rows for and
+# one more
+@pytest.mark.parametrize("slots, hubs, hub_deg", [
+    (524288, 3, 8191), (524289, 3, 4095), (2097153, 1536, 1024), (2097153, 1537, 1024)])
+def test_packed_rows_stratified_equal_oracle(slots, hubs, hub_deg, others):
+    print(f"packed, stratified: {slots} slots, {hubs} nodes of in-degree {hub_deg}", flush=True)
+    g = _graph(slots, hubs, hub_deg, slots + hubs)
+    vs, G = _vs(g), S.load_csr(g)
+    q = S.make_stratified_query(2, eps=0.1, seed=6)
+    want = O.strat_sums(g, 2, 6, O.strat_params(g.n, 0.6, 0.1), vs)
+    assert np.array_equal(S.simrank_single_source_stratified(G, q)[2][vs], want)
+    Gs, _, ovs, _ = others
+    for k in (0, 1):   # in one launch with a small graph's query, with a many-hub graph's
+        other = S.make_stratified_query(5, eps=0.2, seed=8, graph=1)
+        plan = S.BatchPlan([G, Gs[k]], [q, other], groups=False)
+        plan.run()
+        plan.wait()
+        assert np.array_equal(plan.read_stratified(0)[2][vs], want)
+        got = plan.read_stratified(1)[2]
+        plan.free()
+        assert np.array_equal(got, S.simrank_single_source_stratified(Gs[k], S.make_stratified_query(5, eps=0.2, seed=8))[2])
+    srv = S.Server(G, max_slots=4, max_R=4000, max_L=64)   # (room for the sums of n nodes)
+    assert np.array_equal(srv.wait_stratified(srv.submit(q))[2][vs], want)
+    srv.destroy()
+    G.free()
+
+
 def test_all_hubs_and_no_edges():
     """Every node a hub, and a graph of no edges."""
     n = 3000
