@@ -249,19 +249,18 @@ __global__ __launch_bounds__(1024) void k_group_units(const GroupDesc *__restric
 
 template <int GW>
 struct GSlot {
-    uint32_t pos;      // LDS offset of the entry's positions (16 bits) | its longest
-                       // member walk << 16 | node index << 24
+    uint32_t left;     // steps left (16 bits): of the entry's longest member walk, or of walk
+                       // (v, j) if that is shorter | node index << 16
     uint32_t live;     // members still tested (bit q)
     uint32_t b;        // LDS offset of the entry's block for the next step
-    uint32_t t;        // steps taken
     uint32_t o, d;     // current node: slot offset in E and in-degree
     WalkDraws rng;
-    bool busy;
+    uint32_t t;        // stitched: steps taken
     uint32_t ph;       // stitched: 0 head; 1 node id, 2 pool offsets, 3 segment length,
                        // 4 tail step; 5 chain, 6 next segment's length
     uint32_t tsig, tm, tu, tseg, tsl;   // stitched tail: entry slot, chain index, position,
                                         // segment, its length
-    uint32_t cv, jw;   // stratified: class (and last step) of walk (v, j), and j
+    uint32_t cj;       // stratified: class of walk (v, j) | j << 8
 };
 
 // Compares the pair's position at step t with the members' positions at step t,
@@ -315,7 +314,7 @@ __global__ __launch_bounds__(GROUP_BLOCK) void k_meet_group(const GroupDesc *__r
     constexpr bool STITCHED = WK == 1, STRAT = WK == 2;
     constexpr int TJ = group_tile_j(GW, WK), TN = group_tile_nodes(GW, WK), GM = 4 * GW;
     __shared__ __attribute__((aligned(16))) uint32_t s_nodes[TN];
-    __shared__ uint32_t s_j[TJ];
+    __shared__ uint32_t s_jl[TJ];   // walk index of the entry (below 2^24) | longest member walk << 24
     __shared__ uint16_t s_off[TJ];
     __shared__ uint32_t s_cnt[STRAT ? 1 : GM / 2 * MEET_VB];   // members 2i, 2i+1 in the low, high half
     // stratified: weighted sums per (member, node), the nodes' shuffle keys,
@@ -327,14 +326,13 @@ __global__ __launch_bounds__(GROUP_BLOCK) void k_meet_group(const GroupDesc *__r
     __shared__ uint32_t s_vid[MEET_VB];
     __shared__ uint2 s_vrow[MEET_VB];
     __shared__ uint32_t s_srcm[MEET_VB];   // members whose source is the node
-    __shared__ uint8_t s_maxl[TJ];         // longest member walk of the entry
     __shared__ uint32_t s_unit, s_item;
 
     const int lane = threadIdx.x & 63;
     const uint32_t n_units = ustart[ng];
     uint32_t cur_g = 0xffffffffu, cur_tile = 0xffffffffu;
     uint32_t K = 0;
-    uint32_t st_moves = 0, st_draws = 0, st_meets = 0, st_pairs = 0, st_tail = 0;
+    Work work;
 
     for (;;) {
         if (threadIdx.x == 0) s_unit = atomicAdd(cursor, 1u);
@@ -366,14 +364,13 @@ __global__ __launch_bounds__(GROUP_BLOCK) void k_meet_group(const GroupDesc *__r
             const uint32_t nb = d.joff[k0], ne = d.joff[k1];
             K = k1 - k0;
             for (uint32_t i = threadIdx.x; i < K; i += blockDim.x) {
-                s_j[i] = d.jj[k0 + i];
                 s_off[i] = (uint16_t)(d.joff[k0 + i] - nb);
                 uint32_t mx = 0;
                 for (int32_t wd = 0; wd < gw; ++wd) {
                     const uint32_t lw = d.glen[(size_t)(k0 + i) * gw + wd];
                     mx = max(mx, max(max(byte_of(lw, 0), byte_of(lw, 1)), max(byte_of(lw, 2), byte_of(lw, 3))));
                 }
-                s_maxl[i] = (uint8_t)mx;
+                s_jl[i] = d.jj[k0 + i] | (mx << 24);
             }
             for (uint32_t i = threadIdx.x; i < ne - nb; i += blockDim.x) s_nodes[i] = d.pos[nb + i];
             if (STRAT)
@@ -403,14 +400,37 @@ __global__ __launch_bounds__(GROUP_BLOCK) void k_meet_group(const GroupDesc *__r
         // item i = vl * K + k for node vl < nv and entry k < K
         // (K and nv are the same in all lanes; said so, the refill's bookkeeping
         // stays in scalar registers)
-        const uint32_t total = nv * uni(K);
+        const uint32_t Ku = uni(K), total = nv * Ku;
         uint32_t ci = 0, ce = 0, cvl = 0, ck = 0;
         bool drained = false;
+        // node cvl: its row, draw constants, the members tested (all but those
+        // whose source it is; a member whose walk j is empty never reads a
+        // position) and, stratified, its shuffle key
+        uint32_t vo = 0, vd = 0, wa = 0, wb = 0, wcc = 0, vlive = 0;
+        uint4 vfk = make_uint4(0u, 0u, 0u, 0u);
+        uint32_t at_vl = NIL;
+        auto enter_node = [&]() {
+            at_vl = cvl;
+            const uint2 row = s_vrow[cvl];
+            vo = uni(row.x);
+            vd = uni(row.y);
+            const WalkDraws w = walk_draws_begin(uni(s_vid[cvl]), 0u, key, STRAT ? DOM_STRAT : DOM_WALK);
+            wa = uni(w.a);
+            wb = uni(w.b);
+            wcc = uni(w.cc);
+            vlive = gmask & ~uni(s_srcm[cvl]);
+            if (STRAT) {
+                const uint4 k = s_fk[cvl];
+                vfk = make_uint4(uni(k.x), uni(k.y), uni(k.z), uni(k.w));
+            }
+        };
+        // the wave's slots, and which lanes' have a pair
         GSlot<GW> sl[NS];
+        uint64_t busy[NS];
 #pragma unroll
         for (int qq = 0; qq < NS; ++qq) {
-            sl[qq].busy = false;
-            sl[qq].ph = 0;
+            sl[qq] = GSlot<GW>{};
+            busy[qq] = 0ull;
         }
 
         for (;;) {
@@ -418,108 +438,101 @@ __global__ __launch_bounds__(GROUP_BLOCK) void k_meet_group(const GroupDesc *__r
             // member's source is v), or a stratified walk of class 0, is skipped
 #pragma unroll
             for (int qq = 0; qq < NS; ++qq) {
-                uint64_t need = __ballot(!sl[qq].busy);
+                uint64_t need = ~busy[qq];
                 while (need != 0ull) {
                     if (ci == ce) {
                         if (drained) break;
                         uint32_t x = 0;
                         if (lane == 0) x = atomicAdd(&s_item, ITEM_CHUNK);
-                        x = __builtin_amdgcn_readfirstlane(x);
+                        x = uni(x);
                         if (x >= total) {
                             drained = true;
                             break;
                         }
                         ci = x;
                         ce = min(x + ITEM_CHUNK, total);
-                        cvl = x / K;
-                        ck = x - cvl * K;
+                        cvl = uni(x / Ku);
+                        ck = x - cvl * Ku;
+                        if (cvl != at_vl) enter_node();
                     }
-                    const uint32_t want = (uint32_t)__popcll(need);
-                    const uint32_t avail = ce - ci;
-                    const uint32_t take = avail < want ? avail : want;
-                    const uint32_t rank = lane_rank(need);
-                    const bool mine = ((need >> lane) & 1ull) && rank < take;
-                    bool filled = false;
-                    if (mine) {
-                        uint32_t k = ck + rank, vl = cvl;
-                        while (k >= K) {
-                            k -= K;
-                            ++vl;
-                        }
-                        // members tested: all but those whose source is v (a
-                        // member whose walk j is empty never reads a position)
-                        const uint32_t live = gmask & ~s_srcm[vl];
-                        uint32_t r = 0, cv = 0;
-                        if (STRAT && live) {
-                            r = shuffle_slot(s_j[k], NN, sa, sb, s_fk[vl]);
-                            cv = slot_class(r, s_ccum, phi);
-                        }
-                        if (live && (!STRAT || cv > 0u)) {
-                            const uint2 row = s_vrow[vl];
-                            GSlot<GW> &w = sl[qq];
-                            if (STRAT) {
-                                w.rng = walk_draws_begin(s_vid[vl], r, key, DOM_STRAT);
-                                w.cv = cv;
-                                w.jw = s_j[k];
-                            } else {
-                                w.rng = walk_draws_begin(s_vid[vl], s_j[k], key);
+                    uint32_t take = min(ce - ci, Ku - ck);
+                    if (vlive != 0u) {
+                        take = min(take, (uint32_t)__popcll(need));
+                        const uint32_t rank = lane_rank(need);
+                        uint64_t mine = need & __ballot(rank < take);
+                        const uint32_t k = min(ck + rank, Ku - 1u);
+                        const uint32_t jl = s_jl[k], off = s_off[k];
+                        uint32_t j = jl & 0xffffffu, left = jl >> 24, cv = 0;
+                        if (STRAT) {
+                            uint32_t r = 0;
+                            if (in_mask(mine)) {
+                                r = shuffle_slot(j, NN, sa, sb, vfk);
+                                cv = slot_class(r, s_ccum, phi);
                             }
-                            w.pos = (uint32_t)s_off[k] | ((uint32_t)s_maxl[k] << 16) | (vl << 24);
-                            w.live = live;
-                            w.b = s_off[k];
-                            w.t = 0;
-                            w.o = row.x;
-                            w.d = row.y;
-                            w.busy = true;
-                            w.ph = 0;
-                            filled = true;
-                            ++st_pairs;
+                            mine &= __ballot(cv > 0u);
+                            left = min(left, cv);
+                            cv |= j << 8;
+                            j = r;
                         }
+                        GSlot<GW> &w = sl[qq];
+                        const bool me = in_mask(mine);
+                        w.left = me ? left | (cvl << 16) : w.left;
+                        w.live = me ? vlive : w.live;
+                        w.b = me ? off : w.b;
+                        w.o = me ? vo : w.o;
+                        w.d = me ? vd : w.d;
+                        w.rng.j = me ? j : w.rng.j;
+                        w.rng.a = me ? wa : w.rng.a;
+                        w.rng.b = me ? wb : w.rng.b;
+                        w.rng.cc = me ? wcc : w.rng.cc;
+                        w.rng.mt = me ? 0ull : w.rng.mt;
+                        if (STITCHED) {
+                            w.t = me ? 0u : w.t;
+                            w.ph = me ? 0u : w.ph;
+                        }
+                        if (STRAT) w.cj = me ? cv : w.cj;
+                        work.pairs += (uint32_t)__popcll(mine);
+                        busy[qq] |= mine;
+                        need &= ~mine;
                     }
-                    need &= ~__ballot(filled);
                     ci += take;
                     ck += take;
-                    while (ck >= K && K > 0) {
-                        ck -= K;
+                    if (ck == Ku) {
+                        ck = 0;
                         ++cvl;
+                        if (ci < ce) enter_node();
                     }
                 }
             }
-            bool any = false;
+            uint64_t any = 0ull;
 #pragma unroll
-            for (int qq = 0; qq < NS; ++qq) any |= sl[qq].busy;
-            if (__ballot(any) == 0ull) {
+            for (int qq = 0; qq < NS; ++qq) any |= busy[qq];
+            if (any == 0ull) {
                 if (drained) break;
                 continue;
             }
 
             // ---- head steps: draws, then one load per slot (a head step's
             // gather or the load its stitched tail phase needs), then compares
-            bool go[NS];
+            uint64_t go[NS];
             uint32_t at[NS];
 #pragma unroll
             for (int qq = 0; qq < NS; ++qq) {
-                go[qq] = false;
-                at[qq] = 0;
-                if (sl[qq].busy && !(STITCHED && sl[qq].ph)) {
-                    ++sl[qq].t;
-                    const uint2 x = walk_draw_next(sl[qq].rng, key);
-                    ++st_draws;
-                    if (!STRAT && x.x >= T) {
-                        sl[qq].busy = false;
-                    } else {
-                        go[qq] = true;
-                        at[qq] = sl[qq].o + pick32(x.y, sl[qq].d);
-                    }
-                }
+                const uint64_t head = STITCHED ? busy[qq] & __ballot(sl[qq].ph == 0u) : busy[qq];
+                uint2 x = make_uint2(0u, 0u);
+                if (!STITCHED || in_mask(head)) x = walk_draw_next(sl[qq].rng, key);
+                work.draws += (uint32_t)__popcll(head);
+                go[qq] = STRAT ? head : head & __ballot(x.x < T);
+                if (STITCHED) busy[qq] &= ~(head & ~go[qq]);
+                at[qq] = sl[qq].o + pick32(x.y, sl[qq].d);
             }
             uint2 e[NS];
             uint32_t tv[NS];
             int64_t tb[NS], te[NS];
 #pragma unroll
             for (int qq = 0; qq < NS; ++qq) {
-                if (go[qq]) e[qq] = load_edge(E, at[qq]);
-                if (STITCHED && sl[qq].busy && sl[qq].ph) {
+                if (in_mask(go[qq])) e[qq] = load_edge(E, at[qq]);
+                if (STITCHED && in_mask(busy[qq] & ~go[qq])) {
                     const GSlot<GW> &w = sl[qq];
                     switch (w.ph) {
                     case 1: tv[qq] = d.ix.node_of[w.o]; break;
@@ -537,52 +550,59 @@ __global__ __launch_bounds__(GROUP_BLOCK) void k_meet_group(const GroupDesc *__r
 #pragma unroll
             for (int qq = 0; qq < NS; ++qq) {
                 GSlot<GW> &w = sl[qq];
-                const bool tail_step = STITCHED && !go[qq] && w.busy && w.ph == 4u;
-                if (go[qq]) {
-                    ++st_moves;
+                const bool head = in_mask(go[qq]);
+                const bool tail_step = STITCHED && in_mask(busy[qq] & ~go[qq]) && w.ph == 4u;
+                work.moves += (uint32_t)__popcll(go[qq]);
+                if (head) {
                     w.o = e[qq].x;
                     w.d = e[qq].y;
                 } else if (tail_step) {
-                    ++w.t;
-                    ++st_tail;
+                    ++work.tail;
                     w.o = tv[qq];
                     ++w.tu;
                 }
-                {
-                    const uint32_t met = group_compare(w, go[qq] || tail_step, s_nodes, lane);
+                if (head || tail_step) {
+                    --w.left;
+                    if (STITCHED) ++w.t;
+                }
+                const uint32_t met = group_compare(w, head || tail_step, s_nodes, lane);
+                if (const uint64_t mm = __ballot(met != 0u)) {
+                    uint32_t n_met = 0;
+                    for (uint64_t m = mm; m; m &= m - 1ull)
+                        n_met += (uint32_t)__popc(__builtin_amdgcn_readlane(met, __builtin_ctzll(m)));
+                    work.meets += n_met;
                     if (met) {
-                        const uint32_t vl = w.pos >> 24;
-                        st_meets += (uint32_t)__popc(met);
+                        const uint32_t vl = (w.left >> 16) & 0xffu;
                         w.live &= ~met;
                         for (uint32_t m = met; m; m &= m - 1u) {
                             const uint32_t q = (uint32_t)__builtin_ctz(m);
                             if (STRAT)
                                 atomicAdd(&s_w[q * VBW + vl],
-                                          strat_weight(d.tab->a, d.scls[q][w.jw], w.cv));
+                                          strat_weight(d.tab->a, d.scls[q][w.cj >> 8], w.cj & 0xffu));
                             else
                                 atomicAdd(&s_cnt[(q >> 1) * MEET_VB + vl], 1u << (16 * (q & 1u)));
                         }
                     }
                 }
-                if (go[qq]) {
-                    // the pair ends with its last member walk (or, stratified,
-                    // the class of walk (v, j)), when every member tested has
-                    // met, or at a node without in-neighbours
-                    if (w.live == 0u || w.d == 0u || w.t == ((w.pos >> 16) & 0xffu) ||
-                        (STRAT && w.t == w.cv))
-                        w.busy = false;
-                    else if (STITCHED && w.t == (uint32_t)d.ix.seg_len)
-                        w.ph = 1;   // the head made all its moves: enter a pool slot of this node
+                // the pair ends with its last member walk (or, stratified, the
+                // class of walk (v, j)), when every member tested has met, or
+                // at a node without in-neighbours
+                bool more = head && w.live != 0u && w.d != 0u && (w.left & 0xffffu) != 0u;
+                if constexpr (!STITCHED) {
+                    busy[qq] = __ballot(more);
                     continue;
                 }
-                if (!(STITCHED && w.busy && w.ph)) continue;
+                if (more && w.t == (uint32_t)d.ix.seg_len)
+                    w.ph = 1;   // the head made all its moves: enter a pool slot of this node
+                if (in_mask(busy[qq] & ~go[qq])) {
+                more = true;
                 switch (w.ph) {
                 case 1:   // the end node's id
                     w.tsig = tv[qq];
                     w.ph = 2;
                     break;
                 case 2: { // its pool: slot picked by draw (v, j, 0, DOM_ENTRY)
-                    const uint4 x = philox4x32_10(s_vid[w.pos >> 24], w.rng.j, 0u, DOM_ENTRY, key);
+                    const uint4 x = philox4x32_10(s_vid[(w.left >> 16) & 0xffu], w.rng.j, 0u, DOM_ENTRY, key);
                     w.tsig = (uint32_t)(tb[qq] + (int64_t)pick64(x.x, (uint64_t)(te[qq] - tb[qq])));
                     w.tseg = w.tsig;
                     w.tm = 0;
@@ -594,14 +614,14 @@ __global__ __launch_bounds__(GROUP_BLOCK) void k_meet_group(const GroupDesc *__r
                     w.tsl = tv[qq];
                     w.tu = 0;
                     w.ph = 4;
-                    if (w.tsl == 0u) w.busy = false;
+                    if (w.tsl == 0u) more = false;
                     break;
                 case 4:   // after a tail step
-                    if (w.live == 0u || w.t == ((w.pos >> 16) & 0xffu)) {
-                        w.busy = false;
+                    if (w.live == 0u || (w.left & 0xffffu) == 0u) {
+                        more = false;
                     } else if (w.tu == w.tsl) {
                         if (w.tsl < (uint32_t)d.ix.seg_len || w.tm + 1 >= (uint32_t)d.ix.width)
-                            w.busy = false;
+                            more = false;
                         else
                             w.ph = 5;
                     }
@@ -609,10 +629,12 @@ __global__ __launch_bounds__(GROUP_BLOCK) void k_meet_group(const GroupDesc *__r
                 default:  // the chain's next segment
                     ++w.tm;
                     w.tseg = tv[qq];
-                    if (w.tseg == NIL) w.busy = false;
+                    if (w.tseg == NIL) more = false;
                     else w.ph = 6;
                     break;
                 }
+                }
+                busy[qq] = __ballot(more);
             }
         }
         __syncthreads();
@@ -628,7 +650,7 @@ __global__ __launch_bounds__(GROUP_BLOCK) void k_meet_group(const GroupDesc *__r
         }
     }
 
-    add_work(ctr_set(counters), st_moves, st_draws, st_meets, st_tail, st_pairs);
+    add_work(ctr_set(counters), work);
 }
 
 #ifndef SRK_GROUP_SLOTS_STITCHED
