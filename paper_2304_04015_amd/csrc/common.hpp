@@ -312,8 +312,8 @@ struct GroupDesc {
     // Compacted walks: entry e is a walk index jj[e] for which at least one
     // member's walk has a step; from pos[joff[e]], one block per step t of its
     // longest member walk: a word with bit q set for each member q whose walk
-    // j has a position at step t, then those positions in member order, NIL up
-    // to a multiple of four words.
+    // j has a position at step t, then those positions' marks (the low halves
+    // of their o()) in member order, 0xffff up to a multiple of four words.
     // Member q's length is byte q of the entry's gw words glen[e gw ...].
     uint32_t *jj;                        // [Rmax]
     uint32_t *joff;                      // [Rmax + 1]

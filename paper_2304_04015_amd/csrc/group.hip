@@ -66,8 +66,10 @@ __host__ __device__ constexpr int group_tile_nodes(int GW, int WK) {   // < 2^16
 // Nodes per work unit whose sums a stratified instance keeps in LDS.
 __host__ __device__ constexpr int group_strat_vb(int GW) { return GW > 2 ? GROUP_STRAT32_VB : MEET_VB; }
 // Words of an entry's block for a step with c member positions: the members'
-// word and the positions, in whole 16-byte pieces.
-__host__ __device__ constexpr uint32_t block_words(uint32_t c) { return (c + 4u) & ~3u; }
+// word and the positions' marks (half a word each), in whole 16-byte pieces.
+__host__ __device__ constexpr uint32_t block_words(uint32_t c) { return ((c + 1u) / 2u + 4u) & ~3u; }
+// A position's mark: the low half of its o().
+__device__ __forceinline__ uint32_t mark_of(uint32_t o) { return o & 0xffffu; }
 // a tile holds at least one entry of the longest form (L blocks of G positions)
 static_assert(group_tile_nodes(2, 0) < 65536 && group_tile_nodes(2, 0) > 12 * MAX_CAP, "tile shape");
 static_assert(group_tile_nodes(8, 0) < 65536 && group_tile_nodes(8, 0) > 36 * MAX_CAP, "tile shape");
@@ -87,8 +89,8 @@ __device__ __forceinline__ uint32_t byte_of(uint32_t w, int q) { return (w >> (8
 // Keeps the walk indices j for which at least one member's walk j has a step
 // and packs the members' positions of walk j step by step: for each step t up
 // to the longest member walk, the word of members with a position at t, then
-// their positions at t in member order, NIL up to a multiple of four words (the
-// meet kernel reads 16-byte pieces).  grid (x over blocks of PACK_J walk
+// the marks of their positions at t in member order, 0xffff up to a multiple of
+// four words (the meet kernel reads 16-byte pieces).  grid (x over blocks of PACK_J walk
 // indices, y = group); a half wave packs an entry, one member per lane, and a
 // block takes the room of its entries with one atomic on meta[0..1], so entries
 // are in no order of j.  One block per group, a thread per walk index copying
@@ -167,8 +169,9 @@ __global__ __launch_bounds__(256) void k_group_pack(const GroupDesc *__restrict_
             const uint32_t c = (uint32_t)__popc(am), bw = block_words(c);
             if (t < mx) {
                 if (q == 0) d.pos[off] = am;
-                if (t < len[i]) d.pos[off + 1u + (uint32_t)__popc(am & ((1u << q) - 1u))] = here;
-                if ((uint32_t)q < bw - 1u - c) d.pos[off + 1u + c + (uint32_t)q] = NIL;
+                uint16_t *marks = reinterpret_cast<uint16_t *>(d.pos + off + 1u);
+                if (t < len[i]) marks[__popc(am & ((1u << q) - 1u))] = (uint16_t)mark_of(here);
+                if ((uint32_t)q < 2u * (bw - 1u) - c) marks[c + (uint32_t)q] = 0xffffu;
                 off += bw;
             }
         }
@@ -250,7 +253,7 @@ __global__ __launch_bounds__(1024) void k_group_units(const GroupDesc *__restric
 template <int GW>
 struct GSlot {
     uint32_t left;     // steps left (16 bits): of the entry's longest member walk, or of walk
-                       // (v, j) if that is shorter | node index << 16
+                       // (v, j) if that is shorter | node index << 16 | those at its start << 24
     uint32_t live;     // members still tested (bit q)
     uint32_t b;        // LDS offset of the entry's block for the next step
     uint32_t o, d;     // current node: slot offset in E and in-degree
@@ -265,42 +268,53 @@ struct GSlot {
 
 // Compares the pair's position at step t with the members' positions at step t,
 // for the lanes in `act`.  The entry's block for step t is the word of members
-// with a position at t, then those positions in member order, padded with NIL;
-// the slot's offset b moves on to the next step's block (every step is compared
+// with a position at t, then the marks of those positions in member order; the
+// slot's offset b moves on to the next step's block (every step is compared
 // once, in order).  Meets are rare: the common step reads the block in 16-byte
-// pieces and only asks whether any position is the pair's.  For each lane with
-// a hit the whole wave then names the members, one per lane.  Returns the
-// members still tested that meet at this step.  Called by all lanes of a wave.
-// Reading word by word, with each read's index held inside the block, and
-// naming the members one by one on the lane that hit, the kernel took 61.7 ms
-// for 32 queries at n = 2^18 and was bound by its instructions; now 50.9, at
-// 53 G L2 misses/s (random 8-byte gathers over its 33 MB: 58).
-template <int GW>
+// pieces and only asks whether any mark is the pair's.  For each lane with
+// such a mark (a meet, or one in 65,536 positions that differs in the other
+// half) the whole wave then compares the members' positions themselves, one per
+// lane, in their walks' tables.  Returns the members still tested that meet at
+// this step.  Called by all lanes of a wave.
+// The kernel is bound by these reads of LDS: with whole positions in the blocks
+// 32 queries at n = 40,000, R = 1,521, took 1,812 us, with marks 1,314; at n = 2^18,
+// R = 9,502: 50.1 ms and 47.9, bound by the gathers as well.
+template <int GW, int WK>
 __device__ __forceinline__ uint32_t group_compare(GSlot<GW> &w, bool act, const uint32_t *s_nodes,
-                                                  int lane) {
+                                                  const GroupDesc &d, int lane) {
+    typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+    auto as2 = [](uint32_t x) { return __builtin_bit_cast(u16x2, x); };
     bool hit = false;
     uint32_t am = 0;
-    const uint32_t B = w.b;
     if (act) {
-        const uint4 *blk = reinterpret_cast<const uint4 *>(s_nodes + B);
+        const uint32_t mine = mark_of(w.o) | (w.o << 16);
+        const uint4 *blk = reinterpret_cast<const uint4 *>(s_nodes + w.b);
         const uint4 h = blk[0];
         am = h.x;
         const uint32_t pieces = block_words((uint32_t)__popc(am)) >> 2;
-        hit = h.y == w.o || h.z == w.o || h.w == w.o;
+        // the least difference of a mark, per half word
+        u16x2 least = __builtin_elementwise_min(as2(h.y ^ mine), as2(h.z ^ mine));
+        least = __builtin_elementwise_min(least, as2(h.w ^ mine));
         for (uint32_t i = 1; i < pieces; ++i) {
             const uint4 p = blk[i];
-            hit |= p.x == w.o || p.y == w.o || p.z == w.o || p.w == w.o;
+            least = __builtin_elementwise_min(least, __builtin_elementwise_min(as2(p.x ^ mine), as2(p.y ^ mine)));
+            least = __builtin_elementwise_min(least, __builtin_elementwise_min(as2(p.z ^ mine), as2(p.w ^ mine)));
         }
-        w.b = B + 4u * pieces;
+        hit = least.x == 0 || least.y == 0;
+        w.b += 4u * pieces;
     }
     uint32_t met = 0;
     for (uint64_t hm = __ballot(hit); hm != 0ull; hm &= hm - 1ull) {
         const int from = __builtin_ctzll(hm);
-        const uint32_t fam = __builtin_amdgcn_readlane(am, from), fB = __builtin_amdgcn_readlane(B, from),
-                       fo = __builtin_amdgcn_readlane(w.o, from);
-        const bool mine = lane < 32 && ((fam >> lane) & 1u);
-        const uint32_t at = fB + 1u + (uint32_t)__popc(fam & ((1u << (lane & 31)) - 1u));
-        const uint32_t who = (uint32_t)__ballot(mine && s_nodes[mine ? at : fB] == fo);
+        const uint32_t fam = __builtin_amdgcn_readlane(am, from), fo = __builtin_amdgcn_readlane(w.o, from),
+                       fleft = __builtin_amdgcn_readlane(w.left, from),
+                       fj = WK == 2 ? (uint32_t)__builtin_amdgcn_readlane(w.cj, from) >> 8
+                                    : (uint32_t)__builtin_amdgcn_readlane(w.rng.j, from);
+        const uint32_t step = (fleft >> 24) - (fleft & 0xffffu);   // 1, 2, ..
+        bool same = false;
+        if (lane < 32 && ((fam >> lane) & 1u))
+            same = d.sw[lane][(size_t)fj * (size_t)d.L + step - 1u] == fo;
+        const uint32_t who = (uint32_t)__ballot(same);
         if (lane == from) met = who;
     }
     return met & w.live;
@@ -476,7 +490,7 @@ __global__ __launch_bounds__(GROUP_BLOCK) void k_meet_group(const GroupDesc *__r
                         }
                         GSlot<GW> &w = sl[qq];
                         const bool me = in_mask(mine);
-                        w.left = me ? left | (cvl << 16) : w.left;
+                        w.left = me ? left | (cvl << 16) | (left << 24) : w.left;
                         w.live = me ? vlive : w.live;
                         w.b = me ? off : w.b;
                         w.o = me ? vo : w.o;
@@ -565,7 +579,7 @@ __global__ __launch_bounds__(GROUP_BLOCK) void k_meet_group(const GroupDesc *__r
                     --w.left;
                     if (STITCHED) ++w.t;
                 }
-                const uint32_t met = group_compare(w, head || tail_step, s_nodes, lane);
+                const uint32_t met = group_compare<GW, WK>(w, head || tail_step, s_nodes, d, lane);
                 if (const uint64_t mm = __ballot(met != 0u)) {
                     uint32_t n_met = 0;
                     for (uint64_t m = mm; m; m &= m - 1ull)
