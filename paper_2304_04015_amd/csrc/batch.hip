@@ -288,6 +288,8 @@ extern "C" int simrank_batch_plan_create_ex(simrank_graph *const *graphs, int32_
         const int32_t mt = group_max_tiles(gd.Rmax, g_RL[k], gd.L, gd.G, gd.wk);
         (void)take(group_buffers(&gd, g_RL[k], cur));   // carved at cur, which it advances
         gset.units_bound[group_list(gd.G, gd.wk)] += (int64_t)mt * gd.n_chunks;
+        gset.rows[group_list(gd.G, gd.wk)] |=
+            group_rows_wish(*p->graphs[groups[k].front()], group_list(gd.G, gd.wk));
     }
     if (ngr > 0) {
         e = hipMemcpy(p->gdesc_dev, p->gdesc.data(), sizeof(GroupDesc) * ngr, hipMemcpyHostToDevice);

@@ -222,8 +222,7 @@ enum Rows : int { ROWS_E, ROWS_PACKED, ROWS_HUBS, ROWS_MIXED };
 // What a query can use.  E is better where all of it is within an XCD's L2
 // (packed rows only add their decoding; n = 20,000, R = 38,005: 2,677 us with E,
 // 2,717 packed), packed rows are beyond it (n = 2^18, R = 9,502: 11,681 and
-// 9,455; stratified, N = 16,508: 20.2 and 18.1 ms).  Groups are bound by their
-// instructions and read E (32 members: 50.8 ms, 52.3 packed).
+// 9,455; stratified, N = 16,508: 20.2 and 18.1 ms).
 constexpr int WANTS_E = 1, WANTS_PACKED = 2, WANTS_HUBS = 4, HAS_NONE = 8;
 inline int rows_wish(const Graph &g, const QueryDesc &d) {
     if (g.obits == 0) return HAS_NONE;
@@ -329,11 +328,20 @@ struct GroupDesc {
 constexpr int GROUP_LISTS = 6;
 __host__ __device__ inline int group_list(int32_t G, int32_t wk) { return 2 * wk + (G > 8 ? 1 : 0); }
 
+// Rows of hubs that an instance has LDS for, and the rows a group can use: as a
+// lone query (rows_wish).  A launch whose groups cannot all be packed reads E.
+__host__ __device__ constexpr int group_hub_rows(int list) { return list == 5 ? 256 : 1536; }
+inline int group_rows_wish(const Graph &g, int list) {
+    if (g.obits == 0 || g.n_hubs > group_hub_rows(list)) return HAS_NONE;
+    return 8 * g.m_slots <= (int64_t)4 << 20 ? WANTS_E : WANTS_PACKED;
+}
+
 struct GroupSet {
     const GroupDesc *desc = nullptr;     // device [ng]
     int32_t ng = 0;
     int32_t max_R = 0;                   // largest Rmax
     int64_t units_bound[GROUP_LISTS] = {};       // work units per kernel instance (group_list)
+    int rows[GROUP_LISTS] = {};                  // group_rows_wish of its groups
     uint32_t *units = nullptr;           // device [group_units_words(ng)]
 };
 // Unit offsets of a group set: one list of ng + 1 offsets per instance, then

@@ -320,13 +320,15 @@ __device__ __forceinline__ uint32_t group_compare(GSlot<GW> &w, bool act, const 
     return met & w.live;
 }
 
-template <int NS, int GW, int WK>
+template <int NS, int GW, int WK, bool PACKED>
 __global__ __launch_bounds__(GROUP_BLOCK) void k_meet_group(const GroupDesc *__restrict__ gd, int32_t ng,
                                                             const uint32_t *__restrict__ ustart,
                                                             uint32_t *__restrict__ cursor,
                                                             unsigned long long *__restrict__ counters) {
     constexpr bool STITCHED = WK == 1, STRAT = WK == 2;
     constexpr int TJ = group_tile_j(GW, WK), TN = group_tile_nodes(GW, WK), GM = 4 * GW;
+    constexpr int HL = group_hub_rows(2 * WK + (GW > 2 ? 1 : 0));
+    __shared__ uint2 s_hub[PACKED ? HL : 1];   // rows of a packed graph's hubs
     __shared__ __attribute__((aligned(16))) uint32_t s_nodes[TN];
     __shared__ uint32_t s_jl[TJ];   // walk index of the entry (below 2^24) | longest member walk << 24
     __shared__ uint16_t s_off[TJ];
@@ -369,7 +371,7 @@ __global__ __launch_bounds__(GROUP_BLOCK) void k_meet_group(const GroupDesc *__r
         const uint32_t chunk = local - tile * (uint32_t)n_chunks;
         const PhiloxKey key{uni(d.k0), uni(d.k1)};
         const uint32_t T = uni(d.T);
-        const GlobalPtr<uint64_t> E = gp_uni((const uint64_t *)d.E);
+        const Gather rows = gather_of<HL>(d);
         const uint32_t gmask = G >= 32 ? 0xffffffffu : (1u << G) - 1u;
         const uint32_t NN = uni((uint32_t)d.Rmax), sa = uni((uint32_t)d.sa), sb = uni((uint32_t)d.sb);
         const int32_t phi = (int32_t)uni((uint32_t)d.L);
@@ -390,6 +392,8 @@ __global__ __launch_bounds__(GROUP_BLOCK) void k_meet_group(const GroupDesc *__r
             if (STRAT)
                 for (uint32_t i = threadIdx.x; i < (uint32_t)phi + 2; i += blockDim.x)
                     s_ccum[i] = d.tab->ccum[i];
+            if (PACKED)
+                for (uint32_t i = threadIdx.x; i < (uint32_t)d.n_hubs; i += blockDim.x) s_hub[i] = d.hubs[i];
             cur_g = (uint32_t)gi;
             cur_tile = tile;
         }
@@ -545,7 +549,10 @@ __global__ __launch_bounds__(GROUP_BLOCK) void k_meet_group(const GroupDesc *__r
             int64_t tb[NS], te[NS];
 #pragma unroll
             for (int qq = 0; qq < NS; ++qq) {
-                if (in_mask(go[qq])) e[qq] = load_edge(E, at[qq]);
+                if (in_mask(go[qq])) {
+                    if (PACKED) e[qq].x = rows.E4[at[qq]];
+                    else e[qq] = load_edge(rows.E, at[qq]);
+                }
                 if (STITCHED && in_mask(busy[qq] & ~go[qq])) {
                     const GSlot<GW> &w = sl[qq];
                     switch (w.ph) {
@@ -568,8 +575,9 @@ __global__ __launch_bounds__(GROUP_BLOCK) void k_meet_group(const GroupDesc *__r
                 const bool tail_step = STITCHED && in_mask(busy[qq] & ~go[qq]) && w.ph == 4u;
                 work.moves += (uint32_t)__popcll(go[qq]);
                 if (head) {
-                    w.o = e[qq].x;
-                    w.d = e[qq].y;
+                    const uint2 to = PACKED ? unpack_row(e[qq].x, rows.obits, s_hub) : e[qq];
+                    w.o = to.x;
+                    w.d = to.y;
                 } else if (tail_step) {
                     ++work.tail;
                     w.o = tv[qq];
@@ -677,7 +685,7 @@ int group_grid_blocks() {
         int dev = 0, cus = 0, per = 0;
         (void)hipGetDevice(&dev);
         (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-        (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_meet_group<NS, GW, WK>,
+        (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_meet_group<NS, GW, WK, false>,
                                                            GROUP_BLOCK, 0);
         if (cus <= 0) cus = 256;
         if (per <= 0) per = 1;
@@ -690,7 +698,9 @@ template <int NS, int GW, int WK>
 void launch_group_list(const GroupSet &gs, int list, unsigned long long *counters, hipStream_t st) {
     if (gs.units_bound[list] <= 0) return;
     const int blocks = (int)std::min<int64_t>(gs.units_bound[list], group_grid_blocks<NS, GW, WK>());
-    k_meet_group<NS, GW, WK><<<blocks, GROUP_BLOCK, 0, st>>>(
+    const auto kernel = rows_of(gs.rows[list]) == ROWS_PACKED ? k_meet_group<NS, GW, WK, true>
+                                                              : k_meet_group<NS, GW, WK, false>;
+    kernel<<<blocks, GROUP_BLOCK, 0, st>>>(
         gs.desc, gs.ng, gs.units + (size_t)list * (gs.ng + 1),
         gs.units + GROUP_LISTS * ((size_t)gs.ng + 1) + list, counters);
 }
@@ -699,7 +709,8 @@ void launch_group_list(const GroupSet &gs, int list, unsigned long long *counter
 
 int32_t group_max_tiles(int64_t Rmax, int64_t sum_RL, int32_t L, int32_t G, int32_t wk) {
     const int GW = group_gw(G);
-    const int64_t NW = group_tile_nodes(GW, wk) - (int64_t)block_words((uint32_t)G) * L;
+    // (stated with whole positions in the blocks, of which there are never fewer words)
+    const int64_t NW = group_tile_nodes(GW, wk) - (int64_t)((G + 4) & ~3) * L;
     return (int32_t)(2 + Rmax / group_tile_j(GW, wk) + group_pos_words(Rmax, sum_RL, L) / NW);
 }
 
@@ -723,6 +734,10 @@ void describe_group(const QueryDesc *const *members, int32_t G, GroupDesc *gd) {
     *gd = GroupDesc{};
     gd->nodes = d0.nodes;
     gd->E = d0.E;
+    gd->E4 = d0.E4;
+    gd->hubs = d0.hubs;
+    gd->obits = d0.obits;
+    gd->n_hubs = d0.n_hubs;
     gd->active = d0.active;
     gd->n_active = d0.n_active;
     gd->G = G;

@@ -348,6 +348,7 @@ static int launch_group(simrank_server *S, const std::vector<Request *> &rs, hip
     gs.ng = 1;
     gs.max_R = gd->Rmax;
     gs.units_bound[group_list(G, gd->wk)] = units;
+    gs.rows[group_list(G, gd->wk)] = group_rows_wish(*g, group_list(G, gd->wk));
     gs.units = gr.gunits;
     QuerySet qs;
     qs.desc = gr.desc_dev;

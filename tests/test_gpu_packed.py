@@ -118,6 +118,38 @@ def test_packed_rows_stratified_equal_oracle(slots, hubs, hub_deg, others):
     G.free()
 
 
+# groups of both kernel shapes and all walks, with as many hubs as they have rows
+# for (256 the stratified one of more than 8) and one more; the marks of a
+# block's positions (5 and 9 members: part of a word, a second piece)
+@pytest.mark.parametrize("members", [5, 9])
+@pytest.mark.parametrize("slots, hubs, hub_deg", [
+    (524289, 3, 4095), (2097153, 256, 1024), (2097153, 257, 1024), (2097153, 1536, 1024), (2097153, 1537, 1024)])
+def test_packed_rows_groups_equal_oracle(slots, hubs, hub_deg, members, others):
+    print(f"packed, {members} members: {slots} slots, {hubs} nodes of in-degree {hub_deg}", flush=True)
+    g = _graph(slots, hubs, hub_deg, slots + hubs)
+    vs, G, small = _vs(g), S.load_csr(g), others[0][0]
+    S.simrank_build_index(G, seg_log2=1, kappa=0.05, c=0.6, seed=ISEED)
+    src, R = [2 + i for i in range(members)], 300
+    plan = S.BatchPlan([G, small], [S.make_query(s, seed=3, R=R) for s in src] +
+                       [S.make_query(s, seed=3, R=R, mode=S.MODE_STITCHED) for s in src] +
+                       [S.make_stratified_query(s, eps=0.2, seed=6) for s in src] +
+                       [S.make_query(s, seed=8, R=R, graph=1) for s in src[:2]])   # a group that reads E
+    assert plan.n_groups == 4
+    plan.run()
+    plan.wait()
+    P, Q = O.strat_params(g.n, 0.6, 0.2), O.pool_sizes(g, 0.05)
+    for i in (0, members - 1):
+        s = src[i]
+        assert np.array_equal(plan.read(i)[1][vs], O.meet_counts_plain(g, s, 3, 0.6, 64, R, vs))
+        assert np.array_equal(plan.read(members + i)[1][vs],
+                              O.meet_counts_stitched(g, s, 3, ISEED, 0.6, 64, 2, Q, R, vs))
+        assert np.array_equal(plan.read_stratified(2 * members + i)[2][vs], O.strat_sums(g, s, 6, P, vs))
+    lone = S.simrank_single_source_ex(small, S.make_query(src[1], seed=8, R=R))[1]
+    assert np.array_equal(plan.read(3 * members + 1)[1], lone)
+    plan.free()
+    G.free()
+
+
 def test_all_hubs_and_no_edges():
     """Every node a hub, and a graph of no edges."""
     n = 3000
