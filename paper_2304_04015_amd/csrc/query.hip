@@ -1168,6 +1168,14 @@ __global__ __launch_bounds__(256) void k_walks_strat(StratWalkArgs a) {
 #ifndef SRK_MEET_SLOTS_STRAT
 #define SRK_MEET_SLOTS_STRAT 2
 #endif
+// Stratified queries that gather packed rows wait for their gathers: a third
+// pair per lane (with 2 and 3: n = 40,000, N = 16,508: 2,499 and 2,429 us; n =
+// 2^18: 18.1 and 17.4 ms).  Those that gather E, from the L2 or with many hubs,
+// have the more idle slots at a unit's end instead (n = 2,003: 55 and 62 us; n =
+// 2^20: 17.3 and 17.5 ms).
+#ifndef SRK_MEET_SLOTS_STRAT_PACKED
+#define SRK_MEET_SLOTS_STRAT_PACKED 3
+#endif
 
 // Resident blocks of a meet-kernel instance on the whole device (computed
 // once per process; a function-local static is initialised thread-safely).
@@ -1191,9 +1199,10 @@ void launch_meet(const QuerySet &qs, hipStream_t st) {
     const int blocks = meet_grid_blocks<KIND, NS, false>();
     const uint32_t *ustart = qs.units + (size_t)KIND * (qs.nq + 1);
     uint32_t *cursor = qs.units + (size_t)N_KINDS * (qs.nq + 1) + KIND;
+    constexpr int NP = KIND == K_STRAT ? SRK_MEET_SLOTS_STRAT_PACKED : NS;
     const Rows rows = rows_of(qs.rows[KIND]);
     auto kernel = rows == ROWS_E        ? k_meet<KIND, NS, false, ROWS_E>
-                  : rows == ROWS_PACKED ? k_meet<KIND, NS, false, ROWS_PACKED>
+                  : rows == ROWS_PACKED ? k_meet<KIND, NP, false, ROWS_PACKED>
                                         : k_meet<KIND, NS, false, ROWS_MIXED>;
     if constexpr (KIND != K_STRAT)
         if (rows == ROWS_HUBS) kernel = k_meet<KIND, NS, false, ROWS_HUBS>;
