@@ -6,7 +6,7 @@ vertices relabelled by a seeded permutation; c = 0.6, eps = 0.02,
 delta = 1e-3 (R = 9502 walks per node from Hoeffding), walk cap L = 64;
 8 sources drawn uniformly among nodes with in-edges, each run as its own
 single-source query.  One step = those 8 queries, each a full pass of the
-query path (source walks, compaction, fused walk + meet + count, estimate),
+query path (source walks, tiles, fused walk + meet + count, estimate),
 with the graph already resident in HBM.
 
 Prints one JSON line.  `value` is walk steps per second (moves along in-edges

@@ -343,7 +343,7 @@ int simrank_batch(simrank_graph *const *graphs, int32_t ngraphs, const simrank_q
                   simrank_stats *st_opt);
 
 /* A batch plan owns the device buffers of nq queries and a hipGraph of their
- * whole launch sequence: source walks of every query, compaction, one
+ * whole launch sequence: source walks of every query, units, one
  * persistent meet launch per kind whose work units span all its queries,
  * estimates.  It can be run any number of times.  ENOMEM if its buffers
  * exceed free memory. */
@@ -430,7 +430,7 @@ int simrank_tune_index(simrank_graph *g, const simrank_query *q, const simrank_i
  * thread admits queued requests oldest first as soon as a ring entry (at most
  * max_slots requests in flight) and the request's own device memory (its R, L
  * and mode decide how much, taken from the server's pool of hbm_budget bytes)
- * are free.  An admitted request's source walks and compaction are prepared
+ * are free.  An admitted request's source walks and units are prepared
  * on the device and its work units (tiles of source walks x chunks of nodes)
  * are published into a device ring; persistent meet kernels take units from
  * every published request of their kind, oldest first, and exit when none is

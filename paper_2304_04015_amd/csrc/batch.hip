@@ -2,7 +2,7 @@
 //
 // A plan holds the device buffers of a set of queries (carved from one
 // allocation) and a hipGraph of the whole launch sequence: init, source walks
-// of every query, compaction, work-unit offsets, one persistent meet launch
+// of every query, tiles and work units, one persistent meet launch
 // whose work units span all queries (per kind: plain, stitched, stratified),
 // estimate.
 // Queries on graphs of very different sizes share the launch and its tail.

@@ -190,7 +190,8 @@ struct QueryDesc {
     const int32_t *active;
     IndexView ix;
     uint32_t *sw;          // [R][L] source walk positions 1..L (o values)
-    uint8_t *slen;         // [R rounded up to 256]; after the compaction the tiles' first units
+    uint8_t *slen;         // [R rounded up to 256] lengths of a group member's source walks;
+                           // a lone query's tiles' first units
     uint32_t *jj;          // [R] walk index of compact entry k
     uint32_t *joff;        // [R + 1] start of entry k in swc
     uint32_t *swc;         // [R * L] packed positions
@@ -402,7 +403,7 @@ struct StreamRing {
 };
 // Serving (query.hip): enqueue on `st` the preparation of ring entry `slot`
 // for the request described by d (its buffers attached): descriptor, init,
-// source walks, compaction, publication.  Launch a persistent meet kernel of
+// source walks, publication (tiles and units).  Launch a persistent meet kernel of
 // `kind` that takes units from every published entry of that kind and exits
 // when none is left.  Bytes of device memory a request needs for its buffers.
 int enqueue_ring_request(const QueryDesc &d, const StreamRing &ring, int32_t slot, uint32_t seq,

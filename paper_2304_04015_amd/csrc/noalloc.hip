@@ -1,8 +1,8 @@
 // A single-source query that allocates nothing: simrank_single_source_noalloc.
 //
 // It runs the same launch sequence as simrank_single_source_async (source
-// walks, compaction, the fused walk + meet + count kernel, the estimate), but
-// its per-query scratch (source walks and their compacted copy, tile table,
+// walks, tiles and units, the fused walk + meet + count kernel, the estimate),
+// but its per-query scratch (source walks, padded and packed, tile table,
 // descriptor, unit table, counters) lives in `scratch`, a file-scope device
 // array of fixed size that every GPU the library runs on holds until the
 // process ends.  The caller passes the graph, the query, device outputs and a

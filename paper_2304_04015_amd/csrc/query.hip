@@ -276,8 +276,8 @@ __device__ void make_tiles(const QueryDesc &d, int lane) {
 // n = 2^18: 11.56 and 11.65 ms; n = 2^20: 50.3 ms both.
 constexpr int UNIT_ROUNDS_LOG2_PAIRS = 27, UNIT_MAX_ROUNDS = 16;
 
-// First unit of each tile and, behind them, the number of units: kept where the
-// lengths of the source walks were, which only the compaction before reads.
+// First unit of each tile and, behind them, the number of units: kept where a
+// group member has its source walks' lengths.
 // They and one word more fit there: 4 (3 + R / 2048 + R L / (12288 - L))
 // bytes are fewer than R rounded up to 256, for every R and L up to MAX_CAP.
 __device__ __forceinline__ uint32_t *tunits_of(const QueryDesc &d) {

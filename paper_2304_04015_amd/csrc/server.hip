@@ -6,7 +6,7 @@
 // memory are free: each request takes request_bytes(R, L, n) from the
 // server's device pool (admission by memory, sized per request).  An admitted
 // request is prepared on the preparation stream (descriptor, source walks,
-// compaction) and published into the ring (common.hpp); persistent meet
+// tiles and units) and published into the ring (common.hpp); persistent meet
 // kernels, one launch per kind after each round of admissions, alternating
 // between two streams, take work units from every published entry of their
 // kind, oldest first, and exit when no unit is left.  Requests that arrive
