@@ -93,9 +93,9 @@ __host__ __device__ constexpr int meet_block_of(int kind) {
 // tiles of plain and stitched queries cut to HUB_TILE_NODES positions, to make
 // room for HUB_ROWS.
 __host__ __device__ constexpr int hub_rows_of(int kind) {
-    return kind == K_PLAIN ? 1280 : kind == K_STITCHED ? 768 : 1536;
+    return kind == K_PLAIN ? 1216 : kind == K_STITCHED ? 704 : 1472;
 }
-constexpr int HUB_TILE_NODES = 12288, HUB_ROWS = 6912;
+constexpr int HUB_TILE_NODES = 12288, HUB_ROWS = 6848;
 
 // ------------------------------------------------------------ device graph
 // Gather layout of the reversed graph.  Every node v owns the edge slots

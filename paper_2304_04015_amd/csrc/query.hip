@@ -574,9 +574,12 @@ __device__ void ring_report(const StreamRing &ring, const QueryDesc &d, uint32_t
                             uint32_t tag, uint32_t units, Work &work, uint32_t *s_last) {
     add_work(ring.counters + (size_t)slot * 8, work);
     work = Work{};
-    __threadfence();
+    // every wave's counts are at the coherence point (atomics, waited for)
+    // before one thread releases them with the block's report
+    __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     if (threadIdx.x == 0) {
+        __threadfence();
         // the size is read coherently: a plain load could return the size of
         // an earlier request in this entry from a cache and miss the last unit
         const uint32_t old = atomicAdd(&ring.ctl[slot].done, units);
@@ -594,6 +597,16 @@ __device__ void ring_report(const StreamRing &ring, const QueryDesc &d, uint32_t
             __hip_atomic_store(&ring.flags[slot], tag, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
     __syncthreads();
+}
+
+constexpr uint32_t DESC_WORDS = sizeof(QueryDesc) / 4;
+static_assert(sizeof(QueryDesc) % 4 == 0, "whole words");
+__device__ __forceinline__ const QueryDesc &desc_in(const uint32_t *words) {
+    return *reinterpret_cast<const QueryDesc *>(words);
+}
+// A word of memory that another kernel may have written while this one runs.
+__device__ __forceinline__ uint32_t coherent(const uint32_t *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // At most 112 registers, which the attribute counts in pairs: 4 waves leave a
@@ -635,6 +648,9 @@ void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
     // stitched: per-wave ring of pairs waiting for their tails, (vl << 16 | k, o)
     __shared__ uint2 s_tq[STITCHED ? (meet_block_of(KIND) / 64) * TAIL_Q : 1];
 
+    // serving: the descriptor of the request worked on
+    __shared__ __attribute__((aligned(16))) uint32_t s_desc[STREAM ? DESC_WORDS : 1];
+
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint32_t n_units = STREAM ? 0u : ustart[nq];
     uint32_t tq_head = 0, tq_tail = 0;   // stitched: the wave's tail ring (wave-uniform)
@@ -661,14 +677,26 @@ void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
             // the block reports the units it finished of a request, and their
             // work, once: when it moves on to another request or runs out
             if (acc_units && (nslot >= (uint32_t)RING_MAX || nseq != acc_tag)) {
-                ring_report(ring, qd[acc_slot], acc_slot, acc_tag, acc_units, work, &s_last);
+                ring_report(ring, desc_in(s_desc), acc_slot, acc_tag, acc_units, work, &s_last);
                 acc_units = 0;
             }
             if (nslot >= (uint32_t)RING_MAX) break;
             tag_s = nseq;
             // a request this block has not worked on: see its descriptor and
-            // buffers as its publication left them
-            if (tag_s != cur_q) __threadfence();
+            // buffers as its publication left them.  One wave's acquire
+            // empties the CU's vector caches for all (its claim, an acquire
+            // before a barrier, has done so too); a fence by each of a grid's
+            // 4,096 waves, here and at the report, took half a millisecond a
+            // request.  No fence empties the scalar cache, and ring entries and
+            // pool memory are used again: the descriptor is read coherently
+            // into LDS, and so are the other words at addresses that all lanes
+            // share (coherent).
+            if (tag_s != cur_q) {
+                if (threadIdx.x < 64) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                const uint32_t *from = reinterpret_cast<const uint32_t *>(&qd[nslot]);
+                for (uint32_t i = threadIdx.x; i < DESC_WORDS; i += blockDim.x) s_desc[i] = coherent(from + i);
+                __syncthreads();
+            }
         } else {
             if (threadIdx.x == 0) s_unit = next_unit;
             __syncthreads();
@@ -690,16 +718,17 @@ void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
         const int32_t q = lo;
         const uint32_t local = STREAM ? unit : unit - ustart[q];
         const uint32_t tag = STREAM ? tag_s : (uint32_t)q;
-        const QueryDesc &d = qd[q];
+        const QueryDesc &d = STREAM ? desc_in(s_desc) : qd[q];
+        auto word = [](const uint32_t *p) { return STREAM ? coherent(p) : *p; };
         // tile of the unit: the last one that starts at or before it (a tile
         // of a query with units has at least one)
-        uint32_t tile = 0, tile_hi = uni(d.meta[2]);
+        uint32_t tile = 0, tile_hi = uni(word(d.meta + 2));
         while (tile_hi - tile > 1) {
             const uint32_t mid = (tile + tile_hi) >> 1;
-            if (uni(tunits_of(d)[mid]) <= local) tile = mid; else tile_hi = mid;
+            if (uni(word(tunits_of(d) + mid)) <= local) tile = mid; else tile_hi = mid;
         }
-        const uint32_t unit0 = uni(tunits_of(d)[tile]);
-        const uint32_t chunks = uni(tunits_of(d)[tile + 1]) - unit0, chunk = local - unit0;
+        const uint32_t unit0 = uni(word(tunits_of(d) + tile));
+        const uint32_t chunks = uni(word(tunits_of(d) + tile + 1)) - unit0, chunk = local - unit0;
         const PhiloxKey key{uni(d.k0), uni(d.k1)};
         const uint32_t T = uni(d.T);
         const Gather rows = gather_of<HL>(d);
@@ -707,10 +736,11 @@ void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
         const int32_t src = (int32_t)uni((uint32_t)d.s);
         const uint32_t NN = uni((uint32_t)d.R), sa = uni((uint32_t)d.sa), sb = uni((uint32_t)d.sb);
         const int32_t phi = (int32_t)uni((uint32_t)d.L);
+        const uint32_t head_len = STITCHED ? uni((uint32_t)d.ix.seg_len) : 0u;
         const uint32_t run_log2 = STRAT ? class_run_log2(NN) : 0u;
         if (tag != cur_q || tile != cur_tile) {
-            const uint32_t k0 = uni(tiles_of(d)[tile]), k1 = uni(tiles_of(d)[tile + 1]);
-            const uint32_t nb = d.joff[k0], ne = d.joff[k1];
+            const uint32_t k0 = uni(word(tiles_of(d) + tile)), k1 = uni(word(tiles_of(d) + tile + 1));
+            const uint32_t nb = uni(word(d.joff + k0)), ne = uni(word(d.joff + k1));
             K = k1 - k0;
             for (uint32_t i = threadIdx.x; i < K; i += blockDim.x) {
                 const uint32_t jw = d.jj[k0 + i], at = d.joff[k0 + i];
@@ -948,10 +978,8 @@ void k_meet(const QueryDesc *__restrict__ qd, int32_t nq,
                             const uint32_t k = min(ck + rank, Ku - 1u);
                             const uint32_t jl = s_jl[k], off = s_off[k];
                             uint32_t end = off + (jl >> 24) + ((cvl << 16) - 1u);
-                            if (STITCHED) {
-                                const uint32_t seg_len = (uint32_t)d.ix.seg_len;
-                                if (jl >> 24 > seg_len) end = (off + seg_len + ((cvl << 16) - 1u)) | HEAD_ONLY;
-                            }
+                            if (STITCHED && jl >> 24 > head_len)
+                                end = (off + head_len + ((cvl << 16) - 1u)) | HEAD_ONLY;
                             start(sl[qq], mine, off, end, jl & 0xffffffu, k);
                             busy[qq] |= mine;
                             need &= ~mine;

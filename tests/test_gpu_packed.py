@@ -61,8 +61,8 @@ def others():
 # and one more (there R is such that small tiles are several)
 @pytest.mark.parametrize("slots, hubs, hub_deg", [
     (4000, 0, 0), (524288, 3, 8191), (524289, 3, 4095), (700001, 255, 2000), (1048577, 5, 2047),
-    (2097153, 3, 1023), (2097153, 768, 1024), (2097153, 769, 1024), (2097153, 1280, 1024),
-    (2097153, 1281, 1024), (4194305, 6912, 512), (4194305, 6913, 512)])
+    (2097153, 3, 1023), (2097153, 704, 1024), (2097153, 705, 1024), (2097153, 1216, 1024),
+    (2097153, 1217, 1024), (4194305, 6848, 512), (4194305, 6849, 512)])
 def test_packed_rows_equal_oracle(slots, hubs, hub_deg, others):
     print(f"packed: {slots} slots, {hubs} nodes of in-degree {hub_deg}", flush=True)
     g = _graph(slots, hubs, hub_deg, slots + hubs)
@@ -94,7 +94,7 @@ def test_packed_rows_equal_oracle(slots, hubs, hub_deg, others):
 # E and packed rows, with as many hubs as the stratified kernel has rows for and
 # one more
 @pytest.mark.parametrize("slots, hubs, hub_deg", [
-    (524288, 3, 8191), (524289, 3, 4095), (2097153, 1536, 1024), (2097153, 1537, 1024)])
+    (524288, 3, 8191), (524289, 3, 4095), (2097153, 1472, 1024), (2097153, 1473, 1024)])
 def test_packed_rows_stratified_equal_oracle(slots, hubs, hub_deg, others):
     print(f"packed, stratified: {slots} slots, {hubs} nodes of in-degree {hub_deg}", flush=True)
     g = _graph(slots, hubs, hub_deg, slots + hubs)
