@@ -370,29 +370,30 @@ int launch_groups(const GroupSet &gs, unsigned long long *counters, hipStream_t 
 
 // ------------------------------------------------------------ serving ring
 // The server's in-flight requests (server.hip) sit in a ring of entries that
-// persistent meet kernels take work units from.  An entry's `claim` word holds
-// everything a block needs to decide whether it may take units from it:
-//   claim = (seq << 2 | kind) << 32 | units not yet claimed,
-// so availability, kind and age come from one atomic read, never from fields
-// that a reuse of the entry may be rewriting.  An entry is published by the
-// last kernel of its request's preparation: the other fields first, then
-// `claim` with all n_units units unclaimed (release).  A block takes up to a
-// run of units by moving the count down with compare-and-swap (acquire), then
-// reads n_units (the first unit it took is n_units minus the count it saw).
-// A swap cannot succeed on an older request's word once the entry has been
-// reused (seq differs), and a fully claimed word (count 0) is never a
-// candidate.  The block that finishes the entry's last unit writes the
-// estimate and then the entry's flag in host memory (the request's seq).
+// persistent meet kernels take work units from.  An entry has a claim word per
+// kind, which holds everything a block needs to decide whether it may take units:
+//   claim[kind] = seq << 32 | CLAIM_ZERO + units not yet claimed,
+// so availability and age come from one atomic read, never from fields that a
+// reuse of the entry may be rewriting.  An entry is published by the last kernel
+// of its request's preparation: the other fields first, then its kind's word with
+// all n_units units unclaimed (release).  A block that sees a word above
+// CLAIM_ZERO takes up to a run of units by an atomic subtraction (acquire), and
+// has those that the word it returns says were left: of that request, or of a
+// later one of the kind if the entry has been published again since; none if it
+// is CLAIM_ZERO or below, to which blocks that came too late move it (by a run
+// each, far less than CLAIM_ZERO).  It then reads n_units, which stays until its
+// units are finished (the first unit it took is n_units minus those left).  An
+// entry published again as another kind leaves this kind's word exhausted.  The
+// block that finishes the entry's last unit writes the estimate and then the
+// entry's flag in host memory (the request's seq).
 // seq is nonzero and below 2^30.
+constexpr uint32_t CLAIM_ZERO = 1u << 20;
 constexpr int RING_MAX = 64;
 constexpr uint32_t RING_SEQ_LIMIT = 1u << 30;
 struct RingCtl {
-    unsigned long long claim;   // see above; 0 = never published
+    unsigned long long claim[N_KINDS];   // see above; 0 = never published
     uint32_t n_units;           // tiles x node chunks of the request
     uint32_t done;              // units finished
-    int32_t kind;               // Kind of the meet kernel that takes it
-    uint32_t seq;               // the request's sequence number
-    uint32_t pad[2];
 };
 struct StreamRing {
     QueryDesc *desc;                 // device [RING_MAX]
