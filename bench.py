@@ -37,7 +37,8 @@ METRIC = "walk-steps/s + single-source queries/s at eps=0.02; batched vs plain, 
 HBM_PEAK_GBS = 8000.0
 # Algorithmic bytes per walk step: reading the current node's row (offset and
 # degree, 8 bytes) and one edge of it (4 bytes).  The library's gather layout
-# reads the two as one 8-byte slot per step; that figure is reported beside.
+# reads the two as one 8-byte slot per step (packed in 4 bytes where the slots
+# exceed the L2); the figure of 8 is reported beside.
 BYTES_PER_MOVE = 12
 BYTES_PER_MOVE_GATHERED = 8
 # Host threads for the threaded CPU baseline: the host share of one GPU.
@@ -323,7 +324,7 @@ def main():
                             "profiles/traffic_meet_medium.json") if traffic else None),
     }
     result["roofline"]["bound_detail"] = (
-        "the graph's 133 MB gather array sits in the 256 MB Infinity Cache; the kernel is "
+        "the graph's packed rows (66 MB) sit in the 256 MB Infinity Cache; the kernel is "
         "limited by the rate of random 128-byte line requests the memory system serves "
         "(measured_roofs.line_requests_vs_random_gather), not by HBM bytes")
 
@@ -368,7 +369,7 @@ def main():
 
     if not args.no_roofs:
         info = G.info()
-        slots_bytes = 8 * (info["m"] + info["n"] - info["n_active"])
+        slots_bytes = 4 * (info["m"] + info["n"] - info["n_active"])   # packed rows
         gi = S.simrank_roofline_gather(slots_bytes, 8, dependent=False)
         gd = S.simrank_roofline_gather(slots_bytes, 8, dependent=True)
         # the same gathers from half the CUs, and from one wave per CU: the rate
