@@ -203,6 +203,7 @@ struct QueryDesc {
     uint32_t T;            // continue threshold
     int32_t n, n_active, s, R, L;
     int32_t vb;            // nodes per work unit at most (<= MEET_VB); 0: sized on the device
+    uint32_t cost;         // of a pair, for the sizes of units (pair_cost)
     int32_t kind;          // Kind
     int32_t items;         // items a wave takes at once, at most (item_chunk)
     int32_t tile_j;        // source walks per LDS tile, MIN_TILE_J .. tile_j_of(kind)
@@ -481,6 +482,9 @@ int query_params(const simrank_query *q, int32_t n, simrank_params *out, int *mo
 // Stratified estimator: z, N, phi, shuffle width and (if tab) the class table.
 int strat_params(const simrank_query *q, int32_t n, StratParams *sp, StratTab *tab);
 int32_t max_tiles_for(int32_t R, int32_t L);
+// What a pair of stitched walks costs on average, 1 at least: the steps of its
+// tail behind a head of `head` steps, in the 1.5 steps of a plain pair at c = 0.6.
+uint32_t pair_cost(double c, int32_t L, int32_t head);
 // Nodes per unit that the unit counts of a query are bounded with; a graph that
 // was not tuned has its units sized on the device (lay_units, query.hip).
 int32_t default_unit_nodes(const Graph *g);

@@ -265,16 +265,22 @@ __device__ void make_tiles(const QueryDesc &d, int lane) {
 // in-edges; a persistent block takes one at a time.  A unit costs a block 10
 // to 25 us beside its pairs (claim, staging, the wait for its longest pair),
 // and the grid waits for the block that ends last.  Unless the graph was
-// tuned, the units of a launch therefore all hold about the same number of
-// pairs, such that every block of the grid takes a whole number of rounds of
-// them: one round per 2^27 pairs (about 0.5 ms of work), 16 at most, more only
-// where MEET_VB nodes a unit ask for it.  Meet kernel, with units of a fixed
+// tuned, the units of a launch therefore all hold about the same work, such
+// that every block of the grid takes a whole number of rounds of them: one
+// round per 2^27 pairs (about 0.5 ms), 16 at most, more only where MEET_VB nodes
+// a unit ask for it.  A pair of stitched walks counts as several where its tail
+// is long (pair_cost; up to 32 rounds then): tails are of very different lengths,
+// and long units of them end far apart (c = 0.95, R = 2,000, segments of 1 and 4
+// steps: counted as one and as several, n = 20,000: 8.64 and 6.80 ms, 6.09 and
+// 5.55; n = 2^18: 154.4 and 153.4, 105.2 and 104.0).  Plain and
+// stratified pairs count as one at any c: at c = 0.95 and 255 steps several rounds
+// instead of one take 3.07 and 4.08 ms, one 2.85 and 3.67.  Meet kernel, with units of a fixed
 // number of nodes by graph size (256 from 2^19 nodes with in-edges, 128, 64,
 // 32 below) and with this rule: n = 500, R = 2,000: 96 and 32 us; n = 5,003,
 // R = 1,521: 98 and 61; R = 9,502: 404 and 264; n = 40,000, R = 1,521: 386 and
 // 303; R = 9,502: 1,738 and 1,680; n = 150,001, R = 9,502: 6,108 and 6,061;
 // n = 2^18: 11.56 and 11.65 ms; n = 2^20: 50.3 ms both.
-constexpr int UNIT_ROUNDS_LOG2_PAIRS = 27, UNIT_MAX_ROUNDS = 16;
+constexpr int UNIT_ROUNDS_LOG2_WORK = 27, UNIT_MAX_ROUNDS = 16, UNIT_MAX_ROUNDS_TAILS = 32;
 
 // First unit of each tile and, behind them, the number of units: kept where a
 // group member has its source walks' lengths.
@@ -284,55 +290,63 @@ __device__ __forceinline__ uint32_t *tunits_of(const QueryDesc &d) {
     return reinterpret_cast<uint32_t *>(d.slen);
 }
 
-// Rounds of units that a launch of `pairs` pairs on `grid` blocks is cut into,
-// its largest tile holding km walks.
-__device__ __forceinline__ uint64_t unit_rounds(uint64_t pairs, uint32_t km, uint32_t grid) {
-    const uint64_t by_work = (pairs + ((1ull << UNIT_ROUNDS_LOG2_PAIRS) - 1)) >> UNIT_ROUNDS_LOG2_PAIRS;
-    const uint64_t rounds = by_work < 1 ? 1 : by_work > UNIT_MAX_ROUNDS ? UNIT_MAX_ROUNDS : by_work;
-    const uint64_t full = (uint64_t)MEET_VB * max(km, 1u) * grid;   // a round of full units
-    const uint64_t least = (pairs + full - 1) / full;
+// Work of nodes x walks pairs of query d (below 2^62: 2^31 nodes, 2^24 walks, a
+// cost of 43).
+__device__ __forceinline__ uint64_t work_of(const QueryDesc &d, uint32_t nodes, uint32_t walks) {
+    return (uint64_t)nodes * walks * d.cost;
+}
+
+// Rounds of units that a launch of `work` on `grid` blocks is cut into, its
+// dearest pair costing `cost` and its largest full unit holding `most` of the
+// work (MEET_VB nodes of its largest tile).
+__device__ __forceinline__ uint64_t unit_rounds(uint64_t work, uint32_t cost, uint64_t most, uint32_t grid) {
+    const uint64_t limit = cost > 1 ? UNIT_MAX_ROUNDS_TAILS : UNIT_MAX_ROUNDS;
+    const uint64_t by_work = (work + ((1ull << UNIT_ROUNDS_LOG2_WORK) - 1)) >> UNIT_ROUNDS_LOG2_WORK;
+    const uint64_t rounds = by_work < 1 ? 1 : by_work > limit ? limit : by_work;
+    const uint64_t full = (most < 1 ? 1 : most) * grid;   // a round of full units
+    const uint64_t least = (work + full - 1) / full;
     return rounds < least ? least : rounds;
 }
 
-__device__ __forceinline__ uint64_t pairs_each(uint64_t pairs, uint64_t units) {
-    const uint64_t per = units ? (pairs + units - 1) / units : pairs;
+__device__ __forceinline__ uint64_t work_each(uint64_t work, uint64_t units) {
+    const uint64_t per = units ? (work + units - 1) / units : work;
     return per < 1 ? 1 : per;
 }
 
-// Pairs per unit of the queries of a kind in qd[0 .. nq).  A tile of few walks
-// reaches MEET_VB nodes a unit below the common number of pairs, so it has more
-// units than its share; the other tiles then take that many fewer.  Called by
-// all lanes of one wave; results uniform.
-__device__ uint64_t unit_pairs(const QueryDesc *qd, int32_t nq, int32_t kind, uint64_t pairs,
-                               uint32_t km, uint32_t grid, int lane) {
-    uint64_t units = unit_rounds(pairs, km, grid) * grid;
-    uint64_t per = pairs_each(pairs, units);
+// Work per unit of the queries of a kind in qd[0 .. nq).  A tile of few walks
+// reaches MEET_VB nodes a unit below the common work, so it has more units than
+// its share; the other tiles then take that many fewer.  Called by all lanes of
+// one wave; results uniform.
+__device__ uint64_t unit_work(const QueryDesc *qd, int32_t nq, int32_t kind, uint64_t work,
+                              uint32_t cost, uint64_t most, uint32_t grid, int lane) {
+    uint64_t units = unit_rounds(work, cost, most, grid) * grid;
+    uint64_t per = work_each(work, units);
     for (int it = 0; it < 3; ++it) {
-        unsigned long long small_pairs = 0, small_units = 0;
+        unsigned long long small_work = 0, small_units = 0;
         for (int32_t q = 0; q < nq; ++q) {
             if (qd[q].kind != kind) continue;
             const uint32_t n = (uint32_t)qd[q].n_active, nt = qd[q].meta[2];
             const uint64_t least = (n + MEET_VB - 1) / MEET_VB;
             for (uint32_t t = (uint32_t)lane; t < nt; t += 64) {
-                const uint64_t p = (uint64_t)n * (tiles_of(qd[q])[t + 1] - tiles_of(qd[q])[t]);
+                const uint64_t p = work_of(qd[q], n, tiles_of(qd[q])[t + 1] - tiles_of(qd[q])[t]);
                 if (p < least * per) {
-                    small_pairs += p;
+                    small_work += p;
                     small_units += least;
                 }
             }
         }
         for (int dd = 32; dd > 0; dd >>= 1) {
-            small_pairs += __shfl_xor(small_pairs, dd, 64);
+            small_work += __shfl_xor(small_work, dd, 64);
             small_units += __shfl_xor(small_units, dd, 64);
         }
-        if (small_units == 0ull || small_pairs >= pairs) break;
+        if (small_units == 0ull || small_work >= work) break;
         while (units < small_units + grid / 2) units += grid;   // room for the others
-        per = pairs_each(pairs - small_pairs, units - small_units);
+        per = work_each(work - small_work, units - small_units);
     }
     return per;
 }
 
-// Lays the units of query d, `per` pairs each where the graph is not tuned:
+// Lays the units of query d, of work `per` each where the graph is not tuned:
 // writes the first unit of each tile and returns their number.  Called by all
 // lanes of one wave.
 __device__ uint32_t lay_units(const QueryDesc &d, uint64_t per, int lane) {
@@ -345,7 +359,7 @@ __device__ uint32_t lay_units(const QueryDesc &d, uint64_t per, int lane) {
         if (t < nt) {
             c = (n + vb - 1) / vb;
             if (d.vb <= 0 && n) {
-                const uint64_t want = (uint64_t)n * (tiles_of(d)[t + 1] - tiles_of(d)[t]) / per;
+                const uint64_t want = work_of(d, n, tiles_of(d)[t + 1] - tiles_of(d)[t]) / per;
                 c = max(c, (uint32_t)min(want, (uint64_t)n));
             }
         }
@@ -375,11 +389,11 @@ __global__ __launch_bounds__(64) void k_tiles(const QueryDesc *__restrict__ qd) 
 __global__ __launch_bounds__(1024) void k_unit_offsets(const QueryDesc *__restrict__ qd, int32_t nq,
                                                        uint32_t *units, uint3 grid,
                                                        unsigned long long *counters) {
-    __shared__ unsigned long long s_pairs[N_KINDS], s_per[N_KINDS];
-    __shared__ uint32_t s_km[N_KINDS];
+    __shared__ unsigned long long s_work[N_KINDS], s_most[N_KINDS], s_per[N_KINDS];
+    __shared__ uint32_t s_cost[N_KINDS];
     if (threadIdx.x < N_KINDS) {
-        s_pairs[threadIdx.x] = 0ull;
-        s_km[threadIdx.x] = 0u;
+        s_work[threadIdx.x] = s_most[threadIdx.x] = 0ull;
+        s_cost[threadIdx.x] = 0u;
     }
     for (int32_t q = threadIdx.x >> 6; nq <= TILES_IN_UNITS && q < nq; q += (int32_t)(blockDim.x >> 6))
         if (qd[q].kind < N_KINDS) make_tiles(qd[q], (int)(threadIdx.x & 63));
@@ -387,17 +401,18 @@ __global__ __launch_bounds__(1024) void k_unit_offsets(const QueryDesc *__restri
     for (int32_t q = threadIdx.x; q < nq; q += blockDim.x) {
         const int32_t kind = qd[q].kind;
         if (kind >= N_KINDS) continue;
-        atomicAdd(&s_pairs[kind], (unsigned long long)qd[q].meta[0] * (unsigned long long)qd[q].n_active);
-        atomicMax(&s_km[kind], qd[q].meta[3]);
+        atomicAdd(&s_work[kind], (unsigned long long)work_of(qd[q], (uint32_t)qd[q].n_active, qd[q].meta[0]));
+        atomicMax(&s_cost[kind], qd[q].cost);
+        atomicMax(&s_most[kind], (unsigned long long)work_of(qd[q], MEET_VB, qd[q].meta[3]));
     }
     __syncthreads();
     if (threadIdx.x < 64 * N_KINDS) {
         // (many queries in one launch have units of all sizes: their common
-        // number of pairs is not refined)
+        // work is not refined)
         const int kind = (int)(threadIdx.x >> 6);
-        const uint64_t p = unit_pairs(qd, nq <= 16 ? nq : 0, kind, s_pairs[kind], s_km[kind],
-                                      kind == 0 ? grid.x : kind == 1 ? grid.y : grid.z,
-                                      (int)(threadIdx.x & 63));
+        const uint64_t p = unit_work(qd, nq <= 16 ? nq : 0, kind, s_work[kind], s_cost[kind],
+                                     s_most[kind], kind == 0 ? grid.x : kind == 1 ? grid.y : grid.z,
+                                     (int)(threadIdx.x & 63));
         if ((threadIdx.x & 63) == 0) s_per[kind] = p;
     }
     __syncthreads();
@@ -449,9 +464,9 @@ __global__ __launch_bounds__(64) void k_units_one(QueryDesc d, uint32_t *__restr
             n_units = (n + most - 1) / most;
             if (d.vb <= 0) {
                 // (rounds enough for full units: no tile is smaller than the others)
-                const uint64_t pairs = (uint64_t)n * R1;
-                const uint64_t per = pairs_each(pairs, unit_rounds(pairs, R1, blocks) * blocks);
-                n_units = max(n_units, (uint32_t)min(pairs / per, (uint64_t)n));
+                const uint64_t work = work_of(d, n, R1);
+                const uint64_t per = work_each(work, unit_rounds(work, d.cost, work_of(d, MEET_VB, R1), blocks) * blocks);
+                n_units = max(n_units, (uint32_t)min(work / per, (uint64_t)n));
             }
         }
         if (lane == 0) {
@@ -465,8 +480,8 @@ __global__ __launch_bounds__(64) void k_units_one(QueryDesc d, uint32_t *__restr
         }
     } else {
         make_tiles(d, lane);
-        const uint64_t pairs = (uint64_t)R1 * n;
-        n_units = lay_units(d, unit_pairs(&d, 1, d.kind, pairs, d.meta[3], blocks, lane), lane);
+        n_units = lay_units(d, unit_work(&d, 1, d.kind, work_of(d, n, R1), d.cost, work_of(d, MEET_VB, d.meta[3]),
+                                         blocks, lane), lane);
     }
     if (lane < N_KINDS) {
         units[lane * 2] = 0u;
@@ -1258,9 +1273,9 @@ __global__ __launch_bounds__(256) void k_publish(StreamRing ring, int32_t slot, 
     __shared__ uint32_t s_nu;
     if (threadIdx.x < 64) {
         make_tiles(d, (int)threadIdx.x);
-        const uint64_t pairs = (uint64_t)d.meta[0] * (uint64_t)(uint32_t)d.n_active;
         const uint32_t nu = lay_units(
-            d, unit_pairs(&d, 1, d.kind, pairs, d.meta[3], grid, (int)threadIdx.x), (int)threadIdx.x);
+            d, unit_work(&d, 1, d.kind, work_of(d, (uint32_t)d.n_active, d.meta[0]), d.cost,
+                         work_of(d, MEET_VB, d.meta[3]), grid, (int)threadIdx.x), (int)threadIdx.x);
         if (threadIdx.x == 0) s_nu = nu;
     }
     __syncthreads();
@@ -1336,6 +1351,11 @@ static int32_t items_for(const Graph *g) {
     return e <= (int64_t)8 << 20 ? 256 : e <= (int64_t)24 << 20 ? 128 : 64;
 }
 
+uint32_t pair_cost(double c, int32_t L, int32_t head) {
+    const double tail = pow(c, (double)head) * std::min(c / (1.0 - c), (double)std::max(L - head, 0));
+    return (uint32_t)std::max(1.0, floor(tail / 1.5 + 0.5));
+}
+
 void describe_query(const Graph *g, const simrank_query *q, const simrank_params &p, int mode,
                     QueryDesc *d) {
     *d = QueryDesc{};
@@ -1360,6 +1380,7 @@ void describe_query(const Graph *g, const simrank_query *q, const simrank_params
     d->items = items_for(g);
     d->kind = mode == SIMRANK_MODE_STITCHED ? K_STITCHED
               : mode == SIMRANK_MODE_STRATIFIED ? K_STRAT : K_PLAIN;
+    d->cost = d->kind == K_STITCHED ? pair_cost(q->c, p.L, d->ix.seg_len) : 1u;
     const int32_t tj = g->tuned_tile_j[d->kind];
     d->tile_nodes = tile_nodes_for(*g, d->kind, p.R, p.L);
     d->tile_j = tj > 0 ? std::min<int32_t>(tj, tile_j_of(d->kind)) : tile_j_of(d->kind);

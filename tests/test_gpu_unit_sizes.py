@@ -1,0 +1,51 @@
+"""Sizes of the meet kernels' work units: the blocks of a launch must end together.
+
+Times are the least of several runs on the device's clock, compared within one
+process; the bounds lie between what equal and unequal units take.  Counts are
+integers and must equal the CPU oracle's bit for bit.
+"""
+import numpy as np
+import pytest
+
+import oracle as O
+from paper_2304_04015_amd import inputs
+from paper_2304_04015_amd import simrank as S
+
+pytestmark = pytest.mark.gpu
+
+SEED, ISEED = 21, 9
+
+
+def _meet_ms(G, q, runs=7):
+    return min(S.simrank_single_source_ex(G, q)[2].meet_ms for _ in range(runs))
+
+
+# Pairs with long tails (c = 0.95, segments of one step) take several rounds of
+# units where short ones take one.  The bound lies between one round's time, 1.12
+# times that of units of 32 nodes, and several's, 0.96.
+def test_long_walks_take_units_of_their_length():
+    g = inputs.erdos_renyi_in(20000, 8.0, seed=1)
+    G = S.load_csr(g)
+    S.simrank_build_index(G, seg_log2=0, kappa=1.0, c=0.95, seed=ISEED)
+    q = S.make_query(1, c=0.95, seed=SEED, R=2000, mode=S.MODE_STITCHED)
+    auto = _meet_ms(G, q)
+    S.simrank_set_tuning(G, 32, 0)
+    fixed = _meet_ms(G, q)
+    print(f"long walks: {auto:.3f} ms, units of 32 nodes {fixed:.3f}", flush=True)
+    assert auto < 1.04 * fixed
+    G.free()
+
+
+# one block's worth of work and several rounds of it, lone and beside a query of
+# short walks
+@pytest.mark.parametrize("n, R, c, L", [(1, 5, 0.95, 255), (300, 700, 0.99, 255), (20000, 1521, 0.95, 64)])
+def test_long_walks_equal_oracle(n, R, c, L):
+    g = inputs.erdos_renyi_in(n, 3.0, seed=n)
+    G = S.load_csr(g)
+    vs = np.unique(np.linspace(0, n - 1, 40).astype(np.int32))
+    qs = [S.make_query(0, c=c, seed=SEED, walk_cap=L, R=R), S.make_query(n - 1, seed=SEED, R=R)]
+    want = [O.meet_counts_plain(g, 0, SEED, c, L, R, vs), O.meet_counts_plain(g, n - 1, SEED, 0.6, 64, R, vs)]
+    assert np.array_equal(S.simrank_single_source_ex(G, qs[0])[1][vs], want[0])
+    for cnt, w in zip(S.simrank_batch([G], qs)[1], want):
+        assert np.array_equal(cnt[vs], w)
+    G.free()
