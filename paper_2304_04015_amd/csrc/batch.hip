@@ -272,10 +272,17 @@ extern "C" int simrank_batch_plan_create_ex(simrank_graph *const *graphs, int32_
                      : d.kind == K_STRAT  ? K_GROUPED_STRAT : K_GROUPED;
         } else {
             set.units_bound[d.kind] += units_bound_of(g, pp.R, pp.L);
-            // (small tiles could make the units twice as many)
-            if (kind_units[d.kind] >= (int64_t)1 << 30) d.tile_nodes = tile_nodes_of(d.kind);
-            set.rows[d.kind] |= rows_wish(*g, d);
         }
+    }
+    for (int k = 0; k < N_KINDS; ++k) {
+        std::vector<const Graph *> gk;
+        std::vector<QueryDesc *> dk;
+        for (int32_t i = 0; i < nq; ++i) {
+            if (p->desc[i].kind != k) continue;
+            gk.push_back(p->graphs[i]);
+            dk.push_back(&p->desc[i]);
+        }
+        set.rows[k] = settle_tiles(gk.data(), dk.data(), dk.size(), kind_units[k]);
     }
     GroupSet gset;
     p->gdesc.resize(ngr);

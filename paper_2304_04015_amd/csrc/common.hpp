@@ -250,6 +250,24 @@ inline int32_t tile_nodes_for(const Graph &g, int kind, int32_t R, int32_t L) {
                ? HUB_TILE_NODES : tile_nodes_of(kind);
 }
 
+// Settles the tiles of a launch's queries of one kind (`units` of them nominally)
+// and returns their wishes.  Small tiles are for launches that read packed rows
+// with them.  A graph with many hubs beside others is gathered from E, where they
+// cost time (a query at n = 2^20, R = 9,502, 6,256 hubs, with one at n = 5,000: 50.4
+// ms with 12,288 positions a tile, 49.6 with 24,576; with one at n = 150,000: 60.4 and
+// 59.4); and they make the units up to twice as many.
+inline int settle_tiles(const Graph *const *g, QueryDesc *const *d, size_t nq, int64_t units) {
+    int wishes = 0;
+    for (size_t i = 0; i < nq; ++i) wishes |= rows_wish(*g[i], *d[i]);
+    if (!(wishes & WANTS_HUBS) || (rows_of(wishes) == ROWS_HUBS && units < (int64_t)1 << 30)) return wishes;
+    wishes = 0;
+    for (size_t i = 0; i < nq; ++i) {
+        d[i]->tile_nodes = tile_nodes_of(d[i]->kind);
+        wishes |= rows_wish(*g[i], *d[i]);
+    }
+    return wishes;
+}
+
 // A set of queries whose descriptors are already in device memory.
 struct QuerySet {
     const QueryDesc *desc;        // device [nq]
