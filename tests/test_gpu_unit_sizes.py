@@ -49,3 +49,21 @@ def test_long_walks_equal_oracle(n, R, c, L):
     for cnt, w in zip(S.simrank_batch([G], qs)[1], want):
         assert np.array_equal(cnt[vs], w)
     G.free()
+
+
+# Two tiles of source walks, the second of so few that its units reach the most
+# nodes, and beside it queries of less than a round: in front, behind, both.
+@pytest.mark.parametrize("order", [(0, 1), (1, 0), (1, 0, 2), (0, 1, 2)])
+def test_small_queries_beside_one_of_unequal_tiles(order):
+    gs = [inputs.erdos_renyi_in(60000, 8.0, seed=2), inputs.erdos_renyi_in(700, 5.0, seed=3),
+          inputs.erdos_renyi_in(2500, 5.0, seed=4)]
+    Gs, Rs = [S.load_csr(g) for g in gs], [7000, 9502, 900]
+    qs = [S.make_query(3, seed=SEED + i, R=Rs[i], graph=i) for i in order]
+    cnts = S.simrank_batch(Gs, qs)[1]
+    for i, cnt in zip(order, cnts):
+        vs = np.unique(np.linspace(0, gs[i].n - 1, 60).astype(np.int32))
+        assert np.array_equal(cnt[vs], O.meet_counts_plain(gs[i], 3, SEED + i, 0.6, 64, Rs[i], vs)), i
+        lone = S.simrank_single_source_ex(Gs[i], S.make_query(3, seed=SEED + i, R=Rs[i]))[1]
+        assert np.array_equal(cnt, lone), i
+    for G in Gs:
+        G.free()
