@@ -118,7 +118,7 @@ struct Graph {
     uint2 *nodes = nullptr;       // [n]     (o(v), deg(v))
     uint2 *E = nullptr;           // [m_slots]
     uint32_t *E4 = nullptr;       // [m_slots] E packed for the meet kernels (graph.hip), or NULL
-    uint2 *hubs = nullptr;        // [HUB_CAP] rows of the nodes whose degree E4 cannot hold
+    uint2 *hubs = nullptr;        // [n_hubs] rows of the nodes whose degree E4 cannot hold
     int32_t obits = 0;            // bits of o() in an E4 entry; 0: there is no E4
     int32_t n_hubs = 0;
     uint32_t *node_of = nullptr;  // [m_slots] node id owning slot o (valid at o(v))

@@ -32,7 +32,7 @@ namespace {
 struct PackArgs {
     uint32_t *E4;
     uint32_t obits;
-    uint2 *hubs;                  // [HUB_CAP]
+    uint2 *hubs;                  // one for each of them
     uint32_t *hub_at;             // [n] place of a node that is a hub
     unsigned long long *last_hub;   // place of the last hub, -1 before
 };
@@ -61,7 +61,7 @@ __global__ void k_nodes(const int32_t *__restrict__ off, const int64_t *__restri
     if (d == 0) pk.E4[o[v]] = 0u;
     if ((uint32_t)d >= 0xffffffffu >> pk.obits) {
         const unsigned long long k = atomicAdd(pk.last_hub, 1ull) + 1ull;
-        if (k < HUB_CAP) pk.hubs[k] = make_uint2((uint32_t)o[v], (uint32_t)d);
+        pk.hubs[k] = make_uint2((uint32_t)o[v], (uint32_t)d);
         pk.hub_at[v] = (uint32_t)k;
     }
 }
@@ -229,12 +229,16 @@ extern "C" int simrank_load_graph(int32_t n, int64_t m, const int32_t *in_off,
     if (in_off[0] != 0) return fail(SIMRANK_EINVAL, "in_off[0] must be 0");
     int32_t max_deg = 0;
     int32_t n_active = 0;
-    for (int32_t v = 0; v < n; ++v) {
-        const int64_t d = (int64_t)in_off[v + 1] - in_off[v];
-        if (d < 0) return fail(SIMRANK_EINVAL, "in_off decreases at row " + std::to_string(v));
-        if (d > max_deg) max_deg = (int32_t)d;
+    bool falls = false;
+    for (int32_t v = 0; v < n; ++v) {   // (no exit: vectorised)
+        const int32_t d = (int32_t)((uint32_t)in_off[v + 1] - (uint32_t)in_off[v]);
+        falls |= in_off[v + 1] < in_off[v];
+        max_deg = d > max_deg ? d : max_deg;
         n_active += d > 0;
     }
+    for (int32_t v = 0; falls && v < n; ++v)
+        if (in_off[v + 1] < in_off[v])
+            return fail(SIMRANK_EINVAL, "in_off decreases at row " + std::to_string(v));
     if ((int64_t)in_off[n] != m) return fail(SIMRANK_EINVAL, "in_off[n] != m");
     // The sources are checked by the kernel that reads them; here where there
     // is no device to do it.
@@ -279,11 +283,15 @@ extern "C" int simrank_load_graph(int32_t n, int64_t m, const int32_t *in_off,
         // E, node_of and the packed rows in one piece (a free of its own for each
         // took 0.3 ms at n = 300,007); a graph that leaves no room for the packed
         // rows does without them
-        const int32_t obits = pack_bits(g->m_slots);
-        const bool may_hub = obits && (uint32_t)max_deg >= 0xffffffffu >> obits;
+        int32_t obits = pack_bits(g->m_slots);
+        int64_t hubs = 0;
+        const uint32_t most = 0xffffffffu >> obits;
+        if (obits && (uint32_t)max_deg >= most)
+            for (int32_t v = 0; v < n; ++v) hubs += (uint32_t)in_off[v + 1] - (uint32_t)in_off[v] >= most;
+        if (hubs > (int64_t)HUB_CAP) obits = 0;   // (before memory is taken that nothing would read)
         const size_t sE = align256(sizeof(uint2) * (size_t)g->m_slots);
         const size_t s4 = align256(sizeof(uint32_t) * (size_t)g->m_slots);
-        const size_t packed = obits ? s4 + (may_hub ? sizeof(uint2) * HUB_CAP : 0) : 0;
+        const size_t packed = obits ? s4 + sizeof(uint2) * (size_t)hubs : 0;
         rc = device_alloc((void **)&g->E, sE + s4 + packed, &g->bytes);
         const bool pack = packed && rc == SIMRANK_OK;
         if (packed && !pack) {
@@ -335,9 +343,11 @@ extern "C" int simrank_load_graph(int32_t n, int64_t m, const int32_t *in_off,
             rc = fail(SIMRANK_EDEVICE, "ingest totals disagree with the host count");
             goto bad;
         }
-        const int64_t hubs = tot[3] + 1;
-        // (no more than HUB_CAP have a row; with more, E4 stays unused)
-        if (pack && hubs <= (int64_t)HUB_CAP) {
+        if (pack) {
+            if (tot[3] + 1 != hubs) {
+                rc = fail(SIMRANK_EDEVICE, "ingest hubs disagree with the host count");
+                goto bad;
+            }
             g->obits = obits;
             g->n_hubs = (int32_t)hubs;
         }
