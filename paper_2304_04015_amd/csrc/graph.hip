@@ -86,7 +86,15 @@ __global__ void k_fill_u32(uint32_t *__restrict__ p, int64_t n, uint32_t val) {
 // (4.5e6 edges) took 2.23 ms and one of n = 2^22 (6.5e7 edges) 30.8; now 1.35
 // and 17.5, k_edges 0.21 and 2.76 of them (257 us and, at n = 2^20, 855 before,
 // 713 now: the atomics on distinct nodes remain).
+//
+// Between the edges of a tile may lie a great many rows without any, which one
+// block would go through 256 at a time: with more than EDGE_GAP rows per edge
+// (edges counted as 256 at least) each edge's row is searched for among them.
+// Loading a graph of one tile of 4,096 edges and 2^14 / 2^15 / 2^16 / 2^18 / 2^20
+// rows: 208 / 234 / 295 / 714 / 2,535 us gone through, 215 / 230 / 263 / 491 / 1,479
+// searched; of 1,000 edges and 2^13 / 2^14 / 2^16: 174 / 200 / 290 and 168 / 188 / 243.
 constexpr int EDGE_BLOCK = 256, EDGE_ITEMS = 16, EDGE_TILE = EDGE_BLOCK * EDGE_ITEMS;
+constexpr int32_t EDGE_GAP = 16;
 constexpr uint32_t EDGE_HASH = 2048;
 __global__ __launch_bounds__(EDGE_BLOCK) void k_edges(const int32_t *__restrict__ off,
                                                       const int32_t *__restrict__ src, int32_t n,
@@ -105,23 +113,24 @@ __global__ __launch_bounds__(EDGE_BLOCK) void k_edges(const int32_t *__restrict_
         s_key[i] = NIL;
         s_cnt[i] = 0u;
     }
-    // the last row that starts at or before edge e
-    auto row_of = [&](int64_t e) {
-        int32_t lo = 0, hi = n;
+    // the last row of [lo, hi) that starts at or before edge e
+    auto row_of = [&](int64_t e, int32_t lo, int32_t hi) {
         while (hi - lo > 1) {
             const int32_t mid = lo + ((hi - lo) >> 1);
             if ((int64_t)off[mid] <= e) lo = mid; else hi = mid;
         }
         return lo;
     };
-    const int32_t v0 = row_of(e0), v1 = row_of(e0 + cnt - 1);
+    const int32_t v0 = row_of(e0, 0, n), v1 = row_of(e0 + cnt - 1, v0, n);
     __syncthreads();
-    if (threadIdx.x == 0) s_row[0] = v0;
-    __syncthreads();
-    for (int32_t v = v0 + 1 + (int32_t)threadIdx.x; v <= v1; v += EDGE_BLOCK)
-        atomicMax(&s_row[(int64_t)off[v] - e0], v);
-    __syncthreads();
-    {
+    if (v1 - v0 > EDGE_GAP * max(cnt, EDGE_BLOCK)) {
+        for (int32_t i = threadIdx.x; i < cnt; i += EDGE_BLOCK) s_row[i] = row_of(e0 + i, v0, v1 + 1);
+    } else {
+        if (threadIdx.x == 0) s_row[0] = v0;
+        __syncthreads();
+        for (int32_t v = v0 + 1 + (int32_t)threadIdx.x; v <= v1; v += EDGE_BLOCK)
+            atomicMax(&s_row[(int64_t)off[v] - e0], v);
+        __syncthreads();
         const int b = threadIdx.x * EDGE_ITEMS;
         int32_t r[EDGE_ITEMS], run = -1;
 #pragma unroll
