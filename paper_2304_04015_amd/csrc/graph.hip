@@ -72,7 +72,7 @@ __global__ void k_fill_u32(uint32_t *__restrict__ p, int64_t n, uint32_t val) {
         p[i] = val;
 }
 
-// A block lays out EDGE_TILE consecutive edges.  The row that owns each is found
+// A block lays out a tile of consecutive edges.  The row that owns each is found
 // for the tile at once: the rows that start in it mark their first edge in LDS,
 // and a running maximum over the marks gives every edge its row (empty rows
 // share the start of the next and lose to it, the larger).  dbar[u] counts the
@@ -90,12 +90,18 @@ __global__ void k_fill_u32(uint32_t *__restrict__ p, int64_t n, uint32_t val) {
 // Between the edges of a tile may lie a great many rows without any, which one
 // block would go through 256 at a time: with more than EDGE_GAP rows per edge
 // (edges counted as 256 at least) each edge's row is searched for among them.
-// Loading a graph of one tile of 4,096 edges and 2^14 / 2^15 / 2^16 / 2^18 / 2^20
-// rows: 208 / 234 / 295 / 714 / 2,535 us gone through, 215 / 230 / 263 / 491 / 1,479
+// Loading a graph of 4,096 edges and 2^14 / 2^15 / 2^16 / 2^18 / 2^20 rows in one
+// tile: 208 / 234 / 295 / 714 / 2,535 us gone through, 215 / 230 / 263 / 491 / 1,479
 // searched; of 1,000 edges and 2^13 / 2^14 / 2^16: 174 / 200 / 290 and 168 / 188 / 243.
-constexpr int EDGE_BLOCK = 256, EDGE_ITEMS = 16, EDGE_TILE = EDGE_BLOCK * EDGE_ITEMS;
+//
+// A tile is 4,096 edges, or 1,024 up to EDGE_FEW edges, which tiles of 4,096 give to
+// too few blocks: loading 4e4 edges took 213 us with these and takes 196 with the
+// small ones, 1.6e5 280 and 262, 8e5 456 and 451; 4.5e6 1,546 and 1,572.
+constexpr int EDGE_BLOCK = 256;
+constexpr int64_t EDGE_FEW = 1 << 20;
 constexpr int32_t EDGE_GAP = 16;
 constexpr uint32_t EDGE_HASH = 2048;
+template <int EDGE_ITEMS>
 __global__ __launch_bounds__(EDGE_BLOCK) void k_edges(const int32_t *__restrict__ off,
                                                       const int32_t *__restrict__ src, int32_t n,
                                                       int64_t m, const uint2 *__restrict__ nodes,
@@ -103,6 +109,7 @@ __global__ __launch_bounds__(EDGE_BLOCK) void k_edges(const int32_t *__restrict_
                                                       uint32_t *__restrict__ dbar,
                                                       unsigned long long *__restrict__ bad,
                                                       PackArgs pk) {
+    constexpr int EDGE_TILE = EDGE_BLOCK * EDGE_ITEMS;
     __shared__ int32_t s_row[EDGE_TILE];
     __shared__ int32_t s_part[EDGE_BLOCK / 64];
     __shared__ uint32_t s_key[EDGE_HASH], s_cnt[EDGE_HASH];
@@ -337,7 +344,9 @@ extern "C" int simrank_load_graph(int32_t n, int64_t m, const int32_t *in_off,
                                                    g->active, pk);
         if (m) {
             SRK_TRYHIP(hipMemcpyAsync(d_src, in_src, sizeof(int32_t) * (size_t)m, hipMemcpyHostToDevice, st));
-            k_edges<<<grid_for(m, EDGE_TILE), EDGE_BLOCK, 0, st>>>(
+            const int items = m <= EDGE_FEW ? 4 : 16;
+            const auto kernel = m <= EDGE_FEW ? k_edges<4> : k_edges<16>;
+            kernel<<<grid_for(m, EDGE_BLOCK * items), EDGE_BLOCK, 0, st>>>(
                 d_off, d_src, n, m, g->nodes, g->E, g->dbar, (unsigned long long *)(d_tot + 2), pk);
         }
         SRK_TRYHIP(hipGetLastError());

@@ -14,26 +14,34 @@ from paper_2304_04015_amd import simrank as S
 pytestmark = pytest.mark.gpu
 
 
-def _gap(rows, m, seed, where=1):
-    """m edges in four rows, `rows` rows without any behind row number `where`."""
+FEW = 1 << 20     # edges up to which tiles are of 1,024, beyond it of 4,096
+
+
+def _gap(rows, m, seed, where=1, front=0):
+    """m edges in four rows, `rows` rows without any behind row number `where`;
+    `front` edges more in a row in front."""
     rng = np.random.Generator(np.random.PCG64(seed))
-    n = rows + 4
-    at = [i if i <= where else i + rows for i in range(4)]
+    n = rows + 5
+    at = [1 + (i if i <= where else i + rows) for i in range(4)]
     deg = np.zeros(n, np.int64)
+    deg[0] = front
     deg[at] = m // 4
     deg[at[3]] += m - 4 * (m // 4)
+    m += front
     off = np.concatenate([[0], np.cumsum(deg)])
     return inputs.CSR(n, off.astype(np.int32), rng.choice(at, m).astype(np.int32)), at
 
 
 # rows per edge around the most that are gone through (16, edges counted as 256 at
-# least); one tile of edges, and a second one that starts inside the last rows
-@pytest.mark.parametrize("m", [4, 255, 257, 4096, 4100, 9000])
+# least); one tile of edges, and a second one that starts inside the last rows;
+# both sizes of tiles
+@pytest.mark.parametrize("front, tile", [(0, 1024), (FEW, 4096)])
+@pytest.mark.parametrize("m", [4, 255, 257, 1024, 1030, 4096, 4100, 9000])
 @pytest.mark.parametrize("around", [-8, 0, 1, 3000])
-def test_rows_behind_a_gap_equal_oracle(m, around):
-    rows = 16 * min(max(m, 256), 4096) + around
-    print(f"gap: {rows} rows, {m} edges", flush=True)
-    g, at = _gap(rows, m, rows)
+def test_rows_behind_a_gap_equal_oracle(m, around, front, tile):
+    rows = 16 * min(max(m, 256), tile) + around
+    print(f"gap: {rows} rows, {m} edges behind {front}", flush=True)
+    g, at = _gap(rows, m, rows, front=front)
     G = S.load_csr(g)
     vs = np.array(at + [2, g.n - 2], np.int32)
     cnt = S.simrank_single_source_ex(G, S.make_query(at[1], seed=3, R=300, walk_cap=16))[1]
@@ -45,6 +53,27 @@ def test_rows_behind_a_gap_equal_oracle(m, around):
         for t in range(lens[i]):
             v, u = paths[i][t], paths[i][t + 1]
             assert u in g.in_src[g.in_off[v]:g.in_off[v + 1]]
+    G.free()
+
+
+# Rows around the edges of the large tiles (of the small ones where there are no
+# more edges), as walks and pool sizes see them.
+@pytest.mark.parametrize("front, tile", [(0, 1024), (FEW, 4096), (FEW - 4096, 1024)])
+@pytest.mark.parametrize("behind", [(-1, 0), (0, 0), (1, 0), (7, 2), (0, 900)])
+def test_rows_around_tiles_equal_oracle(front, tile, behind):
+    more, empty = behind
+    deg = [front] + [0] * empty + [tile + more, 3, 0] + [0] * empty + [1, 2 * tile - 4 + more, 0, 5]
+    print(f"rows: {deg[0]} edges in front, tiles of {tile}, {behind}", flush=True)
+    off = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    src = np.random.Generator(np.random.PCG64(3)).integers(0, len(deg), off[-1]).astype(np.int32)
+    g = inputs.CSR(len(deg), off, src)
+    G = S.load_csr(g)
+    act = np.flatnonzero(g.in_degree() > 0)
+    v, j = np.repeat(act, 400).astype(np.int32), np.tile(np.arange(400, dtype=np.uint32), act.size)
+    paths, lens = S.simrank_walks(G, S.make_query(0, seed=3, walk_cap=8, R=400), v, j)
+    opaths, olens = O.walk_table_plain(g, 3, 0.6, 8, v, j)
+    assert np.array_equal(paths, opaths) and np.array_equal(lens, olens)
+    assert S.simrank_build_index(G, seg_log2=1, kappa=0.5, c=0.6, seed=1)["segments"] == int(O.pool_sizes(g, 0.5).sum())
     G.free()
 
 
