@@ -270,15 +270,21 @@ struct GSlot {
 // for the lanes in `act`.  The entry's block for step t is the word of members
 // with a position at t, then the marks of those positions in member order; the
 // slot's offset b moves on to the next step's block (every step is compared
-// once, in order).  Meets are rare: the common step reads the block in 16-byte
-// pieces and only asks whether any mark is the pair's.  For each lane with
-// such a mark (a meet, or one in 65,536 positions that differs in the other
-// half) the whole wave then compares the members' positions themselves, one per
-// lane, in their walks' tables.  Returns the members still tested that meet at
-// this step.  Called by all lanes of a wave.
+// once, in order).  Meets are rare on large graphs: the common step reads the
+// block in 16-byte pieces and only asks whether any mark is the pair's (a meet, or
+// one in 65,536 positions that differs in the other half).  Up to GROUP_FEW_HITS
+// lanes with such a mark are taken in turn, and the whole wave compares the
+// members' positions themselves, one per lane, in their walks' tables.  Beyond it
+// each lane finds the places of its marks in the block and compares those
+// members' positions: in turn, the wave waited for a load per lane, and groups on
+// small graphs, where meets are frequent, took (8 members, R = 2,000) 671 us at n =
+// 1,000, now 292, at n = 100 730 and 340, on a star of 1,000 nodes 1,635 and 615.
+// Returns the members still tested that meet at this step.  Called by all lanes
+// of a wave.
 // The kernel is bound by these reads of LDS: with whole positions in the blocks
 // 32 queries at n = 40,000, R = 1,521, took 1,812 us, with marks 1,314; at n = 2^18,
 // R = 9,502: 50.1 ms and 47.9, bound by the gathers as well.
+constexpr int GROUP_FEW_HITS = 4;
 template <int GW, int WK>
 __device__ __forceinline__ uint32_t group_compare(GSlot<GW> &w, bool act, const uint32_t *s_nodes,
                                                   const GroupDesc &d, int lane) {
@@ -304,18 +310,52 @@ __device__ __forceinline__ uint32_t group_compare(GSlot<GW> &w, bool act, const 
         w.b += 4u * pieces;
     }
     uint32_t met = 0;
-    for (uint64_t hm = __ballot(hit); hm != 0ull; hm &= hm - 1ull) {
-        const int from = __builtin_ctzll(hm);
-        const uint32_t fam = __builtin_amdgcn_readlane(am, from), fo = __builtin_amdgcn_readlane(w.o, from),
-                       fleft = __builtin_amdgcn_readlane(w.left, from),
-                       fj = WK == 2 ? (uint32_t)__builtin_amdgcn_readlane(w.cj, from) >> 8
-                                    : (uint32_t)__builtin_amdgcn_readlane(w.rng.j, from);
-        const uint32_t step = (fleft >> 24) - (fleft & 0xffffu);   // 1, 2, ..
-        bool same = false;
-        if (lane < 32 && ((fam >> lane) & 1u))
-            same = d.sw[lane][(size_t)fj * (size_t)d.L + step - 1u] == fo;
-        const uint32_t who = (uint32_t)__ballot(same);
-        if (lane == from) met = who;
+    if (const uint64_t hits = __ballot(hit)) {
+        if (__popcll(hits) > GROUP_FEW_HITS) {
+            if (hit) {
+                // the places of the marks that are the pair's, then those members' positions
+                const uint32_t mine = mark_of(w.o) | (w.o << 16);
+                const uint32_t c = (uint32_t)__popc(am), words = block_words(c);
+                const uint32_t *blk = s_nodes + w.b - words;
+                uint32_t at = 0;
+                for (uint32_t i = 0; 2u * i < c; ++i) {
+                    const uint32_t x = blk[1u + i] ^ mine;
+                    at |= ((x & 0xffffu) == 0u ? 1u : 0u) << (2u * i);
+                    at |= (x >> 16 == 0u ? 2u : 0u) << (2u * i);
+                }
+                at &= c < 32u ? (1u << c) - 1u : 0xffffffffu;
+                const uint32_t step = (w.left >> 24) - (w.left & 0xffffu);   // 1, 2, ..
+                const uint32_t j = WK == 2 ? w.cj >> 8 : w.rng.j;
+                for (; at; at &= at - 1u) {
+                    // the member of place p is bit p of those set in am
+                    uint32_t p = (uint32_t)__builtin_ctz(at), q = 0, rest = am;
+#pragma unroll
+                    for (uint32_t half = 16u; half > 0u; half >>= 1) {
+                        const uint32_t low = (uint32_t)__popc(rest & ((1u << half) - 1u));
+                        if (p >= low) {
+                            p -= low;
+                            q += half;
+                            rest >>= half;
+                        }
+                    }
+                    if (d.sw[q][(size_t)j * (size_t)d.L + step - 1u] == w.o) met |= 1u << q;
+                }
+            }
+        } else {
+            for (uint64_t hm = hits; hm != 0ull; hm &= hm - 1ull) {
+                const int from = __builtin_ctzll(hm);
+                const uint32_t fam = __builtin_amdgcn_readlane(am, from), fo = __builtin_amdgcn_readlane(w.o, from),
+                               fleft = __builtin_amdgcn_readlane(w.left, from),
+                               fj = WK == 2 ? (uint32_t)__builtin_amdgcn_readlane(w.cj, from) >> 8
+                                            : (uint32_t)__builtin_amdgcn_readlane(w.rng.j, from);
+                const uint32_t step = (fleft >> 24) - (fleft & 0xffffu);   // 1, 2, ..
+                bool same = false;
+                if (lane < 32 && ((fam >> lane) & 1u))
+                    same = d.sw[lane][(size_t)fj * (size_t)d.L + step - 1u] == fo;
+                const uint32_t who = (uint32_t)__ballot(same);
+                if (lane == from) met = who;
+            }
+        }
     }
     return met & w.live;
 }
