@@ -8,9 +8,9 @@
 // tuple's start node, counted once per pair.
 //
 // The first two parts of the key need no sort: a block takes the walks j of a
-// run of TU_ROWS start nodes and of the sources, steps them together, and so
+// run of start nodes and of the sources, steps them together, and so
 // makes the tuples of one (j, i) at a time, of several once fewer walks are
-// left (up to TU_STEPS steps that fit the buffer).  It sorts those in LDS by
+// left (up to 8 steps that fit the buffer).  It sorts those in LDS by
 // (i, node), sources first (an LSD radix sort, stable), finds each tuple's predecessor
 // among the sources' tuples as a running maximum, and links; the pairs that
 // have met are kept in one bit per source and start node.  Tuples never leave
@@ -41,17 +41,31 @@ namespace srk {
 namespace {
 
 constexpr int MAX_TUPLE_SOURCES = 32;
-constexpr int TU_BLOCK = 512;                     // two blocks a CU
-constexpr int TU_WAVES = TU_BLOCK / 64;
-constexpr int TU_RPT = 7;                         // start nodes per thread
-constexpr int TU_ROWS = TU_RPT * TU_BLOCK;        // start nodes per unit
-constexpr int TU_CAP = TU_ROWS + MAX_TUPLE_SOURCES;   // tuples sorted at once
-constexpr int TU_STEP_BITS = 3;                   // of up to 8 steps
-constexpr int TU_DIGITS = 512;                    // digits of a sort pass, at most (9 bits)
-constexpr int TU_ROUNDS = (TU_CAP + TU_BLOCK - 1) / TU_BLOCK;
+constexpr int TU_STEP_BITS = 3;                   // steps sorted at once: up to 8
 constexpr uint32_t TU_SRC = 0x8000u;              // payload flag of a source's tuple
-static_assert(TU_DIGITS == TU_BLOCK, "one digit per thread");
-static_assert(TU_ROWS < (int)TU_SRC, "payloads in 16 bits");
+
+// Blocks of the tuple kernel: TU_LARGE two to a CU; TU_SMALL of one wave, for few
+// start nodes.  A unit of those leaves most of a large block's threads idle, and its
+// barriers and passes take as long; of small blocks a CU holds some 25.  Calls
+// with large and with small blocks, 8 sources: R = 9,502, n = 10: 1,190 and 294 us, n =
+// 250: 1,626 and 341; R = 2,000, c = 0.95, 255 steps, n = 10: 3,019 and 619, n = 250:
+// 2,960 and 839.  Where the large blocks take all units at once, a small one's
+// four nodes per thread cost more than its barriers save from two per thread on:
+// R = 100, n = 120: 138 and 137 us, n = 250: 165 and 177.
+template <int BLOCK_, int RPT_>
+struct TupleBlock {
+    static constexpr int BLOCK = BLOCK_;
+    static constexpr int WAVES = BLOCK / 64;
+    static constexpr int RPT = RPT_;                          // start nodes per thread
+    static constexpr int ROWS = RPT * BLOCK;                  // start nodes per unit
+    static constexpr int CAP = ROWS + MAX_TUPLE_SOURCES;      // tuples sorted at once
+    static constexpr int ROUNDS = (CAP + BLOCK - 1) / BLOCK;
+    static constexpr int DIGIT_BITS = BLOCK == 512 ? 9 : 6;   // of a sort pass, at most
+    static_assert(1 << DIGIT_BITS == BLOCK, "one digit per thread");
+    static_assert(ROWS < (int)TU_SRC, "payloads in 16 bits");
+};
+using TU_LARGE = TupleBlock<512, 7>;
+using TU_SMALL = TupleBlock<64, 4>;
 
 struct TupleArgs {
     const uint2 *nodes;
@@ -115,8 +129,10 @@ __device__ __forceinline__ bool walker_goes(const TupleArgs &a, const Walker &w,
     return STRAT || x.x < a.T;
 }
 
-template <bool STRAT>
-__global__ __launch_bounds__(TU_BLOCK) void k_tuples(TupleArgs a) {
+template <bool STRAT, typename B>
+__global__ __launch_bounds__(B::BLOCK) void k_tuples(TupleArgs a) {
+    constexpr int TU_BLOCK = B::BLOCK, TU_WAVES = B::WAVES, TU_RPT = B::RPT, TU_ROWS = B::ROWS,
+                  TU_CAP = B::CAP, TU_ROUNDS = B::ROUNDS, TU_DIGITS = 1 << B::DIGIT_BITS;
     __shared__ uint32_t s_key[2][TU_CAP];            // tuples: step within the sort, o-value
     __shared__ uint16_t s_val[2][TU_CAP];            // and start node (run-local) or source
     __shared__ uint32_t s_met[TU_ROWS];              // sources that walk (v, j) has met
@@ -247,7 +263,7 @@ __global__ __launch_bounds__(TU_BLOCK) void k_tuples(TupleArgs a) {
             // ---- stable LSD sort by (step, o-value): wave w takes the w-th run of
             // the tuples, so earlier waves, rounds and lanes come first
             const int bits = a.nb + (steps > 1u ? 32 - __builtin_clz(steps - 1u) : 0);
-            const int passes = (bits + 8) / 9, digit_bits = (bits + passes - 1) / passes;
+            const int passes = (bits + B::DIGIT_BITS - 1) / B::DIGIT_BITS, digit_bits = (bits + passes - 1) / passes;
             if (threadIdx.x == 0) sorted += (unsigned long long)count * passes;
             const uint32_t rounds = (count + TU_BLOCK - 1) / TU_BLOCK;
             int buf = 0;
@@ -417,16 +433,23 @@ struct DevBuf {
 };
 
 // Blocks of the tuple kernel that are resident at once.
-template <bool STRAT>
+template <bool STRAT, typename B>
 int tuple_grid() {
     static const int blocks = [] {
         int dev = 0, cus = 0, per = 0;
         (void)hipGetDevice(&dev);
         (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-        (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_tuples<STRAT>, TU_BLOCK, 0);
+        (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_tuples<STRAT, B>, B::BLOCK, 0);
         return (cus > 0 ? cus : 256) * (per > 0 ? per : 1);
     }();
     return blocks;
+}
+
+template <bool STRAT, typename B>
+void launch_tuples(TupleArgs &a, hipStream_t st) {
+    a.units = (int64_t)((a.na + B::ROWS - 1) / B::ROWS) * a.N;
+    if (a.units > 0)
+        k_tuples<STRAT, B><<<(unsigned)std::min<int64_t>(a.units, tuple_grid<STRAT, B>()), B::BLOCK, 0, st>>>(a);
 }
 
 }  // namespace
@@ -511,7 +534,6 @@ extern "C" int simrank_tuple_meets(const simrank_graph *g, const simrank_query *
     a.counters = counters;
     a.nb = bits_for((uint64_t)std::max<int64_t>(g->m_slots - 1, 1));   // at most 31
     a.step_bits = std::min(TU_STEP_BITS, 32 - a.nb);
-    a.units = (int64_t)((a.na + TU_ROWS - 1) / TU_ROWS) * N;
 
     // The tuples of one start node and of all sources are counted in 32 bits.
     const int64_t src_tuples_max = (int64_t)k * N * L;
@@ -530,11 +552,14 @@ extern "C" int simrank_tuple_meets(const simrank_graph *g, const simrank_query *
             return fail(SIMRANK_EINVAL, "one node's walks exceed the tuple buffer");
     }
     SRK_HIP(hipEventRecord(s0, st));
-    if (a.units > 0) {
-        if (strat)
-            k_tuples<true><<<(unsigned)std::min<int64_t>(a.units, tuple_grid<true>()), TU_BLOCK, 0, st>>>(a);
-        else
-            k_tuples<false><<<(unsigned)std::min<int64_t>(a.units, tuple_grid<false>()), TU_BLOCK, 0, st>>>(a);
+    const bool small = a.na <= TU_SMALL::ROWS / 2 ||
+                       (a.na <= TU_SMALL::ROWS && N > (strat ? tuple_grid<true, TU_LARGE>() : tuple_grid<false, TU_LARGE>()));
+    if (strat) {
+        if (small) launch_tuples<true, TU_SMALL>(a, st);
+        else launch_tuples<true, TU_LARGE>(a, st);
+    } else {
+        if (small) launch_tuples<false, TU_SMALL>(a, st);
+        else launch_tuples<false, TU_LARGE>(a, st);
     }
     SRK_HIP(hipEventRecord(s1, st));
     k_tuples_end<<<1, 64, 0, st>>>(a, strat);
