@@ -145,7 +145,7 @@ __global__ __launch_bounds__(B::BLOCK) void k_tuples(TupleArgs a) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const GlobalPtr<uint64_t> E = (GlobalPtr<uint64_t>)a.E;
     unsigned long long moves = 0, sorted = 0;
-    uint32_t meets = 0;
+    uint32_t meets = 0;   // (in 64 bits 1% slower: n = 50,000 7.00 ms, not 6.93)
     if (STRAT) {
         for (int i = threadIdx.x; i < a.L + 2; i += TU_BLOCK) s_ccum[i] = a.tab->ccum[i];
         __syncthreads();
@@ -365,6 +365,11 @@ __global__ __launch_bounds__(B::BLOCK) void k_tuples(TupleArgs a) {
             steps = held = 0;
             __syncthreads();
         }
+        // (a unit adds fewer than 2^17, and the wave's sum below is of 64)
+        if (meets >= 1u << 24) {
+            atomicAdd(&ctr_set(a.counters)[C_MEETS], (unsigned long long)meets);
+            meets = 0;
+        }
         __syncthreads();
     }
     for (int dd = 32; dd > 0; dd >>= 1) {
@@ -380,7 +385,7 @@ __global__ __launch_bounds__(B::BLOCK) void k_tuples(TupleArgs a) {
 }
 
 // Steps of each start node's walks (grid: x over j, y over nodes, strided), for
-// the limit on one node's tuples.
+// the limit on one node's and the sources' tuples.
 __global__ __launch_bounds__(256) void k_row_tuples(TupleArgs a, bool strat, unsigned long long *row_sum) {
     const int32_t j = blockIdx.x * 256 + threadIdx.x;
     for (int32_t row = blockIdx.y; row < a.na; row += gridDim.y) {
@@ -535,7 +540,9 @@ extern "C" int simrank_tuple_meets(const simrank_graph *g, const simrank_query *
     a.nb = bits_for((uint64_t)std::max<int64_t>(g->m_slots - 1, 1));   // at most 31
     a.step_bits = std::min(TU_STEP_BITS, 32 - a.nb);
 
-    // The tuples of one start node and of all sources are counted in 32 bits.
+    // Queries whose sources and one start node could have 2^32 - 1 tuples between
+    // them are refused: a limit of the interface (simrank.h), which a sort of whole
+    // start nodes set; k_tuples itself holds no more than a block's at once.
     const int64_t src_tuples_max = (int64_t)k * N * L;
     if (a.na > 0 && src_tuples_max + (int64_t)N * L >= (int64_t)0xffffffffu) {
         DevBuf rs;
@@ -549,7 +556,7 @@ extern "C" int simrank_tuple_meets(const simrank_graph *g, const simrank_query *
         SRK_HIP(hipStreamSynchronize(st));
         const int64_t most = (int64_t)*std::max_element(row_sum.begin(), row_sum.end());
         if (src_tuples_max + most >= (int64_t)0xffffffffu)
-            return fail(SIMRANK_EINVAL, "one node's walks exceed the tuple buffer");
+            return fail(SIMRANK_EINVAL, "one node's and the sources' tuples exceed 2^32 - 2");
     }
     SRK_HIP(hipEventRecord(s0, st));
     const bool small = a.na <= TU_SMALL::ROWS / 2 ||
