@@ -389,7 +389,8 @@ int simrank_batch_plan_free(simrank_batch_plan *plan);
 
 /* A tuner's choice for a graph. */
 typedef struct simrank_tuning {
-    int32_t unit_nodes;   /* nodes v per meet work unit (walks per block: unit_nodes x tile) */
+    int32_t unit_nodes;   /* nodes v per meet work unit: the fastest fixed number (32 .. 256);
+                             units sized on the device, the default, may be faster still */
     int32_t tile_walks;   /* source walks j per LDS tile */
     int32_t seg_log2;     /* the index's segment length 2^k (-1: no index) */
     int32_t reserved;
@@ -399,15 +400,17 @@ typedef struct simrank_tuning {
 
 /* Measures the meet kernel of query q (plain or stitched) on g for each tile
  * of source walks (the kind's largest tile, 8192 for plain walks, halved down
- * to 2048) and each work-unit size (nodes per unit 32, 64, 128, 256, as long
- * as the units still number 64 or more) and keeps the fastest pair for later
- * queries on g, batches and servers included (*out, may be NULL).  Results
- * never depend on the choice.  Not to be called while other threads query g. */
+ * to 2048) and each work-unit size (sized on the device, as by default, and
+ * nodes per unit 32, 64, 128, 256, as long as the units still number 64 or
+ * more) and keeps the fastest pair for later queries on g, batches and servers
+ * included (*out, may be NULL: meet_ms and tile_walks of the pair that is kept,
+ * unit_nodes of the fastest fixed size).  Results never depend on the choice.
+ * Not to be called while other threads query g. */
 int simrank_tune_ex(simrank_graph *g, const simrank_query *q, simrank_tuning *out);
 /* simrank_tune_ex, returning the nodes per unit only (*vb_out, may be NULL). */
 int simrank_tune(simrank_graph *g, const simrank_query *q, int32_t *vb_out);
-/* Fixes the tuning by hand: unit_nodes in [0, 256] (0: the library's default
- * by graph size), tile_walks 0 (each kind's largest tile) or in [2048, 8192]
+/* Fixes the tuning by hand: unit_nodes in [0, 256] (0, the default: sized on
+ * the device by a launch's work), tile_walks 0 (each kind's largest tile) or in [2048, 8192]
  * (clamped to each kind's largest tile).  Results never depend on it.  Not to
  * be called while other threads query g. */
 int simrank_set_tuning(simrank_graph *g, int32_t unit_nodes, int32_t tile_walks);

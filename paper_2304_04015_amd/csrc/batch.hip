@@ -11,6 +11,7 @@
 // Each query's result is exactly the one a lone simrank_single_source_ex call
 // returns: results depend only on (graph, query).
 #include <algorithm>
+#include <cmath>
 #include <cstring>
 #include <map>
 #include <tuple>
@@ -537,34 +538,36 @@ extern "C" int simrank_tune_ex(simrank_graph *g, const simrank_query *q, simrank
     rc = workspace_init(g, p.R, p.L, &ws);
     if (!rc) rc = device_alloc((void **)&cnt, 4 * (size_t)g->n, nullptr);
     const int32_t saved_vb = g->tuned_vb, saved_tj = g->tuned_tile_j[kind];
-    int32_t best_vb = 0, best_tj = 0;
-    float best_ms = 0.f;
+    struct Choice {
+        int32_t vb, tj;
+        float ms;
+    };
+    Choice best{0, 0, INFINITY}, fixed{0, 0, INFINITY};   // of all, of units of a fixed size
     // walks per tile: the kind's tile and each halving down to MIN_TILE_J;
-    // nodes per unit: 32 .. MEET_VB while the units still fill a GPU
+    // nodes per unit: sized on the device (0), 32 .. MEET_VB while the units
+    // still fill a GPU
     for (int32_t tj = tile_j_of(kind); tj >= MIN_TILE_J && !rc; tj /= 2) {
-        for (int32_t vb = 32; vb <= MEET_VB && !rc; vb *= 2) {
+        for (int32_t vb = 0; vb <= MEET_VB && !rc; vb = vb ? 2 * vb : 32) {
             if (vb > 32 && (g->n_active + vb - 1) / vb < 64) break;
             g->tuned_vb = vb;
             g->tuned_tile_j[kind] = tj;
-            float ms = 0.f;
-            rc = time_meet(g, q, p, mode, &ws, cnt, &ms);
-            if (!rc && (best_vb == 0 || ms < best_ms)) {
-                best_vb = vb;
-                best_tj = tj;
-                best_ms = ms;
-            }
+            Choice c{vb, tj, 0.f};
+            rc = time_meet(g, q, p, mode, &ws, cnt, &c.ms);
+            if (rc) break;
+            if (c.ms < best.ms) best = c;
+            if (vb && c.ms < fixed.ms) fixed = c;
         }
     }
-    g->tuned_vb = rc ? saved_vb : best_vb;
-    g->tuned_tile_j[kind] = rc ? saved_tj : best_tj;
+    g->tuned_vb = rc ? saved_vb : best.vb;
+    g->tuned_tile_j[kind] = rc ? saved_tj : best.tj;
     device_free(cnt);
     workspace_release(&ws);
     if (!rc && out) {
         *out = simrank_tuning{};
-        out->unit_nodes = best_vb;
-        out->tile_walks = best_tj;
+        out->unit_nodes = fixed.vb;
+        out->tile_walks = best.tj;
         out->seg_log2 = g->index ? g->index->seg_log2 : -1;
-        out->meet_ms = best_ms;
+        out->meet_ms = best.ms;
         out->build_ms = g->index ? g->index->build_ms : 0.0;
     }
     return rc;
@@ -637,7 +640,7 @@ extern "C" int simrank_tune_index(simrank_graph *g, const simrank_query *q,
     }
     if (!rc && out) {
         *out = simrank_tuning{};
-        out->unit_nodes = default_unit_nodes(g);
+        out->unit_nodes = default_unit_nodes(g);   // (nominal where sized on the device)
         out->tile_walks = g->tuned_tile_j[K_STITCHED] > 0 ? g->tuned_tile_j[K_STITCHED]
                                                           : tile_j_of(K_STITCHED);
         out->seg_log2 = best;

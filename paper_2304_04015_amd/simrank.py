@@ -663,7 +663,9 @@ def simrank_tune(g: Graph, q: simrank_query) -> int:
 
 
 def simrank_tune_ex(g: Graph, q: simrank_query) -> dict:
-    """Nodes per unit and walks per tile chosen for g (kept for later queries)."""
+    """Tunes g for later queries: walks per tile and meet time of the choice, and
+    the fastest fixed number of nodes per unit (units sized on the device, the
+    default, are kept where they are faster)."""
     t = simrank_tuning()
     _check(lib().simrank_tune_ex(g.handle, C.byref(q), C.byref(t)))
     return t.asdict()

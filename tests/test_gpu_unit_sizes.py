@@ -67,3 +67,21 @@ def test_small_queries_beside_one_of_unequal_tiles(order):
         assert np.array_equal(cnt, lone), i
     for G in Gs:
         G.free()
+
+
+# The tuner keeps units sized on the device where they are fastest: on a small
+# graph the best fixed size takes three times as long.
+def test_tuner_keeps_units_sized_on_the_device():
+    g = inputs.erdos_renyi_in(500, 8.0, seed=1)
+    G = S.load_csr(g)
+    q = S.make_query(1, seed=SEED, R=2000)
+    before, want = _meet_ms(G, q), S.simrank_single_source_ex(G, q)[1]
+    t = S.simrank_tune_ex(G, q)
+    after = _meet_ms(G, q)
+    print(f"tuner: {before:.4f} ms before, {after:.4f} after, {t}", flush=True)
+    assert after < 1.75 * before and t["meet_ms"] < 1.75 * before
+    assert t["unit_nodes"] in (32, 64, 128, 256)
+    assert np.array_equal(S.simrank_single_source_ex(G, q)[1], want)
+    S.simrank_set_tuning(G, t["unit_nodes"], 0)          # the fixed size it reports
+    assert np.array_equal(S.simrank_single_source_ex(G, q)[1], want)
+    G.free()
