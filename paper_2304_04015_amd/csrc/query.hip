@@ -610,12 +610,16 @@ __device__ void ring_report(const StreamRing &ring, const QueryDesc &d, uint32_t
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     if (threadIdx.x == 0) {
-        __threadfence();
-        // the size is read coherently: a plain load could return the size of
-        // an earlier request in this entry from a cache and miss the last unit
-        const uint32_t old = atomicAdd(&ring.ctl[slot].done, units);
+        // The size is read coherently (a plain load could return the size of an
+        // earlier request in this entry from a cache and miss the last unit), and
+        // before the report, while these units keep the entry from being finished:
+        // behind it, another block may finish the entry and the host publish it
+        // again, and the new request's size would be compared.  The fence waits
+        // for the load.
         const uint32_t nu =
             __hip_atomic_load(&ring.ctl[slot].n_units, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __threadfence();
+        const uint32_t old = atomicAdd(&ring.ctl[slot].done, units);
         *s_last = (old + units == nu) ? 1u : 0u;
     }
     __syncthreads();
