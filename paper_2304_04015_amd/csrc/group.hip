@@ -190,15 +190,9 @@ __global__ __launch_bounds__(64) void k_group_tiles(const GroupDesc *__restrict_
     if (threadIdx.x == 0) d.joff[E1] = total;
     __threadfence_block();
     const uint32_t n_tiles = cut_tiles(d.joff, E1, TJ, TN, d.tiles, (int)threadIdx.x);
-    __threadfence_block();
-    uint32_t km = 0;
-    for (uint32_t t = threadIdx.x; t < n_tiles; t += 64)
-        km = max(km, (t + 1 < n_tiles ? d.tiles[t + 1] : E1) - d.tiles[t]);
-    for (int dd = 32; dd > 0; dd >>= 1) km = max(km, __shfl_xor(km, dd, 64));
     if (threadIdx.x == 0) {
         d.tiles[n_tiles] = E1;
         d.meta[2] = n_tiles;
-        d.meta[3] = km;
     }
 }
 
