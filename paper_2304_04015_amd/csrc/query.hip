@@ -14,6 +14,8 @@
 
 #include <algorithm>
 #include <cstring>
+#include <memory>
+#include <new>
 #include <vector>
 
 #include "common.hpp"
@@ -1795,8 +1797,11 @@ static int read_stats(Workspace *ws, simrank_stats *st) {
 
 // A synchronous call's results: its counters and up to three arrays of n, which
 // lie behind one another in device memory.  A copy to the host costs 11 to 13
-// us however small, so small results come in one and are dealt out here: the
-// call at n = 500 took 118 us with a copy for each and takes @S12@.
+// us however small, so results of up to 1 MB come in one and are dealt out here;
+// larger ones each go where they belong, which costs less than dealing them out.
+// A call of hardly any work with one copy and with one for each: n = 500: 61 and
+// 93 us; n = 40,000 (484 KB): 95 and 115; n = 80,000 (965 KB): 141 and 154; n =
+// 100,000 (1.2 MB): 184 and 165; n = 170,000: 256 and 231.
 struct Results {
     char *dev = nullptr;
     size_t at[4] = {0, 0, 0, 0}, bytes[4] = {0, 0, 0, 0}, total = 0;
@@ -1815,17 +1820,17 @@ struct Results {
     T *at_dev(int i) { return bytes[i] ? reinterpret_cast<T *>(dev + at[i]) : nullptr; }
     // Copies behind the work on st and waits.
     int fetch(hipStream_t st) {
-        constexpr size_t SMALL = 1 << 19;
-        if (total <= SMALL) {
-            std::vector<char> tmp(total);
-            SRK_HIP(hipMemcpyAsync(tmp.data(), dev, total, hipMemcpyDeviceToHost, st));
+        constexpr size_t SMALL = 1 << 20;
+        const std::unique_ptr<char[]> tmp(total <= SMALL ? new (std::nothrow) char[total] : nullptr);
+        if (tmp) {
+            SRK_HIP(hipMemcpyAsync(tmp.get(), dev, total, hipMemcpyDeviceToHost, st));
             SRK_HIP(hipStreamSynchronize(st));
             for (int i = 0; i < 4; ++i)
-                if (host[i]) std::memcpy(host[i], tmp.data() + at[i], bytes[i]);
+                if (host[i]) std::memcpy(host[i], tmp.get() + at[i], bytes[i]);
             return SIMRANK_OK;
         }
-        // (the synchronous copy pins large arrays in place; the asynchronous
-        // one took 100 us more for 320 and 160 KB)
+        // (synchronous copies: asynchronous ones of each array took 100 us more for
+        // 320 and 160 KB)
         SRK_HIP(hipStreamSynchronize(st));
         for (int i = 0; i < 4; ++i)
             if (host[i]) SRK_HIP(hipMemcpy(host[i], dev + at[i], bytes[i], hipMemcpyDeviceToHost));
