@@ -521,14 +521,14 @@ __global__ __launch_bounds__(64) void k_units_one(QueryDesc d, uint32_t *__restr
 // stages the chunk's nodes (id, row) per unit.
 //
 // Inside a unit the pairs (v, k), v-major, are handed out from one block-wide
-// cursor in chunks of 64 to the waves, so all waves of a block work on the same
-// one or two nodes v at a time: the rows a walk reads at its first two steps
+// cursor in chunks of 64 to 256 (items_for) to the waves, so all waves of a block
+// work on the same few nodes v at a time: the rows a walk reads at its first two steps
 // (v's own row and those of its in-neighbours) are then shared by the whole
 // block and stay in the CU's L1.  Each lane runs NS independent pairs (slots)
 // so that NS gathers per lane are in flight at once; a slot whose pair ended
 // (stop, meet, or end of walk (s, j)) is refilled before the next step.
-// A step: one Philox draw, a multiply-high neighbour pick, one 8-byte gather
-// of E, one LDS compare.  Meets go to an LDS counter per node, flushed to the
+// A step: one Philox draw, a multiply-high neighbour pick, one gather of a row (4
+// bytes where the graph's are packed, else 8 of E), one LDS compare.  Meets go to an LDS counter per node, flushed to the
 // global counts once per unit.
 //
 // KIND selects the walks: K_PLAIN (sqrt(c)-walks), K_STITCHED (private head,
