@@ -395,7 +395,6 @@ __global__ __launch_bounds__(1024) void k_unit_offsets(const QueryDesc *__restri
                                                        uint32_t *units, uint3 grid,
                                                        unsigned long long *counters) {
     __shared__ unsigned long long s_work[N_KINDS], s_most[N_KINDS], s_per[N_KINDS];
-    __shared__ unsigned long long s_even[N_KINDS];   // work per unit if no tile were small
     __shared__ uint32_t s_cost[N_KINDS];
     if (threadIdx.x < N_KINDS) {
         s_work[threadIdx.x] = s_most[threadIdx.x] = 0ull;
@@ -416,30 +415,16 @@ __global__ __launch_bounds__(1024) void k_unit_offsets(const QueryDesc *__restri
         // (many queries in one launch have units of all sizes: their common
         // work is not refined)
         const int kind = (int)(threadIdx.x >> 6);
-        const uint32_t blocks = kind == 0 ? grid.x : kind == 1 ? grid.y : grid.z;
         const uint64_t p = unit_work(qd, nq <= 16 ? nq : 0, kind, s_work[kind], s_cost[kind],
-                                     s_most[kind], blocks, (int)(threadIdx.x & 63));
-        if ((threadIdx.x & 63) == 0) {
-            s_per[kind] = p;
-            s_even[kind] = work_each(s_work[kind], unit_rounds(s_work[kind], s_cost[kind], s_most[kind], blocks) * blocks);
-        }
+                                     s_most[kind], kind == 0 ? grid.x : kind == 1 ? grid.y : grid.z,
+                                     (int)(threadIdx.x & 63));
+        if ((threadIdx.x & 63) == 0) s_per[kind] = p;
     }
     __syncthreads();
     for (int32_t q = threadIdx.x >> 6; q < nq; q += (int32_t)(blockDim.x >> 6)) {
         const int32_t kind = qd[q].kind;
         uint32_t total = 0;
-        if (kind < N_KINDS) {
-            // A query of less than a round does not make up for the small tiles of
-            // others: its few units, twice as large for it, would take a round of
-            // their own where they come last (one at n = 5,000 behind one at n = 2^20,
-            // R = 9,502: 50.8 ms, and 50.3 so; R = 20,000: 50.9 and 50.4).
-            uint64_t each = s_per[kind];
-            if (each != s_even[kind]) {
-                const uint32_t blocks = kind == 0 ? grid.x : kind == 1 ? grid.y : grid.z;
-                if (work_of(qd[q], (uint32_t)qd[q].n_active, qd[q].meta[0]) < each * blocks) each = s_even[kind];
-            }
-            total = lay_units(qd[q], each, (int)(threadIdx.x & 63));
-        }
+        if (kind < N_KINDS) total = lay_units(qd[q], s_per[kind], (int)(threadIdx.x & 63));
         if ((threadIdx.x & 63) < N_KINDS)
             units[(threadIdx.x & 63) * (nq + 1) + q] = (int32_t)(threadIdx.x & 63) == kind ? total : 0u;
     }
