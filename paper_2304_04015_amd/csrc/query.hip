@@ -593,6 +593,14 @@ __device__ void ring_claim(const StreamRing &ring, int lane, uint32_t *o_slot, u
 // request's estimate and then its flag in host memory.  Block-wide.
 __device__ void ring_report(const StreamRing &ring, const QueryDesc &d, uint32_t slot,
                             uint32_t tag, uint32_t units, Work &work, uint32_t *s_last) {
+    // The entry's size is read before the report, while these units keep the entry
+    // from being finished: behind it, another block may finish the entry and the
+    // host publish it again, and the new request's size would be compared.  It is
+    // read coherently: a plain load could return the size of an earlier request in
+    // this entry from a cache and miss the last unit.
+    uint32_t nu = 0;
+    if (threadIdx.x == 0)
+        nu = __hip_atomic_load(&ring.ctl[slot].n_units, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     add_work(ring.counters + (size_t)slot * 8, work);
     work = Work{};
     // every wave's counts are at the coherence point (atomics, waited for)
@@ -600,14 +608,6 @@ __device__ void ring_report(const StreamRing &ring, const QueryDesc &d, uint32_t
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     if (threadIdx.x == 0) {
-        // The size is read coherently (a plain load could return the size of an
-        // earlier request in this entry from a cache and miss the last unit), and
-        // before the report, while these units keep the entry from being finished:
-        // behind it, another block may finish the entry and the host publish it
-        // again, and the new request's size would be compared.  The fence waits
-        // for the load.
-        const uint32_t nu =
-            __hip_atomic_load(&ring.ctl[slot].n_units, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __threadfence();
         const uint32_t old = atomicAdd(&ring.ctl[slot].done, units);
         *s_last = (old + units == nu) ? 1u : 0u;
