@@ -392,7 +392,8 @@ int simrank_batch_plan_free(simrank_batch_plan *plan);
 /* A tuner's choice for a graph. */
 typedef struct simrank_tuning {
     int32_t unit_nodes;   /* nodes v per meet work unit: the fastest fixed number (32 .. 256);
-                             units sized on the device, the default, may be faster still */
+                             units sized on the device, the default, may be faster still
+                             (simrank_tune_index: the tuned number, or a nominal one) */
     int32_t tile_walks;   /* source walks j per LDS tile */
     int32_t seg_log2;     /* the index's segment length 2^k (-1: no index) */
     int32_t reserved;
