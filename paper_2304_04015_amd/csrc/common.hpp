@@ -460,7 +460,7 @@ struct Workspace {
 
 enum Counter : int {
     C_MOVES = 0, C_DRAWS = 1, C_MEETS = 2, C_TAIL = 3, C_PAIRS = 4, C_SRC_MOVES = 5,
-    C_SORTED = 6, C_END = 7
+    C_UNITS = 6, C_SPARE = 7
 };
 
 // Work counters of a query set: the 8 totals, then CTR_SETS sets of 8 that the
@@ -472,13 +472,13 @@ enum Counter : int {
 // n = 5,003, 980 and 686 at n = 40,000.
 constexpr int CTR_SETS = 64;
 constexpr int CTR_SUMS = 8 * (1 + CTR_SETS);
-// Behind them, device times of a lone query (ticks of the constant 100 MHz clock):
+// Behind them, device times of a query (ticks of the constant 100 MHz clock):
 // start of its first kernel, end of the kernel before the meet kernel, start of
-// the one behind it.  Its end is the largest C_END of the sets, to which the last
-// kernel's blocks each give the end of theirs.  HIP events there were packets of
-// their own between the kernels and held each of them up by 3 to 6 us.  A query at
+// the one behind it, end of the last.  HIP events there were packets of their
+// own between the kernels and held each of them up by 3 to 6 us.  A query at
 // n = 5,003 took 95 us with them and 84 without.
-enum Stamp : int { STAMP_BEGIN = CTR_SUMS, STAMP_MEET = CTR_SUMS + 1, STAMP_MET = CTR_SUMS + 2 };
+enum Stamp : int { STAMP_BEGIN = CTR_SUMS, STAMP_MEET = CTR_SUMS + 1, STAMP_MET = CTR_SUMS + 2,
+                   STAMP_END = CTR_SUMS + 3 };
 constexpr int CTR_WORDS = CTR_SUMS + 8;
 
 // ----------------------------------------------------------------- helpers

@@ -82,13 +82,11 @@ __device__ __forceinline__ void estimate_one(const QueryDesc &d, int64_t v) {
 }
 
 // grid (x over nodes, y = query); the last kernel of a launch sequence, it also
-// folds the sets of work counters into the totals.  ends: its blocks' ends are
-// wanted (a lone query).
-__global__ void k_estimate(const QueryDesc *__restrict__ qd, unsigned long long *__restrict__ counters,
-                           bool ends) {
+// folds the sets of work counters into the totals.
+__global__ void k_estimate(const QueryDesc *__restrict__ qd, unsigned long long *__restrict__ counters) {
     const unsigned long long begun = wall_clock64();
     const QueryDesc &d = qd[blockIdx.y];
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < C_END) {
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 8) {
         unsigned long long sum = 0;
         for (int i = 1; i <= CTR_SETS; ++i) sum += counters[8 * i + threadIdx.x];
         counters[threadIdx.x] = sum;
@@ -97,9 +95,8 @@ __global__ void k_estimate(const QueryDesc *__restrict__ qd, unsigned long long 
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < d.n;
          v += (int64_t)gridDim.x * blockDim.x)
         estimate_one(d, v);
-    if (!ends) return;
-    __syncthreads();
-    if (threadIdx.x == 0) atomicMax(&ctr_set(counters)[C_END], (unsigned long long)wall_clock64());
+    if (blockIdx.x == gridDim.x - 1 && blockIdx.y == gridDim.y - 1 && threadIdx.x == 0)
+        counters[STAMP_END] = wall_clock64();
 }
 
 // ------------------------------------------------------------ source walks
@@ -1422,7 +1419,7 @@ int launch_query_set(const QuerySet &qs, hipStream_t st, const QueryDesc *one) {
         const int rc = launch_groups(*qs.groups, qs.counters, st);
         if (rc) return rc;
     }
-    k_estimate<<<dim3(gx_n, nq), 256, 0, st>>>(qs.desc, qs.counters, one != nullptr);
+    k_estimate<<<dim3(gx_n, nq), 256, 0, st>>>(qs.desc, qs.counters);
     SRK_HIP(hipGetLastError());
     return SIMRANK_OK;
 }
@@ -1736,9 +1733,7 @@ static int times_of(const Workspace *ws, const unsigned long long *c, double *ms
     int khz = 0;   // of the device's constant clock
     SRK_HIP(hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, ws->g->device));
     const double tick = 1.0 / (double)std::max(khz, 1);
-    unsigned long long end = 0;
-    for (int i = 1; i <= CTR_SETS; ++i) end = std::max(end, c[8 * i + C_END]);
-    if (ms) *ms = (double)(end - c[STAMP_BEGIN]) * tick;
+    if (ms) *ms = (double)(c[STAMP_END] - c[STAMP_BEGIN]) * tick;
     if (meet_ms) *meet_ms = (double)(c[STAMP_MET] - c[STAMP_MEET]) * tick;
     return SIMRANK_OK;
 }

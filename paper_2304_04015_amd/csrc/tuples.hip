@@ -380,7 +380,7 @@ __global__ __launch_bounds__(B::BLOCK) void k_tuples(TupleArgs a) {
         unsigned long long *to = ctr_set(a.counters);
         if (moves) atomicAdd(&to[C_MOVES], moves);
         if (meets) atomicAdd(&to[C_MEETS], (unsigned long long)meets);
-        if (sorted) atomicAdd(&to[C_SORTED], sorted);
+        if (sorted) atomicAdd(&to[C_SPARE], sorted);
     }
 }
 
@@ -585,7 +585,7 @@ extern "C" int simrank_tuple_meets(const simrank_graph *g, const simrank_query *
         st_opt->moves = c[C_MOVES];
         // bytes the sort passes move (see simrank.h): 4 per key a pass counts,
         // 12 per tuple it reads and writes
-        st_opt->draws = c[C_SORTED] * 16u;
+        st_opt->draws = c[C_SPARE] * 16u;
         st_opt->meet_ms = sms;
         st_opt->meets = c[C_MEETS];
         st_opt->ms = ms;
