@@ -100,8 +100,11 @@ typedef struct simrank_stats {
     uint64_t meets;        /* pairs that met (sum of counts minus R for s) */
     uint64_t tail_steps;   /* stitched mode: steps read from the segment index */
     uint64_t source_moves; /* steps of the R source walks */
-    double ms;             /* device time of the call, on the device's constant clock
-                              (batches: HIP events) */
+    double ms;             /* device time of the call on the device's constant clock, from
+                              its first kernel to the end of its last kernel's block of the
+                              highest number (within 2 us of its end; a stratified query's
+                              class table goes up before); batches and the tuple form:
+                              between HIP events */
     double meet_ms;        /* device time of the fused walk + meet kernel alone */
     int32_t R, L;
     uint32_t T;

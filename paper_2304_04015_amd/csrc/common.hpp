@@ -472,11 +472,13 @@ enum Counter : int {
 // n = 5,003, 980 and 686 at n = 40,000.
 constexpr int CTR_SETS = 64;
 constexpr int CTR_SUMS = 8 * (1 + CTR_SETS);
-// Behind them, device times of a query (ticks of the constant 100 MHz clock):
+// Behind them, device times of a lone query (ticks of the constant 100 MHz clock):
 // start of its first kernel, end of the kernel before the meet kernel, start of
-// the one behind it, end of the last.  HIP events there were packets of their
-// own between the kernels and held each of them up by 3 to 6 us.  A query at
-// n = 5,003 took 95 us with them and 84 without.
+// the one behind it, end of the last one's block of the highest number.  (The
+// latest of all its blocks' ends comes 1 us later, 22.7 and 24.0 us at n = 500, 577.1 and
+// 577.8 at n = 2^22, and finding it took each query 0.3 us.)  HIP events there
+// were packets of their own between the kernels and held each of them up by 3 to
+// 6 us.  A query at n = 5,003 took 95 us with them and 84 without.
 enum Stamp : int { STAMP_BEGIN = CTR_SUMS, STAMP_MEET = CTR_SUMS + 1, STAMP_MET = CTR_SUMS + 2,
                    STAMP_END = CTR_SUMS + 3 };
 constexpr int CTR_WORDS = CTR_SUMS + 8;
