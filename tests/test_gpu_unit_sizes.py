@@ -69,6 +69,37 @@ def test_small_queries_beside_one_of_unequal_tiles(order):
         G.free()
 
 
+# Large graphs in front of small ones, whose units would start last, and the same
+# queries the other way round.  The bound lies between 1.06 where the list's order is
+# the launch's and 1 where it is not.
+def test_order_of_a_batch_does_not_set_its_time():
+    sizes = [150001, 150001, 40000, 5000, 500, 500, 500]
+    Gs = {n: S.load_csr(inputs.erdos_renyi_in(n, 8.0, seed=1)) for n in set(sizes)}
+    vs = np.arange(40)
+    front = [(n, 7 + i, 3 + i) for i, n in enumerate(sizes)]
+    ms, counts = [], []
+    for order in (front, front[::-1]):
+        plan = S.BatchPlan([Gs[n] for n, _, _ in order],
+                           [S.make_query(s, seed=k, R=9502, graph=i) for i, (_, s, k) in enumerate(order)])
+        best = []
+        for _ in range(7):
+            plan.run()
+            best.append(plan.wait().ms)
+        ms.append(min(best))
+        counts.append([plan.read(i, want_out=False)[1] for i in range(len(order))])
+        plan.free()
+    print(f"large graphs in front {ms[0]:.3f} ms, behind {ms[1]:.3f}", flush=True)
+    for a, b in zip(counts[0], counts[1][::-1]):
+        assert np.array_equal(a, b)
+    small = inputs.erdos_renyi_in(500, 8.0, seed=1)
+    for i in (4, 5, 6):
+        _, s, k = front[i]
+        assert np.array_equal(counts[0][i][vs], O.meet_counts_plain(small, s, k, 0.6, 64, 9502, vs))
+    assert ms[0] < 1.03 * ms[1]
+    for G in Gs.values():
+        G.free()
+
+
 # The tuner keeps units sized on the device where they are fastest: on a small
 # graph the best fixed size takes three times as long.
 def test_tuner_keeps_units_sized_on_the_device():
